@@ -95,10 +95,10 @@ int tf_last_hip_error(const tf_ctx* ctx);
  * Disabled by default; costs nothing when disabled.
  */
 typedef enum {
-    TF_KERNEL_DX_MFMA = 0,      /* input-gradient GEMMs on the matrix cores   */
-    TF_KERNEL_DW_MFMA = 1,      /* weight-gradient GEMMs on the matrix cores  */
-    TF_KERNEL_DX_GENERIC = 2,   /* input-gradient GEMMs, fp32-FMA kernel      */
-    TF_KERNEL_DW_GENERIC = 3,   /* weight-gradient GEMMs, fp32-FMA kernel     */
+    TF_KERNEL_DX_MFMA = 0,      /* input-gradient GEMMs, bf16, shapes for 256 x 256 tiles  */
+    TF_KERNEL_DW_MFMA = 1,      /* weight-gradient GEMMs, bf16, shapes for 256 x 256 tiles */
+    TF_KERNEL_DX_GENERIC = 2,   /* input-gradient GEMMs of any other shape or type  */
+    TF_KERNEL_DW_GENERIC = 3,   /* weight-gradient GEMMs of any other shape or type */
     TF_KERNEL_ADAMW = 4,        /* fused masked AdamW (+ stability EMAs)      */
     TF_KERNEL_STABILITY = 5,    /* stand-alone stability update               */
     TF_KERNEL_AUTOFREEZE = 6,   /* norms of the cumulative updates            */
@@ -295,8 +295,7 @@ int32_t tf_num_frozen(double r, int32_t n);
  *     dW_l[b*block_rows .. (b+1)*block_rows) (+)= X_l[:, those columns]^T * dY_l
  * Rows of frozen blocks of dW_l are neither read nor written; dX is always
  * computed in full.  Runs of unfrozen blocks are single GEMM problems; on the
- * matrix cores when the run has a multiple of 256 rows (and N_l % 256 == 0,
- * T % 64 == 0, bf16 inputs), otherwise on the fp32-FMA kernel.
+ * 256 x 256-tile kernel when its shape allows (bf16 inputs, T % 64 == 0), otherwise on the generic one.
  *   row_block_mask   host array of n_layers HOST pointers (entries may be NULL: layer
  *                    without row mask), each K_l / block_rows bytes, 1 = frozen; or NULL
  *   block_rows       > 0; must divide K_l of every layer that has a row mask

@@ -1,135 +1,436 @@
-// Edge-safe grouped GEMM on plain fp32 FMAs (no matrix cores).
+// Grouped GEMM for every shape, on the matrix cores: the fp32 configuration and whatever bf16
+// problems the 256 x 256-tile kernel does not take (fewer than 256 rows or columns, pitches or
+// extents that are no multiple of 8).  Computes both halves of a backward action (TimelyFreeze
+// Sec. 3.2.1): the input gradient dX = dY W^T (layout kNT) and the parameter gradient dW = X^T dY
+// (layout kTN); frozen tensors never reach this file.
 //
-// Serves the fp32 configuration (true fp32 arithmetic, needed for the 1e-5
-// parity bound) and any bf16 problem whose dimensions the MFMA kernel does not
-// take.  Computes both halves of a backward action (TimelyFreeze Sec. 3.2.1):
-// the input gradient dX = dY W^T (layout kNT) and the parameter gradient
-// dW = X^T dY (layout kTN); frozen tensors never reach this file.
+// fp32 operands go through v_mfma_f32_16x16x4_f32 (true fp32 products and sums, twice the rate of
+// the vector FMA), bf16 operands through v_mfma_f32_16x16x32_bf16.
 //
-// 64 x 64 output tile per 256-thread block, 4 x 4 outputs per thread,
-// contraction staged through LDS 16 at a time.
+// Against plain fp32 vector FMAs in 64 x 64 tiles (what this file held before): fp32 stage of width 1024,
+// 1000 tokens, input gradients of two blocks 750 -> 380 us (58 -> 116 TFLOP/s); bf16, 200 tokens of a
+// LLaMA-1B block pair, input gradients 1199 -> 115 us; bf16, weight gradients over 3001 tokens 9460 ->
+// 870 us.  fp32 is bound by the matrix pipe, bf16 by the operands' way through L1 and LDS.
+//
+// One output tile per workgroup of four waves in a 2 x 2 grid.  The contraction advances 128 bytes
+// per operand row (64 bf16 or 32 fp32 values) through two LDS stages; the 16-byte pieces of the
+// steps ahead travel through registers, so that no element needs an alignment beyond its own
+// (a global 128-bit load takes any address) and what lies outside the contraction can be zeroed.
+//   kNT stage: [row][128 bytes of contraction], 16-byte chunks of a row XOR-swizzled; an operand
+//              is one 128-bit LDS read per lane.
+//   kTN stage: [contraction][rows] as in memory.  bf16: operands by the LDS transpose read; fp32:
+//              by four 32-bit reads.  32- / 64-byte units XOR-swizzled against bank conflicts.
+// Nothing is ever read outside a matrix: rows past its end are clamped to the last one (their
+// outputs are not stored); pieces that run over the end of a row stay inside the matrix except in
+// its last row, and the last contraction step checks that and zeroes the values past the contraction.
 #include "tf_internal.h"
+
+#include <type_traits>
+#include <utility>
 
 namespace tf {
 namespace {
 
-constexpr int kTile = 64;
-constexpr int kBK = 16;
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;           // four waves, 2 x 2 over the tile
+constexpr int kStepBytes = 128;         // contraction bytes of an operand row per step
+constexpr int kXcds = 8;
+constexpr int kXcdRun = 8;              // consecutive logical tiles kept on one XCD
+constexpr int kGroupM = 8;              // tile rows per L2 locality group
 
-template <typename T> __device__ __forceinline__ float to_f32(T x);
-template <> __device__ __forceinline__ float to_f32<float>(float x) { return x; }
-template <> __device__ __forceinline__ float to_f32<uint16_t>(uint16_t x) {
-    return __uint_as_float(uint32_t(x) << 16);
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+typedef uint32_t U2 __attribute__((ext_vector_type(2)));
+typedef U4 U4any __attribute__((aligned(2)));       // a 16-byte piece at any element address
+typedef f32x4 F4any __attribute__((aligned(4)));
+typedef __attribute__((address_space(3))) bf16x4* LdsBf16x4Ptr;
+
+#define TF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return uint16_t((u >> 16) | 0x40u);
-    return uint16_t((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// kContig: the contraction index is the fast (contiguous) index of A and B.
-template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate>
-__global__ __launch_bounds__(kThreads) void gemm_generic_kernel(GemmBatch batch) {
-    __shared__ float As[kBK][kTile + 4];
-    __shared__ float Bs[kBK][kTile + 4];
+// kNT stage: where a row's 16-byte chunk c lies: c ^ nt_swizzle(row).  An operand read takes 16
+// consecutive rows of one chunk per 16 lanes; the LDS serves 8 consecutive lanes together with the 8
+// lanes 32 further on, so rows r .. r + 7 of chunks q and q ^ 2 have to fall into different banks.
+__device__ __forceinline__ constexpr int nt_swizzle(int r) {
+    return ((r >> 1) & 1) | (((r >> 3) & 1) << 1) | (((r >> 2) & 1) << 2);
+}
 
-    int pi = 0;
-    const int bid = blockIdx.x;
-    for (int i = 1; i < batch.n_problems; ++i)
-        if (bid >= batch.p[i].tile_start) pi = i;
+// One operand of a workgroup's tile: kRows rows of it, kRows x 128 bytes per stage.
+template <typename TIn, bool kContig, int kRows>
+struct Operand {
+    static constexpr int kSize = int(sizeof(TIn));
+    static constexpr int kE = 16 / kSize;                       // elements of a 16-byte piece
+    static constexpr int kBK = kStepBytes / kSize;              // contraction values per step
+    static constexpr int kPieces = kRows * kStepBytes / 16 / kThreads;      // per thread and step
+    static constexpr int kPitch = kContig ? kStepBytes : kRows * kSize;     // bytes of a stage row
+    static constexpr int kRowPieces = kPitch / 16;              // pieces of a stage row
+    static constexpr int kStageBytes = kRows * kStepBytes;
+    static constexpr int kFrags = kRows / 32;                   // 16-row blocks of a wave (it owns half of the rows)
+    static_assert(kPieces >= 1, "at least one piece per thread");
+
+    const TIn* p[kPieces];      // this thread's pieces of the step to be loaded next
+    int k[kPieces];             // contraction index of the piece's first element (kNT) or of its row (kTN), inside a step
+    int lds[kPieces];           // byte offset of the piece inside a stage
+    int64_t step;               // elements from one step to the next
+    const TIn* matrix;
+    int over;                   // kTN: elements by which this thread's pieces run over the end of their rows
+    bool narrow;                // rows shorter than a piece: fetched element by element
+
+    __device__ __forceinline__ Operand(const void* base, int64_t ld, int extent, int kc, int origin)
+        : matrix(static_cast<const TIn*>(base)), narrow(kContig ? kc < kE : ld < kE || extent < kE) {
+        step = kContig ? int64_t(kBK) : int64_t(kBK) * ld;
+        const int tid = int(threadIdx.x), c = tid % kRowPieces;                            // the same piece of every kThreads / kRowPieces-th row
+        static_assert(kThreads % kRowPieces == 0, "a thread's pieces lie below each other");
+        const int col = origin + c * kE < extent ? origin + c * kE : 0;
+        over = max(col + kE - extent, 0);
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int r = tid / kRowPieces + i * (kThreads / kRowPieces);      // stage row
+            k[i] = kContig ? c * kE : r;
+            lds[i] = kContig ? r * kPitch + ((c ^ nt_swizzle(r)) << 4) : piece_tn(r, c);
+            p[i] = matrix + (kContig ? int64_t(min(origin + r, extent - 1)) * ld + k[i] : int64_t(k[i]) * ld + col);
+        }
+    }
+
+    // kTN stage: byte offset of 16-byte piece c of contraction row t.  bf16: the transpose read of a
+    // 16-row block takes 32 bytes (a unit) of contraction rows 8 G + x, x = 0..3, G = lane / 16, 32
+    // lanes at a time: 8 rows, whose units must differ (128 rows: pitch = all banks; 64 rows: half
+    // of them).  fp32: a read takes 64 bytes of rows 4 q + j, q = lane / 16: 4 rows to keep apart.
+    __device__ __forceinline__ static int unit_xor(int t) {
+        if (kSize == 4) return (t >> 2) & (kRows >= 64 ? 3 : 1);
+        return kRows >= 128 ? 4 * ((t >> 3) & 1) + (t & 3) : 2 * ((t >> 3) & 1) + ((t >> 1) & 1);
+    }
+    __device__ __forceinline__ static int piece_tn(int t, int c) {
+        if (kSize == 4) return t * kPitch + (((c >> 2) ^ unit_xor(t)) << 6) + ((c & 3) << 4);
+        return t * kPitch + (((c >> 1) ^ unit_xor(t)) << 5) + ((c & 1) << 4);
+    }
+
+    // A step of whole pieces that all lie inside the matrix.
+    __device__ __forceinline__ void load(U4 (&v)[kPieces]) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            v[i] = *reinterpret_cast<const U4any*>(p[i]);
+            p[i] += step;
+        }
+    }
+    // How many elements of piece i have to be fetched from in front of it, `left` being what is left of
+    // the contraction from the step's first value on: what runs over the end of a row (kNT) or of the
+    // matrix (kTN: of its last row).
+    __device__ __forceinline__ int past(int i, int left) const {
+        if (kContig) return max(k[i] + kE - left, 0);
+        return k[i] < left - 1 ? 0 : over;
+    }
+    // Any step: nothing outside the matrix is read; finish() puts the values in their places.
+    __device__ __forceinline__ void load_inside(U4 (&v)[kPieces], int left) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            if (!narrow) {
+                const TIn* q = p[i] - past(i, left);
+                if (!kContig && k[i] >= left) q = matrix;
+                v[i] = *reinterpret_cast<const U4any*>(q);
+            } else {
+                uint64_t lo = 0, hi = 0;
+                for (int e = (kContig ? min(left - k[i], kE) : k[i] < left ? kE - over : 0) - 1; e >= 0; --e) {
+                    const uint64_t x = kSize == 4 ? reinterpret_cast<const uint32_t*>(p[i])[e] : reinterpret_cast<const uint16_t*>(p[i])[e];
+                    hi = hi << (8 * kSize) | lo >> (64 - 8 * kSize);
+                    lo = lo << (8 * kSize) | x;
+                }
+                v[i] = U4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
+            }
+            p[i] += step;
+        }
+    }
+    // What load_inside() fetched, moved down; zeros past the end of the contraction.
+    __device__ __forceinline__ void finish(U4 (&v)[kPieces], int left) const {
+        if (narrow) return;
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int n = past(i, left);
+            if (kContig ? n >= kE : k[i] >= left) {
+                v[i] = U4{0, 0, 0, 0};
+            } else if (n > 0) {
+                const int bits = n * (8 * kSize);
+                uint64_t lo = v[i][0] | uint64_t(v[i][1]) << 32, hi = v[i][2] | uint64_t(v[i][3]) << 32;
+                if (bits >= 64) { lo = hi; hi = 0; }
+                if (bits & 63) { lo = lo >> (bits & 63) | hi << (64 - (bits & 63)); hi >>= bits & 63; }
+                v[i] = U4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
+            }
+        }
+    }
+    __device__ __forceinline__ void store(const U4 (&v)[kPieces], char* stage) const {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) *reinterpret_cast<U4*>(stage + lds[i]) = v[i];
+    }
+
+    // The 16 bytes that a lane contributes to the matrix instructions of 16-row block b and half
+    // step u: one instruction of 32 contraction values (bf16) or four of 4 (fp32: instruction j takes
+    // contraction values 16 u + 4 (lane / 16) + j, the same for both operands).
+    __device__ __forceinline__ static U4 fragment(const char* stage, int b, int u) {
+        const int lane = threadIdx.x & 63, q = lane >> 4;
+        if (kContig) {
+            const int r = b * 16 + (lane & 15);
+            return *reinterpret_cast<const U4*>(stage + r * kPitch + (((4 * u + q) ^ nt_swizzle(r)) << 4));
+        }
+        if (kSize == 2) {
+            const int ii = lane & 15, t = 8 * q + (ii >> 2);
+            const char* a = stage + (32 * u + t) * kPitch + ((b ^ unit_xor(t)) << 5) + ((ii & 3) << 3);
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsBf16x4Ptr)TF_LPTR(a));
+            const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsBf16x4Ptr)TF_LPTR(a + 4 * kPitch));
+            return __builtin_bit_cast(U4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+        const char* a = stage + (16 * u + 4 * q) * kPitch + ((b ^ unit_xor(4 * q)) << 6) + ((lane & 15) << 2);
+        U4 x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const uint32_t*>(a + j * kPitch);
+        return x;
+    }
+};
+
+// Between the last matrix instruction and the first vector instruction that reads its result.  Left to
+// itself the compiler counts a wait and a barrier in between as wait states, and an fp32 sum's last
+// register, read first behind the two, was the old one.
+__device__ __forceinline__ void wait_for_sums() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 3");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Block number -> logical tile: runs of consecutive tiles stay on one XCD (block b runs on XCD b % 8).
+__device__ __forceinline__ int logical_tile(int b, int nb) {
+    const int span = kXcds * kXcdRun;
+    if (b >= (nb / span) * span) return b;
+    const int xcd = b % kXcds, idx = b / kXcds;
+    return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
+}
+
+// kDepth: steps whose pieces are on their way in registers.
+template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN, int kDepth>
+__global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
+    typedef Operand<TIn, kContig, kTileM> OpA;
+    typedef Operand<TIn, kContig, kTileN> OpB;
+    constexpr int kStage = OpA::kStageBytes + OpB::kStageBytes;
+    static_assert(kTileM * kTileN * 4 <= 2 * kStage, "the sums are turned around in the stages");
+    __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
+
+    // this block's problem: lane i looks at the first tile of problem i
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    static_assert(kMaxProblemsPerLaunch == 64, "one lane per problem");
+    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
+    const bool started = lane < batch.n_problems && batch.p[lane].tile_start <= lt;
+    const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(started)) - 1);
     const GemmProblem& P = batch.p[pi];
     const int M = P.M, N = P.N, Kc = P.Kc;
-    const int tiles_n = (N + kTile - 1) / kTile;
-    const int t = bid - P.tile_start;
-    const int m0 = (t / tiles_n) * kTile;
-    const int n0 = (t % tiles_n) * kTile;
-    const TIn* A = static_cast<const TIn*>(P.A);
-    const TIn* B = static_cast<const TIn*>(P.B);
+    const int tiles_m = (M + kTileM - 1) / kTileM, tiles_n = (N + kTileN - 1) / kTileN;
+    int t = lt - P.tile_start;
+    const int per_group = kGroupM * tiles_n;
+    const int first_m = (t / per_group) * kGroupM;
+    const int gsz = min(tiles_m - first_m, kGroupM);
+    t %= per_group;
+    const int m0 = (first_m + t % gsz) * kTileM, n0 = (t / gsz) * kTileN;
 
-    const int tid = threadIdx.x;
-    const int ty = tid / 16, tx = tid % 16;      // 16 x 16 threads, 4 x 4 outputs each
-    float acc[4][4] = {};
-
-    for (int k0 = 0; k0 < Kc; k0 += kBK) {
-        // stage A(m0.., k0..) and B(n0.., k0..) into LDS as [k][row]
+    OpA a(P.A, P.lda, M, Kc, m0);
+    OpB b(P.B, P.ldb, N, Kc, n0);
+    U4 va[kDepth][OpA::kPieces], vb[kDepth][OpB::kPieces];
+    const int steps = Kc / OpA::kBK + (Kc % OpA::kBK != 0);
+    // steps whose pieces are whole: all but the last one
+    const int free_steps = a.narrow || b.narrow ? 0 : steps - 1;
+    f32x4 acc[OpA::kFrags][OpB::kFrags];
 #pragma unroll
-        for (int i = 0; i < (kTile * kBK) / kThreads; ++i) {
-            const int idx = tid + i * kThreads;
-            int r, k;
-            if (kContig) { k = idx % kBK; r = idx / kBK; }    // consecutive threads walk the contraction
-            else         { r = idx % kTile; k = idx / kTile; }  // consecutive threads walk the rows
-            const int gk = k0 + k;
-            float a = 0.f, b = 0.f;
-            if (gk < Kc) {
-                if (m0 + r < M)
-                    a = to_f32<TIn>(kContig ? A[int64_t(m0 + r) * P.lda + gk] : A[int64_t(gk) * P.lda + (m0 + r)]);
-                if (n0 + r < N)
-                    b = to_f32<TIn>(kContig ? B[int64_t(n0 + r) * P.ldb + gk] : B[int64_t(gk) * P.ldb + (n0 + r)]);
-            }
-            As[k][r] = a;
-            Bs[k][r] = b;
+    for (int i = 0; i < OpA::kFrags; ++i)
+#pragma unroll
+        for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int wm = wave >> 1, wn = wave & 1;
+    constexpr bool kWide = sizeof(TIn) == 2;            // 32 contraction values per instruction, not 4
+    auto contract = [&](const char* stage) {
+        // fp32: a step's 32 products are summed by themselves and then added to the sums so far.  The
+        // error grows with the root of 32 + K / 32 instead of the root of K (against 64 bits, K = 256:
+        // 2.9e-7 -> 1.3e-7), the additions ride beside the matrix instructions.
+        f32x4 part[OpA::kFrags][OpB::kFrags];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            U4 fa[OpA::kFrags], fb[OpB::kFrags];
+#pragma unroll
+            for (int i = 0; i < OpA::kFrags; ++i) fa[i] = OpA::fragment(stage, wm * OpA::kFrags + i, u);
+#pragma unroll
+            for (int j = 0; j < OpB::kFrags; ++j) fb[j] = OpB::fragment(stage + OpA::kStageBytes, wn * OpB::kFrags + j, u);
+            // D rows <- n (B rows), D columns <- m: a lane then owns 4 consecutive n of one output row
+#pragma unroll
+            for (int e = 0; e < (kWide ? 1 : 4); ++e)
+#pragma unroll
+                for (int i = 0; i < OpA::kFrags; ++i)
+#pragma unroll
+                    for (int j = 0; j < OpB::kFrags; ++j) {
+                        if constexpr (kWide)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[j]),
+                                                                               __builtin_bit_cast(bf16x8, fa[i]), acc[i][j], 0, 0, 0);
+                        else
+                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[j][e]), __uint_as_float(fa[i][e]),
+                                                                              u == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[i][j], 0, 0, 0);
+                    }
         }
-        __syncthreads();
+        if constexpr (!kWide) {
+            wait_for_sums();
 #pragma unroll
-        for (int k = 0; k < kBK; ++k) {
-            float a[4], b[4];
+            for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = As[k][ty * 4 + i]; b[i] = Bs[k][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+                for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] += part[i][j];
         }
-        __syncthreads();
-    }
+    };
 
+    // Step s sits in stage s % 2, the kDepth steps after it in registers (set s % kDepth) or on their
+    // way there while step s is contracted.  One barrier per step: a stage is written one step after
+    // every wave has read it.
+    // (what is left of the contraction from step s on, as far as it matters)
+    auto left = [&](int s) { return int(min(int64_t(Kc) - int64_t(s) * OpA::kBK, int64_t(0x10000))); };
+    auto put = [&](int s, auto q) __attribute__((always_inline)) {
+        if (s >= free_steps) { a.finish(va[q], left(s)); b.finish(vb[q], left(s)); }
+        a.store(va[q], lds + (s & 1) * kStage);
+        b.store(vb[q], lds + (s & 1) * kStage + OpA::kStageBytes);
+    };
+    auto fetch = [&](int s, auto q) __attribute__((always_inline)) {
+        if (s >= steps) return;
+        if (s < free_steps) { a.load(va[q]); b.load(vb[q]); }
+        else { a.load_inside(va[q], left(s)); b.load_inside(vb[q], left(s)); }
+    };
+    static_for<kDepth>([&](auto q) __attribute__((always_inline)) { fetch(q, q); });
+    put(0, std::integral_constant<int, 0>{});
+    __syncthreads();
+    // The long part has no branch around a load: with one, the wait in front of a store is for the
+    // loads just issued instead of the oldest ones.
+    int s0 = 0;
+    for (; s0 + 2 * kDepth <= free_steps; s0 += kDepth)
+        static_for<kDepth>([&](auto q) __attribute__((always_inline)) {
+            constexpr int now = decltype(q)::value, nxt = (now + 1) % kDepth;
+            const int s = s0 + now;
+            a.load(va[now]);
+            b.load(vb[now]);
+            contract(lds + (s & 1) * kStage);
+            a.store(va[nxt], lds + (~s & 1) * kStage);
+            b.store(vb[nxt], lds + (~s & 1) * kStage + OpA::kStageBytes);
+            __syncthreads();
+        });
+    for (; s0 < steps; s0 += kDepth)
+        static_for<kDepth>([&](auto q) __attribute__((always_inline)) {
+            constexpr int now = decltype(q)::value, nxt = (now + 1) % kDepth;
+            const int s = s0 + now;
+            if (s >= steps) return;
+            fetch(s + kDepth, q);
+            contract(lds + (s & 1) * kStage);
+            if (s + 1 < steps) put(s + 1, std::integral_constant<int, nxt>{});
+            __syncthreads();
+        });
+
+    if (kWide) wait_for_sums();
+    // Epilogue: acc[i][j][e] is C[m][n], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16) + e of the
+    // wave's part.  The sums are turned around in LDS ([row][16-byte chunks, XOR-swizzled]) and whole
+    // rows of the tile are stored, 16 bytes per lane.
+    constexpr int kRow = kTileN * 4, kTurn = kTileN / 4 < 16 ? kTileN / 4 - 1 : 15;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = m0 + ty * 4 + i;
-        if (m >= M) continue;
+    for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            const int64_t off = int64_t(m) * N + n;
-            if (kOutBf16) {
-                static_cast<uint16_t*>(P.C)[off] = f32_to_bf16_rne(acc[i][j]);
+        for (int j = 0; j < OpB::kFrags; ++j) {
+            const int r = wm * (kTileM / 2) + 16 * i + (lane & 15), c = wn * (kTileN / 8) + 4 * j + (lane >> 4);
+            *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
+        }
+    __syncthreads();
+    constexpr int kOutE = kOutBf16 ? 8 : 4, kLanes = kTileN / kOutE, kRowsPerPass = kThreads / kLanes;
+    const int c = int(threadIdx.x) % kLanes, n = n0 + c * kOutE;
+#pragma unroll
+    for (int r0 = 0; r0 < kTileM; r0 += kRowsPerPass) {
+        const int r = r0 + int(threadIdx.x) / kLanes, m = m0 + r;
+        f32x4 v[kOutE / 4];
+#pragma unroll
+        for (int h = 0; h < kOutE / 4; ++h)
+            v[h] = *reinterpret_cast<const f32x4*>(lds + r * kRow + (((c * (kOutE / 4) + h) ^ (r & kTurn)) << 4));
+        if (m >= M || n >= N) continue;
+        if constexpr (kOutBf16) {
+            const U4 x = {f32x2_to_bf16x2(v[0][0], v[0][1]), f32x2_to_bf16x2(v[0][2], v[0][3]),
+                          f32x2_to_bf16x2(v[1][0], v[1][1]), f32x2_to_bf16x2(v[1][2], v[1][3])};
+            uint16_t* out = static_cast<uint16_t*>(P.C) + int64_t(m) * N + n;
+            if (n + kOutE <= N) {
+                *reinterpret_cast<U4any*>(out) = x;
             } else {
-                float* c = static_cast<float*>(P.C) + off;
-                *c = kAccumulate ? (*c + acc[i][j]) : acc[i][j];
+#pragma unroll
+                for (int e = 0; e < kOutE; ++e)
+                    if (n + e < N) out[e] = uint16_t(x[e >> 1] >> (16 * (e & 1)));
+            }
+        } else {
+            float* out = static_cast<float*>(P.C) + int64_t(m) * N + n;
+            if (n + kOutE <= N) {
+                if (kAccumulate) v[0] += *reinterpret_cast<const F4any*>(out);
+                *reinterpret_cast<F4any*>(out) = v[0];
+            } else {
+#pragma unroll
+                for (int e = 0; e < kOutE; ++e)
+                    if (n + e < N) out[e] = kAccumulate ? out[e] + v[0][e] : v[0][e];
             }
         }
     }
 }
 
-template <typename TIn, bool kContig>
-void dispatch_out(hipStream_t stream, const GemmBatch& batch, Dtype out_dtype, bool accumulate) {
+// The launch shapes.  step_us, chain_us: a step's share of a compute unit when all are full, and its
+// time in a workgroup that has the unit to itself; tile_steps: what a tile costs beside its steps.
+// Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps are
+// bound by the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
+// tokens: 128 x 128 tiles 906 TFLOP/s, 128 x 64 753, 64 x 64 598), the fp32 steps by the matrix pipe
+// (2048 tokens, width 1024: 128 x 64 tiles 125 TFLOP/s, 32 x 64 115, 32 x 32 105).
+// Small tiles are for calls with few of them: an fp32 chain of 64 steps takes 24 us in 32 x 32 tiles,
+// 30 in 32 x 64, 46 in 64 x 64, 96 in 128 x 64 and 155 in 128 x 128.
+constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 1.7f}, {128, 64, 0.348f, 0.45f, 2.5f}, {128, 128, 0.575f, 0.60f, 3.4f}};
+constexpr GenericShape kShapes32[] = {{32, 32, 0.157f, 0.30f, 1.0f}, {32, 64, 0.286f, 0.40f, 1.0f}, {128, 64, 1.04f, 1.45f, 1.0f}};
+static_assert(sizeof(kShapes16) == kGenericShapes * sizeof(GenericShape) && sizeof(kShapes32) == sizeof(kShapes16), "as many for both types");
+
+template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate>
+void launch(hipStream_t stream, const GemmBatch& batch, int shape) {
     const dim3 grid(batch.total_tiles), block(kThreads);
-    if (out_dtype == Dtype::BF16)
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, true, false>), grid, block, 0, stream, batch);
-    else if (accumulate)
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, false, true>), grid, block, 0, stream, batch);
+    constexpr bool k16 = sizeof(TIn) == 2;
+    constexpr const GenericShape* kS = k16 ? kShapes16 : kShapes32;
+    if (shape == 0)
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[0].tile_m, kS[0].tile_n, 2>), grid, block, 0, stream, batch);
+    else if (shape == 1)
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[1].tile_m, kS[1].tile_n, 2>), grid, block, 0, stream, batch);
     else
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, false, false>), grid, block, 0, stream, batch);
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[2].tile_m, kS[2].tile_n, k16 ? 2 : 1>), grid, block, 0, stream, batch);
 }
 
 }  // namespace
 
-int gemm_generic_tile() { return kTile; }
+const GenericShape& generic_shape(Dtype in_dtype, int shape) { return in_dtype == Dtype::BF16 ? kShapes16[shape] : kShapes32[shape]; }
 
-hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems,
+hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems, int shape,
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate) {
     batch.n_problems = n_problems;
     if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
     const bool contig = layout == Layout::kNT;
     if (in_dtype == Dtype::F32) {
-        if (contig) dispatch_out<float, true>(stream, batch, out_dtype, accumulate);
-        else        dispatch_out<float, false>(stream, batch, out_dtype, accumulate);
+        if (out_dtype != Dtype::F32) return hipErrorInvalidValue;
+        if (contig) accumulate ? launch<float, true, false, true>(stream, batch, shape) : launch<float, true, false, false>(stream, batch, shape);
+        else        accumulate ? launch<float, false, false, true>(stream, batch, shape) : launch<float, false, false, false>(stream, batch, shape);
+    } else if (contig) {
+        if (out_dtype != Dtype::BF16 || accumulate) return hipErrorInvalidValue;       // an input gradient has the inputs' type
+        launch<uint16_t, true, true, false>(stream, batch, shape);
+    } else if (out_dtype == Dtype::BF16) {
+        launch<uint16_t, false, true, false>(stream, batch, shape);
     } else {
-        if (contig) dispatch_out<uint16_t, true>(stream, batch, out_dtype, accumulate);
-        else        dispatch_out<uint16_t, false>(stream, batch, out_dtype, accumulate);
+        accumulate ? launch<uint16_t, false, false, true>(stream, batch, shape) : launch<uint16_t, false, false, false>(stream, batch, shape);
     }
     return hipGetLastError();
 }

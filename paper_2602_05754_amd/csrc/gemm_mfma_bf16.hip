@@ -873,6 +873,7 @@ int persistent_grid(int total_tiles, int units) {
 }
 
 int gemm_mfma_tile() { return kBM; }
+int compute_units() { return compute_units(current_device()); }
 
 }  // namespace tf
 

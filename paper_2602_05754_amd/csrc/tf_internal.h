@@ -52,10 +52,18 @@ struct GemmBatch {          // passed by value as the kernel argument (64 x 64 B
     int32_t total_tiles;
 };
 
-// Edge-safe LDS-tiled FMA kernel (any M, N, Kc >= 1).  in: fp32 or bf16,
-// accumulate fp32, out: fp32 (optionally +=) or bf16.
-hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems,
+// Matrix-core kernel for any M, N, Kc >= 1, pitch and alignment.  in: fp32 or bf16, accumulate
+// fp32, out: fp32 (optionally +=) or bf16.  It comes in several launch shapes; the batch's tiles are
+// those of generic_shape(in_dtype, shape).
+struct GenericShape {
+    int tile_m, tile_n;
+    float step_us, chain_us, tile_steps;    // what a contraction step of a tile costs (see there)
+};
+constexpr int kGenericShapes = 3;
+const GenericShape& generic_shape(Dtype in_dtype, int shape);
+hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems, int shape,
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
+int compute_units();              // of the current device
 
 // MFMA kernel for bf16 inputs.  What it takes (mfma_shape_ok): contraction a multiple of 64; output
 // columns N >= 256 and a multiple of 8; output rows M >= 256, or fewer with rows_before +
@@ -65,7 +73,6 @@ bool mfma_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda,
                    int64_t rows_before = 0, int64_t rows_after = 0);
 hipError_t launch_gemm_mfma_bf16(hipStream_t stream, GemmBatch& batch, int n_problems,
                                  Layout layout, Dtype out_dtype, bool accumulate);
-int gemm_generic_tile();          // tile edge of the generic kernel (square)
 int gemm_mfma_tile();             // tile edge of the MFMA kernel (square)
 int persistent_grid(int total_tiles, int units);    // workgroups of an MFMA launch on `units` compute units
 

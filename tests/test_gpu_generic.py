@@ -1,0 +1,128 @@
+"""GPU parity of the generic matrix-core GEMM (Sec. 3.2.1, both halves of the backward) where it can
+go wrong: extents around its tiles and contraction steps, rows shorter than one 16-byte piece,
+pitches that leave rows on any element address, every launch shape, both types.  Outputs lie inside
+guard bands, which must come back untouched."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+import paper_2602_05754_amd as tf
+from gpu_util import CODE, TDT, assert_elementwise, canary, dev, host64, raw_bytes
+
+pytestmark = pytest.mark.gpu
+GUARD = 64
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = tf.Context(0)
+    yield c
+    c.close()
+
+
+def _launch_tile(M, N, Kc, io):
+    """Tile of the launch shape that a call with these problems gets."""
+    n = len(M)
+    arr = lambda v: (ctypes.c_int64 * n)(*v)
+    tile = (ctypes.c_int32 * 2)()
+    tf.load_library().tf_internal_generic_shape(n, arr(M), arr(N), arr(Kc), CODE[io], tile)
+    return tuple(tile)
+
+
+class Guarded:
+    """An output of a stage backward between two guard bands."""
+
+    def __init__(self, shape, dtype, fill=None):
+        self.n, self.shape = int(np.prod(shape)), shape
+        self.all = canary((self.n + 2 * GUARD,), TDT[dtype])
+        self.t = self.all[GUARD:GUARD + self.n].view(shape)
+        if fill is not None:
+            self.t.copy_(fill)
+        self.before = raw_bytes(self.all[:GUARD]), raw_bytes(self.all[GUARD + self.n:])
+
+    def check(self, what):
+        assert (raw_bytes(self.all[:GUARD]), raw_bytes(self.all[GUARD + self.n:])) == self.before, f"{what}: written outside"
+
+
+def _case(ctx, shapes, T, io, dw, accumulate=False, seed=0):
+    rs = np.random.default_rng(seed)
+    L = len(shapes)
+    f32 = lambda a: np.ascontiguousarray(a, dtype=np.float32)
+    low = (lambda a: wl.round_to_bf16(f32(a))) if io == "bf16" else f32
+    W = [low(rs.standard_normal(s) * 0.02) for s in shapes]
+    X = [low(rs.standard_normal((T, k))) for k, n in shapes]
+    dY = [low(rs.standard_normal((T, n)) * 1e-3) for k, n in shapes]
+    old = [f32(rs.standard_normal(s) * 1e-2) for s in shapes]
+    f64 = lambda t: [np.asarray(a, dtype=np.float64) for a in t]
+    rX = [np.zeros((T, k)) for k, n in shapes]
+    rW = f64(old) if accumulate else [np.zeros(s) for s in shapes]
+    if T * sum(k * n for k, n in shapes) < 2e8:
+        oracle.stage_backward(shapes, T, f64(W), f64(X), f64(dY), np.zeros(L, np.uint8), rX, rW, accumulate=accumulate)
+    else:                                                            # the same in numpy, for the oracle's loops too much
+        rX = [y @ w.T for y, w in zip(f64(dY), f64(W))]
+        rW = [x.T @ y for x, y in zip(f64(X), f64(dY))]
+    gX = [Guarded((T, k), io) for k, n in shapes]
+    gW = [Guarded(s, dw, torch.from_numpy(o) if accumulate else None) for s, o in zip(shapes, old)]
+    tf.tf_stage_backward(ctx, shapes, T, CODE[io], [dev(a, io) for a in W], [dev(a, io) for a in X], [dev(a, io) for a in dY],
+                         None, [g.t for g in gX], [g.t for g in gW], CODE[dw], accumulate=accumulate)
+    torch.cuda.synchronize()
+    for l in range(L):
+        # one rounding of a sum in 32 bits: the bounds of assert_elementwise
+        assert_elementwise(host64(gX[l].t), rX[l], io, f"dX[{l}] {shapes[l]} T={T} {io}")
+        assert_elementwise(host64(gW[l].t), rW[l], dw, f"dW[{l}] {shapes[l]} T={T} {io}->{dw}")
+        gX[l].check(f"dX[{l}] {shapes[l]} T={T}")
+        gW[l].check(f"dW[{l}] {shapes[l]} T={T}")
+
+
+# steps of 64 (bf16) / 32 (fp32) contraction values, tiles of 32, 64, 128, pieces of 8 / 4 elements
+@pytest.mark.parametrize("io,dw,accumulate", [("f32", "f32", False), ("f32", "f32", True), ("bf16", "bf16", False),
+                                              ("bf16", "f32", False), ("bf16", "f32", True)])
+@pytest.mark.parametrize("T,shapes", [
+    (1, [(1, 1), (3, 2), (8, 9), (33, 64)]),                       # outer products, rows shorter than a piece
+    (2, [(1, 7), (7, 1), (5, 130)]),
+    (31, [(31, 33), (32, 32), (65, 7), (64, 129)]),
+    (64, [(128, 64), (127, 63), (129, 65), (4, 200)]),
+    (65, [(66, 257), (192, 320), (2, 3)]),
+    (191, [(72, 136), (100, 385), (260, 31)]),                     # three bf16 steps less one value
+])
+def test_edges_of_tiles_steps_and_pieces(ctx, io, dw, accumulate, T, shapes):
+    _case(ctx, shapes, T, io, dw, accumulate, seed=T)
+
+
+@pytest.mark.parametrize("half,io,T,shapes,tile", [
+    ("dX", "f32", 130, [(97, 161), (160, 96)], (32, 32)),
+    ("dX", "f32", 643, [(1290, 99), (1283, 95)], (32, 64)),
+    ("dX", "f32", 2001, [(2050, 331), (2049, 333), (2051, 250), (2050, 331)], (128, 64)),
+    ("dX", "bf16", 130, [(97, 161), (160, 96)], (64, 64)),
+    ("dX", "bf16", 770, [(1027, 1101), (1101, 2030), (1027, 2003)], (128, 64)),
+    ("dX", "bf16", 1531, [(1027, 1101), (1101, 2030), (2047, 1003)], (128, 128)),
+    ("dW", "f32", 130, [(97, 161), (160, 96)], (32, 32)),
+    ("dW", "f32", 331, [(2050, 1001), (2049, 1005)], (32, 64)),
+    ("dW", "f32", 415, [(2047, 2001), (2046, 2005), (2047, 2001), (2045, 2003)], (128, 64)),
+    ("dW", "bf16", 130, [(97, 161), (160, 96)], (64, 64)),
+    ("dW", "bf16", 1101, [(1027, 771), (2030, 773)], (128, 64)),
+    ("dW", "bf16", 770, [(1027, 1101), (1101, 2030), (1027, 2003)], (128, 128)),
+])
+def test_every_launch_shape(ctx, half, io, T, shapes, tile):
+    K, N = zip(*shapes)
+    problems = ([T] * len(K), K, N) if half == "dX" else (K, N, [T] * len(K))
+    assert _launch_tile(*problems, io) == tile
+    _case(ctx, shapes, T, io, "f32" if io == "f32" else "bf16", seed=3)
+
+
+def test_infinities_stay_where_they_are(ctx):
+    """What is past a contraction's end must not meet an infinity of a row's last values."""
+    T, shapes = 37, [(45, 70)]
+    for io in ("f32", "bf16"):
+        W, X, dY = torch.ones(45, 70), torch.ones(T, 45), torch.ones(T, 70)
+        dY[36, 69] = float("inf")
+        dt = TDT[io]
+        dX, dW = torch.empty(T, 45, device="cuda", dtype=dt), torch.empty(45, 70, device="cuda", dtype=dt)
+        tf.tf_stage_backward(ctx, shapes, T, CODE[io], [W.to(dt).cuda()], [X.to(dt).cuda()], [dY.to(dt).cuda()], None, [dX], [dW], CODE[io])
+        rX, rW = torch.full((T, 45), 70.0), torch.full((45, 70), 37.0)
+        rX[36], rW[:, 69] = float("inf"), float("inf")
+        assert torch.equal(dX.float().cpu(), rX) and torch.equal(dW.float().cpu(), rW)
