@@ -12,10 +12,15 @@
 //    reproducible by ranking candidates by the image of their stage-wide index under a
 //    keyed permutation of [0, 2^32) (6-round Feistel network on 16-bit halves, round
 //    function: top half of ((half ^ key) + 1) * 0x9E3779B1 mod 2^32) and taking the
-//    lowest ranks.  The rank threshold is found by a radix select over the keys
-//    (digits of 11, 11 and 10 bits): one histogram pass per digit and a one-thread
-//    kernel that picks the bin, all on the stream - the host never waits.
-//    ALU-bound: ~40 integer operations per candidate and pass, 1 bit of traffic.
+//    lowest ranks.  The rank threshold is found by a radix select over the keys (digits of 11, 11
+//    and 10 bits): a histogram of the first digit over all candidates; then the permutation is run
+//    BACKWARDS over the 2^21 keys with that digit, and over the 2^10 with the first two - a key's
+//    element is looked up in the mask - so that only the first digit and the final comparison take
+//    a pass over the elements.  All of it on the stream: the host never waits.
+//    ALU-bound: two keys at a time in 16-bit halves, 5 instructions per round and pair (see Halves),
+//    the top half of a key needs five rounds, and the first round is worked out once for all the
+//    words that a thread visits.  1.74e9 elements, 30 % -> 50 %: 6.2 -> 1.5 ms against four passes of six
+//    rounds each, key by key, with a 32-bit multiplication (a quarter of the rate).
 #include "tf_internal.h"
 
 namespace tf {
@@ -51,15 +56,6 @@ __global__ __launch_bounds__(kSumSlots) void norm_finish_kernel(NormBatch batch)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
     if (threadIdx.x == 0) *batch.t[blockIdx.x].out = x;
-}
-
-__device__ __forceinline__ double block_sum(double x, double* lds4) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) lds4[wave] = x;
-    __syncthreads();
-    return lds4[0] + lds4[1] + lds4[2] + lds4[3];       // meaningful in every thread
 }
 
 __global__ __launch_bounds__(kNormThreads) void norm_kernel(NormBatch batch) {
@@ -102,32 +98,109 @@ __global__ __launch_bounds__(kNormThreads) void norm_kernel(NormBatch batch) {
 // ------------------------------------------------------------------------------------------
 // Budget reconciliation
 // ------------------------------------------------------------------------------------------
-constexpr int kWordsPerThread = 4;
-constexpr int kWordsPerBlock = kThreads * kWordsPerThread;          // 1024 words = 32768 elements
 constexpr int kBins = 2048;
+// A thread visits words that lie 2^16 elements apart: their elements share the low halves of their
+// indices.  A task is 256 neighbouring words in each of kRows such rows of a tensor.
+constexpr int kRowWords = 65536 / 32;
+constexpr int kColumns = kRowWords / kThreads;      // tasks side by side
+constexpr int kRows = 16;
+constexpr int kGrid = 256 * 8;                      // blocks walk the tasks (keyed passes, 4 per compute unit at a time: 2048 blocks 0.67 ms, 1024 0.71)
 
-struct RcWord {
-    uint32_t* ptr;        // the word, or nullptr past the end of the tensor
-    uint32_t valid;       // bits of the word that are elements of the tensor
-    uint32_t index0;      // stage-wide index of bit 0
+struct RcTask {
+    uint32_t* bits;       // the tensor's words
+    int64_t n_words, first;     // first: this thread's first word
+    int64_t numel;
+    uint32_t index0;      // stage-wide index of that word's bit 0
 };
-
-__device__ __forceinline__ RcWord rc_word(const RcBatch& batch, int w) {
+__device__ __forceinline__ RcTask rc_task(const RcBatch& batch, int task) {
     int ti = 0;
-    const int bid = blockIdx.x;
-    for (int i = 1; i < batch.n_tensors; ++i)
-        if (bid >= batch.t[i].block_start) ti = i;
+#pragma unroll
+    for (int step = kMaxRcTensors / 2; step > 0; step >>= 1)
+        if (ti + step < batch.n_tensors && batch.t[ti + step].block_start <= task) ti += step;
     const RcTensor& T = batch.t[ti];
-    const int64_t word = int64_t(bid - T.block_start) * kWordsPerBlock + int64_t(w) * kThreads + threadIdx.x;
-    const int64_t n_words = (T.numel + 31) >> 5;
-    RcWord r;
-    if (word >= n_words) { r.ptr = nullptr; r.valid = 0; r.index0 = 0; return r; }
-    const int64_t left = T.numel - (word << 5);
-    r.ptr = T.bits + word;
-    r.valid = left >= 32 ? 0xffffffffu : ((1u << int(left)) - 1u);
-    r.index0 = uint32_t(T.goff + (word << 5));
+    const int t = task - T.block_start;
+    RcTask r;
+    r.bits = T.bits;
+    r.numel = T.numel;
+    r.n_words = (T.numel + 31) >> 5;
+    r.first = int64_t(t / kColumns) * kRows * kRowWords + (t % kColumns) * kThreads + threadIdx.x;
+    r.index0 = uint32_t(T.goff + (r.first << 5));
     return r;
 }
+// Bits of the word that are elements of the tensor (0 past its end).
+__device__ __forceinline__ uint32_t rc_valid(const RcTask& r, int64_t word) {
+    const int64_t left = r.numel - (word << 5);
+    return left >= 32 ? 0xffffffffu : left > 0 ? (1u << int(left)) - 1u : 0u;
+}
+
+// The round function of the permutation on two 16-bit halves at once: z -> bits 16..31 of (z + 1) C,
+// C = 0x9E3779B1 = Chi 2^16 + Clo.  With p = z Clo + C these are Chi z + (p >> 16), mod 2^16.
+typedef unsigned short U16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t round_pair(uint32_t z, uint32_t c) {
+    uint32_t p0, p1;
+    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(p0) : "v"(z), "s"(0x79B1u), "v"(c));
+    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(p1) : "v"(z), "s"(0x79B1u), "v"(c));
+    const U16x2 high = __builtin_bit_cast(U16x2, __builtin_amdgcn_perm(p1, p0, 0x07060302u));
+    return __builtin_bit_cast(uint32_t, U16x2(__builtin_bit_cast(U16x2, z) * (unsigned short)0x9E37u + high));
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+
+// The top halves of the keys of a word's 32 elements, two per register (element 2 p in the low half).
+// With x0 = high half of the index, x1 = low half, x[r + 2] = x[r] ^ F(x[r + 1] ^ key r), the key is x6 : x7.
+struct Halves {
+    uint32_t a[16];       // x2 without x0, ^ key 1: the first round, the same for all words of a thread
+    uint32_t l[16];       // x1 ^ key 2
+    uint32_t k13, k24, k3, c;
+    bool carry;           // an element of the word has a low half of 0: those from there on have x0 + 1
+    uint32_t low0;
+
+    __device__ __forceinline__ void init(uint32_t index0, const RcKeys& k) {
+        auto twice = [](uint32_t x) { return x * 0x10001u; };
+        c = 0x9E3779B1u;
+        asm("" : "+v"(c));
+        low0 = index0 & 0xffffu;
+        carry = low0 + 31 > 0xffffu;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) {
+            const uint32_t x1 = ((low0 + 2 * p) & 0xffffu) | (low0 + 2 * p + 1) << 16;
+            a[p] = round_pair(x1 ^ twice(k.k[0]), c) ^ twice(k.k[1]);
+            l[p] = x1 ^ twice(k.k[2]);
+        }
+        k13 = twice(k.k[1] ^ k.k[3]);
+        k24 = twice(k.k[2] ^ k.k[4]);
+        k3 = twice(k.k[3]);
+    }
+    // Registers p and p + 1, step by step side by side: an instruction that reads the one before it waits.
+    template <bool kCarry>
+    __device__ __forceinline__ void top(int p, uint32_t high2, uint32_t (&x)[2]) const {
+        uint32_t z2[2], z3[2], z4[2], z5[2], q[2];
+        auto each = [](auto f) __attribute__((always_inline)) { f(0); f(1); };
+        each([&](int j) __attribute__((always_inline)) {
+            const uint32_t e = low0 + 2 * (p + j);
+            z2[j] = a[p + j] ^ (kCarry ? high2 + (e >> 16 | (e + 1) >> 16 << 16) : high2);
+        });
+        round_pair2(z2, q);
+        each([&](int j) __attribute__((always_inline)) { z3[j] = l[p + j] ^ q[j]; });
+        round_pair2(z3, q);
+        each([&](int j) __attribute__((always_inline)) { z4[j] = xor3(z2[j], q[j], k13); });
+        round_pair2(z4, q);
+        each([&](int j) __attribute__((always_inline)) { z5[j] = xor3(z3[j], q[j], k24); });
+        round_pair2(z5, q);
+        each([&](int j) __attribute__((always_inline)) { x[j] = xor3(z4[j], q[j], k3); });
+    }
+    __device__ __forceinline__ void round_pair2(const uint32_t (&z)[2], uint32_t (&q)[2]) const {
+        uint32_t p0, p1, r0, r1;
+        asm("v_mad_u32_u16 %0, %4, %6, %7\n\t"
+            "v_mad_u32_u16 %1, %4, %6, %7 op_sel:[1,0,0,0]\n\t"
+            "v_mad_u32_u16 %2, %5, %6, %7\n\t"
+            "v_mad_u32_u16 %3, %5, %6, %7 op_sel:[1,0,0,0]"
+            : "=&v"(p0), "=&v"(p1), "=&v"(r0), "=&v"(r1) : "v"(z[0]), "v"(z[1]), "s"(0x79B1u), "v"(c));
+        const U16x2 h0 = __builtin_bit_cast(U16x2, __builtin_amdgcn_perm(p1, p0, 0x07060302u));
+        const U16x2 h1 = __builtin_bit_cast(U16x2, __builtin_amdgcn_perm(r1, r0, 0x07060302u));
+        q[0] = __builtin_bit_cast(uint32_t, U16x2(__builtin_bit_cast(U16x2, z[0]) * (unsigned short)0x9E37u + h0));
+        q[1] = __builtin_bit_cast(uint32_t, U16x2(__builtin_bit_cast(U16x2, z[1]) * (unsigned short)0x9E37u + h1));
+    }
+};
 
 __global__ void rc_reset_kernel(RcState* st) {
     for (int i = threadIdx.x; i < kBins; i += blockDim.x) st->hist[i] = 0;
@@ -135,15 +208,26 @@ __global__ void rc_reset_kernel(RcState* st) {
 }
 
 __global__ __launch_bounds__(kThreads) void rc_count_kernel(RcBatch batch, RcState* st) {
-    __shared__ double part[4];
-    uint32_t c = 0;
+    uint32_t c = 0;                                                // a thread's share of fewer than 2^32 elements
+    for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
+        const RcTask r = rc_task(batch, task);
 #pragma unroll
-    for (int w = 0; w < kWordsPerThread; ++w) {
-        const RcWord r = rc_word(batch, w);
-        if (r.ptr) c += __popc(*r.ptr & r.valid);
+        for (int i = 0; i < kRows; ++i) {
+            const int64_t w = r.first + i * kRowWords;            // past the end: the last word, of which nothing counts
+            c += __popc(r.bits[w < r.n_words ? w : r.n_words - 1] & rc_valid(r, w));
+        }
     }
-    const double total = block_sum(double(c), part);               // <= 32768 per block: exact
-    if (threadIdx.x == 0 && total > 0.0) atomicAdd(&st->count, (unsigned long long)total);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
+    // one addition per block: with one per wave the queue at the one address took twice the time of the pass
+    __shared__ uint32_t part[kThreads / 64];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long all = 0;
+        for (int i = 0; i < kThreads / 64; ++i) all += part[i];
+        if (all) atomicAdd(&st->count, all);
+    }
 }
 
 // mode 0: the base mask already holds n_freeze ones; 1: add `need` of its zeros; 2: remove `need` of its ones
@@ -156,32 +240,88 @@ __global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, long 
     if (stats) { stats[0] = (long long)c; stats[1] = st->mode; stats[2] = 0; }
 }
 
-// Histogram of the digit (key >> shift) & (2^nbits - 1) over the candidates whose key starts with
-// the prefix found so far.
-__global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcState* st, RcKeys keys, int shift, int nbits) {
-    __shared__ uint32_t h[kBins];
+// Histogram of the candidates' first digit, the top 11 bits of the key.
+template <bool kCarry>
+__device__ __forceinline__ void rc_hist_word(const Halves& h, uint32_t cand, uint32_t high2, uint32_t* bins) {
+#pragma unroll
+    for (int p = 0; p < 16; p += 2) {
+        uint32_t x[2];
+        h.top<kCarry>(p, high2, x);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            atomicAdd(&bins[(x[j] >> 5) & 0x7ffu], (cand >> (2 * (p + j))) & 1u);
+            atomicAdd(&bins[x[j] >> 21], (cand >> (2 * (p + j) + 1)) & 1u);
+        }
+    }
+}
+__global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcState* st, RcKeys keys) {
+    __shared__ uint32_t bins[kBins];
     const uint32_t mode = st->mode;
     if (mode == 0) return;                                          // block-uniform
-    for (int i = threadIdx.x; i < kBins; i += kThreads) h[i] = 0;
+    for (int i = threadIdx.x; i < kBins; i += kThreads) bins[i] = 0;
     __syncthreads();
-    const uint32_t prefix = st->prefix;
-    const int pbits = int(st->prefix_bits);
-    const uint32_t dmask = (1u << nbits) - 1u;
+    for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
+        const RcTask r = rc_task(batch, task);
+        Halves h;
+        h.init(r.index0, keys);
+        const bool any_carry = __ballot(h.carry) != 0;
+        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
 #pragma unroll 1
-    for (int w = 0; w < kWordsPerThread; ++w) {
-        const RcWord r = rc_word(batch, w);
-        if (!r.ptr) continue;
-        uint32_t cand = (mode == 1 ? ~*r.ptr : *r.ptr) & r.valid;
-        while (cand) {
-            const int b = __ffs(cand) - 1;
-            cand &= cand - 1;
-            const uint32_t key = perm32(r.index0 + uint32_t(b), keys);
-            if (pbits == 0 || (key >> (32 - pbits)) == prefix) atomicAdd(&h[(key >> shift) & dmask], 1u);
+        for (int i = 0; i < kRows; ++i) {
+            const int64_t w = r.first + i * kRowWords;
+            const uint32_t word = next;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            const uint32_t cand = (mode == 1 ? ~word : word) & rc_valid(r, w);
+            if (__ballot(cand != 0) == 0) continue;
+            const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
+            if (any_carry) rc_hist_word<true>(h, cand, high2, bins);
+            else rc_hist_word<false>(h, cand, high2, bins);
         }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += kThreads)
-        if (h[i]) atomicAdd(&st->hist[i], h[i]);
+        if (bins[i]) atomicAdd(&st->hist[i], bins[i]);
+}
+
+// Histogram of the digit behind the prefix, over the candidates whose key starts with the prefix: the
+// 2^open keys are taken back to their indices and those looked up in the mask.  One key per thread;
+// the digit is the top nbits of the open ones.
+__global__ __launch_bounds__(kThreads) void rc_enum_kernel(RcBatch batch, RcState* st, RcKeys keys, int open, int nbits) {
+    __shared__ int64_t start[kMaxRcTensors + 1];
+    const uint32_t mode = st->mode;
+    if (mode == 0) return;
+    if (threadIdx.x < kMaxRcTensors) {
+        const int n = batch.n_tensors, i = threadIdx.x;
+        start[i] = i < n ? batch.t[i].goff : INT64_MAX;
+        if (i == n - 1) start[kMaxRcTensors] = batch.t[i].goff + batch.t[i].numel;
+    }
+    __syncthreads();
+    const uint32_t k = blockIdx.x * kThreads + threadIdx.x;        // grid: 2^open threads
+    uint32_t hi = st->prefix << open | k, lo = hi & 0xffffu;
+    hi >>= 16;
+#pragma unroll
+    for (int r = 5; r >= 0; --r) {                                 // (hi, lo) = (x[r + 1], x[r + 2]) -> (x[r], x[r + 1])
+        const uint32_t x = lo ^ (((hi ^ keys.k[r]) + 1u) * 0x9E3779B1u >> 16);
+        lo = hi;
+        hi = x;
+    }
+    const int64_t index = int64_t(hi << 16 | lo);
+    bool cand = false;
+    if (index >= start[0] && index < start[kMaxRcTensors]) {
+        int t = 0;
+#pragma unroll
+        for (int step = kMaxRcTensors / 2; step > 0; step >>= 1)
+            if (start[t + step] <= index) t += step;
+        const int64_t e = index - start[t];
+        cand = (((batch.t[t].bits[e >> 5] >> (e & 31)) & 1u) != 0) == (mode == 2);
+    }
+    const int below = open - nbits;
+    if (below >= 6) {                                              // a wave's keys have one digit
+        const unsigned long long ones = __ballot(cand);
+        if ((threadIdx.x & 63) == 0 && ones) atomicAdd(&st->hist[k >> below], uint32_t(__popcll(ones)));
+    } else if (cand) {
+        atomicAdd(&st->hist[k >> below], 1u);
+    }
 }
 
 // Pick the bin in which the need-th smallest key lies; extend the prefix by its digit.
@@ -218,25 +358,64 @@ __global__ __launch_bounds__(kThreads) void rc_pick_kernel(RcState* st, int nbit
     for (int q = 0; q < kPer; ++q) st->hist[threadIdx.x * kPer + q] = 0;
 }
 
+// bits << 1 | (x < bound)
+__device__ __forceinline__ uint32_t shift_in_less(uint32_t bits, uint32_t x, uint32_t bound) {
+    asm("v_cmp_gt_u32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(x), "s"(bound) : "vcc");
+    return bits;
+}
+
 // After the last digit the prefix is a full key: the need-th smallest.  Candidates with a key
-// not above it are the drawn ones.
+// not above it are the drawn ones.  The top halves of the keys decide, but for those that equal
+// the threshold's: a word that has one is looked at element by element (one word in 2000).
+template <bool kCarry>
+__device__ __forceinline__ uint32_t rc_drawn(const Halves& h, uint32_t high2, uint32_t threshold, bool& tie) {
+    const uint32_t top = threshold & 0xffff0000u, top2 = top | top >> 16;
+    uint32_t drawn = 0;
+    U16x2 nearest = {0xffff, 0xffff};
+#pragma unroll
+    for (int p = 14; p >= 0; p -= 2) {
+        uint32_t x[2];
+        h.top<kCarry>(p, high2, x);
+#pragma unroll
+        for (int j = 1; j >= 0; --j) {
+            drawn = shift_in_less(drawn, x[j], top);              // the high half's comparison: the low one does not matter
+            drawn = shift_in_less(drawn, x[j] << 16, top);
+            nearest = __builtin_elementwise_min(nearest, __builtin_bit_cast(U16x2, x[j] ^ top2));
+        }
+    }
+    tie = nearest.x == 0 || nearest.y == 0;
+    return drawn;
+}
 __global__ __launch_bounds__(kThreads) void rc_apply_kernel(RcBatch batch, const RcState* st, RcKeys keys) {
     const uint32_t mode = st->mode;
     if (mode == 0) return;
     const uint32_t threshold = st->prefix;
+    for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
+        const RcTask r = rc_task(batch, task);
+        Halves h;
+        h.init(r.index0, keys);
+        const bool any_carry = __ballot(h.carry) != 0;
+        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
 #pragma unroll 1
-    for (int w = 0; w < kWordsPerThread; ++w) {
-        const RcWord r = rc_word(batch, w);
-        if (!r.ptr) continue;
-        const uint32_t old = *r.ptr;
-        uint32_t cand = (mode == 1 ? ~old : old) & r.valid;
-        uint32_t drawn = 0;
-        while (cand) {
-            const int b = __ffs(cand) - 1;
-            cand &= cand - 1;
-            if (perm32(r.index0 + uint32_t(b), keys) <= threshold) drawn |= 1u << b;
+        for (int i = 0; i < kRows; ++i) {
+            const int64_t w = r.first + i * kRowWords;
+            const uint32_t old = next;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
+            if (__ballot(cand != 0) == 0) continue;
+            const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
+            bool tie;
+            uint32_t drawn = any_carry ? rc_drawn<true>(h, high2, threshold, tie) : rc_drawn<false>(h, high2, threshold, tie);
+            drawn &= cand;
+            if (tie) {
+                drawn = 0;
+                for (uint32_t left = cand; left; left &= left - 1) {
+                    const int b = __ffs(left) - 1;
+                    if (perm32(r.index0 + (uint32_t(i) << 16) + uint32_t(b), keys) <= threshold) drawn |= 1u << b;
+                }
+            }
+            if (drawn) r.bits[w] = mode == 1 ? (old | drawn) : (old & ~drawn);
         }
-        if (drawn) *r.ptr = mode == 1 ? (old | drawn) : (old & ~drawn);
     }
 }
 
@@ -246,6 +425,8 @@ __global__ __launch_bounds__(kThreads) void fill_words_kernel(FillBatch batch) {
     for (int64_t w = int64_t(blockIdx.x) * kThreads + threadIdx.x; w < R.n_words; w += int64_t(gridDim.x) * kThreads)
         R.dst[w] = R.value;
 }
+
+int rc_grid(const RcBatch& batch) { return batch.total_blocks < kGrid ? batch.total_blocks : kGrid; }
 
 }  // namespace
 
@@ -261,7 +442,10 @@ hipError_t launch_fill_words(hipStream_t stream, const FillBatch& batch) {
 }
 
 int64_t norm_elems_per_block() { return kNormElemsPerBlock; }
-int64_t rc_elems_per_block() { return int64_t(kWordsPerBlock) * 32; }
+int rc_tasks(int64_t numel) {
+    const int64_t rows = ((numel + 31) / 32 + kRowWords - 1) / kRowWords;
+    return int((rows + kRows - 1) / kRows * kColumns);
+}
 size_t rc_state_bytes() { return sizeof(RcState); }
 
 hipError_t launch_autofreeze_norms(hipStream_t stream, NormBatch& batch, int n_tensors, bool update_snapshot) {
@@ -280,7 +464,7 @@ hipError_t launch_rc_begin(hipStream_t stream, RcState* st) {
 }
 hipError_t launch_rc_count(hipStream_t stream, RcBatch& batch, RcState* st) {
     if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(rc_count_kernel, dim3(batch.total_blocks), dim3(kThreads), 0, stream, batch, st);
+    hipLaunchKernelGGL(rc_count_kernel, dim3((rc_grid(batch) + 1) / 2), dim3(kThreads), 0, stream, batch, st);
     return hipGetLastError();
 }
 hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, int64_t* stats) {
@@ -288,9 +472,14 @@ hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, 
                        reinterpret_cast<long long*>(stats));
     return hipGetLastError();
 }
-hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int shift, int nbits) {
+hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys) {
     if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(rc_hist_kernel, dim3(batch.total_blocks), dim3(kThreads), 0, stream, batch, st, keys, shift, nbits);
+    hipLaunchKernelGGL(rc_hist_kernel, dim3(rc_grid(batch)), dim3(kThreads), 0, stream, batch, st, keys);
+    return hipGetLastError();
+}
+hipError_t launch_rc_enum(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int open, int nbits) {
+    if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(rc_enum_kernel, dim3((1u << open) / kThreads), dim3(kThreads), 0, stream, batch, st, keys, open, nbits);
     return hipGetLastError();
 }
 hipError_t launch_rc_pick(hipStream_t stream, RcState* st, int nbits, bool last, int64_t* stats) {
@@ -300,7 +489,7 @@ hipError_t launch_rc_pick(hipStream_t stream, RcState* st, int nbits, bool last,
 }
 hipError_t launch_rc_apply(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys) {
     if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(rc_apply_kernel, dim3(batch.total_blocks), dim3(kThreads), 0, stream, batch, st, keys);
+    hipLaunchKernelGGL(rc_apply_kernel, dim3(rc_grid(batch)), dim3(kThreads), 0, stream, batch, st, keys);
     return hipGetLastError();
 }
 

@@ -903,15 +903,14 @@ static hipError_t reconcile_passes(hipStream_t stream, int32_t n_tensors, const 
                                    uint32_t* const* elem_bits, int64_t n_freeze, uint64_t seed,
                                    int64_t* stats, RcState* st) {
     const RcKeys keys = perm32_keys(seed);
-    const int64_t epb = rc_elems_per_block();
     // calls fn(batch) for every launch-sized group of tensors, in order
     auto for_each_batch = [&](auto&& fn) -> hipError_t {
         RcBatch b;
         b.n_tensors = 0; b.total_blocks = 0;
         int64_t goff = 0, blocks = 0;
         for (int32_t i = 0; i < n_tensors; ++i) {
-            const int64_t nb = (numel[i] + epb - 1) / epb;
-            if (b.n_tensors == kMaxTensorsPerLaunch || blocks + nb > 0x3fffffff) {
+            const int nb = rc_tasks(numel[i]);
+            if (b.n_tensors == kMaxRcTensors) {
                 b.total_blocks = int32_t(blocks);
                 const hipError_t e = fn(b);
                 if (e != hipSuccess) return e;
@@ -929,9 +928,12 @@ static hipError_t reconcile_passes(hipStream_t stream, int32_t n_tensors, const 
     hipError_t e = launch_rc_begin(stream, st);               // a kernel clears the state: nothing survives from the call before
     if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_count(stream, b, st); });
     if (e == hipSuccess) e = launch_rc_decide(stream, st, uint64_t(n_freeze), stats);
-    const int shifts[3] = {21, 10, 0}, widths[3] = {11, 11, 10};
+    const int open[3] = {32, 21, 10}, widths[3] = {11, 11, 10};        // key bits not fixed yet, bits of the digit
     for (int pass = 0; pass < 3; ++pass) {
-        if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_hist(stream, b, st, keys, shifts[pass], widths[pass]); });
+        if (e == hipSuccess)
+            e = for_each_batch([&](RcBatch& b) {
+                return pass == 0 ? launch_rc_hist(stream, b, st, keys) : launch_rc_enum(stream, b, st, keys, open[pass], widths[pass]);
+            });
         if (e == hipSuccess) e = launch_rc_pick(stream, st, widths[pass], pass == 2, stats);
     }
     if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_apply(stream, b, st, keys); });

@@ -153,11 +153,12 @@ struct RcTensor {
     uint32_t* bits;         // element mask, 1 = frozen, LSB first
     int64_t numel;
     int64_t goff;           // stage-wide index of element 0
-    int32_t block_start;
+    int32_t block_start;    // first task of the tensor inside the launch
     int32_t pad_;
 };
+constexpr int kMaxRcTensors = 64;
 struct RcBatch {            // passed by value as the kernel argument
-    RcTensor t[kMaxTensorsPerLaunch];
+    RcTensor t[kMaxRcTensors];
     int32_t n_tensors;
     int32_t total_blocks;
 };
@@ -199,12 +200,13 @@ struct RcState {            // device memory owned by the context
     uint32_t prefix, prefix_bits;       // leading key bits fixed so far
     uint32_t pad_;
 };
-int64_t rc_elems_per_block();
+int rc_tasks(int64_t numel);        // tasks of a tensor (RcTensor::block_start counts them)
 size_t rc_state_bytes();
 hipError_t launch_rc_begin(hipStream_t stream, RcState* st);
 hipError_t launch_rc_count(hipStream_t stream, RcBatch& batch, RcState* st);
 hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, int64_t* stats);
-hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int shift, int nbits);
+hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys);
+hipError_t launch_rc_enum(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int open, int nbits);
 hipError_t launch_rc_pick(hipStream_t stream, RcState* st, int nbits, bool last, int64_t* stats);
 hipError_t launch_rc_apply(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys);
 

@@ -168,6 +168,23 @@ def test_reconcile_more_tensors_than_one_launch_holds(ctx):
         assert all(np.array_equal(g, e) for g, e in zip(got, ref))
 
 
+@pytest.mark.parametrize("first", [7, 32, 65535])
+@pytest.mark.parametrize("r", [0.2, 0.6])
+def test_reconcile_where_indices_cross_65536_inside_a_word(ctx, first, r):
+    """Tensors of more than 16 rows of 2^16 elements (a task of the keyed passes) that start anywhere in the
+    stage's index space: low halves of the indices wrap inside a word, and with 3.4e6 keys some fifty
+    share the top half of the threshold."""
+    rs = np.random.default_rng(first)
+    numel = [first, 17 * 65536 + 5, 3, 2200001]
+    base = [(rs.random(n) < 0.4).astype(np.uint8) for n in numel]
+    base[3][600000:800000] = 1                                          # stretches without a candidate
+    base[3][900000:1100000] = 0
+    nf = math.floor(r * sum(numel))
+    got, _, stats = _run_reconcile(ctx, base, numel, nf, 9 + first)
+    ref, count = oracle.reconcile_mask(base, numel, nf, 9 + first)
+    assert all(np.array_equal(g, e) for g, e in zip(got, ref)) and stats[0] == count
+
+
 def test_reconcile_threshold_is_the_largest_key_drawn(ctx):
     rs = np.random.default_rng(3)
     numel = [50000, 70001]
