@@ -235,6 +235,18 @@ __device__ __forceinline__ Run make_run(const GemmProblem& P, int m0, int n0) {
     f.nk = P.Kc / kBK;
     return f;
 }
+// The contraction's last 64 values as a run of their own, of a problem whose contraction is no
+// multiple of 64: it overlaps the steps before it, and the step that consumes it masks out what
+// they have contracted already.  So nothing outside the operands is ever fetched.
+template <bool kTN>
+__device__ __forceinline__ Run make_tail_run(const GemmProblem& P, int m0, int n0) {
+    Run f;
+    const int64_t k0 = P.Kc - kBK;
+    f.a = make_side<kTN>(static_cast<const uint16_t*>(P.A) + (kTN ? k0 * P.lda : k0), P.lda, m0);
+    f.b = make_side<kTN>(static_cast<const uint16_t*>(P.B) + (kTN ? k0 * P.ldb : k0), P.ldb, n0);
+    f.nk = 1;
+    return f;
+}
 
 // One direct-to-LDS load: lane i fetches 16 bytes from gbase + voff and the wave's 1 KB lands
 // at LDS byte address lds_wave_base + kLdsOff + 16 i (the LDS address goes through M0).
@@ -288,13 +300,14 @@ struct StreamPos {             // identifies the run held in `nxt`
     int pi;                    // the tile's problem (the first segment's entry)
     int seg, n_seg;            // which contraction segment, segments of the problem
     int m0, n0;                // tile origin
+    bool tail;                 // it is a tail run (kTail kernels)
 };
 
 template <bool kTN>
 __device__ __forceinline__ Run stream_first(StreamPos& c, const GemmBatch& batch, int vb) {
     const TilePos tp = locate_tile(batch, logical_tile(vb, batch.total_tiles, int(gridDim.x)), c.pi);
     c.vb = vb; c.pi = tp.pi; c.m0 = tp.m0; c.n0 = tp.n0;
-    c.seg = 0; c.n_seg = batch.p[tp.pi].n_seg;
+    c.seg = 0; c.n_seg = batch.p[tp.pi].n_seg; c.tail = false;
     return make_run<kTN>(batch.p[c.pi], c.m0, c.n0);
 }
 
@@ -302,9 +315,12 @@ __device__ __forceinline__ Run stream_first(StreamPos& c, const GemmBatch& batch
 // Past the workgroup's last run the stand-in is that run's last step as a run of its own: it
 // is then fetched again, into a stage nobody reads any more, for the two steps by which the
 // matrix cores lag behind the stream, which keeps the main loop free of special cases.
-template <bool kTN>
+template <bool kTN, bool kTail>
 __device__ __forceinline__ void stream_prepare(StreamPos& c, const Run& cur, Run& nxt, const GemmBatch& batch) {
-    if (c.seg + 1 < c.n_seg) {
+    if (kTail && !c.tail) {            // (a problem with a tail has one segment)
+        c.tail = true;
+        nxt = make_tail_run<kTN>(batch.p[c.pi], c.m0, c.n0);
+    } else if (!kTail && c.seg + 1 < c.n_seg) {
         ++c.seg;
         nxt = make_run<kTN>(batch.p[c.pi + c.seg], c.m0, c.n0);
     } else if (c.vb + int(gridDim.x) < batch.total_tiles) {
@@ -561,7 +577,8 @@ __device__ __forceinline__ constexpr FragRead frag_read_at(int u, int i, int jj)
     return {0, 0, 0, 0};
 }
 
-template <bool kTN, bool kOutBf16, bool kAccumulate>
+// kTail: the problems' contractions are no multiples of 64 (and at least 64): a tile's last step is the masked one.
+template <bool kTN, bool kOutBf16, bool kAccumulate, bool kTail>
 __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -589,7 +606,7 @@ __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
     pos.pi = 0;
     Run cur = stream_first<kTN>(pos, batch, int(blockIdx.x));
     Run nxt;
-    stream_prepare<kTN>(pos, cur, nxt, batch);
+    stream_prepare<kTN, kTail>(pos, cur, nxt, batch);
     int kt = 0;
     bool sw = false;           // the position has just entered a new run
     Side lag;                  // shallow side of the step before the one `cur` stands on
@@ -662,11 +679,11 @@ __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
     fill_side<0, 8>(deep(cur), lds_wave_base);
     fill_side<0, 8>(shallow(cur), lds_wave_base + kShallowBase);
     advance();
-    if (sw) stream_prepare<kTN>(pos, cur, nxt, batch);
+    if (sw) stream_prepare<kTN, kTail>(pos, cur, nxt, batch);
     fill_side<0, 8>(deep(cur), lds_wave_base + kTileBytes);
     fill_side<0, 8>(shallow(cur), lds_wave_base + kShallowBase + kTileBytes);
     advance();
-    if (sw) stream_prepare<kTN>(pos, cur, nxt, batch);
+    if (sw) stream_prepare<kTN, kTail>(pos, cur, nxt, batch);
     __builtin_amdgcn_s_waitcnt(0x4f70);        // vmcnt(16): step 0 has landed
     __syncthreads();
 
@@ -719,8 +736,24 @@ __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
     // jj-th MFMA of the row).  `first_tag` says whether it opens a tile: then its first sub-step
     // takes a zero constant as addend.  With one wave per SIMD a wave issues one instruction every
     // 4 cycles and an MFMA occupies the matrix pipe for 16: three other instructions fit behind it.
-    auto contraction_step = [&](auto first_tag) {
-        constexpr bool kFirst = decltype(first_tag)::value;
+    // `drop_tag`: the first 64 - Kc % 64 contraction values of the step are masked out of both operands
+    // (of both, so that an infinity there meets no zero), each fragment once it has arrived.
+    auto contraction_step = [&](auto first_tag, auto drop_tag, int drop) {
+        constexpr bool kFirst = decltype(first_tag)::value, kDrop = decltype(drop_tag)::value;
+        U4 keep;
+        auto keep_of = [&](int u) {                 // of a lane's 8 values of sub-step u: 32 u + 8 (lane / 16) + 0..7
+            const int n = drop - 32 * u - 8 * (int(threadIdx.x & 63) >> 4);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) keep[d] = (2 * d >= n ? 0xffffu : 0u) | (2 * d + 1 >= n ? 0xffff0000u : 0u);
+        };
+        auto mask = [&](bf16x8& f) { f = __builtin_bit_cast(bf16x8, U4(__builtin_bit_cast(U4, f) & keep)); };
+        if constexpr (kDrop) {
+            keep_of(0);
+#pragma unroll
+            for (int q = 0; q < 7; ++q) mask(fa[q]);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) mask(fb[0][q]);
+        }
         // LDS addresses of this step's stages and the next step's: A is the shallow operand, B the deep one
         const uint32_t stage_lds[2][2] = {{lds_base + s0, lds_base + d0}, {lds_base + s1, lds_base + d1}};
         const uint32_t deep_fill = lds_wave_base + d2;
@@ -783,6 +816,14 @@ __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
             if constexpr (u == 1 && i == 0 && jj == 2) rotate_deep(0);     // the step itself works on copies taken at its top
             if constexpr (u == 1 && i == 0 && jj == 3) rotate_deep(1);
             if constexpr (u == 1 && i == 0 && jj == 5) rotate_shallow();
+            if constexpr (kDrop && ((u == 0 && i == 6 && jj == 1) || (u == 1 && i == 3 && jj == 1))) mask(fa[7]);
+            if constexpr (kDrop && u == 0 && i == 7 && jj == 7) {
+                keep_of(1);
+#pragma unroll
+                for (int q = 0; q < 7; ++q) mask(fa[q]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) mask(fb[1][q]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
@@ -794,23 +835,27 @@ __global__ __launch_bounds__(kThreads) void gemm_mfma_kernel(GemmBatch batch) {
     int fill_left = cur.nk - kt;                   // steps until the fill position enters a new run
     auto after_step = [&]() {
         if (__builtin_expect(--fill_left == 0, 0)) {
-            stream_prepare<kTN>(pos, cur, nxt, batch);
+            stream_prepare<kTN, kTail>(pos, cur, nxt, batch);
             fill_left = cur.nk;
         }
     };
     for (;;) {
         const int cnk = tile_steps(batch, ct.pi);
-        contraction_step(std::true_type{});
+        contraction_step(std::true_type{}, std::false_type{}, 0);
         after_step();
         for (int k = 1; k < cnk; ++k) {
-            contraction_step(std::false_type{});
+            contraction_step(std::false_type{}, std::false_type{}, 0);
+            after_step();
+        }
+        if constexpr (kTail) {
+            contraction_step(std::false_type{}, std::true_type{}, kBK - batch.p[ct.pi].Kc % kBK);
             after_step();
         }
         // The deep stage that the last step consumed (d2 after the rotation) is the epilogue's:
         // every wave is past that step's barrier, and its next fill is issued by the next step.
         const GemmProblem& P = batch.p[ct.pi];
         if (__builtin_expect(ct.whole(), 1))
-            store_block<kOutBf16, kAccumulate, kTN ? 2 : 1, false>(acc, lds + d2 + wave * kEpiBytes, P.C, P.N,
+            store_block<kOutBf16, kAccumulate, kTN && !kTail ? 2 : 1, false>(acc, lds + d2 + wave * kEpiBytes, P.C, P.N,
                                                                    ct.m0 + wm * 128, ct.n0 + wn * 128);
         else
             store_block<kOutBf16, kAccumulate, 1, true>(acc, lds + d2 + wave * kEpiBytes, P.C, P.N,
@@ -843,9 +888,9 @@ int compute_units(int dev) {
     return cached[dev];
 }
 
-template <bool kTN, bool kOutBf16, bool kAccumulate>
+template <bool kTN, bool kOutBf16, bool kAccumulate, bool kTail>
 hipError_t launch_one(hipStream_t stream, const GemmBatch& batch) {
-    auto kern = gemm_mfma_kernel<kTN, kOutBf16, kAccumulate>;
+    auto kern = gemm_mfma_kernel<kTN, kOutBf16, kAccumulate, kTail>;
     // the 160 KB of dynamic LDS are allowed once per kernel instantiation and device
     static bool lds_allowed[kMaxDevices] = {false};
     const int dev = current_device();
@@ -890,26 +935,38 @@ namespace tf {
 
 bool mfma_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb,
                    int64_t rows_before, int64_t rows_after) {
+    return Kc % kBK == 0 && mfma_tail_shape_ok(layout, M, N, Kc, lda, ldb, rows_before, rows_after);
+}
+
+bool mfma_tail_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb,
+                        int64_t rows_before, int64_t rows_after) {
     // 16-byte direct loads and 16-byte stores: row pitches (C's is N) must keep every row 16-byte
     // aligned, and 256 rows of either operand must lie within the 32-bit per-lane offsets of a stage fill
     constexpr int64_t kMaxPitch = int64_t(1) << 22;
-    if (!(M > 0 && N >= kBN && Kc > 0 && Kc % kBK == 0 && N % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 &&
+    if (!(M > 0 && N >= kBN && Kc >= kBK && N % 8 == 0 && lda % 8 == 0 && ldb % 8 == 0 &&
           lda <= kMaxPitch && ldb <= kMaxPitch))
         return false;
-    if (layout == Layout::kTN && M % 8 != 0) return false;           // a window's first column of A stays 16-byte aligned
+    if (layout == Layout::kTN ? M % 8 != 0 : Kc % 8 != 0) return false;   // a window's first column / contraction value stays 16-byte aligned
     return M >= kBM || rows_before + rows_after >= kBM - M;          // a 256-row window must fit into what exists
 }
 
-hipError_t launch_gemm_mfma_bf16(hipStream_t stream, GemmBatch& batch, int n_problems,
-                                 Layout layout, Dtype out_dtype, bool accumulate) {
-    batch.n_problems = n_problems;
-    if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
-    const bool tn = layout == Layout::kTN;
+template <bool kTail>
+static hipError_t launch_typed(hipStream_t stream, const GemmBatch& batch, bool tn, Dtype out_dtype, bool accumulate) {
     if (out_dtype == Dtype::BF16)
-        return tn ? launch_one<true, true, false>(stream, batch) : launch_one<false, true, false>(stream, batch);
+        return tn ? launch_one<true, true, false, kTail>(stream, batch) : launch_one<false, true, false, kTail>(stream, batch);
     // fp32 outputs are weight gradients (an input gradient has the inputs' type)
     if (!tn) return hipErrorInvalidValue;
-    return accumulate ? launch_one<true, false, true>(stream, batch) : launch_one<true, false, false>(stream, batch);
+    return accumulate ? launch_one<true, false, true, kTail>(stream, batch) : launch_one<true, false, false, kTail>(stream, batch);
+}
+
+hipError_t launch_gemm_mfma_bf16(hipStream_t stream, GemmBatch& batch, int n_problems,
+                                 Layout layout, Dtype out_dtype, bool accumulate, bool tail) {
+    batch.n_problems = n_problems;
+    if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
+    for (int i = 0; i < n_problems; ++i)
+        if ((batch.p[i].Kc % kBK != 0) != tail || (tail && (batch.p[i].n_seg != 1 || batch.p[i].Kc < kBK))) return hipErrorInvalidValue;
+    const bool tn = layout == Layout::kTN;
+    return tail ? launch_typed<true>(stream, batch, tn, out_dtype, accumulate) : launch_typed<false>(stream, batch, tn, out_dtype, accumulate);
 }
 
 }  // namespace tf

@@ -111,46 +111,91 @@ inline bool planned_mfma_ok(const Planned& it, Layout layout, Dtype in_dtype) {
            aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
 }
 
+inline bool planned_tail_ok(const Planned& it, Layout layout, Dtype in_dtype) {
+    return in_dtype == Dtype::BF16 && mfma_tail_shape_ok(layout, it.M, it.N, it.Kc, it.lda, it.ldb, it.rows_before, it.rows_after) &&
+           aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
+}
+
+// What a launch is expected to take.  Its work spread evenly over the compute units and its longest
+// chain of steps overlap for the most part; `overlap` says how much of the smaller of the two is left.
+struct Estimate {
+    double work = 0, longest = 0, tiles = 0;
+    void add(const Planned& it, int tile_m, int tile_n, int per_step, double tile_steps, double chain_steps) {
+        const double steps = std::ceil(double(it.Kc) / per_step);
+        const double n = std::ceil(double(it.M) / tile_m) * std::ceil(double(it.N) / tile_n);
+        tiles += n;
+        work += n * (steps + tile_steps);
+        longest = std::max(longest, steps + chain_steps);
+    }
+    static double us(double even, double chain, double overlap) { return std::max(even, chain) + overlap * std::min(even, chain); }
+};
+
 // Launch shape of the generic kernel for these problems: the one with the least estimated time.  The
-// work spread evenly over the compute units and the longest chain of steps overlap for the most
-// part: the larger of the two plus a quarter of the smaller was within 15 % of the measured times and
-// in their order (input gradients of a LLaMA-1B block, 200 tokens: 64 x 64 tiles 65 us, 128 x 64
-// 69, 128 x 128 91; 3001 tokens: 605, 485, 400).
-int pick_generic_shape(const std::vector<Planned>& items, Dtype in_dtype) {
-    const int per_step = in_dtype == Dtype::BF16 ? 64 : 32, units = compute_units();
+// estimates were within 15 % of the measured times and in their order (input gradients of a LLaMA-1B
+// block, 200 tokens: 64 x 64 tiles 65 us, 128 x 64 69, 128 x 128 91; 3001 tokens: 605, 485, 400).
+int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype, double* best_us) {
     int best = 0;
-    double best_us = 0;
+    *best_us = 0;
+    if (items.empty()) return best;
     for (int i = 0; i < kGenericShapes; ++i) {
         const GenericShape& s = generic_shape(in_dtype, i);
-        double work = 0, longest = 0;
-        for (const Planned& it : items) {
-            const double steps = std::ceil(double(it.Kc) / per_step) + s.tile_steps;
-            work += std::ceil(double(it.M) / s.tile_m) * std::ceil(double(it.N) / s.tile_n) * steps;
-            longest = std::max(longest, steps);
-        }
-        const double even = work / units * s.step_us, chain = longest * s.chain_us;
-        const double us = std::max(even, chain) + 0.25 * std::min(even, chain);
-        if (i == 0 || us < best_us) { best = i; best_us = us; }
+        Estimate e;
+        for (const Planned* it : items) e.add(*it, s.tile_m, s.tile_n, in_dtype == Dtype::BF16 ? 64 : 32, s.tile_steps, s.tile_steps);
+        const double us = Estimate::us(e.work / compute_units() * s.step_us, e.longest * s.chain_us, 0.25);
+        if (i == 0 || us < *best_us) { best = i; *best_us = us; }
     }
     return best;
 }
 
-// Launch `items` in batches of at most kMaxProblemsPerLaunch, MFMA-eligible ones on the
-// matrix cores, the rest on the generic kernel.
+// The 256 x 256-tile kernel on these problems.  A step takes 1.45 us when all units are busy (the power
+// limit), 1.15 in the long tiles at a launch's end, 1.0 when there are fewer tiles than units; a tile's
+// epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages.  Measured
+// against the generic kernel, us, in brackets the latter: LLaMA-1B block, input gradients, 512 tokens
+// 134 (92), 1024 191 (158), 2048 242 (288); LLaMA-8B block 512 tokens 335 (274), 1024 423 (500); weight
+// gradients of width 512, 256 tokens 16 (9), of the LLaMA-1B block, 256 tokens 49 (64).
+double tile256_us(const std::vector<const Planned*>& items, bool tail) {
+    if (items.empty()) return 0;
+    Estimate e;
+    for (const Planned* it : items) e.add(*it, gemm_mfma_tile(), gemm_mfma_tile(), 64, tail ? 5.5 : 4.5, tail ? 7 : 6);
+    const int units = compute_units();
+    return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
+}
+
+// Launch `items` in batches of at most kMaxProblemsPerLaunch: on the 256 x 256-tile kernel what it
+// takes, on the generic kernel the rest - and what it takes when the generic one's smaller tiles
+// are expected to be done first (few tiles, or few long ones).
 hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
                           Dtype in_dtype, Dtype out_dtype, bool accumulate) {
-    std::vector<Planned> fast, slow;
+    // problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
+    enum { kWhole = 0, kTail = 1, kOther = 2 };
+    std::vector<const Planned*> cls[3];
+    bool plain = true;                          // no row bits, no segments: the generic kernel could take them too
     for (const Planned& it : items) {
         bool ok = planned_mfma_ok(it, layout, in_dtype);
         for (const Planned& q : it.more) ok = ok && planned_mfma_ok(q, layout, in_dtype);
-        if (ok) fast.push_back(it);
-        else if (~it.row_bits != 0 || !it.more.empty()) return hipErrorInvalidValue;   // only the matrix-core kernel knows these
-        else slow.push_back(it);
+        const bool special = ~it.row_bits != 0 || !it.more.empty();
+        if (ok) { cls[kWhole].push_back(&it); plain = plain && !special; }
+        else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
+        else cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
     }
-    // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
-    auto by_cost = [](const Planned& a, const Planned& b) { return a.total_kc() > b.total_kc(); };
-    std::stable_sort(fast.begin(), fast.end(), by_cost);
-    std::stable_sort(slow.begin(), slow.end(), by_cost);
+    double generic_us;
+    int shape[3] = {-1, -1, -1};                // of the generic kernel; -1: 256 x 256 tiles
+    if (plain) {
+        const int s = pick_generic_shape(cls[kWhole], in_dtype, &generic_us);
+        if (generic_us < tile256_us(cls[kWhole], false)) shape[kWhole] = s;
+    }
+    if (!cls[kTail].empty()) {
+        std::vector<const Planned*> both = cls[kTail];
+        both.insert(both.end(), cls[kOther].begin(), cls[kOther].end());
+        double rest_us;
+        pick_generic_shape(both, in_dtype, &generic_us);
+        pick_generic_shape(cls[kOther], in_dtype, &rest_us);
+        if (generic_us < tile256_us(cls[kTail], true) + rest_us) {
+            cls[kOther] = both;
+            cls[kTail].clear();
+        }
+    }
+    shape[kOther] = pick_generic_shape(cls[kOther], in_dtype, &generic_us);
 
     GemmBatch batch;
     auto fill = [](GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
@@ -164,17 +209,18 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
         const int64_t after = std::min(it.rows_after, short_by), before = std::min(it.rows_before, short_by - after);
         gp.m_slack = uint32_t(before) | (uint32_t(after) << 16);
     };
-    for (int pass = 0; pass < 2; ++pass) {
-        const std::vector<Planned>& v = pass == 0 ? fast : slow;
-        const int shape = pass == 0 ? 0 : pick_generic_shape(slow, in_dtype);
-        const int64_t tile_m = pass == 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape).tile_m;
-        const int64_t tile_n = pass == 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape).tile_n;
+    for (int c = 0; c < 3; ++c) {
+        std::vector<const Planned*>& v = cls[c];
+        // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
+        std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
+        const int64_t tile_m = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_m;
+        const int64_t tile_n = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_n;
         size_t i = 0;
         while (i < v.size()) {
             int n = 0;
             int64_t tiles = 0;
             while (i < v.size()) {
-                const Planned& it = v[i];
+                const Planned& it = *v[i];
                 const int slots = 1 + int(it.more.size());
                 if (slots > kMaxProblemsPerLaunch) return hipErrorInvalidValue;
                 if (n + slots > kMaxProblemsPerLaunch) break;
@@ -188,11 +234,11 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
                 ++i;
             }
             batch.total_tiles = int32_t(tiles);
-            const int kind = (layout == Layout::kNT ? TF_KERNEL_DX_MFMA : TF_KERNEL_DW_MFMA) + (pass == 0 ? 0 : 2);
+            const int kind = (layout == Layout::kNT ? TF_KERNEL_DX_MFMA : TF_KERNEL_DW_MFMA) + (c == kWhole ? 0 : 2);
             ProfScope prof(ctx, stream, kind);
-            const hipError_t e = pass == 0
-                ? launch_gemm_mfma_bf16(stream, batch, n, layout, out_dtype, accumulate)
-                : launch_gemm_generic(stream, batch, n, shape, layout, in_dtype, out_dtype, accumulate);
+            const hipError_t e = shape[c] < 0
+                ? launch_gemm_mfma_bf16(stream, batch, n, layout, out_dtype, accumulate, c == kTail)
+                : launch_gemm_generic(stream, batch, n, shape[c], layout, in_dtype, out_dtype, accumulate);
             if (e != hipSuccess) return e;
         }
     }
@@ -1058,14 +1104,18 @@ int tf_row_blocks_to_bits(tf_ctx* ctx, void* hip_stream,
 
 }  // extern "C"
 
-// Test hook (not part of the public header): which launch shape of the generic kernel a call with these
-// problems gets; its tile goes to tile[0..1].
-extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, int in_dtype, int32_t* tile) {
+// Test hook (not part of the public header): which launch shape of the generic kernel a launch of these
+// problems gets, its tile goes to tile[0..1]; and what it and the 256 x 256-tile kernel (for problems
+// whose contraction is a multiple of 64, or for all others) are expected to take, us[0..1].
+extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, int in_dtype, int32_t* tile, double* us) {
     std::vector<Planned> items;
     for (int i = 0; i < n; ++i) items.push_back(Planned{nullptr, nullptr, nullptr, M[i], N[i], Kc[i], 0, 0, ~0ull, {}});
-    const int shape = pick_generic_shape(items, to_dtype(tf_dtype(in_dtype)));
-    const GenericShape& s = generic_shape(to_dtype(tf_dtype(in_dtype)), shape);
-    tile[0] = s.tile_m;
-    tile[1] = s.tile_n;
+    std::vector<const Planned*> p;
+    for (const Planned& it : items) p.push_back(&it);
+    const Dtype dt = to_dtype(tf_dtype(in_dtype));
+    const int shape = pick_generic_shape(p, dt, us);
+    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0);
+    tile[0] = generic_shape(dt, shape).tile_m;
+    tile[1] = generic_shape(dt, shape).tile_n;
     return shape;
 }

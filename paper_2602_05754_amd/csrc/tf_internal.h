@@ -71,8 +71,12 @@ int compute_units();              // of the current device
 // pitches multiples of 8 and at most 2^22.  Extents need not be multiples of the 256 x 256 tile.
 bool mfma_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb,
                    int64_t rows_before = 0, int64_t rows_after = 0);
+// The same for a contraction that is no multiple of 64 (it may be one): at least 64, in layout kNT a
+// multiple of 8.  A launch holds problems of one kind, `tail` = no multiples of 64, one segment each.
+bool mfma_tail_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb,
+                        int64_t rows_before = 0, int64_t rows_after = 0);
 hipError_t launch_gemm_mfma_bf16(hipStream_t stream, GemmBatch& batch, int n_problems,
-                                 Layout layout, Dtype out_dtype, bool accumulate);
+                                 Layout layout, Dtype out_dtype, bool accumulate, bool tail);
 int gemm_mfma_tile();             // tile edge of the MFMA kernel (square)
 int persistent_grid(int total_tiles, int units);    // workgroups of an MFMA launch on `units` compute units
 

@@ -24,13 +24,14 @@ def ctx():
     c.close()
 
 
-def _launch_tile(M, N, Kc, io):
-    """Tile of the launch shape that a call with these problems gets."""
+def _expected(M, N, Kc, io):
+    """Tile of the generic kernel's launch shape for these problems, and the expected times of it and of the
+    256 x 256-tile kernel."""
     n = len(M)
     arr = lambda v: (ctypes.c_int64 * n)(*v)
-    tile = (ctypes.c_int32 * 2)()
-    tf.load_library().tf_internal_generic_shape(n, arr(M), arr(N), arr(Kc), CODE[io], tile)
-    return tuple(tile)
+    tile, us = (ctypes.c_int32 * 2)(), (ctypes.c_double * 2)()
+    tf.load_library().tf_internal_generic_shape(n, arr(M), arr(N), arr(Kc), CODE[io], tile, us)
+    return tuple(tile), us[0], us[1]
 
 
 class Guarded:
@@ -64,7 +65,7 @@ def _case(ctx, shapes, T, io, dw, accumulate=False, seed=0):
         oracle.stage_backward(shapes, T, f64(W), f64(X), f64(dY), np.zeros(L, np.uint8), rX, rW, accumulate=accumulate)
     else:                                                            # the same in numpy, for the oracle's loops too much
         rX = [y @ w.T for y, w in zip(f64(dY), f64(W))]
-        rW = [x.T @ y for x, y in zip(f64(X), f64(dY))]
+        rW = [r + x.T @ y for r, x, y in zip(rW, f64(X), f64(dY))]
     gX = [Guarded((T, k), io) for k, n in shapes]
     gW = [Guarded(s, dw, torch.from_numpy(o) if accumulate else None) for s, o in zip(shapes, old)]
     tf.tf_stage_backward(ctx, shapes, T, CODE[io], [dev(a, io) for a in W], [dev(a, io) for a in X], [dev(a, io) for a in dY],
@@ -110,19 +111,46 @@ def test_edges_of_tiles_steps_and_pieces(ctx, io, dw, accumulate, T, shapes):
 def test_every_launch_shape(ctx, half, io, T, shapes, tile):
     K, N = zip(*shapes)
     problems = ([T] * len(K), K, N) if half == "dX" else (K, N, [T] * len(K))
-    assert _launch_tile(*problems, io) == tile
+    assert _expected(*problems, io)[0] == tile
     _case(ctx, shapes, T, io, "f32" if io == "f32" else "bf16", seed=3)
 
 
-def test_infinities_stay_where_they_are(ctx):
-    """What is past a contraction's end must not meet an infinity of a row's last values."""
-    T, shapes = 37, [(45, 70)]
-    for io in ("f32", "bf16"):
-        W, X, dY = torch.ones(45, 70), torch.ones(T, 45), torch.ones(T, 70)
-        dY[36, 69] = float("inf")
+@pytest.mark.parametrize("dw,accumulate", [("bf16", False), ("f32", False), ("f32", True)])
+@pytest.mark.parametrize("T,shapes", [
+    # layers large enough for 256 x 256 tiles to pay: contractions of the weight gradients with 1, 63, 1, 8 and 1
+    # values more than whole steps; ragged last tiles
+    (1025, [(4096, 4096), (4096, 2048)]),
+    (1087, [(4104, 2048), (4096, 4104)]),
+    (577, [(4096, 4104), (4104, 2056)]),
+    (264, [(4096, 2056), (2568, 4096), (2048, 2376)]),
+    (65, [(8192, 4104), (8192, 4104)]),
+])
+def test_contractions_that_are_no_multiple_of_a_step_on_256_tiles(ctx, T, shapes, dw, accumulate):
+    K, N = zip(*shapes)
+    _, generic, tiles256 = _expected(K, N, [T] * len(K), "bf16")
+    assert tiles256 < generic                                        # so this is the route
+    _case(ctx, shapes, T, "bf16", dw, accumulate, seed=T)
+
+
+def test_input_gradients_over_ragged_feature_counts_on_256_tiles(ctx):
+    T, shapes = 2048, [(4096, 1032), (4104, 1096), (4096, 328)]
+    K, N = zip(*shapes)
+    _, generic, tiles256 = _expected([T] * 3, K, N, "bf16")
+    assert tiles256 < generic
+    _case(ctx, shapes, T, "bf16", "bf16", seed=5)
+
+
+@pytest.mark.parametrize("io,T,K,N", [("f32", 37, 45, 70), ("bf16", 37, 45, 70), ("bf16", 577, 4096, 8200), ("bf16", 2048, 4096, 1096)])
+def test_infinities_stay_where_they_are(ctx, io, T, K, N):
+    """What a last step takes from outside the contraction, or a second time, must not meet an infinity."""
+    for t, n in ((T - 1, N - 1), (T - 64, N - 64)):
+        if t < 0:
+            continue
+        W, X, dY = torch.ones(K, N), torch.ones(T, K), torch.ones(T, N)
+        dY[t, n] = float("inf")
         dt = TDT[io]
-        dX, dW = torch.empty(T, 45, device="cuda", dtype=dt), torch.empty(45, 70, device="cuda", dtype=dt)
-        tf.tf_stage_backward(ctx, shapes, T, CODE[io], [W.to(dt).cuda()], [X.to(dt).cuda()], [dY.to(dt).cuda()], None, [dX], [dW], CODE[io])
-        rX, rW = torch.full((T, 45), 70.0), torch.full((45, 70), 37.0)
-        rX[36], rW[:, 69] = float("inf"), float("inf")
+        dX, dW = torch.empty(T, K, device="cuda", dtype=dt), torch.empty(K, N, device="cuda", dtype=dt)
+        tf.tf_stage_backward(ctx, [(K, N)], T, CODE[io], [W.to(dt).cuda()], [X.to(dt).cuda()], [dY.to(dt).cuda()], None, [dX], [dW], CODE[io])
+        rX, rW = torch.full((T, K), float(N)).to(dt).float(), torch.full((K, N), float(T)).to(dt).float()
+        rX[t], rW[:, n] = float("inf"), float("inf")
         assert torch.equal(dX.float().cpu(), rX) and torch.equal(dW.float().cpu(), rW)
