@@ -251,42 +251,68 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     const int steps = Kc / OpA::kBK + (Kc % OpA::kBK != 0);
     // steps whose pieces are whole: all but the last one
     const int free_steps = a.narrow || b.narrow ? 0 : steps - 1;
-    f32x4 acc[OpA::kFrags][OpB::kFrags];
+    constexpr bool kWide = sizeof(TIn) == 2;            // 32 contraction values per instruction, not 4
+    // fp32: the products of a step (8 instructions of 4) are summed by themselves and then added to the sums
+    // so far.  In the smallest tiles, for calls that wait for memory more than for the matrix pipe, those
+    // of each instruction are, and the sums are kept in 64 bits.  Error against 64 bits,
+    // contraction 256: 4.0e-8 and 1.2e-7 (one chain of additions: 2.9e-7).
+    constexpr bool kExact = !kWide && OpA::kFrags * OpB::kFrags == 1;
+    typedef std::conditional_t<kExact, double, float> Sum;
+    typedef Sum Sum4 __attribute__((ext_vector_type(4)));
+    Sum4 acc[OpA::kFrags][OpB::kFrags];
 #pragma unroll
     for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
-        for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] = Sum4{0, 0, 0, 0};
 
     const int wm = wave >> 1, wn = wave & 1;
-    constexpr bool kWide = sizeof(TIn) == 2;            // 32 contraction values per instruction, not 4
     auto contract = [&](const char* stage) {
-        // fp32: a step's 32 products are summed by themselves and then added to the sums so far.  The
-        // error grows with the root of 32 + K / 32 instead of the root of K (against 64 bits, K = 256:
-        // 2.9e-7 -> 1.3e-7), the additions ride beside the matrix instructions.
-        f32x4 part[OpA::kFrags][OpB::kFrags];
+        U4 fa[2][OpA::kFrags], fb[2][OpB::kFrags];
+        auto fragments = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            U4 fa[OpA::kFrags], fb[OpB::kFrags];
+            for (int i = 0; i < OpA::kFrags; ++i) fa[u][i] = OpA::fragment(stage, wm * OpA::kFrags + i, u);
 #pragma unroll
-            for (int i = 0; i < OpA::kFrags; ++i) fa[i] = OpA::fragment(stage, wm * OpA::kFrags + i, u);
+            for (int j = 0; j < OpB::kFrags; ++j) fb[u][j] = OpB::fragment(stage + OpA::kStageBytes, wn * OpB::kFrags + j, u);
+        };
+        // D rows <- n (B rows), D columns <- m: a lane then owns 4 consecutive n of one output row
+        if constexpr (kWide) {
 #pragma unroll
-            for (int j = 0; j < OpB::kFrags; ++j) fb[j] = OpB::fragment(stage + OpA::kStageBytes, wn * OpB::kFrags + j, u);
-            // D rows <- n (B rows), D columns <- m: a lane then owns 4 consecutive n of one output row
-#pragma unroll
-            for (int e = 0; e < (kWide ? 1 : 4); ++e)
+            for (int u = 0; u < 2; ++u) {
+                fragments(u);
 #pragma unroll
                 for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
-                    for (int j = 0; j < OpB::kFrags; ++j) {
-                        if constexpr (kWide)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[j]),
-                                                                               __builtin_bit_cast(bf16x8, fa[i]), acc[i][j], 0, 0, 0);
-                        else
-                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[j][e]), __uint_as_float(fa[i][e]),
+                    for (int j = 0; j < OpB::kFrags; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fb[u][j]),
+                                                                           __builtin_bit_cast(bf16x8, fa[u][i]), acc[i][j], 0, 0, 0);
+            }
+        } else if constexpr (kExact) {
+            f32x4 part[8];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                fragments(u);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    part[4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[u][0][e]), __uint_as_float(fa[u][0][e]),
+                                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            }
+            wait_for_sums();
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[0][0] += __builtin_convertvector(part[q], Sum4);
+        } else {
+            f32x4 part[OpA::kFrags][OpB::kFrags];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                fragments(u);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < OpA::kFrags; ++i)
+#pragma unroll
+                        for (int j = 0; j < OpB::kFrags; ++j)
+                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[u][j][e]), __uint_as_float(fa[u][i][e]),
                                                                               u == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[i][j], 0, 0, 0);
-                    }
-        }
-        if constexpr (!kWide) {
+            }
             wait_for_sums();
 #pragma unroll
             for (int i = 0; i < OpA::kFrags; ++i)
@@ -348,7 +374,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 #pragma unroll
         for (int j = 0; j < OpB::kFrags; ++j) {
             const int r = wm * (kTileM / 2) + 16 * i + (lane & 15), c = wn * (kTileN / 8) + 4 * j + (lane >> 4);
-            *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
+            *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = __builtin_convertvector(acc[i][j], f32x4);
         }
     __syncthreads();
     constexpr int kOutE = kOutBf16 ? 8 : 4, kLanes = kTileN / kOutE, kRowsPerPass = kThreads / kLanes;
@@ -391,11 +417,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 // Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps are
 // bound by the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
 // tokens: 128 x 128 tiles 906 TFLOP/s, 128 x 64 753, 64 x 64 598), the fp32 steps by the matrix pipe
-// (2048 tokens, width 1024: 128 x 64 tiles 125 TFLOP/s, 32 x 64 115, 32 x 32 105).
-// Small tiles are for calls with few of them: an fp32 chain of 64 steps takes 24 us in 32 x 32 tiles,
-// 30 in 32 x 64, 46 in 64 x 64, 96 in 128 x 64 and 155 in 128 x 128.
+// (2048 tokens, width 1024: 128 x 64 tiles 125 TFLOP/s, 32 x 64 115; 512 tokens, width 512: 32 x 64 46 us, 32 x 32 with
+// its sums in 64 bits 78).
+// Small tiles are for calls with few of them: an fp32 chain of 64 steps takes 30 us in 32 x 32 and 32 x 64 tiles,
+// 46 in 64 x 64, 96 in 128 x 64 and 155 in 128 x 128.
 constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 1.7f}, {128, 64, 0.348f, 0.45f, 2.5f}, {128, 128, 0.575f, 0.60f, 3.4f}};
-constexpr GenericShape kShapes32[] = {{32, 32, 0.157f, 0.30f, 1.0f}, {32, 64, 0.286f, 0.40f, 1.0f}, {128, 64, 1.04f, 1.45f, 1.0f}};
+constexpr GenericShape kShapes32[] = {{32, 32, 0.28f, 0.43f, 1.0f}, {32, 64, 0.286f, 0.40f, 1.0f}, {128, 64, 1.04f, 1.45f, 2.0f}};
 static_assert(sizeof(kShapes16) == kGenericShapes * sizeof(GenericShape) && sizeof(kShapes32) == sizeof(kShapes16), "as many for both types");
 
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate>
