@@ -126,6 +126,8 @@ def load_library():
     lib.tf_reconcile_mask.argtypes = [vp, vp, i32, vp, vp, i64, ctypes.c_uint64, vp]
     lib.tf_reconcile_mask_static.restype = ctypes.c_int
     lib.tf_reconcile_mask_static.argtypes = [vp, vp, i32, vp, vp, i64, ctypes.c_uint64, vp]
+    lib.tf_internal_check_tables.restype = ctypes.c_int
+    lib.tf_internal_check_tables.argtypes = [i32, vp, i32, vp, i32]
     _lib = lib
     return lib
 
@@ -169,9 +171,11 @@ class PtrTable:
         self._items = list(seq)
         n = len(self._items)
         self.arr = (ctypes.c_void_p * max(n, 1))()
-        self.nbytes = np.full(n, np.iinfo(np.int64).max, dtype=np.int64)     # raw ints: size unknown
-        self.dtype_code = np.full(n, -2, dtype=np.int64)                     # -2 unknown (raw int), -1 neither f32 nor bf16
-        self.device = np.full(n, -2, dtype=np.int64)                         # -2 unknown, -1 host
+        self._info = np.empty((4, n), dtype=np.int64)                        # rows of tf_internal_check_tables
+        self.nbytes, self.dtype_code, self.device = self._info[:3]
+        self.nbytes[:] = np.iinfo(np.int64).max                              # raw ints: size unknown
+        self.dtype_code[:] = -2                                              # -2 unknown (raw int), -1 neither f32 nor bf16
+        self.device[:] = -2                                                  # -2 unknown, -1 host
         for i, x in enumerate(self._items):
             self.arr[i] = _dptr(x)
             if x is not None and not isinstance(x, int):
@@ -181,6 +185,8 @@ class PtrTable:
                 self.dtype_code[i] = _DTYPE_CODE.get(str(x.dtype), -1)
                 self.device[i] = _device_index(x)
         self.present = np.array([x is not None for x in self._items], dtype=bool)
+        self._info[3] = self.present
+        self.info_address = self._info.ctypes.data
         self.ptr = ctypes.cast(self.arr, ctypes.c_void_p)
 
     def __len__(self):
@@ -271,6 +277,30 @@ def _check_seq(seq, numels, dtype_code, what, skip=None, ctx=None):
         _check_numel(x, int(numels[i]), dtype_code, f"{what}[{i}]", ctx)
 
 
+def _check_all(ctx, n, skip, tables):
+    """_check_seq over several lists: (list, a, b, stride, scale, element type, what, whether `skip` is looked
+    at), the elements needed being a[i] * b[i] * scale (b may be None; a and b views with that stride).
+    Lists that were marshalled once are checked by one native call; what does not pass there, and
+    all other lists, go through _check_seq, which says what is wrong."""
+    desc, rest = [], []
+    for t in tables:
+        seq, a, b, stride, scale, code = t[:6]
+        if seq is None:
+            continue
+        if isinstance(seq, PtrTable) and len(seq) == n and n > 0:
+            desc += [seq.info_address, a.ctypes.data, b.ctypes.data if b is not None else 0, stride, scale, code, t[7], 0]
+        else:
+            rest.append(t)
+    if desc:
+        arr = (ctypes.c_int64 * len(desc))(*desc)
+        bad = load_library().tf_internal_check_tables(len(desc) // 8, arr, n, None if skip is None else skip.ctypes.data,
+                                                      -1 if ctx is None else ctx.device_id)
+        if bad >= 0:
+            rest = tables
+    for seq, a, b, stride, scale, code, what, skipping in rest:
+        _check_seq(seq, a * scale if b is None else a * b * scale, code, what, skip if skipping else None, ctx=ctx)
+
+
 class Context:
     """Owns a tf_ctx bound to one HIP device."""
 
@@ -342,6 +372,14 @@ def _ctx_handle(ctx):
     return None if ctx is None else ctx.handle
 
 
+def _check_backward(ctx, sh, T, io_dtype, dw_dtype, fm, W, X, dY, dX, dW):
+    K, N = sh[:, 0], sh[:, 1]
+    T = int(T)
+    _check_all(ctx, len(sh), fm, [(W, K, N, 2, 1, io_dtype, "W", 0), (dY, N, None, 2, T, io_dtype, "dY", 0),
+                                  (dX, K, None, 2, T, io_dtype, "dX", 0), (X, K, None, 2, T, io_dtype, "X", 1),
+                                  (dW, K, N, 2, 1, dw_dtype, "dW", 1)])
+
+
 # ----------------------------------------------------------------------------
 # entry points (same names as the C ABI)
 # ----------------------------------------------------------------------------
@@ -354,11 +392,7 @@ def tf_stage_backward(ctx, shapes: Sequence[tuple], T: int, io_dtype: int,
     L = len(shapes)
     sh = np.ascontiguousarray(np.asarray(shapes, dtype=np.int64).reshape(L, 2))
     fm, fm_p = _host(freeze_mask, np.uint8, L)
-    _check_seq(W, sh[:, 0] * sh[:, 1], io_dtype, "W", ctx=ctx)
-    _check_seq(dY, T * sh[:, 1], io_dtype, "dY", ctx=ctx)
-    _check_seq(dX, T * sh[:, 0], io_dtype, "dX", ctx=ctx)
-    _check_seq(X, T * sh[:, 0], io_dtype, "X", fm, ctx=ctx)
-    _check_seq(dW, sh[:, 0] * sh[:, 1], dw_dtype, "dW", fm, ctx=ctx)
+    _check_backward(ctx, sh, T, io_dtype, dw_dtype, fm, W, X, dY, dX, dW)
     kW, pW = _ptr_array(W, L)
     kX, pX = _ptr_array(X, L)
     kdY, pdY = _ptr_array(dY, L)
@@ -380,11 +414,7 @@ def tf_stage_backward_microbatch(ctx, shapes: Sequence[tuple], T: int, io_dtype:
     sh = np.ascontiguousarray(np.asarray(shapes, dtype=np.int64).reshape(L, 2))
     fm, fm_p = _host(freeze_mask, np.uint8, L)
     am, am_p = _host(accumulate_mask, np.uint8, L)
-    _check_seq(W, sh[:, 0] * sh[:, 1], io_dtype, "W", ctx=ctx)
-    _check_seq(dY, T * sh[:, 1], io_dtype, "dY", ctx=ctx)
-    _check_seq(dX, T * sh[:, 0], io_dtype, "dX", ctx=ctx)
-    _check_seq(X, T * sh[:, 0], io_dtype, "X", fm, ctx=ctx)
-    _check_seq(dW, sh[:, 0] * sh[:, 1], dw_dtype, "dW", fm, ctx=ctx)
+    _check_backward(ctx, sh, T, io_dtype, dw_dtype, fm, W, X, dY, dX, dW)
     kW, pW = _ptr_array(W, L)
     kX, pX = _ptr_array(X, L)
     kdY, pdY = _ptr_array(dY, L)
@@ -408,10 +438,10 @@ def tf_masked_adamw(ctx, numel: Sequence[int], p_master, m, v, grad, grad_dtype:
     ne, ne_p = _host(numel, np.int64, n)
     st, st_p = _host(step, np.int32, n)
     fm, fm_p = _host(tensor_freeze_mask, np.uint8, n)
-    for name, seq, dt in (("p", p_master, TF_F32), ("m", m, TF_F32), ("v", v, TF_F32),
-                          ("grad", grad, grad_dtype), ("p_lowp", p_lowp, TF_BF16),
-                          ("ema", ema, TF_F32), ("ema_abs", ema_abs, TF_F32)):
-        _check_seq(seq, ne, dt, name, fm, ctx=ctx)
+    _check_all(ctx, n, fm, [(seq, ne, None, 1, 1, dt, name, 1)
+                            for name, seq, dt in (("p", p_master, TF_F32), ("m", m, TF_F32), ("v", v, TF_F32),
+                                                  ("grad", grad, grad_dtype), ("p_lowp", p_lowp, TF_BF16),
+                                                  ("ema", ema, TF_F32), ("ema_abs", ema_abs, TF_F32))])
     for i in range(n if elem_freeze_bits is not None else 0):
         if fm is not None and fm[i]:
             continue

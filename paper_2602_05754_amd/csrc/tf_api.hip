@@ -1107,6 +1107,28 @@ int tf_row_blocks_to_bits(tf_ctx* ctx, void* hip_stream,
 
 }  // extern "C"
 
+// For the binding, which knows what its tables of device buffers hold: is table t's entry i on the
+// device, of the element type and large enough for what a call will index?  Per table eight numbers:
+// address of its int64 rows [bytes][type][device][present] of n entries each (type and device -2 =
+// unknown), addresses of two int64 arrays whose products a[i * stride] * b[i * stride] * scale are the elements needed
+// (b may be 0: just a), stride, scale, element type, skip the entries that `skip` marks.
+// Returns -1, or the number of the first table that does not pass.
+extern "C" int tf_internal_check_tables(int32_t n_tables, const int64_t* desc, int32_t n, const uint8_t* skip, int32_t device) {
+    for (int32_t t = 0; t < n_tables; ++t, desc += 8) {
+        const int64_t* info = reinterpret_cast<const int64_t*>(desc[0]);
+        const int64_t* a = reinterpret_cast<const int64_t*>(desc[1]);
+        const int64_t* b = reinterpret_cast<const int64_t*>(desc[2]);
+        const int64_t stride = desc[3], scale = desc[4], dtype = desc[5], size = dtype == TF_BF16 ? 2 : 4;
+        for (int32_t i = 0; i < n; ++i) {
+            if (!info[3 * int64_t(n) + i] || (desc[6] && skip && skip[i])) continue;
+            const int64_t type = info[int64_t(n) + i], dev = info[2 * int64_t(n) + i];
+            if (info[i] < int64_t(uint64_t(a[i * stride]) * uint64_t(b ? b[i * stride] : 1) * uint64_t(scale) * uint64_t(size))) return t;
+            if ((type != -2 && type != dtype) || (device >= 0 && dev != -2 && dev != device)) return t;
+        }
+    }
+    return -1;
+}
+
 // Test hook (not part of the public header): which launch shape of the generic kernel a launch of these
 // problems gets, its tile goes to tile[0..1]; and what it and the 256 x 256-tile kernel (for problems
 // whose contraction is a multiple of 64, or for all others) are expected to take, us[0..1].
