@@ -219,7 +219,9 @@ __device__ __forceinline__ int logical_tile(int b, int nb) {
     return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
 }
 
-// kDepth: steps whose pieces are on their way in registers.
+// kDepth: steps whose pieces are on their way in registers.  The output is stored past the caches: left in
+// the memory-side cache it pushed out the weights that the next call reads (32 tokens, LLaMA-1B block
+// pair: input gradients 85 us, 62 so).
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN, int kDepth>
 __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
     typedef Operand<TIn, kContig, kTileM> OpA;
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
                           f32x2_to_bf16x2(v[1][0], v[1][1]), f32x2_to_bf16x2(v[1][2], v[1][3])};
             uint16_t* out = static_cast<uint16_t*>(P.C) + int64_t(m) * N + n;
             if (n + kOutE <= N) {
-                *reinterpret_cast<U4any*>(out) = x;
+                __builtin_nontemporal_store(x, reinterpret_cast<U4any*>(out));
             } else {
 #pragma unroll
                 for (int e = 0; e < kOutE; ++e)
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
             float* out = static_cast<float*>(P.C) + int64_t(m) * N + n;
             if (n + kOutE <= N) {
                 if (kAccumulate) v[0] += *reinterpret_cast<const F4any*>(out);
-                *reinterpret_cast<F4any*>(out) = v[0];
+                __builtin_nontemporal_store(v[0], reinterpret_cast<F4any*>(out));
             } else {
 #pragma unroll
                 for (int e = 0; e < kOutE; ++e)
@@ -417,12 +419,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 // Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps are
 // bound by the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
 // tokens: 128 x 128 tiles 906 TFLOP/s, 128 x 64 753, 64 x 64 598), the fp32 steps by the matrix pipe
-// (2048 tokens, width 1024: 128 x 64 tiles 125 TFLOP/s, 32 x 64 115; 512 tokens, width 512: 32 x 64 46 us, 32 x 32 with
-// its sums in 64 bits 78).
-// Small tiles are for calls with few of them: an fp32 chain of 64 steps takes 30 us in 32 x 32 and 32 x 64 tiles,
-// 46 in 64 x 64, 96 in 128 x 64 and 155 in 128 x 128.
-constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 1.7f}, {128, 64, 0.348f, 0.45f, 2.5f}, {128, 128, 0.575f, 0.60f, 3.4f}};
-constexpr GenericShape kShapes32[] = {{32, 32, 0.28f, 0.43f, 1.0f}, {32, 64, 0.286f, 0.40f, 1.0f}, {128, 64, 1.04f, 1.45f, 2.0f}};
+// (2048 tokens, width 1024: 64 x 64 tiles 545 us, 32 x 64 558, 128 x 64 553; width 512, 512 tokens: 32 x 64
+// 47 us, 64 x 64 64, 32 x 32 with its sums in 64 bits 78).  Small tiles are for calls with few of them: an
+// fp32 chain of 64 steps takes 30 us in 32 x 32 and 32 x 64 tiles, 46 in 64 x 64 and 155 in 128 x 128.
+constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 2.7f}, {128, 64, 0.348f, 0.45f, 3.1f}, {128, 128, 0.575f, 0.60f, 3.5f}};
+constexpr GenericShape kShapes32[] = {{32, 32, 0.28f, 0.43f, 1.0f}, {32, 64, 0.275f, 0.42f, 1.2f}, {64, 64, 0.53f, 0.62f, 1.5f}};
 static_assert(sizeof(kShapes16) == kGenericShapes * sizeof(GenericShape) && sizeof(kShapes32) == sizeof(kShapes16), "as many for both types");
 
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate>
@@ -435,7 +436,7 @@ void launch(hipStream_t stream, const GemmBatch& batch, int shape) {
     else if (shape == 1)
         hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[1].tile_m, kS[1].tile_n, 2>), grid, block, 0, stream, batch);
     else
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[2].tile_m, kS[2].tile_n, k16 ? 2 : 1>), grid, block, 0, stream, batch);
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[2].tile_m, kS[2].tile_n, 2>), grid, block, 0, stream, batch);
 }
 
 }  // namespace

@@ -97,13 +97,13 @@ def test_edges_of_tiles_steps_and_pieces(ctx, io, dw, accumulate, T, shapes):
 @pytest.mark.parametrize("half,io,T,shapes,tile", [
     ("dX", "f32", 130, [(97, 161), (160, 96)], (32, 32)),
     ("dX", "f32", 643, [(1290, 399), (1283, 395)], (32, 64)),
-    ("dX", "f32", 2033, [(2047, 731), (2046, 733)] * 3, (128, 64)),
+    ("dX", "f32", 2033, [(2047, 731), (2046, 733)] * 3, (64, 64)),
     ("dX", "bf16", 130, [(97, 161), (160, 96)], (64, 64)),
     ("dX", "bf16", 770, [(1027, 1101), (1101, 2030), (1027, 2003)], (128, 64)),
     ("dX", "bf16", 1531, [(1027, 1101), (1101, 2030), (2047, 1003)], (128, 128)),
     ("dW", "f32", 130, [(97, 161), (160, 96)], (32, 32)),
     ("dW", "f32", 391, [(1290, 643), (1283, 643)], (32, 64)),
-    ("dW", "f32", 815, [(2047, 2001), (2046, 2005), (2047, 2001)], (128, 64)),
+    ("dW", "f32", 815, [(2047, 2001), (2046, 2005), (2047, 2001)], (64, 64)),
     ("dW", "bf16", 130, [(97, 161), (160, 96)], (64, 64)),
     ("dW", "bf16", 1101, [(1027, 771), (2030, 773)], (128, 64)),
     ("dW", "bf16", 770, [(1027, 1101), (1101, 2030), (1027, 2003)], (128, 128)),
