@@ -5,11 +5,12 @@
 // (layout kTN); frozen tensors never reach this file.
 //
 // fp32 operands go through v_mfma_f32_16x16x4_f32 (true fp32 products and sums, twice the rate of
-// the vector FMA), bf16 operands through v_mfma_f32_16x16x32_bf16.
+// the vector FMA; in the smallest tiles through the 64-bit form), bf16 operands through
+// v_mfma_f32_16x16x32_bf16.
 //
 // Against plain fp32 vector FMAs in 64 x 64 tiles (what this file held before): fp32 stage of width 1024,
 // 1000 tokens, input gradients of two blocks 750 -> 380 us (58 -> 116 TFLOP/s); bf16, 200 tokens of a
-// LLaMA-1B block pair, input gradients 1199 -> 115 us; bf16, weight gradients over 3001 tokens 9460 ->
+// LLaMA-1B block pair, input gradients 1199 -> 103 us; bf16, weight gradients over 3001 tokens 9460 ->
 // 870 us.  fp32 is bound by the matrix pipe, bf16 by the operands' way through L1 and LDS.
 //
 // One output tile per workgroup of four waves in a 2 x 2 grid.  The contraction advances 128 bytes
@@ -207,7 +208,7 @@ struct Operand {
 // register, read first behind the two, was the old one.
 __device__ __forceinline__ void wait_for_sums() {
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 3");
+    asm volatile("s_nop 15\n\ts_nop 15");
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -255,9 +256,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     const int free_steps = a.narrow || b.narrow ? 0 : steps - 1;
     constexpr bool kWide = sizeof(TIn) == 2;            // 32 contraction values per instruction, not 4
     // fp32: the products of a step (8 instructions of 4) are summed by themselves and then added to the sums
-    // so far.  In the smallest tiles, for calls that wait for memory more than for the matrix pipe, those
-    // of each instruction are, and the sums are kept in 64 bits.  Error against 64 bits,
-    // contraction 256: 4.0e-8 and 1.2e-7 (one chain of additions: 2.9e-7).
+    // so far.  The smallest tiles, for calls that wait for memory and the host more than for the matrix
+    // pipe, contract in 64 bits (half the fp32 rate): one rounding, also of a sum that has cancelled.
+    // Error against 64 bits, contraction 256: 1.2e-7 and 2.5e-8 (one chain of fp32 additions: 2.9e-7).
     constexpr bool kExact = !kWide && OpA::kFrags * OpB::kFrags == 1;
     typedef std::conditional_t<kExact, double, float> Sum;
     typedef Sum Sum4 __attribute__((ext_vector_type(4)));
@@ -266,6 +267,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
         for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] = Sum4{0, 0, 0, 0};
+
+    Sum4 second = {0, 0, 0, 0};                          // kExact: the second half steps' sums, so that two chains alternate
 
     const int wm = wave >> 1, wn = wave & 1;
     auto contract = [&](const char* stage) {
@@ -289,18 +292,14 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
                                                                            __builtin_bit_cast(bf16x8, fa[u][i]), acc[i][j], 0, 0, 0);
             }
         } else if constexpr (kExact) {
-            f32x4 part[8];
+            fragments(0);
+            fragments(1);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                fragments(u);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    part[4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[u][0][e]), __uint_as_float(fa[u][0][e]),
-                                                                           f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            for (int e = 0; e < 4; ++e) {
+                auto wide = [](uint32_t x) { return double(__uint_as_float(x)); };
+                acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide(fb[0][0][e]), wide(fa[0][0][e]), acc[0][0], 0, 0, 0);
+                second = __builtin_amdgcn_mfma_f64_16x16x4f64(wide(fb[1][0][e]), wide(fa[1][0][e]), second, 0, 0, 0);
             }
-            wait_for_sums();
-#pragma unroll
-            for (int q = 0; q < 8; ++q) acc[0][0] += __builtin_convertvector(part[q], Sum4);
         } else {
             f32x4 part[OpA::kFrags][OpB::kFrags];
 #pragma unroll
@@ -366,9 +365,9 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
             __syncthreads();
         });
 
-    if (kWide) wait_for_sums();
-    // Epilogue: acc[i][j][e] is C[m][n], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16) + e of the
-    // wave's part.  The sums are turned around in LDS ([row][16-byte chunks, XOR-swizzled]) and whole
+    if (kWide || kExact) wait_for_sums();
+    // Epilogue: acc[i][j][e] is C[m][n], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16) + e (kExact: lane / 16
+    // + 4 e) of the wave's part.  The sums are turned around in LDS ([row][16-byte chunks, XOR-swizzled]) and whole
     // rows of the tile are stored, 16 bytes per lane.
     constexpr int kRow = kTileN * 4, kTurn = kTileN / 4 < 16 ? kTileN / 4 - 1 : 15;
 #pragma unroll
@@ -376,7 +375,13 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 #pragma unroll
         for (int j = 0; j < OpB::kFrags; ++j) {
             const int r = wm * (kTileM / 2) + 16 * i + (lane & 15), c = wn * (kTileN / 8) + 4 * j + (lane >> 4);
-            *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = __builtin_convertvector(acc[i][j], f32x4);
+            if constexpr (kExact) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    *reinterpret_cast<float*>(lds + r * kRow + (((c - (lane >> 4) + e) ^ (r & kTurn)) << 4) + (lane >> 4) * 4) = float(acc[0][0][e] + second[e]);
+            } else {
+                *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
+            }
         }
     __syncthreads();
     constexpr int kOutE = kOutBf16 ? 8 : 4, kLanes = kTileN / kOutE, kRowsPerPass = kThreads / kLanes;
@@ -420,7 +425,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 // bound by the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
 // tokens: 128 x 128 tiles 906 TFLOP/s, 128 x 64 753, 64 x 64 598), the fp32 steps by the matrix pipe
 // (2048 tokens, width 1024: 64 x 64 tiles 545 us, 32 x 64 558, 128 x 64 553; width 512, 512 tokens: 32 x 64
-// 47 us, 64 x 64 64, 32 x 32 with its sums in 64 bits 78).  Small tiles are for calls with few of them: an
+// 47 us, 64 x 64 64, 32 x 32 in 64 bits 78).  Small tiles are for calls with few of them: an
 // fp32 chain of 64 steps takes 30 us in 32 x 32 and 32 x 64 tiles, 46 in 64 x 64 and 155 in 128 x 128.
 constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 2.7f}, {128, 64, 0.348f, 0.45f, 3.1f}, {128, 128, 0.575f, 0.60f, 3.5f}};
 constexpr GenericShape kShapes32[] = {{32, 32, 0.28f, 0.43f, 1.0f}, {32, 64, 0.275f, 0.42f, 1.2f}, {64, 64, 0.53f, 0.62f, 1.5f}};

@@ -143,8 +143,8 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
         for (const Planned* it : items) e.add(*it, s.tile_m, s.tile_n, in_dtype == Dtype::BF16 ? 64 : 32, s.tile_steps, s.tile_steps);
         const double us = Estimate::us(e.work / compute_units() * s.step_us, e.longest * s.chain_us, 0.25);
         if (i == 0 || us < *best_us) { best = i; *best_us = us; }
-        // The smallest fp32 tiles keep their sums in 64 bits.  A launch that takes less than the host needs
-        // for the call (30 us with its other half) loses nothing by them.
+        // The smallest fp32 tiles contract in 64 bits.  A launch that takes less than the host needs for
+        // the call (30 us with its other half) loses nothing by them.
         if (i == 0 && in_dtype == Dtype::F32 && us < 20) break;
     }
     return best;
