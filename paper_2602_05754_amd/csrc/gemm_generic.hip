@@ -34,6 +34,7 @@ namespace {
 
 constexpr int kThreads = 256;           // four waves, 2 x 2 over the tile
 constexpr int kStepBytes = 128;         // contraction bytes of an operand row per step
+constexpr int kDepth = 2;               // steps whose pieces are on their way in registers
 constexpr int kXcds = 8;
 constexpr int kXcdRun = 8;              // consecutive logical tiles kept on one XCD
 constexpr int kGroupM = 8;              // tile rows per L2 locality group
@@ -96,7 +97,7 @@ struct Operand {
     __device__ __forceinline__ Operand(const void* base, int64_t ld, int extent, int kc, int origin)
         : matrix(static_cast<const TIn*>(base)), narrow(kContig ? kc < kE : ld < kE || extent < kE) {
         step = kContig ? int64_t(kBK) : int64_t(kBK) * ld;
-        const int tid = int(threadIdx.x), c = tid % kRowPieces;                            // the same piece of every kThreads / kRowPieces-th row
+        const int tid = int(threadIdx.x), c = tid % kRowPieces;     // the same piece of every kThreads / kRowPieces-th row
         static_assert(kThreads % kRowPieces == 0, "a thread's pieces lie below each other");
         const int col = origin + c * kE < extent ? origin + c * kE : 0;
         over = max(col + kE - extent, 0);
@@ -220,10 +221,9 @@ __device__ __forceinline__ int logical_tile(int b, int nb) {
     return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
 }
 
-// kDepth: steps whose pieces are on their way in registers.  The output is stored past the caches: left in
-// the memory-side cache it pushed out the weights that the next call reads (32 tokens, LLaMA-1B block
-// pair: input gradients 85 us, 62 so).
-template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN, int kDepth>
+// The output is stored past the caches: left in the memory-side cache it pushed out the weights that the
+// next call reads (32 tokens, LLaMA-1B block pair: input gradients 85 us, 62 so).
+template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN>
 __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
     typedef Operand<TIn, kContig, kTileM> OpA;
     typedef Operand<TIn, kContig, kTileN> OpB;
@@ -437,11 +437,11 @@ void launch(hipStream_t stream, const GemmBatch& batch, int shape) {
     constexpr bool k16 = sizeof(TIn) == 2;
     constexpr const GenericShape* kS = k16 ? kShapes16 : kShapes32;
     if (shape == 0)
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[0].tile_m, kS[0].tile_n, 2>), grid, block, 0, stream, batch);
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[0].tile_m, kS[0].tile_n>), grid, block, 0, stream, batch);
     else if (shape == 1)
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[1].tile_m, kS[1].tile_n, 2>), grid, block, 0, stream, batch);
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[1].tile_m, kS[1].tile_n>), grid, block, 0, stream, batch);
     else
-        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[2].tile_m, kS[2].tile_n, 2>), grid, block, 0, stream, batch);
+        hipLaunchKernelGGL((gemm_generic_kernel<TIn, kContig, kOutBf16, kAccumulate, kS[2].tile_m, kS[2].tile_n>), grid, block, 0, stream, batch);
 }
 
 }  // namespace
