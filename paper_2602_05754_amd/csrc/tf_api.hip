@@ -25,6 +25,7 @@ struct tf_ctx {
     tf::RcState* rc_state_static;       // this device's static scratch array (tf_reconcile_mask_static)
     bool lowp_is_rounded_master;        // tf_assume_lowp_is_rounded_master
     double* ew_partials;                // device memory of the score sums' first level (zero between launches)
+    int gemm_route;                     // tf_internal_gemm_route
 };
 
 // Device memory of tf_reconcile_mask_static: one array per GPU, part of the loaded code object,
@@ -164,6 +165,10 @@ double tile256_us(const std::vector<const Planned*>& items, bool tail) {
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
 }
 
+// tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
+// last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
+enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3 };
+
 // Launch `items` in batches of at most kMaxProblemsPerLaunch: on the 256 x 256-tile kernel what it
 // takes, on the generic kernel the rest - and what it takes when the generic one's smaller tiles
 // are expected to be done first (few tiles, or few long ones).
@@ -183,17 +188,18 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
     }
     double generic_us;
     int shape[3] = {-1, -1, -1};                // of the generic kernel; -1: 256 x 256 tiles
-    if (plain) {
+    const int route = ctx->gemm_route;
+    if (plain && route != kRouteWhole256 && route != kRouteAll256) {
         const int s = pick_generic_shape(cls[kWhole], in_dtype, &generic_us);
-        if (generic_us < tile256_us(cls[kWhole], false)) shape[kWhole] = s;
+        if (generic_us < tile256_us(cls[kWhole], false) || route == kRouteGeneric) shape[kWhole] = s;
     }
-    if (!cls[kTail].empty()) {
+    if (!cls[kTail].empty() && route != kRouteAll256) {
         std::vector<const Planned*> both = cls[kTail];
         both.insert(both.end(), cls[kOther].begin(), cls[kOther].end());
         double rest_us;
         pick_generic_shape(both, in_dtype, &generic_us);
         pick_generic_shape(cls[kOther], in_dtype, &rest_us);
-        if (generic_us < tile256_us(cls[kTail], true) + rest_us) {
+        if (generic_us < tile256_us(cls[kTail], true) + rest_us || route == kRouteGeneric) {
             cls[kOther] = both;
             cls[kTail].clear();
         }
@@ -237,7 +243,7 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
                 ++i;
             }
             batch.total_tiles = int32_t(tiles);
-            const int kind = (layout == Layout::kNT ? TF_KERNEL_DX_MFMA : TF_KERNEL_DW_MFMA) + (c == kWhole ? 0 : 2);
+            const int kind = (layout == Layout::kNT ? TF_KERNEL_DX_MFMA : TF_KERNEL_DW_MFMA) + (shape[c] < 0 ? 0 : 2);     // the kernel that runs
             ProfScope prof(ctx, stream, kind);
             const hipError_t e = shape[c] < 0
                 ? launch_gemm_mfma_bf16(stream, batch, n, layout, out_dtype, accumulate, c == kTail)
@@ -522,6 +528,7 @@ int tf_create(tf_ctx** out, int device_id) {
     ctx->rc_state = nullptr;
     ctx->rc_state_static = nullptr;
     ctx->lowp_is_rounded_master = false;
+    ctx->gemm_route = 0;
     ctx->ew_partials = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&ctx->rc_state), tf::rc_state_bytes()) != hipSuccess) {
         delete ctx;
@@ -1127,6 +1134,14 @@ extern "C" int tf_internal_check_tables(int32_t n_tables, const int64_t* desc, i
         }
     }
     return -1;
+}
+
+// Test hook (not part of the public header): the kernels that this context's GEMM launches take, so that a
+// small problem can be sent through each of them.  A context starts with 0, the estimated times.
+extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
+    if (!ctx || route < kRouteEstimated || route > kRouteGeneric) return TF_ERR_INVALID_ARG;
+    ctx->gemm_route = route;
+    return TF_OK;
 }
 
 // Test hook (not part of the public header): which launch shape of the generic kernel a launch of these

@@ -7,6 +7,25 @@ import workloads as wl
 import paper_2602_05754_amd as tf
 
 
+# tf_internal_gemm_route: which kernel the GEMM launches of a context take
+BY_ESTIMATE, WHOLE_256, ALL_256, GENERIC = range(4)
+
+
+def set_route(ctx, route: int) -> None:
+    assert tf.load_library().tf_internal_gemm_route(ctx.handle, route) == 0
+
+
+def kinds_of(ctx, fn) -> list:
+    """Kernel kinds that ran inside fn(), in launch order."""
+    ctx.profile_enable(True)
+    ctx.profile_collect()
+    fn()
+    torch.cuda.synchronize()
+    kinds = [k for k, _ in ctx.profile_collect()]
+    ctx.profile_enable(False)
+    return kinds
+
+
 def dev(a_f32: np.ndarray, dtype: str) -> torch.Tensor:
     """float32 host array -> device tensor of storage type dtype ("f32"/"bf16")."""
     if dtype == "bf16":

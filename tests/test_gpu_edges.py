@@ -2,8 +2,9 @@
 (Sec. 3.2.1: both halves of the backward): the last tile of a problem computes a whole window
 that overlaps its neighbour, or the rows around a sub-tensor problem, and stores only its own
 part.  Every output element against the oracle (one bf16 rounding of an fp32 sum), rows of frozen
-blocks bit-identical, and the kernel kinds that ran are checked so that a silent fall to the
-fp32-FMA kernel would fail the test."""
+blocks bit-identical.  Problems as small as these would go to the generic kernel's smaller tiles: the
+context is told to take 256 x 256 tiles wherever they fit, and the kernel kinds that ran are
+checked."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import assert_elementwise, canary, dev, host64, raw_bytes
+from gpu_util import WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, set_route
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +20,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(scope="module")
 def ctx():
     c = tf.Context(0)
+    set_route(c, WHOLE_256)
     yield c
     c.close()
 
@@ -29,16 +31,6 @@ def _inputs(rs, shapes, T):
     X = [wl.round_to_bf16(f32(rs.standard_normal((T, k)))) for k, n in shapes]
     dY = [wl.round_to_bf16(f32(rs.standard_normal((T, n)) * 1e-3)) for k, n in shapes]
     return W, X, dY
-
-
-def _kinds(ctx, fn):
-    ctx.profile_enable(True)
-    ctx.profile_collect()
-    fn()
-    torch.cuda.synchronize()
-    kinds = [k for k, _ in ctx.profile_collect()]
-    ctx.profile_enable(False)
-    return kinds
 
 
 def _case(ctx, shapes, T, seed, row_masks=None, block_rows=0, dw="bf16", calls=1, expect=None):
@@ -67,7 +59,7 @@ def _case(ctx, shapes, T, seed, row_masks=None, block_rows=0, dw="bf16", calls=1
             ref_dW[l] += one[l]
         gdX = [canary((T, k), torch.bfloat16) for k, n in shapes]
         gW, gX, gdY = ([dev(a, "bf16") for a in t] for t in (W, X, dY))
-        kinds += _kinds(ctx, lambda: tf.tf_stage_backward_blocks(
+        kinds += kinds_of(ctx, lambda: tf.tf_stage_backward_blocks(
             ctx, shapes, T, tf.TF_BF16, gW, gX, gdY, None, row_masks, block_rows if row_masks is not None else 0,
             gdX, gdW, tf.TF_F32 if acc else tf.TF_BF16, accumulate=acc))
         for l in range(L):
@@ -90,7 +82,7 @@ def test_token_counts_that_are_no_multiple_of_the_tile(ctx):
     # 960 tokens = 3 tiles and 192 rows, 15 contraction steps for the weight gradients: all on the matrix cores
     _case(ctx, shapes, 960, seed=1, expect={"dx_mfma", "dw_mfma"})
     # 1000 tokens: input gradients on the matrix cores (their contraction is N_l); the weight
-    # gradients' contraction, 1000, is no multiple of 64 and takes the fp32-FMA kernel
+    # gradients' contraction, 1000, is no multiple of 64 and takes the generic kernel
     _case(ctx, shapes, 1000, seed=2, expect={"dx_mfma", "dw_generic"})
     # 264 tokens: one whole tile and a window of 8 new rows
     _case(ctx, shapes, 264, seed=3, expect={"dx_mfma", "dw_generic"})

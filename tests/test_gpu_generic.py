@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import CODE, TDT, assert_elementwise, canary, dev, host64, raw_bytes
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, set_route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -154,3 +154,24 @@ def test_infinities_stay_where_they_are(ctx, io, T, K, N):
         rX, rW = torch.full((T, K), float(N)).to(dt).float(), torch.full((K, N), float(T)).to(dt).float()
         rX[t], rW[:, n] = float("inf"), float("inf")
         assert torch.equal(dX.float().cpu(), rX) and torch.equal(dW.float().cpu(), rW)
+
+
+@pytest.mark.parametrize("T,shapes,route,dx,dw", [
+    (256, [(256, 256)], BY_ESTIMATE, "dx_generic", "dw_generic"),       # 256 x 256 tiles fit, the smaller ones are faster
+    (256, [(256, 256)], WHOLE_256, "dx_mfma", "dw_mfma"),
+    (257, [(256, 256)], WHOLE_256, "dx_mfma", "dw_generic"),
+    (257, [(256, 264)], ALL_256, "dx_mfma", "dw_mfma"),
+    (4096, [(4096, 4096)] * 2, BY_ESTIMATE, "dx_mfma", "dw_mfma"),
+    (2048, [(4096, 4096)], GENERIC, "dx_generic", "dw_generic"),
+    (4097, [(4096, 4096)] * 2, BY_ESTIMATE, "dx_mfma", "dw_mfma"),
+])
+def test_profile_kinds_name_the_kernel_that_ran(ctx, T, shapes, route, dx, dw):
+    """The kinds follow the kernel, whatever the shape would allow: the other tests go by them."""
+    z = lambda s: [torch.zeros(q, dtype=torch.bfloat16, device="cuda") for q in s]
+    W, dW, X, dX, dY = z(shapes), z(shapes), z([(T, k) for k, n in shapes]), z([(T, k) for k, n in shapes]), z([(T, n) for k, n in shapes])
+    set_route(ctx, route)
+    try:
+        kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, None, dX, dW, tf.TF_BF16))
+    finally:
+        set_route(ctx, BY_ESTIMATE)
+    assert kinds == [dx, dw]
