@@ -165,46 +165,75 @@ double tile256_us(const std::vector<const Planned*>& items, bool tail) {
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
 }
 
+// What the generic kernel's launch is compared with tile256_us() by.  Its weight gradients take longer than the
+// estimate, which knows no outputs: they are stored past the caches, and what is added to is fetched again from
+// where an earlier call has left it.  With a tenth more and 0.04 us per MB of outputs (`out_bytes` per value, both
+// ways counted) the kernel chosen was the faster one for all but 2 of 384 launches (block widths 256 to 4096, 64 to
+// 3001 tokens; without, up to 1.76 times the time: LLaMA widths 1024 / 256 / 2816, 256 tokens, fp32 gradients
+// added to 43 us, 256 x 256 tiles 25).  Input gradients as estimated.
+double generic_launch_us(const std::vector<const Planned*>& items, double us, Layout layout, int out_bytes) {
+    if (layout == Layout::kNT) return us;
+    double values = 0;
+    for (const Planned* it : items) values += double(it->M) * double(it->N);
+    return 1.1 * us + 0.04e-6 * values * out_bytes;
+}
+
 // tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
 // last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
 enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3 };
 
-// Launch `items` in batches of at most kMaxProblemsPerLaunch: on the 256 x 256-tile kernel what it
-// takes, on the generic kernel the rest - and what it takes when the generic one's smaller tiles
-// are expected to be done first (few tiles, or few long ones).
-hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
-                          Dtype in_dtype, Dtype out_dtype, bool accumulate) {
-    // problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
-    enum { kWhole = 0, kTail = 1, kOther = 2 };
+// problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
+enum { kWhole = 0, kTail = 1, kOther = 2 };
+
+// Which kernel takes which problems: on the 256 x 256-tile kernel what it takes, on the generic kernel the
+// rest - and what it takes when the generic one's smaller tiles are expected to be done first (few tiles, or
+// few long ones).
+struct Routes {
     std::vector<const Planned*> cls[3];
+    int shape[3] = {-1, -1, -1};                // launch shape of the generic kernel; -1: 256 x 256 tiles
+};
+hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
     bool plain = true;                          // no row bits, no segments: the generic kernel could take them too
     for (const Planned& it : items) {
         bool ok = planned_mfma_ok(it, layout, in_dtype);
         for (const Planned& q : it.more) ok = ok && planned_mfma_ok(q, layout, in_dtype);
         const bool special = ~it.row_bits != 0 || !it.more.empty();
-        if (ok) { cls[kWhole].push_back(&it); plain = plain && !special; }
+        if (ok) { r.cls[kWhole].push_back(&it); plain = plain && !special; }
         else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
-        else cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
+        else r.cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
     }
-    double generic_us;
-    int shape[3] = {-1, -1, -1};                // of the generic kernel; -1: 256 x 256 tiles
-    const int route = ctx->gemm_route;
+    const int out_bytes = (out_dtype == Dtype::BF16 ? 2 : 4) * (accumulate ? 2 : 1);
+    auto generic = [&](const std::vector<const Planned*>& v, int* shape) {
+        double us;
+        *shape = pick_generic_shape(v, in_dtype, &us);
+        return generic_launch_us(v, us, layout, out_bytes);
+    };
     if (plain && route != kRouteWhole256 && route != kRouteAll256) {
-        const int s = pick_generic_shape(cls[kWhole], in_dtype, &generic_us);
-        if (generic_us < tile256_us(cls[kWhole], false) || route == kRouteGeneric) shape[kWhole] = s;
+        int s;
+        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false) || route == kRouteGeneric) r.shape[kWhole] = s;
     }
-    if (!cls[kTail].empty() && route != kRouteAll256) {
-        std::vector<const Planned*> both = cls[kTail];
-        both.insert(both.end(), cls[kOther].begin(), cls[kOther].end());
-        double rest_us;
-        pick_generic_shape(both, in_dtype, &generic_us);
-        pick_generic_shape(cls[kOther], in_dtype, &rest_us);
-        if (generic_us < tile256_us(cls[kTail], true) + rest_us || route == kRouteGeneric) {
-            cls[kOther] = both;
-            cls[kTail].clear();
+    if (!r.cls[kTail].empty() && route != kRouteAll256) {
+        std::vector<const Planned*> both = r.cls[kTail];
+        both.insert(both.end(), r.cls[kOther].begin(), r.cls[kOther].end());
+        int s;
+        const double together = generic(both, &s);
+        if (together < tile256_us(r.cls[kTail], true) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
+            r.cls[kOther] = both;
+            r.cls[kTail].clear();
         }
     }
-    shape[kOther] = pick_generic_shape(cls[kOther], in_dtype, &generic_us);
+    generic(r.cls[kOther], &r.shape[kOther]);
+    return hipSuccess;
+}
+
+// Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it.
+hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
+                          Dtype in_dtype, Dtype out_dtype, bool accumulate) {
+    Routes routes;
+    const hipError_t found = find_routes(items, layout, in_dtype, out_dtype, accumulate, ctx->gemm_route, routes);
+    if (found != hipSuccess) return found;
+    std::vector<const Planned*>* const cls = routes.cls;
+    const int* const shape = routes.shape;
 
     GemmBatch batch;
     auto fill = [](GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
@@ -1141,6 +1170,21 @@ extern "C" int tf_internal_check_tables(int32_t n_tables, const int64_t* desc, i
 extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
     if (!ctx || route < kRouteEstimated || route > kRouteGeneric) return TF_ERR_INVALID_ARG;
     ctx->gemm_route = route;
+    return TF_OK;
+}
+
+// Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
+// aligned) are launched together: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the generic kernel.
+extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, int layout_tn,
+                                   int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
+    const Layout layout = layout_tn ? Layout::kTN : Layout::kNT;
+    std::vector<Planned> items;
+    for (int i = 0; i < n; ++i)
+        items.push_back(Planned{nullptr, nullptr, nullptr, M[i], N[i], Kc[i], layout_tn ? M[i] : Kc[i], layout_tn ? N[i] : Kc[i], ~0ull, {}});
+    Routes r;
+    if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
+    for (int c = 0; c < 3; ++c)
+        for (const Planned* it : r.cls[c]) kernel[it - items.data()] = r.shape[c];
     return TF_OK;
 }
 

@@ -1,0 +1,58 @@
+"""Which kernel a GEMM launch takes (no GPU: the choice is made from the sizes, for 256 compute units).
+The launches named here were timed on both kernels; the slower one must not be chosen."""
+import ctypes
+
+import pytest
+
+import paper_2602_05754_amd as tf
+
+TILES_256 = -1
+
+
+def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False):
+    n = len(M)
+    arr = lambda v: (ctypes.c_int64 * n)(*v)
+    kernel = (ctypes.c_int32 * n)(*([99] * n))
+    assert tf.load_library().tf_internal_kernels(n, arr(M), arr(N), arr(Kc), int(tn), io, out, int(accumulate), kernel) == 0
+    return list(kernel)
+
+
+def block(d, kv, ffn, blocks=1):
+    return [(d, d), (d, kv), (d, kv), (d, d), (d, ffn), (d, ffn), (ffn, d)] * blocks
+
+
+# (shapes, tokens, "bf16" / fp32 "set" / fp32 "add", faster on 256 x 256 tiles); us on 256 x 256 tiles and on the generic kernel
+@pytest.mark.parametrize("shapes,T,dw,on256", [
+    (block(1024, 256, 2816), 128, "add", True),          # 22.3, 39.3
+    (block(1024, 256, 2816), 256, "add", True),          # 24.7, 43.0
+    (block(1024, 256, 2816), 200, "add", True),          # 24.4, 42.3: a contraction that is no multiple of 64
+    (block(512, 256, 1536, 3), 256, "add", True),        # 25.0, 42.1
+    (block(512, 256, 1536, 3), 1000, "add", True),       # 38.6, 59.4
+    (block(1024, 256, 2816), 256, "bf16", True),         # 16.9, 21.4
+    (block(1024, 256, 2816), 456, "bf16", True),         # 22.3, 27.0
+    (block(512, 256, 1536, 3), 1024, "set", True),       # 34.4, 41.7
+    (block(512, 256, 1536, 3), 1024, "bf16", True),      # 35.5, 40.9
+    (block(2048, 512, 8192), 256, "add", True),          # 109, 160
+    (block(512, 256, 1536), 1000, "add", False),         # 30.8, 26.4
+    (block(512, 256, 1536), 128, "add", False),          # 17.5, 15.1
+    (block(256, 256, 768), 1024, "add", False),          # 30.3, 14.6
+    (block(768, 384, 2304), 256, "bf16", False),         # 16.7, 13.8
+    (block(768, 384, 2304), 128, "add", False),          # 36.6, 23.6
+])
+def test_weight_gradients_take_the_faster_kernel(shapes, T, dw, on256):
+    K, N = zip(*shapes)
+    got = kernels(K, N, [T] * len(K), True, out=tf.TF_BF16 if dw == "bf16" else tf.TF_F32, accumulate=dw == "add")
+    assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
+
+
+@pytest.mark.parametrize("shapes,T,on256", [
+    (block(1024, 256, 2816), 512, False),                # input gradients: 54.6, 29.1
+    (block(2048, 512, 8192), 1024, False),               # 196, 151
+    (block(2048, 512, 8192, 3), 1024, True),
+    (block(4096, 1024, 14336), 512, False),              # 354, 299
+    (block(4096, 1024, 14336), 2048, True),
+])
+def test_input_gradients_take_the_faster_kernel(shapes, T, on256):
+    K, N = zip(*shapes)
+    got = kernels([T] * len(K), K, N, False)
+    assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
