@@ -131,6 +131,14 @@ struct Estimate {
     static double us(double even, double chain, double overlap) { return std::max(even, chain) + overlap * std::min(even, chain); }
 };
 
+inline int64_t tiles_of(const Planned& it, int64_t tile_m, int64_t tile_n) {
+    return ((it.M + tile_m - 1) / tile_m) * ((it.N + tile_n - 1) / tile_n);
+}
+// A launch of the generic kernel has a block of 256 threads per tile, and fewer than 2^32 threads.  (An extent
+// is then at most that many tiles of 128: rounded up to whole tiles it still fits 31 bits.)
+constexpr int64_t kMaxGenericTiles = (int64_t(1) << 24) - 1;
+constexpr int64_t kMaxTiles256 = 0x3fffffff;       // tile indices are 32-bit on the device
+
 // Launch shape of the generic kernel for these problems: the one with the least estimated time.  The
 // estimates were within 15 % of the measured times and in their order (input gradients of a LLaMA-1B
 // block, 200 tokens: 64 x 64 tiles 65 us, 128 x 64 69, 128 x 128 91; 3001 tokens: 605, 485, 400).
@@ -138,16 +146,22 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
     int best = 0;
     *best_us = 0;
     if (items.empty()) return best;
+    bool any = false;
     for (int i = 0; i < kGenericShapes; ++i) {
         const GenericShape& s = generic_shape(in_dtype, i);
+        bool fits = true;
+        for (const Planned* it : items) fits = fits && tiles_of(*it, s.tile_m, s.tile_n) <= kMaxGenericTiles;
+        if (!fits) continue;
         Estimate e;
         for (const Planned* it : items) e.add(*it, s.tile_m, s.tile_n, in_dtype == Dtype::BF16 ? 64 : 32, s.tile_steps, s.tile_steps);
         const double us = Estimate::us(e.work / compute_units() * s.step_us, e.longest * s.chain_us, 0.25);
-        if (i == 0 || us < *best_us) { best = i; *best_us = us; }
+        if (!any || us < *best_us) { best = i; *best_us = us; }
+        any = true;
         // The smallest fp32 tiles contract in 64 bits.  A launch that takes less than the host needs for
         // the call (30 us with its other half) loses nothing by them.
         if (i == 0 && in_dtype == Dtype::F32 && us < 20) break;
     }
+    if (!any) { best = kGenericShapes - 1; *best_us = HUGE_VAL; }      // too large for a launch: refused there
     return best;
 }
 
@@ -253,6 +267,7 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
         std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
         const int64_t tile_m = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_m;
         const int64_t tile_n = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_n;
+        const int64_t max_tiles = shape[c] < 0 ? kMaxTiles256 : kMaxGenericTiles;
         size_t i = 0;
         while (i < v.size()) {
             int n = 0;
@@ -262,9 +277,9 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
                 const int slots = 1 + int(it.more.size());
                 if (slots > kMaxProblemsPerLaunch) return hipErrorInvalidValue;
                 if (n + slots > kMaxProblemsPerLaunch) break;
-                const int64_t nt = ((it.M + tile_m - 1) / tile_m) * ((it.N + tile_n - 1) / tile_n);
-                if (nt > 0x3fffffff) return hipErrorInvalidValue;      // tile indices are 32-bit on the device
-                if (n > 0 && tiles + nt > 0x3fffffff) break;
+                const int64_t nt = tiles_of(it, tile_m, tile_n);
+                if (nt > max_tiles) return hipErrorInvalidValue;
+                if (n > 0 && tiles + nt > max_tiles) break;
                 fill(batch.p[n], it, tiles, slots);
                 tiles += nt;
                 ++n;

@@ -56,3 +56,17 @@ def test_input_gradients_take_the_faster_kernel(shapes, T, on256):
     K, N = zip(*shapes)
     got = kernels([T] * len(K), K, N, False)
     assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
+
+
+TILES = {tf.TF_F32: [(32, 32), (32, 64), (64, 64)], tf.TF_BF16: [(64, 64), (128, 64), (128, 128)]}
+
+
+@pytest.mark.parametrize("io", [tf.TF_F32, tf.TF_BF16])
+@pytest.mark.parametrize("M,N", [((1 << 29) + 5, 4), (4, (1 << 29) + 5), ((1 << 30) - 64, 1), (1, (1 << 30) - 64), (1 << 18, 1 << 17), ((1 << 31) - 128, 1)])
+def test_a_launch_has_fewer_than_2_to_the_32_threads(io, M, N):
+    """One block of 256 threads per tile: what fits with one of the launch shapes gets it."""
+    tiles = [-(-M // m) * -(-N // n) for m, n in TILES[io]]
+    if min(tiles) * 256 >= 1 << 32:
+        return                                                       # refused, as it was with 64 x 64 tiles
+    shape = kernels([M], [N], [3], False, io=io, out=io)[0]
+    assert shape >= 0 and tiles[shape] * 256 < 1 << 32
