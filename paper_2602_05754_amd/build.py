@@ -73,17 +73,100 @@ def scc_hazards(asm_text: str) -> list:
     return bad
 
 
-def check_scc(hipcc: str, extra: list) -> None:
-    src = os.path.join(CSRC, "gemm_mfma_bf16.hip")
+# Wait states between a matrix instruction and the first other instruction that reads its result, by the
+# passes it takes (f64 16x16x4: 16, and LDS reads need 18; fp32 16x16x4: 8; bf16 16x16x32: 4).
+_MFMA_WAIT = (("f64", 18), ("16x16x4_f32", 10), ("", 8))
+_REGISTERS = re.compile(r"\b([va])(?:(\d+)|\[(\d+):(\d+)\])")
+_VECTOR_OPS = ("v_", "ds_", "global_", "buffer_", "flat_", "scratch_")
+
+
+def _registers(operands) -> set:
+    out = set()
+    for kind, one, lo, hi in (m for o in operands for m in _REGISTERS.findall(o)):
+        out.update(kind + str(i) for i in range(int(one or lo), int(one or hi) + 1))
+    return out
+
+
+def mfma_hazards(asm_text: str) -> list:
+    """Readers of a matrix instruction's result that come too early, waits and barriers not counted.
+
+    The compiler keeps readers away by wait states, and lets s_waitcnt and s_barrier in between count
+    as one each.  The hardware does not: a sum read that way was the one before.  Follows every path through
+    every function with the distance of each register from the matrix instruction that wrote it.
+    Returns a list of (function, line number, instruction)."""
+    functions, name, block = {}, None, None
+    for ln, raw in enumerate(asm_text.splitlines(), 1):
+        line = raw.split(";")[0].strip()
+        m = re.match(r"^([\w.$]+):$", line)
+        if m:
+            if not line.startswith("."):
+                name = m.group(1)
+            if name:
+                block = (m.group(1), [])
+                functions.setdefault(name, []).append(block)
+        elif name and re.match(r"^[a-z]", line):
+            block[1].append((ln, line))
+    bad = {}
+    for name, blocks in functions.items():
+        index = {label: i for i, (label, _) in enumerate(blocks)}
+        entry = [None] * len(blocks)               # register -> (states since its instruction, states needed)
+        entry[0], work = {}, [0]
+
+        def flow(to, state):
+            if to is None or to >= len(blocks):
+                return
+            if entry[to] is None:
+                entry[to] = dict(state)
+            else:
+                nearer = {r: v for r, v in state.items() if r not in entry[to] or v[1] - v[0] > entry[to][r][1] - entry[to][r][0]}
+                if not nearer:
+                    return
+                entry[to].update(nearer)
+            work.append(to)
+
+        while work:
+            i = work.pop()
+            state, falls = dict(entry[i]), True
+            for ln, line in blocks[i][1]:
+                op, _, rest = line.partition(" ")
+                operands, states, written = rest.split(","), 1, {}
+                if op.startswith(("s_cbranch", "s_branch")):
+                    flow(index.get(rest.strip()), state)
+                if op in ("s_branch", "s_endpgm"):
+                    falls = False
+                    break
+                if op == "s_nop":
+                    states = int(rest, 0) + 1
+                elif op in ("s_waitcnt", "s_barrier"):
+                    states = 0
+                elif op.startswith("v_mfma"):
+                    need = next(n for key, n in _MFMA_WAIT if key in op)
+                    written = {r: (0, need) for r in _registers(operands[:1])}
+                elif op.startswith(_VECTOR_OPS):
+                    stores = "store" in op or "write" in op
+                    for r in _registers(operands if stores else operands[1:]):
+                        if r in state and state[r][0] < state[r][1]:
+                            bad[(name, ln)] = line
+                    for r in _registers([] if stores else operands[:1]):
+                        state.pop(r, None)
+                state = {r: (n + states, need) for r, (n, need) in state.items() if n + states < need}
+                state.update(written)
+            if falls:
+                flow(i + 1, state)
+    return [(name, ln, line) for (name, ln), line in sorted(bad.items())]
+
+
+def check_generated_code(hipcc: str, extra: list) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Rpass-analysis=kernel-resource-usage")]
-    cmd = [hipcc] + flags + extra + ["-S", "--cuda-device-only", src, "-o", "-"]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc -S failed:\n" + res.stderr)
-    bad = scc_hazards(res.stdout)
-    if bad:
-        raise RuntimeError("inline assembly between a writer and a reader of SCC:\n" +
-                           "\n".join(f"  {f} line {ln}: {ins}" for f, ln, ins in bad[:10]))
+    for source in ("gemm_mfma_bf16.hip", "gemm_generic.hip"):
+        cmd = [hipcc] + flags + extra + ["-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", "-"]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc -S failed:\n" + res.stderr)
+        for what, bad in (("inline assembly between a writer and a reader of SCC", scc_hazards(res.stdout)),
+                          ("a matrix instruction's result is read too early", mfma_hazards(res.stdout))):
+            if bad:
+                raise RuntimeError(f"{source}: {what}:\n" + "\n".join(f"  {f} line {ln}: {ins}" for f, ln, ins in bad[:10]))
 
 
 def build(verbose: bool = False) -> str:
@@ -113,7 +196,7 @@ def build(verbose: bool = False) -> str:
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", l)
         if m and int(m.group(1)) != 0:
             raise RuntimeError(f"kernel {name} uses {m.group(1)} bytes/lane of scratch memory")
-    check_scc(hipcc, extra)
+    check_generated_code(hipcc, extra)
     return LIB
 
 

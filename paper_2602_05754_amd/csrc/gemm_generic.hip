@@ -206,11 +206,20 @@ struct Operand {
 
 // Between the last matrix instruction and the first vector instruction that reads its result.  Left to
 // itself the compiler counts a wait and a barrier in between as wait states, and an fp32 sum's last
-// register, read first behind the two, was the old one.
-__device__ __forceinline__ void wait_for_sums() {
-    __builtin_amdgcn_sched_barrier(0);
+// register, read first behind the two, was the old one.  The sums pass through statements in front of the
+// wait and behind it: no matrix instruction can follow it, no reader precede it.  (The build looks through
+// the generated code for a reader that comes too early.)
+template <class V, int kI, int kJ>
+__device__ __forceinline__ void wait_for_sums(V (&x)[kI][kJ]) {
+    auto tie = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kI; ++i)
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) asm volatile("" : "+v"(x[i][j]));
+    };
+    tie();
     asm volatile("s_nop 15\n\ts_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
+    tie();
 }
 
 // Block number -> logical tile: runs of consecutive tiles stay on one XCD (block b runs on XCD b % 8).
@@ -268,7 +277,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 #pragma unroll
         for (int j = 0; j < OpB::kFrags; ++j) acc[i][j] = Sum4{0, 0, 0, 0};
 
-    Sum4 second = {0, 0, 0, 0};                          // kExact: the second half steps' sums, so that two chains alternate
+    Sum4 second[1][1] = {{Sum4{0, 0, 0, 0}}};            // kExact: the second half steps' sums, so that two chains alternate
 
     const int wm = wave >> 1, wn = wave & 1;
     auto contract = [&](const char* stage) {
@@ -298,7 +307,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
             for (int e = 0; e < 4; ++e) {
                 auto wide = [](uint32_t x) { return double(__uint_as_float(x)); };
                 acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide(fb[0][0][e]), wide(fa[0][0][e]), acc[0][0], 0, 0, 0);
-                second = __builtin_amdgcn_mfma_f64_16x16x4f64(wide(fb[1][0][e]), wide(fa[1][0][e]), second, 0, 0, 0);
+                second[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide(fb[1][0][e]), wide(fa[1][0][e]), second[0][0], 0, 0, 0);
             }
         } else {
             f32x4 part[OpA::kFrags][OpB::kFrags];
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
                             part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(fb[u][j][e]), __uint_as_float(fa[u][i][e]),
                                                                               u == 0 && e == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[i][j], 0, 0, 0);
             }
-            wait_for_sums();
+            wait_for_sums(part);
 #pragma unroll
             for (int i = 0; i < OpA::kFrags; ++i)
 #pragma unroll
@@ -365,7 +374,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
             __syncthreads();
         });
 
-    if (kWide || kExact) wait_for_sums();
+    if constexpr (kWide || kExact) wait_for_sums(acc);
+    if constexpr (kExact) wait_for_sums(second);
     // Epilogue: acc[i][j][e] is C[m][n], m = 16 i + lane % 16, n = 16 j + 4 (lane / 16) + e (kExact: lane / 16
     // + 4 e) of the wave's part.  The sums are turned around in LDS ([row][16-byte chunks, XOR-swizzled]) and whole
     // rows of the tile are stored, 16 bytes per lane.
@@ -378,7 +388,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
             if constexpr (kExact) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<float*>(lds + r * kRow + (((c - (lane >> 4) + e) ^ (r & kTurn)) << 4) + (lane >> 4) * 4) = float(acc[0][0][e] + second[e]);
+                    *reinterpret_cast<float*>(lds + r * kRow + (((c - (lane >> 4) + e) ^ (r & kTurn)) << 4) + (lane >> 4) * 4) = float(acc[0][0][e] + second[0][0][e]);
             } else {
                 *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
             }
