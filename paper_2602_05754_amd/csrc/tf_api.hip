@@ -117,23 +117,25 @@ inline bool planned_tail_ok(const Planned& it, Layout layout, Dtype in_dtype) {
            aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
 }
 
+inline int64_t tiles_of(const Planned& it, int64_t tile_m, int64_t tile_n) {
+    return ((it.M + tile_m - 1) / tile_m) * ((it.N + tile_n - 1) / tile_n);
+}
+
 // What a launch is expected to take.  Its work spread evenly over the compute units and its longest
 // chain of steps overlap for the most part; `overlap` says how much of the smaller of the two is left.
 struct Estimate {
     double work = 0, longest = 0, tiles = 0;
-    void add(const Planned& it, int tile_m, int tile_n, int per_step, double tile_steps, double chain_steps) {
+    // `part_tiles` of the problem's tiles take `part_steps` more
+    void add(const Planned& it, int tile_m, int tile_n, int per_step, double tile_steps, double chain_steps, double part_tiles = 0, double part_steps = 0) {
         const double steps = std::ceil(double(it.Kc) / per_step);
-        const double n = std::ceil(double(it.M) / tile_m) * std::ceil(double(it.N) / tile_n);
+        const double n = double(tiles_of(it, tile_m, tile_n));
         tiles += n;
-        work += n * (steps + tile_steps);
-        longest = std::max(longest, steps + chain_steps);
+        work += n * (steps + tile_steps) + part_tiles * part_steps;
+        longest = std::max(longest, steps + chain_steps + (part_tiles > 0 ? part_steps : 0));
     }
     static double us(double even, double chain, double overlap) { return std::max(even, chain) + overlap * std::min(even, chain); }
 };
 
-inline int64_t tiles_of(const Planned& it, int64_t tile_m, int64_t tile_n) {
-    return ((it.M + tile_m - 1) / tile_m) * ((it.N + tile_n - 1) / tile_n);
-}
 // A launch of the generic kernel has a block of 256 threads per tile, and fewer than 2^32 threads.  (An extent
 // is then at most that many tiles of 128: rounded up to whole tiles it still fits 31 bits.)
 constexpr int64_t kMaxGenericTiles = (int64_t(1) << 24) - 1;
@@ -167,29 +169,33 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
 
 // The 256 x 256-tile kernel on these problems.  A step takes 1.45 us when all units are busy (the power
 // limit), 1.15 in the long tiles at a launch's end, 1.0 when there are fewer tiles than units; a tile's
-// epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages.  Measured
+// epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages; where the tile
+// is no whole one 5 more, or 10 when it is added to (masked stores; runs of 64 or 128 rows: 1024 tokens of a LLaMA-1B block, half of its
+// 64-row blocks frozen, 164 (135), 256 tokens and 128-row blocks 47 (39)).  Measured
 // against the generic kernel, us, in brackets the latter: LLaMA-1B block, input gradients, 512 tokens
 // 134 (92), 1024 191 (158), 2048 242 (288); LLaMA-8B block 512 tokens 335 (274), 1024 423 (500); weight
 // gradients of width 512, 256 tokens 16 (9), of the LLaMA-1B block, 256 tokens 49 (64).
-double tile256_us(const std::vector<const Planned*>& items, bool tail) {
+double tile256_us(const std::vector<const Planned*>& items, bool tail, bool accumulate) {
     if (items.empty()) return 0;
     Estimate e;
-    for (const Planned* it : items) e.add(*it, gemm_mfma_tile(), gemm_mfma_tile(), 64, tail ? 5.5 : 4.5, tail ? 7 : 6);
+    const int64_t tile = gemm_mfma_tile();
+    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - (it->M / tile) * (it->N / tile)), accumulate ? 10 : 5);
     const int units = compute_units();
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
 }
 
 // What the generic kernel's launch is compared with tile256_us() by.  Its weight gradients take longer than the
 // estimate, which knows no outputs: they are stored past the caches, and what is added to is fetched again from
-// where an earlier call has left it.  With a tenth more and 0.04 us per MB of outputs (`out_bytes` per value, both
-// ways counted) the kernel chosen was the faster one for all but 2 of 384 launches (block widths 256 to 4096, 64 to
-// 3001 tokens; without, up to 1.76 times the time: LLaMA widths 1024 / 256 / 2816, 256 tokens, fp32 gradients
-// added to 43 us, 256 x 256 tiles 25).  Input gradients as estimated.
-double generic_launch_us(const std::vector<const Planned*>& items, double us, Layout layout, int out_bytes) {
+// where an earlier call has left it (MB of outputs, those added to counted both ways).  Timed on both kernels, block
+// widths 256 to 4096, 64 to 3001 tokens: of 410 launches of whole tensors all get the faster kernel or lose at most 7 %
+// by it; of 248 with runs of 64- to 256-row blocks all but 8 are within 10 % (worst: 1.37 times).  Without: up to
+// 1.76 times (block of widths 1024 / 256 / 2816, 256 tokens, added to: 43 us, 256 x 256 tiles 25).  Input gradients
+// as estimated: within 11 %.
+double generic_launch_us(const std::vector<const Planned*>& items, double us, Layout layout, int out_bytes, bool accumulate) {
     if (layout == Layout::kNT) return us;
-    double values = 0;
-    for (const Planned* it : items) values += double(it->M) * double(it->N);
-    return 1.1 * us + 0.04e-6 * values * out_bytes;
+    double mb = 0;
+    for (const Planned* it : items) mb += 1e-6 * double(it->M) * double(it->N) * out_bytes;
+    return accumulate ? us + 0.06 * 2 * mb : 1.15 * us + 0.03 * mb;
 }
 
 // tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
@@ -216,22 +222,22 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
         else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
         else r.cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
     }
-    const int out_bytes = (out_dtype == Dtype::BF16 ? 2 : 4) * (accumulate ? 2 : 1);
+    const int out_bytes = out_dtype == Dtype::BF16 ? 2 : 4;
     auto generic = [&](const std::vector<const Planned*>& v, int* shape) {
         double us;
         *shape = pick_generic_shape(v, in_dtype, &us);
-        return generic_launch_us(v, us, layout, out_bytes);
+        return generic_launch_us(v, us, layout, out_bytes, accumulate);
     };
     if (plain && route != kRouteWhole256 && route != kRouteAll256) {
         int s;
-        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false) || route == kRouteGeneric) r.shape[kWhole] = s;
+        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false, accumulate) || route == kRouteGeneric) r.shape[kWhole] = s;
     }
     if (!r.cls[kTail].empty() && route != kRouteAll256) {
         std::vector<const Planned*> both = r.cls[kTail];
         both.insert(both.end(), r.cls[kOther].begin(), r.cls[kOther].end());
         int s;
         const double together = generic(both, &s);
-        if (together < tile256_us(r.cls[kTail], true) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
+        if (together < tile256_us(r.cls[kTail], true, accumulate) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
             r.cls[kOther] = both;
             r.cls[kTail].clear();
         }
@@ -1190,12 +1196,16 @@ extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
 
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
 // aligned) are launched together: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the generic kernel.
-extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, int layout_tn,
+// after: rows of the tensor behind the problem's own (it is a run of its rows), or NULL.
+extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
                                    int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
     const Layout layout = layout_tn ? Layout::kTN : Layout::kNT;
     std::vector<Planned> items;
-    for (int i = 0; i < n; ++i)
-        items.push_back(Planned{nullptr, nullptr, nullptr, M[i], N[i], Kc[i], layout_tn ? M[i] : Kc[i], layout_tn ? N[i] : Kc[i], ~0ull, {}});
+    for (int i = 0; i < n; ++i) {
+        const int64_t more = after ? after[i] : 0;
+        items.push_back(Planned{nullptr, nullptr, nullptr, M[i], N[i], Kc[i], layout_tn ? M[i] + more : Kc[i], layout_tn ? N[i] : Kc[i], ~0ull, {}});
+        items.back().rows_after = more;
+    }
     Routes r;
     if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
     for (int c = 0; c < 3; ++c)
@@ -1213,7 +1223,7 @@ extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t*
     for (const Planned& it : items) p.push_back(&it);
     const Dtype dt = to_dtype(tf_dtype(in_dtype));
     const int shape = pick_generic_shape(p, dt, us);
-    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0);
+    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0, false);
     tile[0] = generic_shape(dt, shape).tile_m;
     tile[1] = generic_shape(dt, shape).tile_n;
     return shape;

@@ -9,11 +9,11 @@ import paper_2602_05754_amd as tf
 TILES_256 = -1
 
 
-def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False):
+def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False, after=None):
     n = len(M)
     arr = lambda v: (ctypes.c_int64 * n)(*v)
     kernel = (ctypes.c_int32 * n)(*([99] * n))
-    assert tf.load_library().tf_internal_kernels(n, arr(M), arr(N), arr(Kc), int(tn), io, out, int(accumulate), kernel) == 0
+    assert tf.load_library().tf_internal_kernels(n, arr(M), arr(N), arr(Kc), after and arr(after), int(tn), io, out, int(accumulate), kernel) == 0
     return list(kernel)
 
 
@@ -42,6 +42,23 @@ def block(d, kv, ffn, blocks=1):
 def test_weight_gradients_take_the_faster_kernel(shapes, T, dw, on256):
     K, N = zip(*shapes)
     got = kernels(K, N, [T] * len(K), True, out=tf.TF_BF16 if dw == "bf16" else tf.TF_F32, accumulate=dw == "add")
+    assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
+
+
+# runs of unfrozen row blocks of one block's tensors (widths 1024 / 256 / 2816 and 512 / 256 / 1536)
+RUNS_128 = ([128, 256, 256, 128, 128, 256, 128, 128, 128, 128, 128, 128, 384, 384, 128, 128, 128], [1024] * 3 + [256] * 3 + [2816] * 5 + [1024] * 6)
+RUNS_64 = ([128] + [64] * 11 + [128, 64, 128, 128, 64, 64, 128, 64], [512] + [256] * 5 + [512] + [1536] * 7 + [512] * 6)
+RUNS_256 = ([512, 512, 512, 256, 512, 256, 512, 768, 1280, 1280], [1024, 256, 256, 1024, 1024, 2816, 2816, 2816, 1024, 1024])
+
+
+@pytest.mark.parametrize("runs,T,accumulate,on256", [
+    (RUNS_128, 512, False, False),                       # 23.8, 14.1
+    (RUNS_64, 512, False, False),                        # 24.5, 10.4
+    (RUNS_256, 200, True, True),                         # 22.3, 40.0
+])
+def test_row_runs_take_the_faster_kernel(runs, T, accumulate, on256):
+    M, N = runs
+    got = kernels(M, N, [T] * len(M), True, out=tf.TF_F32 if accumulate else tf.TF_BF16, accumulate=accumulate, after=[256] * len(M))
     assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
 
 
