@@ -240,6 +240,12 @@ __global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, long 
     if (stats) { stats[0] = (long long)c; stats[1] = st->mode; stats[2] = 0; }
 }
 
+// No lane's word has more than kFew candidates: key by key is then quicker than all 32 in pairs (a loop of as many
+// rounds as the fullest word has candidates).  1.74e9 elements, 5 % candidates 1.51 -> 0.74 ms, 1 % 0.48; limits of
+// 3 and 5: 1.53 and 0.94 ms.  61e6 elements, 0.1 %: 119 -> 73 us; 30 % as before.
+constexpr int kFew = 7;
+__device__ __forceinline__ bool few_candidates(uint32_t cand) { return __ballot(__popc(cand) > kFew) == 0; }
+
 // Histogram of the candidates' first digit, the top 11 bits of the key.
 template <bool kCarry>
 __device__ __forceinline__ void rc_hist_word(const Halves& h, uint32_t cand, uint32_t high2, uint32_t* bins) {
@@ -273,6 +279,11 @@ __global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcStat
             if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
             const uint32_t cand = (mode == 1 ? ~word : word) & rc_valid(r, w);
             if (__ballot(cand != 0) == 0) continue;
+            if (few_candidates(cand)) {
+                for (uint32_t left = cand; left; left &= left - 1)
+                    atomicAdd(&bins[perm32(r.index0 + (uint32_t(i) << 16) + uint32_t(__ffs(left) - 1), keys) >> 21], 1u);
+                continue;
+            }
             const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
             if (any_carry) rc_hist_word<true>(h, cand, high2, bins);
             else rc_hist_word<false>(h, cand, high2, bins);
@@ -403,11 +414,14 @@ __global__ __launch_bounds__(kThreads) void rc_apply_kernel(RcBatch batch, const
             if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
             const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
             if (__ballot(cand != 0) == 0) continue;
-            const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
-            bool tie;
-            uint32_t drawn = any_carry ? rc_drawn<true>(h, high2, threshold, tie) : rc_drawn<false>(h, high2, threshold, tie);
-            drawn &= cand;
-            if (tie) {
+            bool one_by_one = few_candidates(cand);
+            uint32_t drawn = 0;
+            if (!one_by_one) {
+                const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
+                drawn = any_carry ? rc_drawn<true>(h, high2, threshold, one_by_one) : rc_drawn<false>(h, high2, threshold, one_by_one);
+                drawn &= cand;
+            }
+            if (one_by_one) {
                 drawn = 0;
                 for (uint32_t left = cand; left; left &= left - 1) {
                     const int b = __ffs(left) - 1;

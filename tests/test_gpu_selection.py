@@ -159,7 +159,7 @@ def test_reconcile_matches_the_oracle_bit_for_bit(ctx, density):
 
 def test_reconcile_more_tensors_than_one_launch_holds(ctx):
     rs = np.random.default_rng(8)
-    numel = [int(n) for n in rs.integers(1, 3000, size=70)]           # 70 tensors: three launches per pass
+    numel = [int(n) for n in rs.integers(1, 3000, size=70)]           # 70 tensors: two launches per pass
     base = [(rs.random(n) < 0.4).astype(np.uint8) for n in numel]
     N = sum(numel)
     for nf in (N // 5, (4 * N) // 5):
@@ -183,6 +183,29 @@ def test_reconcile_where_indices_cross_65536_inside_a_word(ctx, first, r):
     got, _, stats = _run_reconcile(ctx, base, numel, nf, 9 + first)
     ref, count = oracle.reconcile_mask(base, numel, nf, 9 + first)
     assert all(np.array_equal(g, e) for g, e in zip(got, ref)) and stats[0] == count
+
+
+@pytest.mark.parametrize("candidate", [0, 1])
+@pytest.mark.parametrize("per_word", [(0, 1), (7,), (0, 7, 8), (1, 2, 32)])
+def test_reconcile_words_with_few_candidates(ctx, per_word, candidate):
+    """Waves whose words have at most seven candidates each look at them one by one, others at all 32
+    elements: stretches of 64 words (a wave's) with every number around that limit, and stretches that mix them."""
+    rs = np.random.default_rng(len(per_word))
+    n_words = 64 * 70
+    numel = [32 * n_words, 32 * n_words - 13, 77]
+    base = []
+    for n in numel:
+        c = rs.choice(per_word, size=(n + 31) // 32)
+        rank = rs.random((len(c), 32)).argsort(axis=1)               # c random places of a word are candidates
+        bits = np.where(rank < c[:, None], candidate, 1 - candidate).astype(np.uint8).reshape(-1)[:n]
+        base.append(np.ascontiguousarray(bits))
+    ones, have = sum(int(b.sum()) for b in base), sum(int((b == candidate).sum()) for b in base)
+    for share in (0.0, 0.4, 1.0):
+        nf = ones + int(share * have) * (-1 if candidate else 1)
+        got, _, stats = _run_reconcile(ctx, base, numel, nf, 31 + int(10 * share))
+        ref, count = oracle.reconcile_mask(base, numel, nf, 31 + int(10 * share))
+        assert all(np.array_equal(g, e) for g, e in zip(got, ref)) and stats[0] == count == ones
+        assert sum(int(g.sum()) for g in got) == nf
 
 
 def test_reconcile_threshold_is_the_largest_key_drawn(ctx):
