@@ -1,5 +1,7 @@
 """Helpers for the GPU parity tests: host <-> device marshalling of the seeded
 inputs and error norms.  No arithmetic of the method lives here."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -13,6 +15,16 @@ BY_ESTIMATE, WHOLE_256, ALL_256, GENERIC = range(4)
 
 def set_route(ctx, route: int) -> None:
     assert tf.load_library().tf_internal_gemm_route(ctx.handle, route) == 0
+
+
+@contextlib.contextmanager
+def route(ctx, which: int):
+    """The GEMM launches inside the block take that kernel."""
+    set_route(ctx, which)
+    try:
+        yield
+    finally:
+        set_route(ctx, BY_ESTIMATE)
 
 
 def kinds_of(ctx, fn) -> list:

@@ -8,7 +8,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import CODE, TDT, TOL, assert_elementwise, canary, dev, host64, raw_bytes, rel_fro
+from gpu_util import CODE, GENERIC, TDT, TOL, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 
@@ -83,7 +83,12 @@ def test_bf16_matrix_core_path_several_tiles(ctx, r):
     # every dimension a multiple of 256: 2-3 tiles per side, contraction 4-12 steps of 64
     cfg = wl.scaled(wl.CONFIGS[2], blocks=1, d=512, kv=256, ffn=768, T=512)
     mask = wl.permutation_mask(cfg, r)
-    _run_case(ctx, cfg, cfg.T, mask, TOL["bf16"])
+    got = {}
+    for which, kind in ((WHOLE_256, "mfma"), (GENERIC, "generic")):
+        with route(ctx, which):
+            kinds = kinds_of(ctx, lambda: got.setdefault(kind, _run_case(ctx, cfg, cfg.T, mask, TOL["bf16"])))
+        assert set(kinds) == {"dx_" + kind} | ({"dw_" + kind} if r < 1 else set())
+    assert got["mfma"][0] == got["generic"][0]             # the same sums in the same order: the same bytes
 
 
 def test_bf16_ragged_shapes_fall_to_the_generic_kernel(ctx):
@@ -103,6 +108,11 @@ def test_mixed_eligible_and_ragged_layers_in_one_call(ctx):
 
 @pytest.mark.parametrize("dims", [dict(d=256, kv=256, ffn=512, T=256), dict(d=136, kv=40, ffn=72, T=50)])
 def test_fp32_accumulation_over_microbatches_with_per_microbatch_masks(ctx, dims):
+    with route(ctx, WHOLE_256):                            # 256-multiples on 256 x 256 tiles, small as they are
+        _accumulate_with_masks(ctx, dims)
+
+
+def _accumulate_with_masks(ctx, dims):
     # sum_m U_m (.) g_m into fp32 accumulators (App. D.1 update rule); bf16 inputs
     cfg = wl.scaled(wl.CONFIGS[5], blocks=1, microbatches=3, **dims)
     sh = cfg.shapes; T = cfg.T; L = cfg.n_layers
@@ -136,6 +146,11 @@ def test_fp32_accumulation_over_microbatches_with_per_microbatch_masks(ctx, dims
 @pytest.mark.parametrize("dims", [dict(d=256, kv=256, ffn=512, T=256), dict(d=512, kv=256, ffn=768, T=320),
                                   dict(d=136, kv=40, ffn=72, T=50)])
 def test_microbatches_where_a_layers_first_product_overwrites_its_accumulator(ctx, dims):
+    with route(ctx, WHOLE_256):
+        _first_product_overwrites(ctx, dims)
+
+
+def _first_product_overwrites(ctx, dims):
     # The same sum over microbatches (App. D.1 update rule), with the choice between "=" and "+="
     # made layer by layer: a layer's first unfrozen microbatch of the step overwrites whatever its
     # accumulator holds (here: NaN canaries, which an addition would keep), later ones add.

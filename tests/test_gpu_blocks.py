@@ -10,7 +10,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import CODE, TDT, TOL, assert_elementwise, canary, dev, host64, raw_bytes, rel_fro
+from gpu_util import CODE, TDT, TOL, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 
@@ -77,14 +77,16 @@ def test_fp32_row_blocks_on_the_generic_kernel(ctx):
 
 @pytest.mark.parametrize("block_rows", [256, 128])
 def test_bf16_row_blocks_on_the_matrix_cores(ctx, block_rows):
-    # runs of unfrozen blocks with a multiple of 256 rows take the MFMA kernel, the others the generic one
+    # 256-row blocks are tile rows of one problem per tensor; runs of 128-row blocks are problems of their own
     shapes = [(1024, 512), (512, 256), (2048, 256), (768, 768), (256, 512)]
     rs = np.random.default_rng(block_rows)
     masks = [(rs.random(k // block_rows) < 0.4).astype(np.uint8) for k, n in shapes]
     masks[1] = None                                        # a layer without row mask
     masks[4] = np.ones(256 // block_rows, np.uint8)        # every block frozen: nothing of dW is touched
     masks[2][:] = 0; masks[2][1] = 1                       # a single hole
-    _case(ctx, shapes, 192, "bf16", block_rows, None, masks, seed=2)
+    with route(ctx, WHOLE_256):
+        kinds = kinds_of(ctx, lambda: _case(ctx, shapes, 192, "bf16", block_rows, None, masks, seed=2))
+    assert set(kinds) == {"dx_generic", "dw_mfma"}         # 192 tokens: fewer rows than a tile for the input gradients
 
 
 def test_row_block_element_masks_and_the_optimizer_that_follows(ctx):
@@ -190,4 +192,6 @@ def test_launches_smaller_than_the_fill_streams_lead(ctx, shapes, T):
     fewer steps than that in the whole launch it reaches the end of its work before the first step
     is consumed and has to stand still on the last step without reading past any buffer."""
     L = len(shapes)
-    _case(ctx, shapes, T, "bf16", 256, np.zeros(L, np.uint8), None, seed=5)
+    with route(ctx, WHOLE_256):
+        kinds = kinds_of(ctx, lambda: _case(ctx, shapes, T, "bf16", 256, np.zeros(L, np.uint8), None, seed=5))
+    assert ("dx_mfma" in kinds) == (T >= 256) and ("dw_mfma" in kinds) == all(n >= 256 for k, n in shapes)

@@ -12,7 +12,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, set_route
+from gpu_util import ALL_256, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, set_route
 
 pytestmark = pytest.mark.gpu
 
@@ -112,3 +112,23 @@ def test_fp32_accumulation_on_partial_tiles(ctx):
     shapes = [(328, 264), (640, 256), (256, 520)]
     masks = [None, np.array([0, 1, 0, 0, 1], np.uint8), np.array([0, 1], np.uint8)]
     _case(ctx, shapes, 128, seed=6, row_masks=masks, block_rows=128, dw="f32", calls=3)
+
+
+@pytest.mark.parametrize("dw,calls", [("bf16", 1), ("f32", 2)])
+@pytest.mark.parametrize("T,block_rows", [(65, 128), (200, 64), (311, 128)])
+def test_row_runs_over_token_counts_that_are_no_multiple_of_64(ctx, T, block_rows, dw, calls):
+    """The masked last step of a contraction together with windows that begin before a run of rows, end
+    behind it, or lie inside the tensor: runs of 64 and 128 rows at a tensor's start, end and between."""
+    shapes = [(1024, 512), (384, 256), (256, 264), (768, 520)]
+    rs = np.random.default_rng(T)
+    masks = [(rs.random(k // block_rows) < 0.45).astype(np.uint8) for k, n in shapes]
+    per = 128 // block_rows
+    masks[1] = np.repeat(np.array([0, 1, 1], np.uint8), per)
+    masks[2] = np.repeat(np.array([1, 0], np.uint8), per)
+    masks[3] = np.repeat(np.array([1, 0, 1, 1, 0, 0], np.uint8), per)
+    set_route(ctx, ALL_256)
+    try:
+        kinds = _case(ctx, shapes, T, seed=T, row_masks=masks, block_rows=block_rows, dw=dw, calls=calls)
+    finally:
+        set_route(ctx, WHOLE_256)
+    assert "dw_mfma" in kinds and "dw_generic" not in kinds

@@ -15,7 +15,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import canary, dev, host64, raw_bytes, rel_fro
+from gpu_util import GENERIC, WHOLE_256, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 
@@ -125,7 +125,8 @@ def test_llama8b_stage_all_eight_blocks(ctx):
         print(f"cfg3 r={r} worst sampled rel_fro {worst:.2e}")
 
 
-def test_operands_and_outputs_that_cross_a_4gib_address_boundary(ctx):
+@pytest.mark.parametrize("which,kind", [(WHOLE_256, "mfma"), (GENERIC, "generic")])
+def test_operands_and_outputs_that_cross_a_4gib_address_boundary(ctx, which, kind):
     """Every tensor of a layer in turn is laid across a multiple of 2^32 in the device address
     space, so that the fill addresses of some tile (inputs) or the rows of some tile's epilogue
     (outputs) carry into the high word; whole outputs against the oracle."""
@@ -164,9 +165,11 @@ def test_operands_and_outputs_that_cross_a_4gib_address_boundary(ctx):
         for name in src:
             view[name].copy_(dev(src[name], "bf16"))
         view["dX"].copy_(canary((T, k), torch.bfloat16)); view["dW"].copy_(canary((k, n), torch.bfloat16))
-        tf.tf_stage_backward(ctx, [(k, n)], T, tf.TF_BF16, [view["W"]], [view["X"]], [view["dY"]], np.zeros(1, np.uint8),
-                             [view["dX"]], [view["dW"]], tf.TF_BF16)
-        torch.cuda.synchronize()
+        with route(ctx, which):
+            kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(
+                ctx, [(k, n)], T, tf.TF_BF16, [view["W"]], [view["X"]], [view["dY"]], np.zeros(1, np.uint8),
+                [view["dX"]], [view["dW"]], tf.TF_BF16))
+        assert kinds == ["dx_" + kind, "dw_" + kind]
         assert_elementwise(host64(view["dX"]), ref_dX[0], "bf16", f"dX with {across} across the boundary")
         assert_elementwise(host64(view["dW"]), ref_dW[0], "bf16", f"dW with {across} across the boundary")
     del pool

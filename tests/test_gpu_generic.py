@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, set_route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -68,15 +68,16 @@ def _case(ctx, shapes, T, io, dw, accumulate=False, seed=0):
         rW = [r + x.T @ y for r, x, y in zip(rW, f64(X), f64(dY))]
     gX = [Guarded((T, k), io) for k, n in shapes]
     gW = [Guarded(s, dw, torch.from_numpy(o) if accumulate else None) for s, o in zip(shapes, old)]
-    tf.tf_stage_backward(ctx, shapes, T, CODE[io], [dev(a, io) for a in W], [dev(a, io) for a in X], [dev(a, io) for a in dY],
-                         None, [g.t for g in gX], [g.t for g in gW], CODE[dw], accumulate=accumulate)
-    torch.cuda.synchronize()
+    gin = [[dev(a, io) for a in t] for t in (W, X, dY)]
+    kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, CODE[io], *gin, None, [g.t for g in gX], [g.t for g in gW],
+                                                       CODE[dw], accumulate=accumulate))
     for l in range(L):
         # one rounding of a sum in 32 bits: the bounds of assert_elementwise
         assert_elementwise(host64(gX[l].t), rX[l], io, f"dX[{l}] {shapes[l]} T={T} {io}")
         assert_elementwise(host64(gW[l].t), rW[l], dw, f"dW[{l}] {shapes[l]} T={T} {io}->{dw}")
         gX[l].check(f"dX[{l}] {shapes[l]} T={T}")
         gW[l].check(f"dW[{l}] {shapes[l]} T={T}")
+    return kinds
 
 
 # steps of 64 (bf16) / 32 (fp32) contraction values, tiles of 32, 64, 128, pieces of 8 / 4 elements
@@ -126,37 +127,46 @@ def test_every_launch_shape(ctx, half, io, T, shapes, tile):
     (65, [(8192, 4104), (8192, 4104)]),
 ])
 def test_contractions_that_are_no_multiple_of_a_step_on_256_tiles(ctx, T, shapes, dw, accumulate):
-    K, N = zip(*shapes)
-    _, generic, tiles256 = _expected(K, N, [T] * len(K), "bf16")
-    assert tiles256 < generic                                        # so this is the route
-    _case(ctx, shapes, T, "bf16", dw, accumulate, seed=T)
+    kinds = _case(ctx, shapes, T, "bf16", dw, accumulate, seed=T)
+    assert "dw_mfma" in kinds and "dw_generic" not in kinds
 
 
 def test_input_gradients_over_ragged_feature_counts_on_256_tiles(ctx):
     T, shapes = 2048, [(4096, 1032), (4104, 1096), (4096, 328)]
-    K, N = zip(*shapes)
-    _, generic, tiles256 = _expected([T] * 3, K, N, "bf16")
-    assert tiles256 < generic
-    _case(ctx, shapes, T, "bf16", "bf16", seed=5)
+    kinds = _case(ctx, shapes, T, "bf16", "bf16", seed=5)
+    assert "dx_mfma" in kinds and "dx_generic" not in kinds
 
 
-@pytest.mark.parametrize("io,T,K,N", [("f32", 37, 45, 70), ("bf16", 37, 45, 70), ("bf16", 577, 4096, 8200), ("bf16", 2048, 4096, 1096)])
-def test_infinities_stay_where_they_are(ctx, io, T, K, N):
-    """What a last step takes from outside the contraction, or a second time, must not meet an infinity."""
+@pytest.mark.parametrize("io,T,K,N,which", [
+    ("f32", 37, 45, 70, GENERIC), ("bf16", 37, 45, 70, GENERIC), ("bf16", 577, 4096, 8200, GENERIC), ("bf16", 2048, 4096, 1096, GENERIC),
+    # 256 x 256 tiles: contractions of 8 and 1, of 8 and 1, of 8 and none values more than whole steps
+    ("bf16", 321, 264, 1096, ALL_256), ("bf16", 577, 4096, 8200, ALL_256), ("bf16", 2048, 4096, 1096, ALL_256),
+])
+def test_infinities_stay_where_they_are(ctx, io, T, K, N, which):
+    """What a last step takes from outside the contraction, or a second time, must not meet an infinity
+    or a zero: in either operand, in both layouts."""
+    dt = TDT[io]
     for t, n in ((T - 1, N - 1), (T - 64, N - 64)):
         if t < 0:
             continue
-        W, X, dY = torch.ones(K, N), torch.ones(T, K), torch.ones(T, N)
-        dY[t, n] = float("inf")
-        dt = TDT[io]
-        dX, dW = torch.empty(T, K, device="cuda", dtype=dt), torch.empty(K, N, device="cuda", dtype=dt)
-        tf.tf_stage_backward(ctx, [(K, N)], T, CODE[io], [W.to(dt).cuda()], [X.to(dt).cuda()], [dY.to(dt).cuda()], None, [dX], [dW], CODE[io])
-        rX, rW = torch.full((T, K), float(N)).to(dt).float(), torch.full((K, N), float(T)).to(dt).float()
-        rX[t], rW[:, n] = float("inf"), float("inf")
-        assert torch.equal(dX.float().cpu(), rX) and torch.equal(dW.float().cpu(), rW)
+        for inf in ("dY", "W and X"):
+            W, X, dY = torch.ones(K, N), torch.ones(T, K), torch.ones(T, N)
+            rX, rW = torch.full((T, K), float(N)).to(dt).float(), torch.full((K, N), float(T)).to(dt).float()
+            if inf == "dY":
+                dY[t, n] = float("inf")
+                rX[t], rW[:, n] = float("inf"), float("inf")
+            else:
+                W[K - 1, n] = X[t, K - 1] = float("inf")
+                rX[:, K - 1], rW[K - 1] = float("inf"), float("inf")
+            dX, dW = torch.empty(T, K, device="cuda", dtype=dt), torch.empty(K, N, device="cuda", dtype=dt)
+            gin = [[a.to(dt).cuda()] for a in (W, X, dY)]
+            with route(ctx, which):
+                kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, [(K, N)], T, CODE[io], *gin, None, [dX], [dW], CODE[io]))
+            assert kinds == (["dx_generic", "dw_generic"] if which == GENERIC else ["dx_mfma", "dw_mfma"])
+            assert torch.equal(dX.float().cpu(), rX) and torch.equal(dW.float().cpu(), rW)
 
 
-@pytest.mark.parametrize("T,shapes,route,dx,dw", [
+@pytest.mark.parametrize("T,shapes,which,dx,dw", [
     (256, [(256, 256)], BY_ESTIMATE, "dx_generic", "dw_generic"),       # 256 x 256 tiles fit, the smaller ones are faster
     (256, [(256, 256)], WHOLE_256, "dx_mfma", "dw_mfma"),
     (257, [(256, 256)], WHOLE_256, "dx_mfma", "dw_generic"),
@@ -165,13 +175,10 @@ def test_infinities_stay_where_they_are(ctx, io, T, K, N):
     (2048, [(4096, 4096)], GENERIC, "dx_generic", "dw_generic"),
     (4097, [(4096, 4096)] * 2, BY_ESTIMATE, "dx_mfma", "dw_mfma"),
 ])
-def test_profile_kinds_name_the_kernel_that_ran(ctx, T, shapes, route, dx, dw):
+def test_profile_kinds_name_the_kernel_that_ran(ctx, T, shapes, which, dx, dw):
     """The kinds follow the kernel, whatever the shape would allow: the other tests go by them."""
     z = lambda s: [torch.zeros(q, dtype=torch.bfloat16, device="cuda") for q in s]
     W, dW, X, dX, dY = z(shapes), z(shapes), z([(T, k) for k, n in shapes]), z([(T, k) for k, n in shapes]), z([(T, n) for k, n in shapes])
-    set_route(ctx, route)
-    try:
+    with route(ctx, which):
         kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, None, dX, dW, tf.TF_BF16))
-    finally:
-        set_route(ctx, BY_ESTIMATE)
     assert kinds == [dx, dw]

@@ -1,6 +1,6 @@
 """tf_reconcile_mask_static, the entry point that allocates nothing (its rank-search state is a
 static device array), against tf_reconcile_mask on the same inputs, through the C ABI: masks
-and statistics bit for bit (Alg. 2: integer work), on two calls in a row, the second with a
+and statistics bit for bit (Alg. 2: integer work), on calls in a row, the second with a
 smaller input, so that whatever the first call left in the shared array must not matter; the
 existing entry point's result is itself checked against the oracle."""
 import numpy as np
@@ -22,9 +22,12 @@ def test_static_scratch_entry_point_matches_the_allocating_one():
     ctx = tf.Context(0)
     try:
         rs = np.random.default_rng(2024)
-        # first call: 40 tensors (two launches per pass), additions; second: 3 small tensors, removals
+        # first call: 40 tensors, additions; second: 3 small tensors, removals; third: 140 tensors (three
+        # launches per pass), additions, and a last call that finds what those left
         cases = [([int(n) for n in rs.integers(1, 90000, size=40)], 0.3, 0.6, 0xABCDEF),
-                 ([1000, 33, 70001], 0.7, 0.2, 17)]
+                 ([1000, 33, 70001], 0.7, 0.2, 17),
+                 ([int(n) for n in rs.integers(1, 9000, size=140)], 0.3, 0.6, 0xABCDEF),
+                 ([999], 0.5, 0.9, 5)]
         for numel, density, r, seed in cases:
             base = [(rs.random(n) < density).astype(np.uint8) for n in numel]
             nf = int(r * sum(numel))
