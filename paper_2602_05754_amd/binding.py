@@ -288,13 +288,13 @@ def _check_all(ctx, n, skip, tables):
         if seq is None:
             continue
         if isinstance(seq, PtrTable) and len(seq) == n and n > 0:
-            desc += [seq.info_address, a.ctypes.data, b.ctypes.data if b is not None else 0, stride, scale, code, t[7], 0]
+            desc += [seq.info_address, a.ctypes.data, b.ctypes.data if b is not None else 0, stride, scale, int(code), t[7], 0]
         else:
             rest.append(t)
     if desc:
         arr = (ctypes.c_int64 * len(desc))(*desc)
         bad = load_library().tf_internal_check_tables(len(desc) // 8, arr, n, None if skip is None else skip.ctypes.data,
-                                                      -1 if ctx is None else ctx.device_id)
+                                                      -1 if ctx is None else int(ctx.device_id))
         if bad >= 0:
             rest = tables
     for seq, a, b, stride, scale, code, what, skipping in rest:

@@ -82,3 +82,27 @@ def test_tables_of_another_length_and_raw_pointers():
     def raw(t):
         t["W"][0] = 4096                                                # a pointer of unknown size passes
     assert _backward(tf.PtrTable, raw)[0] is tf.TfError
+
+
+@pytest.mark.parametrize("number", [int, np.int64, np.int32, float])
+def test_type_codes_and_sizes_of_other_number_types(number):
+    """What int() takes, as from an array of codes, works for tables as for lists."""
+    for wrap in (list, tf.PtrTable):
+        t = {k: wrap(v) for k, v in {
+            "W": [torch.zeros(k, n, dtype=torch.bfloat16) for k, n in SHAPES], "X": [torch.zeros(T, k, dtype=torch.bfloat16) for k, n in SHAPES],
+            "dY": [torch.zeros(T, n, dtype=torch.bfloat16) for k, n in SHAPES], "dX": [torch.zeros(T, k, dtype=torch.bfloat16) for k, n in SHAPES],
+            "dW": [torch.zeros(k, n) for k, n in SHAPES]}.items()}
+        with pytest.raises(tf.TfError):                                 # no context: it has passed the checks
+            tf.tf_stage_backward(None, SHAPES, number(T), number(tf.TF_BF16), t["W"], t["X"], t["dY"], None, t["dX"], t["dW"], number(tf.TF_F32))
+
+
+def test_a_device_number_of_another_number_type():
+    class Ctx:
+        device_id, handle = np.int64(0), None
+
+        def last_hip_error(self):
+            return 0
+    with pytest.raises(ValueError) as e:                                # host tensors: refused for that, by name
+        tf.tf_stage_backward(Ctx(), SHAPES[:1], T, tf.TF_F32, *[tf.PtrTable([torch.zeros(T, 16)])] * 3, None,
+                             *[tf.PtrTable([torch.zeros(T, 16)])] * 2, tf.TF_F32)
+    assert "GPU 0" in str(e.value)
