@@ -241,8 +241,9 @@ __global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, long 
 }
 
 // No lane's word has more than kFew candidates: key by key is then quicker than all 32 in pairs (a loop of as many
-// rounds as the fullest word has candidates).  1.74e9 elements, 5 % candidates 1.51 -> 0.74 ms, 1 % 0.48; limits of
-// 3 and 5: 1.53 and 0.94 ms.  61e6 elements, 0.1 %: 119 -> 73 us; 30 % as before.
+// rounds as the fullest word has candidates).  1.74e9 elements, 5 % candidates 1.51 -> 0.85 ms, 1 % 0.45; 61e6
+// elements, 0.1 %: 119 -> 72 us.  From a task's first fuller word on nothing is asked any more (asking at each
+// word took 0.8 % of the time at 30 % candidates), and the 32 registers of a Halves are filled only then.
 constexpr int kFew = 7;
 __device__ __forceinline__ bool few_candidates(uint32_t cand) { return __ballot(__popc(cand) > kFew) == 0; }
 
@@ -268,22 +269,28 @@ __global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcStat
     __syncthreads();
     for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
         const RcTask r = rc_task(batch, task);
+        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
+        int i = 0;
+#pragma unroll 1
+        for (; i < kRows; ++i) {                                   // as long as the words have few candidates
+            const int64_t w = r.first + i * kRowWords;
+            uint32_t cand = (mode == 1 ? ~next : next) & rc_valid(r, w);
+            if (!few_candidates(cand)) break;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            for (; cand; cand &= cand - 1)
+                atomicAdd(&bins[perm32(r.index0 + (uint32_t(i) << 16) + uint32_t(__ffs(cand) - 1), keys) >> 21], 1u);
+        }
+        if (i == kRows) continue;
         Halves h;
         h.init(r.index0, keys);
         const bool any_carry = __ballot(h.carry) != 0;
-        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
 #pragma unroll 1
-        for (int i = 0; i < kRows; ++i) {
+        for (; i < kRows; ++i) {
             const int64_t w = r.first + i * kRowWords;
             const uint32_t word = next;
             if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
             const uint32_t cand = (mode == 1 ? ~word : word) & rc_valid(r, w);
             if (__ballot(cand != 0) == 0) continue;
-            if (few_candidates(cand)) {
-                for (uint32_t left = cand; left; left &= left - 1)
-                    atomicAdd(&bins[perm32(r.index0 + (uint32_t(i) << 16) + uint32_t(__ffs(left) - 1), keys) >> 21], 1u);
-                continue;
-            }
             const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
             if (any_carry) rc_hist_word<true>(h, cand, high2, bins);
             else rc_hist_word<false>(h, cand, high2, bins);
@@ -397,37 +404,49 @@ __device__ __forceinline__ uint32_t rc_drawn(const Halves& h, uint32_t high2, ui
     tie = nearest.x == 0 || nearest.y == 0;
     return drawn;
 }
+// The drawn ones of a word's candidates, one by one.
+__device__ __forceinline__ uint32_t rc_drawn_each(uint32_t cand, uint32_t index0, const RcKeys& keys, uint32_t threshold) {
+    uint32_t drawn = 0;
+    for (; cand; cand &= cand - 1) {
+        const int b = __ffs(cand) - 1;
+        if (perm32(index0 + uint32_t(b), keys) <= threshold) drawn |= 1u << b;
+    }
+    return drawn;
+}
 __global__ __launch_bounds__(kThreads) void rc_apply_kernel(RcBatch batch, const RcState* st, RcKeys keys) {
     const uint32_t mode = st->mode;
     if (mode == 0) return;
     const uint32_t threshold = st->prefix;
     for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
         const RcTask r = rc_task(batch, task);
+        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
+        int i = 0;
+#pragma unroll 1
+        for (; i < kRows; ++i) {                                   // as long as the words have few candidates
+            const int64_t w = r.first + i * kRowWords;
+            const uint32_t old = next;
+            const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
+            if (!few_candidates(cand)) break;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            const uint32_t drawn = rc_drawn_each(cand, r.index0 + (uint32_t(i) << 16), keys, threshold);
+            if (drawn) r.bits[w] = mode == 1 ? (old | drawn) : (old & ~drawn);
+        }
+        if (i == kRows) continue;
         Halves h;
         h.init(r.index0, keys);
         const bool any_carry = __ballot(h.carry) != 0;
-        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
 #pragma unroll 1
-        for (int i = 0; i < kRows; ++i) {
+        for (; i < kRows; ++i) {
             const int64_t w = r.first + i * kRowWords;
             const uint32_t old = next;
             if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
             const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
             if (__ballot(cand != 0) == 0) continue;
-            bool one_by_one = few_candidates(cand);
-            uint32_t drawn = 0;
-            if (!one_by_one) {
-                const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
-                drawn = any_carry ? rc_drawn<true>(h, high2, threshold, one_by_one) : rc_drawn<false>(h, high2, threshold, one_by_one);
-                drawn &= cand;
-            }
-            if (one_by_one) {
-                drawn = 0;
-                for (uint32_t left = cand; left; left &= left - 1) {
-                    const int b = __ffs(left) - 1;
-                    if (perm32(r.index0 + (uint32_t(i) << 16) + uint32_t(b), keys) <= threshold) drawn |= 1u << b;
-                }
-            }
+            const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
+            bool tie;
+            uint32_t drawn = any_carry ? rc_drawn<true>(h, high2, threshold, tie) : rc_drawn<false>(h, high2, threshold, tie);
+            drawn &= cand;
+            if (tie) drawn = rc_drawn_each(cand, r.index0 + (uint32_t(i) << 16), keys, threshold);
             if (drawn) r.bits[w] = mode == 1 ? (old | drawn) : (old & ~drawn);
         }
     }
