@@ -117,19 +117,19 @@ inline bool planned_tail_ok(const Planned& it, Layout layout, Dtype in_dtype) {
            aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
 }
 
-inline int64_t tiles_of(const Planned& it, int64_t tile_m, int64_t tile_n) {
-    return ((it.M + tile_m - 1) / tile_m) * ((it.N + tile_n - 1) / tile_n);
-}
+inline uint32_t parts_of(int64_t extent, uint32_t size) { return (uint32_t(extent) + size - 1) / size; }       // extents have 31 bits
+inline int64_t tiles_of(const Planned& it, uint32_t tile_m, uint32_t tile_n) { return int64_t(parts_of(it.M, tile_m)) * parts_of(it.N, tile_n); }
 
 // What a launch is expected to take.  Its work spread evenly over the compute units and its longest
 // chain of steps overlap for the most part; `overlap` says how much of the smaller of the two is left.
 struct Estimate {
-    double work = 0, longest = 0, tiles = 0;
+    double work = 0, longest = 0, tiles = 0, most_tiles = 0;      // most_tiles: of one problem
     // `part_tiles` of the problem's tiles take `part_steps` more
     void add(const Planned& it, int tile_m, int tile_n, int per_step, double tile_steps, double chain_steps, double part_tiles = 0, double part_steps = 0) {
-        const double steps = std::ceil(double(it.Kc) / per_step);
+        const double steps = parts_of(it.Kc, per_step);
         const double n = double(tiles_of(it, tile_m, tile_n));
         tiles += n;
+        most_tiles = std::max(most_tiles, n);
         work += n * (steps + tile_steps) + part_tiles * part_steps;
         longest = std::max(longest, steps + chain_steps + (part_tiles > 0 ? part_steps : 0));
     }
@@ -151,11 +151,9 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
     bool any = false;
     for (int i = 0; i < kGenericShapes; ++i) {
         const GenericShape& s = generic_shape(in_dtype, i);
-        bool fits = true;
-        for (const Planned* it : items) fits = fits && tiles_of(*it, s.tile_m, s.tile_n) <= kMaxGenericTiles;
-        if (!fits) continue;
         Estimate e;
         for (const Planned* it : items) e.add(*it, s.tile_m, s.tile_n, in_dtype == Dtype::BF16 ? 64 : 32, s.tile_steps, s.tile_steps);
+        if (e.most_tiles > kMaxGenericTiles) continue;
         const double us = Estimate::us(e.work / compute_units() * s.step_us, e.longest * s.chain_us, 0.25);
         if (!any || us < *best_us) { best = i; *best_us = us; }
         any = true;
@@ -178,8 +176,8 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
 double tile256_us(const std::vector<const Planned*>& items, bool tail, bool accumulate) {
     if (items.empty()) return 0;
     Estimate e;
-    const int64_t tile = gemm_mfma_tile();
-    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - (it->M / tile) * (it->N / tile)), accumulate ? 10 : 5);
+    const uint32_t tile = gemm_mfma_tile();
+    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - int64_t(uint32_t(it->M) / tile) * (uint32_t(it->N) / tile)), accumulate ? 10 : 5);
     const int units = compute_units();
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
 }
@@ -271,8 +269,8 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
         std::vector<const Planned*>& v = cls[c];
         // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
         std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
-        const int64_t tile_m = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_m;
-        const int64_t tile_n = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_n;
+        const uint32_t tile_m = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_m;
+        const uint32_t tile_n = shape[c] < 0 ? gemm_mfma_tile() : generic_shape(in_dtype, shape[c]).tile_n;
         const int64_t max_tiles = shape[c] < 0 ? kMaxTiles256 : kMaxGenericTiles;
         size_t i = 0;
         while (i < v.size()) {
