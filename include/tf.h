@@ -132,6 +132,12 @@ const char* tf_version(void);
  *                grad_scale) and requires dw_dtype == TF_F32.
  *   Products accumulate in fp32; bf16 outputs are rounded to nearest even once.
  *   n_layers == 0 is a no-op.  With io_dtype TF_F32 the arithmetic is true fp32.
+ *   With io_dtype TF_BF16 a layer's outputs depend on that layer alone, bit for bit.
+ *   With TF_F32 their last bits also depend on the other layers of the call: the
+ *   sums of a launch - all dX, or the dW of all unfrozen layers - are formed in 64
+ *   bits if the launch is a short one, in 32 bits otherwise (which of the two
+ *   follows from the problems' sizes and the number of compute units).  Under
+ *   another freeze mask an fp32 dW may therefore differ by the error of 32-bit sums.
  */
 int tf_stage_backward(tf_ctx* ctx, void* hip_stream,
                       int32_t n_layers, const tf_shape* shapes,
@@ -294,8 +300,9 @@ int32_t tf_num_frozen(double r, int32_t n);
  * with row_block_mask[l][b] == 0 are computed:
  *     dW_l[b*block_rows .. (b+1)*block_rows) (+)= X_l[:, those columns]^T * dY_l
  * Rows of frozen blocks of dW_l are neither read nor written; dX is always
- * computed in full.  Runs of unfrozen blocks are single GEMM problems; on the
- * 256 x 256-tile kernel when its shape allows (bf16 inputs, T % 64 == 0), otherwise on the generic one.
+ * computed in full.  With bf16 inputs, block_rows and T multiples of 256 and 64 the
+ * unfrozen blocks of a tensor are one GEMM problem of 256 x 256 tiles; otherwise
+ * each run of unfrozen blocks is a problem, on either kernel (TF_KERNEL_DW_*).
  *   row_block_mask   host array of n_layers HOST pointers (entries may be NULL: layer
  *                    without row mask), each K_l / block_rows bytes, 1 = frozen; or NULL
  *   block_rows       > 0; must divide K_l of every layer that has a row mask

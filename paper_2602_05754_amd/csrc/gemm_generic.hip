@@ -138,7 +138,8 @@ struct Operand {
         if (kContig) return max(k[i] + kE - left, 0);
         return k[i] < left - 1 ? 0 : over;
     }
-    // Any step: nothing outside the matrix is read; finish() puts the values in their places.
+    // Any step: nothing outside the matrix is read; finish() puts the values in their places.  The step begins
+    // `back` contraction values early (not in narrow matrices).
     __device__ __forceinline__ void load_inside(U4 (&v)[kPieces], int left) {
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
@@ -158,7 +159,8 @@ struct Operand {
             p[i] += step;
         }
     }
-    // What load_inside() fetched, moved down; zeros past the end of the contraction.
+    // What load_inside() fetched, moved down; zeros past the end of the contraction and for the `back`
+    // values that the step before has contracted.
     __device__ __forceinline__ void finish(U4 (&v)[kPieces], int left) const {
         if (narrow) return;
 #pragma unroll
@@ -173,6 +175,21 @@ struct Operand {
                 if (bits & 63) { lo = lo >> (bits & 63) | hi << (64 - (bits & 63)); hi >>= bits & 63; }
                 v[i] = U4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
             }
+        }
+    }
+    // The next step begins `back` contraction values early ...
+    __device__ __forceinline__ void rewind(int back) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) p[i] -= kContig ? int64_t(back) : back * (step / kBK);
+    }
+    // ... and those are masked out of it.
+    __device__ __forceinline__ void drop(U4 (&v)[kPieces], int back) const {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int n = back - k[i];                  // kNT: that many of the piece's values; kTN: the row, if any
+#pragma unroll
+            for (int d = 0; d < 4; ++d)
+                v[i][d] &= kContig ? (2 * d >= n ? 0xffffu : 0u) | (2 * d + 1 >= n ? 0xffff0000u : 0u) : n > 0 ? 0u : ~0u;
         }
     }
     __device__ __forceinline__ void store(const U4 (&v)[kPieces], char* stage) const {
@@ -230,8 +247,11 @@ __device__ __forceinline__ int logical_tile(int b, int nb) {
     return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
 }
 
-// The output is stored past the caches: left in the memory-side cache it pushed out the weights that the
-// next call reads (32 tokens, LLaMA-1B block pair: input gradients 85 us, 62 so).
+// The output is stored past the caches.  What that is for are weight gradients of few tokens, as large as the
+// weights, which they push out of the memory-side cache: a whole call, us, in brackets with ordinary stores: 32 tokens,
+// widths of LLaMA-8B 241 (284), LLaMA-1B 74 (76; over six layers' operands in turn 97 (104)), 1024 / 256 / 2816 27 (35 in
+// turn).  The next reader of the outputs pays for it with 1 to 2 us a call (LLaMA-1B block, 200 tokens, dX read
+// once 80.1 (78.6)); from 200 tokens on the rest makes no difference.
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN>
 __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
     typedef Operand<TIn, kContig, kTileM> OpA;
@@ -264,6 +284,11 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     // steps whose pieces are whole: all but the last one
     const int free_steps = a.narrow || b.narrow ? 0 : steps - 1;
     constexpr bool kWide = sizeof(TIn) == 2;            // 32 contraction values per instruction, not 4
+    // bf16, a contraction of 64 or more that is no multiple of 64: the last step is the last 64 values, those contracted
+    // already masked out - the step that the 256 x 256-tile kernel does, so that the bits are the same on both.
+    // (Functions of their own: inside load_inside() and finish() they changed the main loop's schedule, 2 % of 104 us at
+    // 200 tokens, LLaMA-1B block pair.)
+    const int back = kWide && Kc > OpA::kBK && !a.narrow && !b.narrow ? (OpA::kBK - Kc % OpA::kBK) % OpA::kBK : 0;
     // fp32: the products of a step (8 instructions of 4) are summed by themselves and then added to the sums
     // so far.  The smallest tiles, for calls that wait for memory and the host more than for the matrix
     // pipe, contract in 64 bits (half the fp32 rate): one rounding, also of a sum that has cancelled.
@@ -334,17 +359,22 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     // Step s sits in stage s % 2, the kDepth steps after it in registers (set s % kDepth) or on their
     // way there while step s is contracted.  One barrier per step: a stage is written one step after
     // every wave has read it.
-    // (what is left of the contraction from step s on, as far as it matters)
-    auto left = [&](int s) { return int(min(int64_t(Kc) - int64_t(s) * OpA::kBK, int64_t(0x10000))); };
+    // (what is left of the contraction from step s on, as far as it matters; with `back` only the last step asks)
+    auto left = [&](int s) { return int(min(int64_t(Kc) - int64_t(s) * OpA::kBK, int64_t(0x10000))) + back; };
     auto put = [&](int s, auto q) __attribute__((always_inline)) {
         if (s >= free_steps) { a.finish(va[q], left(s)); b.finish(vb[q], left(s)); }
+        if (kWide && back > 0 && s == steps - 1) { a.drop(va[q], back); b.drop(vb[q], back); }
         a.store(va[q], lds + (s & 1) * kStage);
         b.store(vb[q], lds + (s & 1) * kStage + OpA::kStageBytes);
     };
     auto fetch = [&](int s, auto q) __attribute__((always_inline)) {
         if (s >= steps) return;
         if (s < free_steps) { a.load(va[q]); b.load(vb[q]); }
-        else { a.load_inside(va[q], left(s)); b.load_inside(vb[q], left(s)); }
+        else {
+            if (kWide && back > 0) { a.rewind(back); b.rewind(back); }
+            a.load_inside(va[q], left(s));
+            b.load_inside(vb[q], left(s));
+        }
     };
     static_for<kDepth>([&](auto q) __attribute__((always_inline)) { fetch(q, q); });
     put(0, std::integral_constant<int, 0>{});

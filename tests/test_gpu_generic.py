@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -182,3 +182,57 @@ def test_profile_kinds_name_the_kernel_that_ran(ctx, T, shapes, which, dx, dw):
     with route(ctx, which):
         kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, None, dX, dW, tf.TF_BF16))
     assert kinds == [dx, dw]
+
+
+def _random(shapes, T, io, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rnd = lambda s, std: (torch.randn(s, generator=g, device="cuda") * std).to(TDT[io])
+    return [rnd(s, 0.02) for s in shapes], [rnd((T, k), 1.0) for k, n in shapes], [rnd((T, n), 1e-3) for k, n in shapes]
+
+
+@pytest.mark.parametrize("dw,accumulate", [("bf16", False), ("f32", True)])
+@pytest.mark.parametrize("T,shapes", [
+    (320, [(256, 320), (264, 256)]),                       # whole steps
+    (321, [(256, 264), (264, 328), (520, 1096)]),          # 1 value more; 8, 8 and 8
+    (127, [(256, 264), (312, 256)]),                       # 63 more (input gradients: fewer rows than a tile)
+    (577, [(264, 3000), (256, 2040)]),
+])
+def test_both_kernels_give_the_same_bf16_bits(ctx, T, shapes, dw, accumulate):
+    """Which kernel takes a layer depends on what else is in the launch: its bits must not."""
+    W, X, dY = _random(shapes, T, "bf16", T)
+    old = [torch.randn(s, device="cuda").to(TDT[dw]) for s in shapes]
+    out = []
+    for which in (ALL_256, GENERIC):
+        dX, dW = [torch.empty_like(x) for x in X], [o.clone() for o in old]
+        with route(ctx, which):
+            kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, None, dX, dW, CODE[dw], accumulate=accumulate))
+        assert ("dw_mfma" in kinds) == (which == ALL_256) and ("dw_generic" in kinds) == (which == GENERIC)
+        out.append([raw_bytes(t) for t in dX + dW])
+    assert out[0] == out[1]
+
+
+@pytest.mark.parametrize("io,T,others", [("bf16", 577, [(4096, 4096)] * 2), ("bf16", 576, [(4096, 4096)] * 2), ("f32", 500, [(1536, 2048)] * 2)])
+def test_a_layers_gradient_does_not_depend_on_the_other_layers(ctx, io, T, others):
+    """With the other layers unfrozen the launch takes another kernel or another launch shape.  bf16: the same
+    bits.  fp32: the sums are 64-bit ones where the launch is short, in 32 bits otherwise, both
+    within the bound of a sum in 32 bits."""
+    shapes = [(256, 264)] + others
+    W, X, dY = _random(shapes, T, io, T)
+    exact = (X[0].double().t().contiguous() @ dY[0].double()).cpu().numpy()
+    got = []
+    for frozen in (0, 1):
+        dX, dW = [torch.empty_like(x) for x in X], [torch.zeros(s, dtype=TDT[io], device="cuda") for s in shapes]
+        mask = np.array([0] + [frozen] * len(others), np.uint8)
+        kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, CODE[io], W, X, dY, mask, dX, dW, CODE[io]))
+        if io == "bf16":
+            assert [k for k in kinds if k.startswith("dw")] == ["dw_generic" if frozen else "dw_mfma"]
+        assert_elementwise(host64(dW[0]), exact, io, f"dW[0] with the other layers {'frozen' if frozen else 'unfrozen'}")
+        got.append((raw_bytes(dX[0]), raw_bytes(dW[0]), host64(dW[0])))
+    assert got[0][0] == got[1][0]
+    if io == "bf16":
+        assert got[0][1] == got[1][1]
+    else:
+        # chains of at most 32 fp32 products and 16 partial sums against one rounding: 2^-24 (32 + 16)^(1/2) each way,
+        # of terms as large as the result's root mean square times sqrt(T) / sqrt(T)
+        assert 0 < rel_fro(got[0][2], got[1][2]) <= 2 * 2.0 ** -24 * 48 ** 0.5
