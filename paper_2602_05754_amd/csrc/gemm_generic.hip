@@ -24,10 +24,7 @@
 // Nothing is ever read outside a matrix: rows past its end are clamped to the last one (their
 // outputs are not stored); pieces that run over the end of a row stay inside the matrix except in
 // its last row, and the last contraction step checks that and zeroes the values past the contraction.
-#include "tf_internal.h"
-
-#include <type_traits>
-#include <utility>
+#include "gemm_device.h"
 
 namespace tf {
 namespace {
@@ -35,43 +32,11 @@ namespace {
 constexpr int kThreads = 256;           // four waves, 2 x 2 over the tile
 constexpr int kStepBytes = 128;         // contraction bytes of an operand row per step
 constexpr int kDepth = 2;               // steps whose pieces are on their way in registers
-constexpr int kXcds = 8;
 constexpr int kXcdRun = 8;              // consecutive logical tiles kept on one XCD
 constexpr int kGroupM = 8;              // tile rows per L2 locality group
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t U4 __attribute__((ext_vector_type(4)));
-typedef uint32_t U2 __attribute__((ext_vector_type(2)));
 typedef U4 U4any __attribute__((aligned(2)));       // a 16-byte piece at any element address
 typedef f32x4 F4any __attribute__((aligned(4)));
-typedef __attribute__((address_space(3))) bf16x4* LdsBf16x4Ptr;
-
-#define TF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
-}
-
-// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// kNT stage: where a row's 16-byte chunk c lies: c ^ nt_swizzle(row).  An operand read takes 16
-// consecutive rows of one chunk per 16 lanes; the LDS serves 8 consecutive lanes together with the 8
-// lanes 32 further on, so rows r .. r + 7 of chunks q and q ^ 2 have to fall into different banks.
-__device__ __forceinline__ constexpr int nt_swizzle(int r) {
-    return ((r >> 1) & 1) | (((r >> 3) & 1) << 1) | (((r >> 2) & 1) << 2);
-}
 
 // One operand of a workgroup's tile: kRows rows of it, kRows x 128 bytes per stage.
 template <typename TIn, bool kContig, int kRows>

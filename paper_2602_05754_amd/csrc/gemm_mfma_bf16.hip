@@ -36,10 +36,7 @@
 //              LDS transpose read (4 contraction values of one row per lane).
 // A direct-to-LDS load writes lane i's 16 bytes at (wave-uniform base) + 16 i,
 // so a swizzle is applied by choosing which global address each lane fetches.
-#include "tf_internal.h"
-
-#include <type_traits>
-#include <utility>
+#include "gemm_device.h"
 
 namespace tf {
 namespace {
@@ -58,37 +55,9 @@ constexpr int kEpiBytes = 8192;                                   // per wave, i
 constexpr int kLdsBytes = (kDeepStages + 2) * kTileBytes;         // 160 KB: all of a compute unit's LDS
 static_assert(kWaves * kEpiBytes == kTileBytes, "the four epilogue areas fill one stage");
 constexpr int kGroupM = 8;                            // tile rows per L2 locality group
-constexpr int kXcds = 8;
 constexpr int kXcdRun = 32;                           // consecutive logical tiles kept on one XCD
 
 static_assert(sizeof(GemmBatch) <= 4160, "the batch travels by value in the kernel-argument segment");
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t U2 __attribute__((ext_vector_type(2)));
-typedef uint32_t U4 __attribute__((ext_vector_type(4)));
-typedef float F4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) bf16x4* LdsBf16x4Ptr;
-
-#define TF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>), in this order
-template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// two binary32 -> packed bf16, round to nearest even (one v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
-}
 
 // Accumulator register -> vector register, at this point of the program.  Left to itself the
 // register allocator copies all 256 accumulators of a wave at the head of the epilogue, which
@@ -168,19 +137,6 @@ __device__ __forceinline__ TilePos locate_tile(const GemmBatch& batch, int lt, i
 //   kTN: that KB is contraction rows T = 2 (4 p + w) + lane/32, 16-byte slot lane%32 of
 //        each; logical 32-byte unit = physical unit ^ (4 ((T / 8) % 4) + T % 4).
 // ---------------------------------------------------------------------------------------------
-// kNT stage: which physical 16-byte chunk of its 128-byte row holds logical chunk c of tile row R:
-// c ^ nt_swizzle(R).  An operand read (ds_read_b128) takes 16 consecutive rows, lane l row l % 16,
-// logical chunk l / 16 (+ 4 for the second sub-step).  The LDS serves such a read 16 lanes at a
-// time, 8 consecutive lanes together with the 8 lanes 32 further on (counters: with a swizzle that
-// only kept 16 consecutive lanes apart, every read took twice its cycles): rows r .. r + 7 of
-// chunks q and q ^ 2 must fall into 16 different 16-byte bank groups, and a row's parity already
-// selects the half of the banks (row pitch 128 bytes).  Bits 1 and 2 of the row go to bits 0 and 2
-// of the swizzle, which the chunk pair does not touch; bit 3 of the row goes to bit 1, which
-// also keeps 16 consecutive lanes (one chunk, 16 rows) apart.
-__host__ __device__ __forceinline__ constexpr int nt_swizzle(int R) {
-    return ((R >> 1) & 1) | (((R >> 3) & 1) << 1) | (((R >> 2) & 1) << 2);
-}
-
 struct Side {
     // One operand of a run.  Loads p = 0..3 of a stage fill go through (g, v[p]), loads 4..7
     // through (g2, v[p - 4]).

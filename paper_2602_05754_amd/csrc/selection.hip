@@ -133,16 +133,7 @@ __device__ __forceinline__ uint32_t rc_valid(const RcTask& r, int64_t word) {
     return left >= 32 ? 0xffffffffu : left > 0 ? (1u << int(left)) - 1u : 0u;
 }
 
-// The round function of the permutation on two 16-bit halves at once: z -> bits 16..31 of (z + 1) C,
-// C = 0x9E3779B1 = Chi 2^16 + Clo.  With p = z Clo + C these are Chi z + (p >> 16), mod 2^16.
 typedef unsigned short U16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t round_pair(uint32_t z, uint32_t c) {
-    uint32_t p0, p1;
-    asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(p0) : "v"(z), "s"(0x79B1u), "v"(c));
-    asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(p1) : "v"(z), "s"(0x79B1u), "v"(c));
-    const U16x2 high = __builtin_bit_cast(U16x2, __builtin_amdgcn_perm(p1, p0, 0x07060302u));
-    return __builtin_bit_cast(uint32_t, U16x2(__builtin_bit_cast(U16x2, z) * (unsigned short)0x9E37u + high));
-}
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
 
 // The top halves of the keys of a word's 32 elements, two per register (element 2 p in the low half).
@@ -161,10 +152,17 @@ struct Halves {
         low0 = index0 & 0xffffu;
         carry = low0 + 31 > 0xffffu;
 #pragma unroll
-        for (int p = 0; p < 16; ++p) {
-            const uint32_t x1 = ((low0 + 2 * p) & 0xffffu) | (low0 + 2 * p + 1) << 16;
-            a[p] = round_pair(x1 ^ twice(k.k[0]), c) ^ twice(k.k[1]);
-            l[p] = x1 ^ twice(k.k[2]);
+        for (int p = 0; p < 16; p += 2) {
+            uint32_t z[2], q[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t e = low0 + 2 * (p + j), x1 = (e & 0xffffu) | (e + 1) << 16;
+                z[j] = x1 ^ twice(k.k[0]);
+                l[p + j] = x1 ^ twice(k.k[2]);
+            }
+            round_pairs(z, q);
+            a[p] = q[0] ^ twice(k.k[1]);
+            a[p + 1] = q[1] ^ twice(k.k[1]);
         }
         k13 = twice(k.k[1] ^ k.k[3]);
         k24 = twice(k.k[2] ^ k.k[4]);
@@ -179,16 +177,18 @@ struct Halves {
             const uint32_t e = low0 + 2 * (p + j);
             z2[j] = a[p + j] ^ (kCarry ? high2 + (e >> 16 | (e + 1) >> 16 << 16) : high2);
         });
-        round_pair2(z2, q);
+        round_pairs(z2, q);
         each([&](int j) __attribute__((always_inline)) { z3[j] = l[p + j] ^ q[j]; });
-        round_pair2(z3, q);
+        round_pairs(z3, q);
         each([&](int j) __attribute__((always_inline)) { z4[j] = xor3(z2[j], q[j], k13); });
-        round_pair2(z4, q);
+        round_pairs(z4, q);
         each([&](int j) __attribute__((always_inline)) { z5[j] = xor3(z3[j], q[j], k24); });
-        round_pair2(z5, q);
+        round_pairs(z5, q);
         each([&](int j) __attribute__((always_inline)) { x[j] = xor3(z4[j], q[j], k3); });
     }
-    __device__ __forceinline__ void round_pair2(const uint32_t (&z)[2], uint32_t (&q)[2]) const {
+    // The round function of the permutation on two 16-bit halves in each of two registers: z -> bits 16..31 of
+    // (z + 1) C, C = 0x9E3779B1 = Chi 2^16 + Clo.  With p = z Clo + C these are Chi z + (p >> 16), mod 2^16.
+    __device__ __forceinline__ void round_pairs(const uint32_t (&z)[2], uint32_t (&q)[2]) const {
         uint32_t p0, p1, r0, r1;
         asm("v_mad_u32_u16 %0, %4, %6, %7\n\t"
             "v_mad_u32_u16 %1, %4, %6, %7 op_sel:[1,0,0,0]\n\t"
@@ -204,7 +204,7 @@ struct Halves {
 
 __global__ void rc_reset_kernel(RcState* st) {
     for (int i = threadIdx.x; i < kBins; i += blockDim.x) st->hist[i] = 0;
-    if (threadIdx.x == 0) { st->count = 0; st->mode = 0; st->need = 0; st->prefix = 0; st->prefix_bits = 0; }
+    if (threadIdx.x == 0) { st->count = 0; st->mode = 0; st->need = 0; st->prefix = 0; }
 }
 
 __global__ __launch_bounds__(kThreads) void rc_count_kernel(RcBatch batch, RcState* st) {
@@ -236,7 +236,7 @@ __global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, long 
     const unsigned long long c = st->count;
     st->mode = c == n_freeze ? 0u : (c < n_freeze ? 1u : 2u);
     st->need = c < n_freeze ? n_freeze - c : c - n_freeze;
-    st->prefix = 0; st->prefix_bits = 0;
+    st->prefix = 0;
     if (stats) { stats[0] = (long long)c; stats[1] = st->mode; stats[2] = 0; }
 }
 
@@ -368,7 +368,6 @@ __global__ __launch_bounds__(kThreads) void rc_pick_kernel(RcState* st, int nbit
         }
         st->need -= before;                      // rank inside the bin, >= 1
         st->prefix = (st->prefix << nbits) | uint32_t(b);
-        st->prefix_bits += uint32_t(nbits);
         if (last && stats) stats[2] = (long long)st->prefix;
     }
     if (threadIdx.x == 0 && st->mode == 0 && last && stats) stats[2] = 0;

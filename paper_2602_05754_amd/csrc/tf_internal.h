@@ -201,8 +201,7 @@ struct RcState {            // device memory owned by the context
     unsigned long long count;           // ones in the base mask
     unsigned long long need;            // rank still to be located
     uint32_t mode;                      // 0 keep, 1 add zeros, 2 remove ones
-    uint32_t prefix, prefix_bits;       // leading key bits fixed so far
-    uint32_t pad_;
+    uint32_t prefix;                    // leading key bits fixed so far
 };
 int rc_tasks(int64_t numel);        // tasks of a tensor (RcTensor::block_start counts them)
 size_t rc_state_bytes();
