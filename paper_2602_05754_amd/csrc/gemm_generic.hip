@@ -9,9 +9,12 @@
 // v_mfma_f32_16x16x32_bf16.
 //
 // Against plain fp32 vector FMAs in 64 x 64 tiles (what this file held before): fp32 stage of width 1024,
-// 1000 tokens, input gradients of two blocks 750 -> 380 us (58 -> 116 TFLOP/s); bf16, 200 tokens of a
-// LLaMA-1B block pair, input gradients 1199 -> 103 us; bf16, weight gradients over 3001 tokens 9460 ->
-// 870 us.  fp32 is bound by the matrix pipe, bf16 by the operands' way through L1 and LDS.
+// 1000 tokens, input gradients of two blocks 740 -> 375 us (59 -> 118 TFLOP/s); bf16, 200 tokens of a
+// LLaMA-1B block pair, input gradients 1195 -> 104 us; bf16, weight gradients over 3001 tokens 9435 ->
+// 870 us.  Counters: fp32 has the matrix pipe busy 77 % of the cycles (weight gradients 70 %).  bf16 has no unit
+// full (3001 tokens: matrix pipe 44 %, LDS 45 %, address unit 50 %, no bank conflicts), two waves per SIMD that wait
+// half of the time for operands on their way through L1, registers and LDS; 200 tokens: a unit holds a
+// tile 65 % of the time, matrix pipe 24 %: chains of up to 128 steps in few tiles.
 //
 // One output tile per workgroup of four waves in a 2 x 2 grid.  The contraction advances 128 bytes
 // per operand row (64 bf16 or 32 fp32 values) through two LDS stages; the 16-byte pieces of the
@@ -426,8 +429,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
 
 // The launch shapes.  step_us, chain_us: a step's share of a compute unit when all are full, and its
 // time in a workgroup that has the unit to itself; tile_steps: what a tile costs beside its steps.
-// Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps are
-// bound by the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
+// Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps wait
+// for the L1 and LDS traffic of their operands (input gradients of a LLaMA-1B block, 3001
 // tokens: 128 x 128 tiles 906 TFLOP/s, 128 x 64 753, 64 x 64 598), the fp32 steps by the matrix pipe
 // (2048 tokens, width 1024: 64 x 64 tiles 545 us, 32 x 64 558, 128 x 64 553; width 512, 512 tokens: 32 x 64
 // 47 us, 64 x 64 64, 32 x 32 in 64 bits 78).  Small tiles are for calls with few of them: an

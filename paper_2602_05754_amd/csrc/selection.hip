@@ -20,7 +20,8 @@
 //    ALU-bound: two keys at a time in 16-bit halves, 5 instructions per round and pair (see Halves),
 //    the top half of a key needs five rounds, and the first round is worked out once for all the
 //    words that a thread visits.  1.74e9 elements, 30 % -> 50 %: 6.2 -> 1.5 ms against four passes of six
-//    rounds each, key by key, with a 32-bit multiplication (a quarter of the rate).
+//    rounds each, key by key, with a 32-bit multiplication (a quarter of the rate).  Of the vector units' instruction
+//    slots the histogram pass uses 98 %, the apply pass 93 % (counters).
 #include "tf_internal.h"
 
 namespace tf {

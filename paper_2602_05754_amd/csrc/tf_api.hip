@@ -142,7 +142,7 @@ constexpr int64_t kMaxGenericTiles = (int64_t(1) << 24) - 1;
 constexpr int64_t kMaxTiles256 = 0x3fffffff;       // tile indices are 32-bit on the device
 
 // Launch shape of the generic kernel for these problems: the one with the least estimated time.  The
-// estimates were within 15 % of the measured times and in their order (input gradients of a LLaMA-1B
+// estimates were within 15 % of the measured times (to which a launch adds some 4 us) and in their order (input gradients of a LLaMA-1B
 // block, 200 tokens: 64 x 64 tiles 65 us, 128 x 64 69, 128 x 128 91; 3001 tokens: 605, 485, 400).
 int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype, double* best_us) {
     int best = 0;
@@ -170,12 +170,12 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
 
 // The 256 x 256-tile kernel on these problems.  A step takes 1.45 us when all units are busy (the power
 // limit), 1.15 in the long tiles at a launch's end, 1.0 when there are fewer tiles than units; a tile's
-// epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages; where the tile
-// is no whole one 5 more, or 10 when it is added to (masked stores; runs of 64 or 128 rows: 1024 tokens of a LLaMA-1B block, half of its
-// 64-row blocks frozen, 164 (135), 256 tokens and 128-row blocks 47 (39)).  Measured
-// against the generic kernel, us, in brackets the latter: LLaMA-1B block, input gradients, 512 tokens
-// 134 (92), 1024 191 (158), 2048 242 (288); LLaMA-8B block 512 tokens 335 (274), 1024 423 (500); weight
-// gradients of width 512, 256 tokens 16 (9), of the LLaMA-1B block, 256 tokens 49 (64).
+// epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages; where the tile is
+// no whole one (masked stores) 5 more, or 10 when it is added to.  Measured in turn with the generic kernel, us, in
+// brackets the latter: LLaMA-1B block, input gradients, 256 tokens 136 (54), 512 140 (96), 1024 192 (144),
+// 2048 251 (287); LLaMA-8B block 512 tokens 345 (259), 1024 440 (495); weight gradients of a block of width 512, 256
+// tokens 16 (11), of the LLaMA-1B block 51 (72), of that block with half of its 64-row blocks frozen, 1024
+// tokens, 164 (135), of its 128-row blocks, 256 tokens, 47 (39).
 double tile256_us(const std::vector<const Planned*>& items, bool tail, bool accumulate) {
     if (items.empty()) return 0;
     Estimate e;
