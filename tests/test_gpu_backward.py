@@ -101,7 +101,12 @@ def test_bf16_ragged_shapes_fall_to_the_generic_kernel(ctx):
 
 
 def test_mixed_eligible_and_ragged_layers_in_one_call(ctx):
-    # ffn = 688 is not a multiple of 256: gate/up/down take the generic kernel, q/k/v/o the MFMA one
+    # kv = 72 columns are fewer than a 256 x 256 tile's, a contraction of 72 is no multiple of 64: k and v take
+    # the generic kernel, the others, told so, the 256 x 256-tile one
+    cfg = wl.scaled(wl.CONFIGS[2], blocks=2, d=256, kv=72, ffn=704, T=256)
+    with route(ctx, WHOLE_256):
+        kinds = kinds_of(ctx, lambda: _run_case(ctx, cfg, cfg.T, wl.permutation_mask(cfg, 0.3), TOL["bf16"]))
+    assert set(kinds) == {"dx_mfma", "dx_generic", "dw_mfma", "dw_generic"}
     cfg = wl.scaled(wl.CONFIGS[2], blocks=2, d=256, kv=256, ffn=688, T=256)
     _run_case(ctx, cfg, cfg.T, wl.permutation_mask(cfg, 0.5), TOL["bf16"])
 
@@ -260,4 +265,7 @@ def test_more_layers_than_one_grouped_launch_holds(ctx):
     cfg = wl.scaled(wl.CONFIGS[2], blocks=11, d=256, kv=512, ffn=768, T=256)
     mask = np.zeros(cfg.n_layers, np.uint8)
     mask[[0, 9, 30, 31, 64, 65, 76]] = 1
-    _run_case(ctx, cfg, cfg.T, mask, TOL["bf16"])
+    for which, kind in ((WHOLE_256, "mfma"), (GENERIC, "generic")):
+        with route(ctx, which):
+            kinds = kinds_of(ctx, lambda: _run_case(ctx, cfg, cfg.T, mask, TOL["bf16"]))
+        assert kinds == ["dx_" + kind] * 2 + ["dw_" + kind] * 2
