@@ -171,16 +171,16 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
 // The 256 x 256-tile kernel on these problems.  A step takes 1.45 us when all units are busy (the power
 // limit), 1.15 in the long tiles at a launch's end, 1.0 when there are fewer tiles than units; a tile's
 // epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages; where the tile is
-// no whole one (masked stores) 5 more, or 10 when it is added to.  Measured in turn with the generic kernel, us, in
+// no whole one (masked stores) 3 more, 5 for weight gradients, 10 when they are added to.  Measured in turn with the generic kernel, us, in
 // brackets the latter: LLaMA-1B block, input gradients, 256 tokens 136 (54), 512 140 (96), 1024 192 (144),
 // 2048 251 (287); LLaMA-8B block 512 tokens 345 (259), 1024 440 (495); weight gradients of a block of width 512, 256
 // tokens 16 (11), of the LLaMA-1B block 51 (72), of that block with half of its 64-row blocks frozen, 1024
 // tokens, 164 (135), of its 128-row blocks, 256 tokens, 47 (39).
-double tile256_us(const std::vector<const Planned*>& items, bool tail, bool accumulate) {
+double tile256_us(const std::vector<const Planned*>& items, bool tail, Layout layout, bool accumulate) {
     if (items.empty()) return 0;
     Estimate e;
     const uint32_t tile = gemm_mfma_tile();
-    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - int64_t(uint32_t(it->M) / tile) * (uint32_t(it->N) / tile)), accumulate ? 10 : 5);
+    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - int64_t(uint32_t(it->M) / tile) * (uint32_t(it->N) / tile)), layout == Layout::kNT ? 3 : accumulate ? 10 : 5);
     const int units = compute_units();
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
 }
@@ -189,7 +189,8 @@ double tile256_us(const std::vector<const Planned*>& items, bool tail, bool accu
 // estimate, which knows no outputs: they are stored past the caches, and what is added to is fetched again from
 // where an earlier call has left it (MB of outputs, those added to counted both ways).  Timed on both kernels, block
 // widths 256 to 4096, 64 to 3001 tokens: of 410 launches of whole tensors all get the faster kernel or lose at most 7 %
-// by it; of 248 with runs of 64- to 256-row blocks all but 8 are within 10 % (worst: 1.37 times).  Without: up to
+// by it; of 248 with runs of 64- to 256-row blocks all but 8 are within 10 % (worst: 1.37 times), of 119 with widths
+// that are no multiples of a tile all but 7 (1.32).  Without: up to
 // 1.76 times (block of widths 1024 / 256 / 2816, 256 tokens, added to: 43 us, 256 x 256 tiles 25).  Input gradients
 // as estimated: within 11 %.
 double generic_launch_us(const std::vector<const Planned*>& items, double us, Layout layout, int out_bytes, bool accumulate) {
@@ -231,14 +232,14 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
     };
     if (plain && route != kRouteWhole256 && route != kRouteAll256) {
         int s;
-        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false, accumulate) || route == kRouteGeneric) r.shape[kWhole] = s;
+        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false, layout, accumulate) || route == kRouteGeneric) r.shape[kWhole] = s;
     }
     if (!r.cls[kTail].empty() && route != kRouteAll256) {
         std::vector<const Planned*> both = r.cls[kTail];
         both.insert(both.end(), r.cls[kOther].begin(), r.cls[kOther].end());
         int s;
         const double together = generic(both, &s);
-        if (together < tile256_us(r.cls[kTail], true, accumulate) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
+        if (together < tile256_us(r.cls[kTail], true, layout, accumulate) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
             r.cls[kOther] = both;
             r.cls[kTail].clear();
         }
@@ -1224,7 +1225,7 @@ extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t*
     for (const Planned& it : items) p.push_back(&it);
     const Dtype dt = to_dtype(tf_dtype(in_dtype));
     const int shape = pick_generic_shape(p, dt, us);
-    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0, false);
+    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0, Layout::kTN, false);
     tile[0] = generic_shape(dt, shape).tile_m;
     tile[1] = generic_shape(dt, shape).tile_n;
     return shape;

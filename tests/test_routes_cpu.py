@@ -68,6 +68,7 @@ def test_row_runs_take_the_faster_kernel(runs, T, accumulate, on256):
     (block(2048, 512, 8192, 3), 1024, True),
     (block(4096, 1024, 14336), 512, False),              # 354, 299
     (block(4096, 1024, 14336), 2048, True),
+    (block(2440, 1216, 8744), 928, False),               # 294, 242: partly filled tiles
 ])
 def test_input_gradients_take_the_faster_kernel(shapes, T, on256):
     K, N = zip(*shapes)
