@@ -74,7 +74,8 @@ typedef enum {
  * its host-side bookkeeping (timing events) and two small device allocations, made
  * here: the 8.2 KB rank-search state of tf_reconcile_mask and 128 KB of partial
  * sums for tf_masked_adamw / tf_stability_update / tf_autofreeze_norms
- * (TF_ERR_WORKSPACE if either fails).  No call allocates device memory afterwards.  Every later call on the
+ * (TF_ERR_WORKSPACE if either fails).  No call allocates device memory afterwards, but for
+ * tf_reconcile_mask on 2^28 elements or more (see there).  Every later call on the
  * context makes device_id current for the calling thread before it launches. */
 int tf_create(tf_ctx** out, int device_id);
 int tf_destroy(tf_ctx* ctx);
@@ -424,7 +425,10 @@ int tf_autofreeze_select(const double* scores, int32_t n, int32_t n_already_froz
  *   stats            optional DEVICE, 3 x int64, 8-byte aligned: {||base||_1, case (0 kept,
  *                    1 added, 2 removed), largest key drawn}; valid after the stream is synchronised
  * Only enqueues (the rank search runs on the device).  Uses device memory owned by the
- * context: calls on one context must not overlap.
+ * context: calls on one context must not overlap.  Masks of 2^28 elements or more: the first call, and one with
+ * a larger mask than any before it, allocates a copy of the mask's size (at most 512 MB), which the context keeps
+ * until tf_destroy.  A call whose stream is being captured, or for which there is no memory left, works
+ * without it: the same result, in twice the time.
  * Errors: TF_ERR_INVALID_ARG, TF_ERR_SHAPE (numel <= 0, sum >= 2^32), TF_ERR_ALIGN
  * (mask pointers not 4-byte, stats not 8-byte aligned), TF_ERR_HIP.
  */

@@ -19,9 +19,9 @@
 //    a pass over the elements.  All of it on the stream: the host never waits.
 //    ALU-bound: two keys at a time in 16-bit halves, 5 instructions per round and pair (see Halves),
 //    the top half of a key needs five rounds, and the first round is worked out once for all the
-//    words that a thread visits.  1.74e9 elements, 30 % -> 50 %: 6.2 -> 1.5 ms against four passes of six
-//    rounds each, key by key, with a 32-bit multiplication (a quarter of the rate).  Of the vector units' instruction
-//    slots the histogram pass uses 98 %, the apply pass 93 % (counters).
+//    words that a thread visits.  Large masks guess their threshold and need one pass over the elements
+//    instead of two (rc_try_kernel).  1.74e9 elements, 30 % -> 50 %: 6.2 ms with four passes of six rounds each,
+//    key by key; 1.47 with the two passes; 0.77 with the guess, of which the keyed pass takes 0.6.
 #include "tf_internal.h"
 
 namespace tf {
@@ -105,10 +105,12 @@ constexpr int kBins = 2048;
 constexpr int kRowWords = 65536 / 32;
 constexpr int kColumns = kRowWords / kThreads;      // tasks side by side
 constexpr int kRows = 16;
+constexpr int kWindowTops = 64;                      // guessed thresholds: at most this many top halves of keys, 2^22 keys
 constexpr int kGrid = 256 * 8;                      // blocks walk the tasks (keyed passes, 4 per compute unit at a time: 2048 blocks 0.67 ms, 1024 0.71)
 
 struct RcTask {
     uint32_t* bits;       // the tensor's words
+    uint32_t* undo;       // where rc_try_kernel() leaves them as they were
     int64_t n_words, first;     // first: this thread's first word
     int64_t numel;
     uint32_t index0;      // stage-wide index of that word's bit 0
@@ -122,6 +124,7 @@ __device__ __forceinline__ RcTask rc_task(const RcBatch& batch, int task) {
     const int t = task - T.block_start;
     RcTask r;
     r.bits = T.bits;
+    r.undo = T.undo;
     r.numel = T.numel;
     r.n_words = (T.numel + 31) >> 5;
     r.first = int64_t(t / kColumns) * kRows * kRowWords + (t % kColumns) * kThreads + threadIdx.x;
@@ -137,7 +140,8 @@ __device__ __forceinline__ uint32_t rc_valid(const RcTask& r, int64_t word) {
 typedef unsigned short U16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
 
-// The top halves of the keys of a word's 32 elements, two per register (element 2 p in the low half).
+// The top halves of the keys of a word's 32 elements, two per register: element p in the low half of register
+// p, element p + 16 in its high half, so that 16 results of one bit each make a word without being interleaved.
 // With x0 = high half of the index, x1 = low half, x[r + 2] = x[r] ^ F(x[r + 1] ^ key r), the key is x6 : x7.
 struct Halves {
     uint32_t a[16];       // x2 without x0, ^ key 1: the first round, the same for all words of a thread
@@ -157,7 +161,7 @@ struct Halves {
             uint32_t z[2], q[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const uint32_t e = low0 + 2 * (p + j), x1 = (e & 0xffffu) | (e + 1) << 16;
+                const uint32_t e = low0 + p + j, x1 = (e & 0xffffu) | (e + 16) << 16;
                 z[j] = x1 ^ twice(k.k[0]);
                 l[p + j] = x1 ^ twice(k.k[2]);
             }
@@ -175,8 +179,8 @@ struct Halves {
         uint32_t z2[2], z3[2], z4[2], z5[2], q[2];
         auto each = [](auto f) __attribute__((always_inline)) { f(0); f(1); };
         each([&](int j) __attribute__((always_inline)) {
-            const uint32_t e = low0 + 2 * (p + j);
-            z2[j] = a[p + j] ^ (kCarry ? high2 + (e >> 16 | (e + 1) >> 16 << 16) : high2);
+            const uint32_t e = low0 + p + j;
+            z2[j] = a[p + j] ^ (kCarry ? high2 + (e >> 16 | (e + 16) >> 16 << 16) : high2);
         });
         round_pairs(z2, q);
         each([&](int j) __attribute__((always_inline)) { z3[j] = l[p + j] ^ q[j]; });
@@ -203,11 +207,63 @@ struct Halves {
     }
 };
 
-__global__ void rc_reset_kernel(RcState* st) {
-    for (int i = threadIdx.x; i < kBins; i += blockDim.x) st->hist[i] = 0;
-    if (threadIdx.x == 0) { st->count = 0; st->mode = 0; st->need = 0; st->prefix = 0; }
+// The permutation backwards: the index whose key this is.
+__device__ __forceinline__ uint32_t unperm32(uint32_t key, const RcKeys& keys) {
+    uint32_t hi = key >> 16, lo = key & 0xffffu;
+#pragma unroll
+    for (int r = 5; r >= 0; --r) {                                 // (hi, lo) = (x[r + 1], x[r + 2]) -> (x[r], x[r + 1])
+        const uint32_t x = lo ^ (((hi ^ keys.k[r]) + 1u) * 0x9E3779B1u >> 16);
+        lo = hi;
+        hi = x;
+    }
+    return hi << 16 | lo;
+}
+// Where the batch's tensors begin in the stage, and the end of the last one.  (Whole block; one barrier.)
+__device__ __forceinline__ void tensor_starts(const RcBatch& batch, int64_t* start) {
+    if (threadIdx.x < kMaxRcTensors) {
+        const int n = batch.n_tensors, i = threadIdx.x;
+        start[i] = i < n ? batch.t[i].goff : INT64_MAX;
+        if (i == n - 1) start[kMaxRcTensors] = batch.t[i].goff + batch.t[i].numel;
+    }
+    __syncthreads();
+}
+// The word that holds an element, its address and the element's bit; null if the element is not one of the batch's.
+__device__ __forceinline__ uint32_t* find_element(const RcBatch& batch, const int64_t* start, uint32_t element, uint32_t* word, uint32_t* bit) {
+    const int64_t index = int64_t(element);
+    if (index < start[0] || index >= start[kMaxRcTensors]) return nullptr;
+    int t = 0;
+#pragma unroll
+    for (int step = kMaxRcTensors / 2; step > 0; step >>= 1)
+        if (start[t + step] <= index) t += step;
+    const int64_t e = index - start[t];
+    *bit = uint32_t(e & 31);
+    uint32_t* const at = batch.t[t].bits + (e >> 5);
+    *word = *at;
+    return at;
 }
 
+__global__ void rc_reset_kernel(RcState* st) {
+    for (int i = threadIdx.x; i < kBins; i += blockDim.x) st->hist[i] = 0;
+    if (threadIdx.x == 0) {
+        st->count = 0; st->mode = 0; st->need = 0; st->prefix = 0;
+        st->drawn = 0; st->rank = 0; st->window_lo = 0; st->window_hi = 0; st->probe = 0; st->done = 0;
+    }
+}
+
+// *sum += the block's threads' counts, in one addition: with one per wave the queue at the one address took twice
+// the time of the counting pass.
+__device__ __forceinline__ void add_block_count(unsigned long long* sum, uint32_t c) {
+    __shared__ uint32_t part[kThreads / 64];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long all = 0;
+        for (int i = 0; i < kThreads / 64; ++i) all += part[i];
+        if (all) atomicAdd(sum, all);
+    }
+}
 __global__ __launch_bounds__(kThreads) void rc_count_kernel(RcBatch batch, RcState* st) {
     uint32_t c = 0;                                                // a thread's share of fewer than 2^32 elements
     for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
@@ -218,27 +274,44 @@ __global__ __launch_bounds__(kThreads) void rc_count_kernel(RcBatch batch, RcSta
             c += __popc(r.bits[w < r.n_words ? w : r.n_words - 1] & rc_valid(r, w));
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off, 64);
-    // one addition per block: with one per wave the queue at the one address took twice the time of the pass
-    __shared__ uint32_t part[kThreads / 64];
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long all = 0;
-        for (int i = 0; i < kThreads / 64; ++i) all += part[i];
-        if (all) atomicAdd(&st->count, all);
-    }
+    add_block_count(&st->count, c);
 }
 
 // mode 0: the base mask already holds n_freeze ones; 1: add `need` of its zeros; 2: remove `need` of its ones
-__global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, long long* stats) {
+// n: elements of the stage if the threshold may be guessed (rc_try_kernel()), or 0.
+__global__ void rc_decide_kernel(RcState* st, unsigned long long n_freeze, unsigned long long n, long long* stats) {
     if (threadIdx.x != 0) return;
     const unsigned long long c = st->count;
     st->mode = c == n_freeze ? 0u : (c < n_freeze ? 1u : 2u);
     st->need = c < n_freeze ? n_freeze - c : c - n_freeze;
     st->prefix = 0;
     if (stats) { stats[0] = (long long)c; stats[1] = st->mode; stats[2] = 0; }
+    if (n == 0 || st->mode == 0) return;
+    // The need-th smallest of `all` keys drawn from [0, 2^32): six standard deviations on either side.
+    const double all = double(st->mode == 1 ? n - c : c), share = double(st->need) / all;
+    const double half = 6 * 65536 * sqrt(share * (1 - share) / all);                 // in top halves of a key
+    const int lo = int(share * 65536 - half) - 1, hi = min(int(share * 65536 + half) + 2, 65536);
+    if (lo < 1 || hi - lo > kWindowTops) return;
+    st->window_lo = uint32_t(lo);
+    st->window_hi = uint32_t(hi);
+}
+
+// Is the mask what the guess takes it for, one that has nothing to do with the keys?  (A mask that the same seed has
+// made is not: its candidates' keys begin where the last threshold was.)  2^16 keys, one in 65536, are looked up:
+// those of candidates below the expected threshold have to be as many as expected, to six standard deviations.
+__global__ __launch_bounds__(kThreads) void rc_probe_kernel(RcBatch batch, RcState* st, RcKeys keys) {
+    __shared__ int64_t start[kMaxRcTensors + 1];
+    if (st->window_hi == 0) return;
+    tensor_starts(batch, start);
+    const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+    if (i * 2 >= st->window_lo + st->window_hi) return;
+    uint32_t word, bit;
+    uint32_t* const at = find_element(batch, start, unperm32(i << 16 | ((i * 0x9E3779B1u) >> 16), keys), &word, &bit);
+    if (at && ((word >> bit) & 1u) == (st->mode == 2 ? 1u : 0u)) atomicAdd(&st->probe, 1u);
+}
+__device__ __forceinline__ bool guess_holds(const RcState* st) {
+    const double expected = double(st->need) / 65536;
+    return st->window_hi != 0 && fabs(double(st->probe) - expected) <= 6 * sqrt(expected) + 8;
 }
 
 // No lane's word has more than kFew candidates: key by key is then quicker than all 32 in pairs (a loop of as many
@@ -257,15 +330,15 @@ __device__ __forceinline__ void rc_hist_word(const Halves& h, uint32_t cand, uin
         h.top<kCarry>(p, high2, x);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            atomicAdd(&bins[(x[j] >> 5) & 0x7ffu], (cand >> (2 * (p + j))) & 1u);
-            atomicAdd(&bins[x[j] >> 21], (cand >> (2 * (p + j) + 1)) & 1u);
+            atomicAdd(&bins[(x[j] >> 5) & 0x7ffu], (cand >> (p + j)) & 1u);
+            atomicAdd(&bins[x[j] >> 21], (cand >> (p + j + 16)) & 1u);
         }
     }
 }
 __global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcState* st, RcKeys keys) {
     __shared__ uint32_t bins[kBins];
     const uint32_t mode = st->mode;
-    if (mode == 0) return;                                          // block-uniform
+    if (mode == 0 || st->done) return;                              // block-uniform
     for (int i = threadIdx.x; i < kBins; i += kThreads) bins[i] = 0;
     __syncthreads();
     for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
@@ -308,32 +381,11 @@ __global__ __launch_bounds__(kThreads) void rc_hist_kernel(RcBatch batch, RcStat
 __global__ __launch_bounds__(kThreads) void rc_enum_kernel(RcBatch batch, RcState* st, RcKeys keys, int open, int nbits) {
     __shared__ int64_t start[kMaxRcTensors + 1];
     const uint32_t mode = st->mode;
-    if (mode == 0) return;
-    if (threadIdx.x < kMaxRcTensors) {
-        const int n = batch.n_tensors, i = threadIdx.x;
-        start[i] = i < n ? batch.t[i].goff : INT64_MAX;
-        if (i == n - 1) start[kMaxRcTensors] = batch.t[i].goff + batch.t[i].numel;
-    }
-    __syncthreads();
+    if (mode == 0 || st->done) return;
+    tensor_starts(batch, start);
     const uint32_t k = blockIdx.x * kThreads + threadIdx.x;        // grid: 2^open threads
-    uint32_t hi = st->prefix << open | k, lo = hi & 0xffffu;
-    hi >>= 16;
-#pragma unroll
-    for (int r = 5; r >= 0; --r) {                                 // (hi, lo) = (x[r + 1], x[r + 2]) -> (x[r], x[r + 1])
-        const uint32_t x = lo ^ (((hi ^ keys.k[r]) + 1u) * 0x9E3779B1u >> 16);
-        lo = hi;
-        hi = x;
-    }
-    const int64_t index = int64_t(hi << 16 | lo);
-    bool cand = false;
-    if (index >= start[0] && index < start[kMaxRcTensors]) {
-        int t = 0;
-#pragma unroll
-        for (int step = kMaxRcTensors / 2; step > 0; step >>= 1)
-            if (start[t + step] <= index) t += step;
-        const int64_t e = index - start[t];
-        cand = (((batch.t[t].bits[e >> 5] >> (e & 31)) & 1u) != 0) == (mode == 2);
-    }
+    uint32_t word, bit;
+    const bool cand = find_element(batch, start, unperm32(st->prefix << open | k, keys), &word, &bit) && ((word >> bit) & 1u) == (mode == 2 ? 1u : 0u);
     const int below = open - nbits;
     if (below >= 6) {                                              // a wave's keys have one digit
         const unsigned long long ones = __ballot(cand);
@@ -343,65 +395,77 @@ __global__ __launch_bounds__(kThreads) void rc_enum_kernel(RcBatch batch, RcStat
     }
 }
 
-// Pick the bin in which the need-th smallest key lies; extend the prefix by its digit.
+// The bin in which the rank-th smallest key lies; *before: keys in the bins in front of it, *total: in all of them.
 // One block of 256 threads: each sums 8 neighbouring bins, thread 0 walks the 256 partial sums
-// and then the 8 bins of the one that holds the rank; all of them clear the histogram.
-__global__ __launch_bounds__(kThreads) void rc_pick_kernel(RcState* st, int nbits, int last, long long* stats) {
+// and then the 8 bins of the one that holds the rank; all of them clear the histogram.  (Thread 0 has the results.)
+__device__ __forceinline__ int find_bin(RcState* st, int bins, unsigned long long rank, unsigned long long* before, unsigned long long* total) {
     __shared__ unsigned long long part[kThreads];
     constexpr int kPer = kBins / kThreads;
     unsigned long long mine = 0;
     for (int q = 0; q < kPer; ++q) mine += st->hist[threadIdx.x * kPer + q];
     part[threadIdx.x] = mine;
     __syncthreads();
-    if (threadIdx.x == 0 && st->mode != 0) {
-        const int bins = 1 << nbits;
-        unsigned long long before = 0;
+    int b = 0;
+    if (threadIdx.x == 0) {
+        *before = *total = 0;
         int g = 0;
         for (; g < kThreads - 1 && (g + 1) * kPer < bins; ++g) {
-            if (before + part[g] >= st->need) break;
-            before += part[g];
+            if (*before + part[g] >= rank) break;
+            *before += part[g];
         }
-        int b = g * kPer;
-        for (; b < bins - 1; ++b) {
+        *total = *before;
+        for (int i = g; i < kThreads; ++i) *total += part[i];
+        for (b = g * kPer; b < bins - 1; ++b) {
             const unsigned long long hb = st->hist[b];
-            if (before + hb >= st->need) break;
-            before += hb;
+            if (*before + hb >= rank) break;
+            *before += hb;
         }
-        st->need -= before;                      // rank inside the bin, >= 1
-        st->prefix = (st->prefix << nbits) | uint32_t(b);
-        if (last && stats) stats[2] = (long long)st->prefix;
     }
-    if (threadIdx.x == 0 && st->mode == 0 && last && stats) stats[2] = 0;
     __syncthreads();
     for (int q = 0; q < kPer; ++q) st->hist[threadIdx.x * kPer + q] = 0;
+    return b;
 }
-
-// bits << 1 | (x < bound)
-__device__ __forceinline__ uint32_t shift_in_less(uint32_t bits, uint32_t x, uint32_t bound) {
-    asm("v_cmp_gt_u32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(x), "s"(bound) : "vcc");
-    return bits;
+// Extend the prefix by the digit of the need-th smallest key.
+__global__ __launch_bounds__(kThreads) void rc_pick_kernel(RcState* st, int nbits, int last, long long* stats) {
+    if (st->done) return;
+    unsigned long long before, total;
+    const int b = find_bin(st, 1 << nbits, st->need, &before, &total);
+    if (threadIdx.x != 0) return;
+    if (st->mode != 0) {
+        st->need -= before;                      // rank inside the bin, >= 1
+        st->prefix = (st->prefix << nbits) | uint32_t(b);
+    }
+    if (last && stats) stats[2] = st->mode == 0 ? 0 : (long long)st->prefix;
 }
 
 // After the last digit the prefix is a full key: the need-th smallest.  Candidates with a key
 // not above it are the drawn ones.  The top halves of the keys decide, but for those that equal
 // the threshold's: a word that has one is looked at element by element (one word in 2000).
-template <bool kCarry>
-__device__ __forceinline__ uint32_t rc_drawn(const Halves& h, uint32_t high2, uint32_t threshold, bool& tie) {
-    const uint32_t top = threshold & 0xffff0000u, top2 = top | top >> 16;
+// Two keys at a time: (top - x, not below 0; at most 1) is shifted into the halves of `drawn` - 3 instructions
+// where comparing them one by one took 5.
+template <bool kCarry, bool kTie>
+__device__ __forceinline__ uint32_t rc_drawn(const Halves& h, uint32_t high2, uint32_t top, bool& tie) {
+    const uint32_t top2 = top * 0x10001u;
     uint32_t drawn = 0;
     U16x2 nearest = {0xffff, 0xffff};
 #pragma unroll
     for (int p = 14; p >= 0; p -= 2) {
-        uint32_t x[2];
+        uint32_t x[2], less0, less1;
         h.top<kCarry>(p, high2, x);
+        // (left to itself the compiler makes comparisons of the halves again)
+        asm("v_pk_sub_u16 %1, %5, %3 clamp\n\t"
+            "v_pk_sub_u16 %2, %5, %4 clamp\n\t"
+            "v_pk_min_u16 %1, %1, %6\n\t"
+            "v_pk_min_u16 %2, %2, %6\n\t"
+            "v_pk_mad_u16 %0, %0, %7, %2\n\t"
+            "v_pk_mad_u16 %0, %0, %7, %1"
+            : "+&v"(drawn), "=&v"(less0), "=&v"(less1) : "v"(x[0]), "v"(x[1]), "s"(top2), "s"(0x10001u), "s"(0x20002u));
+        if (kTie) {
 #pragma unroll
-        for (int j = 1; j >= 0; --j) {
-            drawn = shift_in_less(drawn, x[j], top);              // the high half's comparison: the low one does not matter
-            drawn = shift_in_less(drawn, x[j] << 16, top);
-            nearest = __builtin_elementwise_min(nearest, __builtin_bit_cast(U16x2, x[j] ^ top2));
+            for (int j = 0; j < 2; ++j) nearest = __builtin_elementwise_min(nearest, __builtin_bit_cast(U16x2, x[j] ^ top2));
         }
     }
-    tie = nearest.x == 0 || nearest.y == 0;
+    tie = kTie && (nearest.x == 0 || nearest.y == 0);
     return drawn;
 }
 // The drawn ones of a word's candidates, one by one.
@@ -415,7 +479,7 @@ __device__ __forceinline__ uint32_t rc_drawn_each(uint32_t cand, uint32_t index0
 }
 __global__ __launch_bounds__(kThreads) void rc_apply_kernel(RcBatch batch, const RcState* st, RcKeys keys) {
     const uint32_t mode = st->mode;
-    if (mode == 0) return;
+    if (mode == 0 || st->done) return;
     const uint32_t threshold = st->prefix;
     for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
         const RcTask r = rc_task(batch, task);
@@ -444,10 +508,116 @@ __global__ __launch_bounds__(kThreads) void rc_apply_kernel(RcBatch batch, const
             if (__ballot(cand != 0) == 0) continue;
             const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
             bool tie;
-            uint32_t drawn = any_carry ? rc_drawn<true>(h, high2, threshold, tie) : rc_drawn<false>(h, high2, threshold, tie);
+            uint32_t drawn = any_carry ? rc_drawn<true, true>(h, high2, threshold >> 16, tie) : rc_drawn<false, true>(h, high2, threshold >> 16, tie);
             drawn &= cand;
             if (tie) drawn = rc_drawn_each(cand, r.index0 + (uint32_t(i) << 16), keys, threshold);
             if (drawn) r.bits[w] = mode == 1 ? (old | drawn) : (old & ~drawn);
+        }
+    }
+}
+
+// ---- a large mask: one keyed pass instead of two ----
+// Keys have nothing to do with a mask that was made without them, so how many candidates lie below a threshold is
+// known to a few parts in 10^5 before any key is worked out.  rc_try_kernel() draws, in place, what lies below the
+// lower end of a window around the expected threshold, counts it and keeps the words as they were; the window's keys
+// (at most 2^22) are taken back to their elements, which gives the threshold and the rest of the drawing.  Where the
+// count shows that the threshold was not in the window, rc_restore_kernel() puts the mask back and the passes
+// above do it all; where it was, they return at once.  The result is the same in any case.
+// The pass takes 12.7 vector instructions per element; see the file's head for the times.
+__global__ __launch_bounds__(kThreads) void rc_try_kernel(RcBatch batch, RcState* st, RcKeys keys) {
+    if (!guess_holds(st)) return;
+    const uint32_t mode = st->mode, top = st->window_lo;           // top >= 1
+    const uint32_t last = (top << 16) - 1;                          // the largest key to be drawn
+    uint32_t count = 0;
+    for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
+        const RcTask r = rc_task(batch, task);
+        uint32_t next = r.first < r.n_words ? r.bits[r.first] : 0u;
+        int i = 0;
+        auto done = [&](int64_t w, uint32_t old, uint32_t drawn) __attribute__((always_inline)) {
+            if (w < r.n_words) r.undo[w] = old;
+            if (drawn) r.bits[w] = mode == 1 ? (old | drawn) : (old & ~drawn);
+            count += __popc(drawn);
+        };
+#pragma unroll 1
+        for (; i < kRows; ++i) {                                   // as long as the words have few candidates
+            const int64_t w = r.first + i * kRowWords;
+            const uint32_t old = next;
+            const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
+            if (!few_candidates(cand)) break;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            done(w, old, rc_drawn_each(cand, r.index0 + (uint32_t(i) << 16), keys, last));
+        }
+        if (i == kRows) continue;
+        Halves h;
+        h.init(r.index0, keys);
+        const bool any_carry = __ballot(h.carry) != 0;
+#pragma unroll 1
+        for (; i < kRows; ++i) {
+            const int64_t w = r.first + i * kRowWords;
+            const uint32_t old = next;
+            if (i + 1 < kRows && w + kRowWords < r.n_words) next = r.bits[w + kRowWords];
+            const uint32_t cand = (mode == 1 ? ~old : old) & rc_valid(r, w);
+            uint32_t drawn = 0;
+            if (__ballot(cand != 0) != 0) {
+                const uint32_t high2 = ((r.index0 >> 16) + i) * 0x10001u;
+                bool tie;
+                drawn = any_carry ? rc_drawn<true, false>(h, high2, top, tie) : rc_drawn<false, false>(h, high2, top, tie);
+            }
+            done(w, old, drawn & cand);
+        }
+    }
+    add_block_count(&st->drawn, count);
+}
+
+// The window's keys, taken back to their elements.  level 0: how many are candidates, in bins of 2^11 keys;
+// 1: in the bin found, key by key; 2: draws those up to the threshold.
+__global__ __launch_bounds__(kThreads) void rc_window_kernel(RcBatch batch, RcState* st, RcKeys keys, int level) {
+    __shared__ int64_t start[kMaxRcTensors + 1];
+    if (level == 0 ? !guess_holds(st) : level == 1 ? st->rank == 0 : st->done == 0) return;
+    tensor_starts(batch, start);
+    const uint32_t first = (st->window_lo << 16) + (level == 1 ? st->prefix << 11 : 0u);
+    const uint32_t n = level == 0 ? (st->window_hi - st->window_lo) << 16 : level == 1 ? 2048u : st->prefix - first + 1;
+    const uint32_t one = st->mode == 2 ? 1u : 0u;
+    for (uint32_t k = blockIdx.x * kThreads + threadIdx.x; k < n; k += gridDim.x * kThreads) {      // n: a multiple of 64 but at level 2
+        uint32_t word = 0, bit = 0;
+        uint32_t* const at = find_element(batch, start, unperm32(first + k, keys), &word, &bit);
+        const bool cand = at && ((word >> bit) & 1u) == one;
+        if (level == 0) {                                          // a wave's keys share their bin
+            const unsigned long long ones = __ballot(cand);
+            if ((threadIdx.x & 63) == 0 && ones) atomicAdd(&st->hist[k >> 11], uint32_t(__popcll(ones)));
+        } else if (cand) {
+            if (level == 1) atomicAdd(&st->hist[k], 1u);
+            else if (one) atomicAnd(at, ~(1u << bit));
+            else atomicOr(at, 1u << bit);
+        }
+    }
+}
+// Level 0: is the threshold in the window, and in which bin; 1: the threshold.
+__global__ __launch_bounds__(kThreads) void rc_window_pick_kernel(RcState* st, int level, long long* stats) {
+    if (level == 0 ? !guess_holds(st) : st->rank == 0) return;
+    const bool below = level == 1 || st->drawn < st->need;
+    const unsigned long long rank = level == 1 ? st->rank : below ? st->need - st->drawn : 1;
+    unsigned long long before, total;
+    const uint32_t b = uint32_t(find_bin(st, kBins, rank, &before, &total));
+    if (threadIdx.x != 0 || !below || total < rank) return;        // st->rank stays 0
+    st->rank = rank - before;                                       // >= 1
+    if (level == 0) {
+        st->prefix = b;
+    } else {
+        st->prefix = (st->window_lo << 16) + (st->prefix << 11) + b;
+        st->done = 1;
+        if (stats) stats[2] = (long long)st->prefix;
+    }
+}
+// The guess was wrong: the mask as it was.
+__global__ __launch_bounds__(kThreads) void rc_restore_kernel(RcBatch batch, RcState* st) {
+    if (st->done || !guess_holds(st)) return;
+    for (int task = blockIdx.x; task < batch.total_blocks; task += gridDim.x) {
+        const RcTask r = rc_task(batch, task);
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int64_t w = r.first + i * kRowWords;
+            if (w < r.n_words) r.bits[w] = r.undo[w];
         }
     }
 }
@@ -500,9 +670,33 @@ hipError_t launch_rc_count(hipStream_t stream, RcBatch& batch, RcState* st) {
     hipLaunchKernelGGL(rc_count_kernel, dim3((rc_grid(batch) + 1) / 2), dim3(kThreads), 0, stream, batch, st);
     return hipGetLastError();
 }
-hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, int64_t* stats) {
-    hipLaunchKernelGGL(rc_decide_kernel, dim3(1), dim3(64), 0, stream, st, (unsigned long long)n_freeze,
+hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, uint64_t guess_of, int64_t* stats) {
+    hipLaunchKernelGGL(rc_decide_kernel, dim3(1), dim3(64), 0, stream, st, (unsigned long long)n_freeze, (unsigned long long)guess_of,
                        reinterpret_cast<long long*>(stats));
+    return hipGetLastError();
+}
+hipError_t launch_rc_probe(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys) {
+    if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(rc_probe_kernel, dim3(65536 / kThreads), dim3(kThreads), 0, stream, batch, st, keys);
+    return hipGetLastError();
+}
+hipError_t launch_rc_try(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys) {
+    if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(rc_try_kernel, dim3(rc_grid(batch)), dim3(kThreads), 0, stream, batch, st, keys);
+    return hipGetLastError();
+}
+hipError_t launch_rc_window(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int level) {
+    if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(rc_window_kernel, dim3(level == 1 ? 2048 / kThreads : kGrid), dim3(kThreads), 0, stream, batch, st, keys, level);
+    return hipGetLastError();
+}
+hipError_t launch_rc_window_pick(hipStream_t stream, RcState* st, int level, int64_t* stats) {
+    hipLaunchKernelGGL(rc_window_pick_kernel, dim3(1), dim3(kThreads), 0, stream, st, level, reinterpret_cast<long long*>(stats));
+    return hipGetLastError();
+}
+hipError_t launch_rc_restore(hipStream_t stream, RcBatch& batch, RcState* st) {
+    if (batch.n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(rc_restore_kernel, dim3((rc_grid(batch) + 1) / 2), dim3(kThreads), 0, stream, batch, st);
     return hipGetLastError();
 }
 hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys) {

@@ -23,6 +23,8 @@ struct tf_ctx {
     std::vector<hipEvent_t> pool;       // events ready for reuse
     tf::RcState* rc_state;              // device memory of tf_reconcile_mask (radix-select state)
     tf::RcState* rc_state_static;       // this device's static scratch array (tf_reconcile_mask_static)
+    uint32_t* rc_undo;                  // device memory of large reconciliations, made when first needed
+    int64_t rc_undo_words;
     bool lowp_is_rounded_master;        // tf_assume_lowp_is_rounded_master
     double* ew_partials;                // device memory of the score sums' first level (zero between launches)
     int gemm_route;                     // tf_internal_gemm_route
@@ -579,6 +581,8 @@ int tf_create(tf_ctx** out, int device_id) {
     ctx->profiling = false;
     ctx->rc_state = nullptr;
     ctx->rc_state_static = nullptr;
+    ctx->rc_undo = nullptr;
+    ctx->rc_undo_words = 0;
     ctx->lowp_is_rounded_master = false;
     ctx->gemm_route = 0;
     ctx->ew_partials = nullptr;
@@ -605,6 +609,7 @@ int tf_destroy(tf_ctx* ctx) {
     for (tf_prof_rec& r : ctx->recs) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
     for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
     if (ctx->rc_state) (void)hipFree(ctx->rc_state);
+    if (ctx->rc_undo) (void)hipFree(ctx->rc_undo);
     if (ctx->ew_partials) (void)hipFree(ctx->ew_partials);
     delete ctx;
     return TF_OK;
@@ -1005,17 +1010,52 @@ static int validate_reconcile(int32_t n_tensors, const int64_t* numel, uint32_t*
     return TF_OK;
 }
 
+// Masks of this many elements guess their threshold (rc_try_kernel()).  Both ways timed, us, 30 % -> 50 %: 61e6 elements
+// 122 (general passes 138), 122e6 151 (189), 218e6 193 (263), 436e6 270 (428), 1.74e9 771 (1475).  Where the window would be
+// too wide the launches that go with a guess cost 20 us for nothing: from 2^28 elements on that takes fewer than 15 %
+// candidates, half of them to be drawn.
+constexpr int64_t kGuessFrom = int64_t(1) << 28;
+
+// Room for a copy of the mask, for a reconciliation that guesses its threshold, or null where it does not: masks too
+// small for it; streams that are being captured (a graph keeps its pointers, the context's memory may be replaced by
+// a later, larger call); no memory left.
+static uint32_t* reconcile_undo(tf_ctx* ctx, hipStream_t stream, int32_t n_tensors, const int64_t* numel) {
+    int64_t elements = 0, words = 0;
+    for (int32_t i = 0; i < n_tensors; ++i) { elements += numel[i]; words += (numel[i] + 31) / 32; }
+    if (elements < kGuessFrom) return nullptr;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (words > ctx->rc_undo_words) {
+        // another thread's capture has to live through an allocation here
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (ctx->rc_undo) (void)hipFree(ctx->rc_undo);             // waits for the device
+        ctx->rc_undo = nullptr;
+        ctx->rc_undo_words = 0;
+        if (hipMalloc(reinterpret_cast<void**>(&ctx->rc_undo), size_t(words) * 4) == hipSuccess) ctx->rc_undo_words = words;
+        else ctx->rc_undo = nullptr;
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        (void)hipGetLastError();
+    }
+    return ctx->rc_undo;
+}
+
 // The passes of the reconciliation on the state `st`.  Allocates nothing, on the host or on the
 // device: the tensor descriptors of a launch are built on the stack, pass after pass.
 static hipError_t reconcile_passes(hipStream_t stream, int32_t n_tensors, const int64_t* numel,
                                    uint32_t* const* elem_bits, int64_t n_freeze, uint64_t seed,
-                                   int64_t* stats, RcState* st) {
+                                   int64_t* stats, RcState* st, uint32_t* undo) {
     const RcKeys keys = perm32_keys(seed);
+    int64_t total = 0;
+    for (int32_t i = 0; i < n_tensors; ++i) total += numel[i];
     // calls fn(batch) for every launch-sized group of tensors, in order
     auto for_each_batch = [&](auto&& fn) -> hipError_t {
         RcBatch b;
         b.n_tensors = 0; b.total_blocks = 0;
-        int64_t goff = 0, blocks = 0;
+        int64_t goff = 0, blocks = 0, words = 0;
         for (int32_t i = 0; i < n_tensors; ++i) {
             const int nb = rc_tasks(numel[i]);
             if (b.n_tensors == kMaxRcTensors) {
@@ -1027,15 +1067,26 @@ static hipError_t reconcile_passes(hipStream_t stream, int32_t n_tensors, const 
             RcTensor& t = b.t[b.n_tensors++];
             t.bits = elem_bits[i]; t.numel = numel[i]; t.goff = goff;
             t.block_start = int32_t(blocks); t.pad_ = 0;
+            t.undo = undo ? undo + words : nullptr;
             blocks += nb;
             goff += numel[i];
+            words += (numel[i] + 31) / 32;
         }
         if (b.n_tensors > 0) { b.total_blocks = int32_t(blocks); return fn(b); }
         return hipSuccess;
     };
     hipError_t e = launch_rc_begin(stream, st);               // a kernel clears the state: nothing survives from the call before
     if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_count(stream, b, st); });
-    if (e == hipSuccess) e = launch_rc_decide(stream, st, uint64_t(n_freeze), stats);
+    if (e == hipSuccess) e = launch_rc_decide(stream, st, uint64_t(n_freeze), undo ? uint64_t(total) : 0, stats);
+    if (undo) {
+        if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_probe(stream, b, st, keys); });
+        if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_try(stream, b, st, keys); });
+        for (int level = 0; level < 3; ++level) {
+            if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_window(stream, b, st, keys, level); });
+            if (e == hipSuccess && level < 2) e = launch_rc_window_pick(stream, st, level, stats);
+        }
+        if (e == hipSuccess) e = for_each_batch([&](RcBatch& b) { return launch_rc_restore(stream, b, st); });
+    }
     const int open[3] = {32, 21, 10}, widths[3] = {11, 11, 10};        // key bits not fixed yet, bits of the digit
     for (int pass = 0; pass < 3; ++pass) {
         if (e == hipSuccess)
@@ -1059,7 +1110,8 @@ int tf_reconcile_mask(tf_ctx* ctx, void* hip_stream,
     if (!use_device(ctx)) return TF_ERR_HIP;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     ProfScope prof(ctx, stream, TF_KERNEL_RECONCILE);
-    const hipError_t e = reconcile_passes(stream, n_tensors, numel, elem_bits, n_freeze, seed, stats, ctx->rc_state);
+    const hipError_t e = reconcile_passes(stream, n_tensors, numel, elem_bits, n_freeze, seed, stats, ctx->rc_state,
+                                          reconcile_undo(ctx, stream, n_tensors, numel));
     if (e != hipSuccess) return hip_fail(ctx, e);
     return TF_OK;
 }
@@ -1075,7 +1127,7 @@ int tf_reconcile_mask_static(tf_ctx* ctx, void* hip_stream,
     if (!use_device(ctx)) return TF_ERR_HIP;
     // no timing events here: creating one allocates
     const hipError_t e = reconcile_passes(static_cast<hipStream_t>(hip_stream), n_tensors, numel, elem_bits, n_freeze,
-                                          seed, stats, ctx->rc_state_static);
+                                          seed, stats, ctx->rc_state_static, nullptr);
     if (e != hipSuccess) return hip_fail(ctx, e);
     return TF_OK;
 }

@@ -159,6 +159,7 @@ struct RcTensor {
     int64_t goff;           // stage-wide index of element 0
     int32_t block_start;    // first task of the tensor inside the launch
     int32_t pad_;
+    uint32_t* undo;         // as many words again, for rc_try_kernel(); or null
 };
 constexpr int kMaxRcTensors = 64;
 struct RcBatch {            // passed by value as the kernel argument
@@ -202,12 +203,25 @@ struct RcState {            // device memory owned by the context
     unsigned long long need;            // rank still to be located
     uint32_t mode;                      // 0 keep, 1 add zeros, 2 remove ones
     uint32_t prefix;                    // leading key bits fixed so far
+    // a guessed threshold (large masks)
+    unsigned long long drawn;           // candidates below the window
+    unsigned long long rank;            // of the threshold in its bin of the window; 0: not known to be there
+    uint32_t window_lo, window_hi;      // its top halves lie in [lo, hi); hi = 0: nothing guessed
+    uint32_t probe;                     // candidates found by rc_probe_kernel()
+    uint32_t done;                      // the guess held: nothing left for the passes after it
 };
 int rc_tasks(int64_t numel);        // tasks of a tensor (RcTensor::block_start counts them)
 size_t rc_state_bytes();
 hipError_t launch_rc_begin(hipStream_t stream, RcState* st);
 hipError_t launch_rc_count(hipStream_t stream, RcBatch& batch, RcState* st);
-hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, int64_t* stats);
+// guess_of: elements of the stage, if the launches of a guessed threshold follow (probe, try, window 0, pick 0,
+// window 1, pick 1, window 2, restore), or 0
+hipError_t launch_rc_decide(hipStream_t stream, RcState* st, uint64_t n_freeze, uint64_t guess_of, int64_t* stats);
+hipError_t launch_rc_probe(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys);
+hipError_t launch_rc_try(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys);
+hipError_t launch_rc_window(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int level);
+hipError_t launch_rc_window_pick(hipStream_t stream, RcState* st, int level, int64_t* stats);
+hipError_t launch_rc_restore(hipStream_t stream, RcBatch& batch, RcState* st);
 hipError_t launch_rc_hist(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys);
 hipError_t launch_rc_enum(hipStream_t stream, RcBatch& batch, RcState* st, const RcKeys& keys, int open, int nbits);
 hipError_t launch_rc_pick(hipStream_t stream, RcState* st, int nbits, bool last, int64_t* stats);

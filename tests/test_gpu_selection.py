@@ -223,3 +223,89 @@ def test_reconcile_threshold_is_the_largest_key_drawn(ctx):
     new = np.concatenate(got)
     dropped = np.flatnonzero((new == 0) & (flat == 1))
     assert dropped.size == 999 and stats[2] == keys[dropped].max()
+
+
+# ---- large masks: the threshold is guessed, and the general passes are there where the guess does not hold
+GUESS_FROM = 1 << 28
+
+
+def _random_words(g, n, p):
+    words = torch.zeros(n, dtype=torch.int32, device="cuda")
+    for b in range(16):
+        r = torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+        words = (words | r) if (int(p * 65536) >> b) & 1 else (words & r)
+    return words
+
+
+def _key_words(numel, seed, test):
+    """Words whose bit e says test(key of element e), the elements counted from the first tensor on."""
+    mul, mask, k = 0x9E3779B1, 0xffffffff, [(seed >> (16 * r)) & 0xffff for r in range(4)]
+    s2 = seed * 0xD1342543DE82EF95 % (1 << 64)
+    k += [(s2 >> 32) & 0xffff, (s2 >> 48) & 0xffff]
+    place = (1 << torch.arange(32, device="cuda", dtype=torch.int64))
+    out, first = [], 0
+    for n in numel:
+        parts = []
+        for a in range(0, n, 1 << 25):
+            x = first + a + torch.arange(min(1 << 25, n - a), device="cuda", dtype=torch.int64)
+            hi, lo = x >> 16, x & 0xffff
+            for r in range(6):
+                hi, lo = lo, hi ^ ((((lo ^ k[r]) + 1) * mul & mask) >> 16)
+            bits = torch.nn.functional.pad(test(hi << 16 | lo).to(torch.int64), (0, -x.numel() % 32))
+            parts.append((bits.view(-1, 32) * place).sum(1).to(torch.int32))
+        out.append(torch.cat(parts))
+        first += n
+    return out
+
+
+@pytest.mark.parametrize("what", ["added", "removed", "all", "same seed", "too few below", "too many below"])
+def test_reconcile_large_masks_against_the_general_passes(ctx, what):
+    """tf_reconcile_mask guesses the threshold of a large mask, tf_reconcile_mask_static never does.  Masks
+    whose candidates have to do with the keys: so much that the probe sees it (`same seed`: every candidate has a key
+    above the last threshold), and so little that only the count shows it and the mask has to be put back."""
+    seed = 0x1234_5678_9ABC_DEF1
+    numel = [GUESS_FROM - 77_000_003, 5, 77_000_005, 64]
+    N = sum(numel)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(what))
+    base = [_random_words(g, (n + 31) // 32, 0.3) for n in numel]
+    for w, n in zip(base, numel):
+        if n % 32:
+            w[-1] &= (1 << n % 32) - 1
+    ones = lambda words: sum(int(((w >> b) & 1).sum()) for w in words for b in range(32))
+    nf = N // 2
+    if what == "removed":
+        nf = N // 10
+    elif what == "all":
+        nf = N                                                         # every candidate is drawn
+    elif what == "same seed":
+        tf.tf_reconcile_mask_static(ctx, numel, base, N // 3, seed)
+    elif what != "added":                                              # 5 % of the candidates on one side are none
+        limit = int((0.5 - 0.3) / 0.7 * (1 << 32))
+        side = _key_words(numel, seed, (lambda k: k < limit) if what == "too few below" else (lambda k: k >= limit))
+        some = [_random_words(g, (n + 31) // 32, 0.05) for n in numel]
+        base = [w | (s & x) for w, s, x in zip(base, side, some)]
+    got = [w.clone() for w in base]
+    ref = [w.clone() for w in base]
+    stats, stats_ref = (torch.full((3,), -1, dtype=torch.int64, device="cuda") for _ in range(2))
+    for _ in range(2):                                                 # the second call finds what the first has left
+        for a, b in zip(got, base):
+            a.copy_(b)
+        tf.tf_reconcile_mask(ctx, numel, got, nf, seed, stats=stats)
+        tf.tf_reconcile_mask_static(ctx, numel, ref, nf, seed, stats=stats_ref)
+        assert all(torch.equal(a, b) for a, b in zip(got, ref)) and ones(got) == nf
+        assert torch.equal(stats, stats_ref)
+        for a, b in zip(ref, base):
+            a.copy_(b)
+
+
+def test_reconcile_large_mask_of_many_tensors(ctx):
+    """140 tensors: three launches per pass, the keys of a window spread over them."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    numel = [GUESS_FROM // 140 + 1 + 17 * i for i in range(140)]
+    base = [_random_words(g, (n + 31) // 32, 0.4) for n in numel]
+    got, ref = [w.clone() for w in base], [w.clone() for w in base]
+    tf.tf_reconcile_mask(ctx, numel, got, sum(numel) // 4, 99)
+    tf.tf_reconcile_mask_static(ctx, numel, ref, sum(numel) // 4, 99)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
