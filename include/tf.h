@@ -98,8 +98,8 @@ int tf_last_hip_error(const tf_ctx* ctx);
 typedef enum {
     TF_KERNEL_DX_MFMA = 0,      /* input-gradient GEMMs, bf16 kernel of 256 x 256 tiles  */
     TF_KERNEL_DW_MFMA = 1,      /* weight-gradient GEMMs, bf16 kernel of 256 x 256 tiles */
-    TF_KERNEL_DX_GENERIC = 2,   /* input-gradient GEMMs, generic kernel (any shape)  */
-    TF_KERNEL_DW_GENERIC = 3,   /* weight-gradient GEMMs, generic kernel (any shape) */
+    TF_KERNEL_DX_GENERIC = 2,   /* input-gradient GEMMs, smaller tiles (any shape)   */
+    TF_KERNEL_DW_GENERIC = 3,   /* weight-gradient GEMMs, smaller tiles (any shape)  */
     TF_KERNEL_ADAMW = 4,        /* fused masked AdamW (+ stability EMAs)      */
     TF_KERNEL_STABILITY = 5,    /* stand-alone stability update               */
     TF_KERNEL_AUTOFREEZE = 6,   /* norms of the cumulative updates            */

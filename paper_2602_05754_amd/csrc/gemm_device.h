@@ -1,5 +1,5 @@
-// What both matrix-core GEMMs use on the device: vector types, the LDS address space, compile-time loops, the
-// rounding to bf16 and the swizzle of row-major stages.
+// What the matrix-core GEMMs use on the device: vector types, the LDS address space, compile-time loops, the
+// rounding to bf16, the swizzle of row-major stages, direct loads into LDS and the wait in front of the sums.
 #pragma once
 #include "tf_internal.h"
 
@@ -49,6 +49,48 @@ __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float lo, float hi) {
 // also keeps 16 consecutive lanes (one chunk, 16 rows) apart.
 __host__ __device__ __forceinline__ constexpr int nt_swizzle(int R) {
     return ((R >> 1) & 1) | (((R >> 3) & 1) << 1) | (((R >> 2) & 1) << 2);
+}
+
+typedef U4 U4any __attribute__((aligned(2)));       // a 16-byte piece at any element address
+
+// One direct-to-LDS load: lane i fetches 16 bytes from gbase + voff and the wave's 1 KB lands
+// at LDS byte address lds_wave_base + kLdsOff + 16 i (the LDS address goes through M0).
+// Written as inline assembly so that the compiler's wait-count insertion does not treat every
+// later LDS read as dependent on it (it would drain the load queue before each transpose read);
+// completion is awaited explicitly with wait_direct_loads() before the stage barrier.
+// The addition sets SCC, and the compiler is free to place the statement between the two
+// halves of one of its own 64-bit scalar additions (s_add_u32 / s_addc_u32) unless it is told:
+// a clobbered carry sends the high word of a global address off by one as soon as the addition
+// crosses a 4 GiB boundary.  Hence the "scc" clobber; the build scans the generated code for
+// inline assembly between a producer and a consumer of SCC and refuses it.  M0 is named for the
+// same reason: the compiler keeps values of its own there (LDS-DMA builtins, lane selects).
+template <int kLdsOff>
+__device__ __forceinline__ void direct_load_16B(const char* gbase, uint32_t voff, uint32_t lds_wave_base) {
+    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_wave_base), "v"(voff), "s"(gbase), "n"(kLdsOff)
+                 : "memory", "scc", "m0");
+}
+__device__ __forceinline__ void wait_direct_loads() {
+    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0), other counters untouched
+}
+
+// Between the last matrix instruction and the first vector instruction that reads its result.  Left to
+// itself the compiler counts a wait and a barrier in between as wait states, and an fp32 sum's last
+// register, read first behind the two, was the old one.  The sums pass through statements in front of the
+// wait and behind it: no matrix instruction can follow it, no reader precede it.  (The build looks through
+// the generated code for a reader that comes too early.)
+template <class V, int kI, int kJ>
+__device__ __forceinline__ void wait_for_sums(V (&x)[kI][kJ]) {
+    auto tie = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kI; ++i)
+#pragma unroll
+            for (int j = 0; j < kJ; ++j) asm volatile("" : "+v"(x[i][j]));
+    };
+    tie();
+    asm volatile("s_nop 15\n\ts_nop 15");
+    tie();
 }
 
 }  // namespace

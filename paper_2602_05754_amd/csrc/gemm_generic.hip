@@ -38,7 +38,6 @@ constexpr int kDepth = 2;               // steps whose pieces are on their way i
 constexpr int kXcdRun = 8;              // consecutive logical tiles kept on one XCD
 constexpr int kGroupM = 8;              // tile rows per L2 locality group
 
-typedef U4 U4any __attribute__((aligned(2)));       // a 16-byte piece at any element address
 typedef f32x4 F4any __attribute__((aligned(4)));
 
 // One operand of a workgroup's tile: kRows rows of it, kRows x 128 bytes per stage.
@@ -188,24 +187,6 @@ struct Operand {
         return x;
     }
 };
-
-// Between the last matrix instruction and the first vector instruction that reads its result.  Left to
-// itself the compiler counts a wait and a barrier in between as wait states, and an fp32 sum's last
-// register, read first behind the two, was the old one.  The sums pass through statements in front of the
-// wait and behind it: no matrix instruction can follow it, no reader precede it.  (The build looks through
-// the generated code for a reader that comes too early.)
-template <class V, int kI, int kJ>
-__device__ __forceinline__ void wait_for_sums(V (&x)[kI][kJ]) {
-    auto tie = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kI; ++i)
-#pragma unroll
-            for (int j = 0; j < kJ; ++j) asm volatile("" : "+v"(x[i][j]));
-    };
-    tie();
-    asm volatile("s_nop 15\n\ts_nop 15");
-    tie();
-}
 
 // Block number -> logical tile: runs of consecutive tiles stay on one XCD (block b runs on XCD b % 8).
 __device__ __forceinline__ int logical_tile(int b, int nb) {

@@ -204,28 +204,6 @@ __device__ __forceinline__ Run make_tail_run(const GemmProblem& P, int m0, int n
     return f;
 }
 
-// One direct-to-LDS load: lane i fetches 16 bytes from gbase + voff and the wave's 1 KB lands
-// at LDS byte address lds_wave_base + kLdsOff + 16 i (the LDS address goes through M0).
-// Written as inline assembly so that the compiler's wait-count insertion does not treat every
-// later LDS read as dependent on it (it would drain the load queue before each transpose read);
-// completion is awaited explicitly with wait_direct_loads() before the stage barrier.
-// The addition sets SCC, and the compiler is free to place the statement between the two
-// halves of one of its own 64-bit scalar additions (s_add_u32 / s_addc_u32) unless it is told:
-// a clobbered carry sends the high word of a global address off by one as soon as the addition
-// crosses a 4 GiB boundary.  Hence the "scc" clobber; the build scans the generated code for
-// inline assembly between a producer and a consumer of SCC and refuses it.  M0 is named for the
-// same reason: the compiler keeps values of its own there (LDS-DMA builtins, lane selects).
-template <int kLdsOff>
-__device__ __forceinline__ void direct_load_16B(const char* gbase, uint32_t voff, uint32_t lds_wave_base) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_wave_base), "v"(voff), "s"(gbase), "n"(kLdsOff)
-                 : "memory", "scc", "m0");
-}
-__device__ __forceinline__ void wait_direct_loads() {
-    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0), other counters untouched
-}
-
 // Load p (0..7) of one operand's stage fill: it fetches KB number 4 p + w of the 32 KB stage.
 // lds_stage is the LDS byte address of the stage plus 1 KB times the wave index.  Nothing but
 // the load itself: every address is ready in a register.

@@ -65,6 +65,17 @@ hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_probl
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
 int compute_units();              // of the current device
 
+// bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of
+// 64 or more that are multiples of 8, row pitches that are multiples of 8 and at most 2^22, 16-byte aligned operands.
+struct NarrowShape {
+    int rows, cols;                                     // of its tile
+    float step_us, chain_us, tile_steps, chain_steps;   // what a contraction step of a tile costs (see there)
+};
+constexpr int kNarrowShapes = 4;
+const NarrowShape& narrow_shape(int shape);
+bool narrow_shape_ok(int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb);
+hipError_t launch_gemm_narrow(hipStream_t stream, GemmBatch& batch, int n_problems, int shape);
+
 // MFMA kernel for bf16 inputs.  What it takes (mfma_shape_ok): contraction a multiple of 64; output
 // columns N >= 256 and a multiple of 8; output rows M >= 256, or fewer with rows_before +
 // rows_after >= 256 - M operand rows in memory around them; layout kTN also M a multiple of 8; row

@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, NARROW, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -236,3 +236,46 @@ def test_a_layers_gradient_does_not_depend_on_the_other_layers(ctx, io, T, other
         # chains of at most 32 fp32 products and 16 partial sums against one rounding: 2^-24 (32 + 16)^(1/2) each way,
         # of terms as large as the result's root mean square times sqrt(T) / sqrt(T)
         assert 0 < rel_fro(got[0][2], got[1][2]) <= 2 * 2.0 ** -24 * 48 ** 0.5
+
+
+@pytest.mark.parametrize("tile", sorted(NARROW))
+@pytest.mark.parametrize("T", [1, 63, 65, 128, 200, 257])
+def test_input_gradients_of_few_rows(ctx, T, tile):
+    """The kernel for few rows where it can go wrong: rows and columns around its tiles, contractions of one step, of
+    fewer steps than it has stages, of as many and of more, and 8, 16 or 56 values more than whole steps.  The bits are
+    the generic kernel's; an infinity stays in its row and column."""
+    shapes = [(64, 64), (1, 72), (130, 128), (63, 136), (129, 320), (65, 376), (257, 1096), (7, 64)]
+    with route(ctx, NARROW[tile]):
+        kinds = _case(ctx, shapes, T, "bf16", "bf16", seed=T)
+    assert kinds[0] == "dx_generic"
+    W, X, dY = _random(shapes, T, "bf16", T)
+    W[6][5, 1095] = dY[4][T - 1, 319] = float("inf")
+    got = {}
+    for which in (NARROW[tile], GENERIC):
+        out = [Guarded((T, k), "bf16") for k, n in shapes]
+        with route(ctx, which):
+            tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, np.ones(len(shapes), np.uint8), [g.t for g in out],
+                                 [torch.empty(s, dtype=torch.bfloat16, device="cuda") for s in shapes], tf.TF_BF16)
+        for l, g in enumerate(out):
+            g.check(f"dX[{l}] {shapes[l]} T={T} {tile}")
+        got[which] = [raw_bytes(g.t) for g in out]
+        assert not torch.isfinite(out[6].t[:, 5]).any() and torch.isfinite(out[6].t[:, :5]).all() and torch.isfinite(out[4].t[:T - 1]).all()
+    assert got[NARROW[tile]] == got[GENERIC]
+
+
+def test_few_rows_of_pitches_across_4_gib(ctx):
+    """A weight matrix that crosses a 4 GiB boundary of addresses, whose rows are far apart: 64-bit base addresses,
+    32-bit offsets in a tile."""
+    K, N, T = 300, 1 << 19, 65
+    W, dY = torch.zeros(K, N, dtype=torch.bfloat16, device="cuda"), torch.zeros(T, N, dtype=torch.bfloat16, device="cuda")
+    cols = torch.arange(0, N, 4099, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    W[:, cols] = torch.randn((K, cols.numel()), generator=g, device="cuda").bfloat16()
+    dY[:, cols] = torch.randn((T, cols.numel()), generator=g, device="cuda").bfloat16()
+    dX = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
+    X = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
+    with route(ctx, NARROW[(256, 128)]):
+        tf.tf_stage_backward(ctx, [(K, N)], T, tf.TF_BF16, [W], [X], [dY], np.ones(1, np.uint8), [dX], [torch.empty_like(W)], tf.TF_BF16)
+    ref = dY[:, cols].double() @ W[:, cols].double().t().contiguous()
+    assert rel_fro(host64(dX), ref.cpu().numpy()) < 4e-3

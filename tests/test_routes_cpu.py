@@ -76,6 +76,31 @@ def test_input_gradients_take_the_faster_kernel(shapes, T, on256):
     assert len(set(got)) == 1 and (got[0] == TILES_256) == on256, got
 
 
+FEW_ROWS = range(3, 7)
+
+
+# us on the kernel for few rows and on the better one of the others
+@pytest.mark.parametrize("shapes,T,few", [
+    (block(1024, 256, 2816), 32, True),                  # 13.5, 21.9
+    (block(2048, 512, 8192, 2), 200, True),              # 71, 103
+    (block(2048, 512, 8192, 4), 256, True),              # 132, 161
+    (block(4096, 1024, 14336), 1024, True),              # 382, 434
+    (block(2048, 512, 8192, 2), 1536, False),            # 340, 300 on 256 x 256 tiles
+    (block(2048, 512, 8192, 4), 1024, False),            # 433, 356
+])
+def test_few_rows_take_their_own_kernel(shapes, T, few):
+    K, N = zip(*shapes)
+    got = set(kernels([T] * len(K), K, N, False))
+    assert len(got) == 1 and (got <= set(FEW_ROWS)) == few
+
+
+def test_few_rows_that_their_kernel_cannot_take():
+    """A contraction below 64 or no multiple of 8, fp32, and weight gradients go where they went."""
+    for M, N, Kc, tn, io in ([32, 256, 56, 0, 1], [32, 256, 100, 0, 1], [32, 256, 128, 0, 0], [32, 256, 128, 1, 1]):
+        assert kernels([M], [N], [Kc], tn, io=io, out=io)[0] < 3
+    assert kernels([32, 32], [256, 256], [128, 100], False) == kernels([32, 32], [256, 256], [100, 100], False)
+
+
 TILES = {tf.TF_F32: [(32, 32), (32, 64), (64, 64)], tf.TF_BF16: [(64, 64), (128, 64), (128, 128)]}
 
 
