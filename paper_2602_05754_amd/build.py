@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtf.so")
-SOURCES = ["tf_api.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_mfma_bf16.hip", "elementwise.hip", "selection.hip", "schedule_lp.hip"]
+SOURCES = ["tf_api.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip", "gemm_mfma_bf16.hip", "elementwise.hip", "selection.hip", "schedule_lp.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -158,7 +158,7 @@ def mfma_hazards(asm_text: str) -> list:
 
 def check_generated_code(hipcc: str, extra: list) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Rpass-analysis=kernel-resource-usage")]
-    for source in ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip"):
+    for source in ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip"):
         cmd = [hipcc] + flags + extra + ["-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", "-"]
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:

@@ -233,28 +233,71 @@ int pick_narrow_shape(const std::vector<const Planned*>& items, double* best_us)
     return kGenericShapes + best;
 }
 
+inline bool planned_short_ok(const Planned& it, Layout layout, Dtype in_dtype) {
+    return in_dtype == Dtype::BF16 && layout == Layout::kTN && ~it.row_bits == 0 && it.more.empty() &&
+           short_shape_ok(it.M, it.N, it.Kc, it.lda, it.ldb) && aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
+}
+
+// What the outputs of weight gradients take, `us` per MB: written, fp32 ones added to, each for rows of whole cache lines and others.
+double outputs_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, const float (&us)[4]) {
+    double sum = 0;
+    for (const Planned* it : items) sum += 1e-6 * double(it->M) * double(it->N) * out_bytes * us[(accumulate ? 2 : 0) + (it->N * out_bytes % 128 != 0)];
+    return sum;
+}
+
+// Launch time, events included, of weight gradients on the kernel for few tokens (its best launch shape), and on the 256 x 256-tile
+// kernel.  Fitted to 168 launches on each (seven sets of layers of widths 256 to 4096, two of them with rows that are no whole cache
+// lines, 64 to 1024 tokens, bf16, fp32 and added fp32 outputs, three sets of buffers in turn; 7 % and 19 % rms, the second one's misses
+// where it is far slower).  By them, the second one's taken 5 % lower (14 % for bf16
+// outputs, which gain least), these launches take 1.7 % more than on the faster kernel on average, at worst
+// 18 %, and 0.87 of what they took on the better one of the other two kernels (at worst 1.1: LLaMA-8B block, 100 tokens, 112 -> 123 us).
+double short_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, int* shape) {
+    double best = HUGE_VAL;
+    for (int i = 0; i < kShortShapes; ++i) {
+        const ShortShape& s = short_shape(i);
+        double most = 0, work = 0, chain = 0;
+        for (const Planned* it : items) {
+            const double n = double(tiles_of(*it, s.rows, s.cols)), steps = double(it->Kc / 64 * 2 + (it->Kc % 64 > 32 ? 2 : it->Kc % 64 > 0 ? 1 : 0));
+            most = std::max(most, n);
+            work += n * (steps * s.step_us + s.tile_us);
+            chain = std::max(chain, steps * s.chain_us);
+        }
+        if (most > kMaxGenericTiles) continue;
+        const double us = s.launch_us + Estimate::us(std::max(work / compute_units(), chain), outputs_us(items, out_bytes, accumulate, s.out_us), s.overlap);
+        if (us < best) { best = us; *shape = kGenericShapes + kNarrowShapes + i; }
+    }
+    return best;
+}
+double tile256_launch_us(const std::vector<const Planned*>& items, bool tail, int out_bytes, bool accumulate) {
+    constexpr float kOut[4] = {0.116f, 0.258f, 0.326f, 0.596f};
+    return (out_bytes == 2 ? 0.855 : 0.95) * (10 + Estimate::us(0.695 * tile256_us(items, tail, Layout::kTN, false), outputs_us(items, out_bytes, accumulate, kOut), 0.732));
+}
+
+constexpr int kFirstNarrow = kGenericShapes, kFirstShort = kFirstNarrow + kNarrowShapes;     // numbers of their launch shapes
+
 // Rows and columns of a launch shape's tile (-1: the 256 x 256-tile kernel).
 void tile_of(int shape, Dtype in_dtype, uint32_t* m, uint32_t* n) {
     if (shape < 0) *m = *n = gemm_mfma_tile();
+    else if (shape >= kFirstShort) { *m = short_shape(shape - kFirstShort).rows; *n = short_shape(shape - kFirstShort).cols; }
     else if (shape >= kGenericShapes) { *m = narrow_shape(shape - kGenericShapes).rows; *n = narrow_shape(shape - kGenericShapes).cols; }
     else { *m = generic_shape(in_dtype, shape).tile_m; *n = generic_shape(in_dtype, shape).tile_n; }
 }
 
 // tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
 // last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
-enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4 };      // 4 and on: its shapes
+enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4, kRouteShort = kRouteNarrow + kNarrowShapes };      // 4 and on: their shapes
 
-// problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
-enum { kWhole = 0, kTail = 1, kOther = 2 };
+// problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others; weight gradients of few tokens
+enum { kWhole = 0, kTail = 1, kOther = 2, kFew = 3 };
 
 // Which kernel takes which problems: on the 256 x 256-tile kernel what it takes, on the generic kernel the
 // rest - and what it takes when the generic one's smaller tiles are expected to be done first (few tiles, or
 // few long ones).
 struct Routes {
-    std::vector<const Planned*> cls[3];
-    int shape[3] = {-1, -1, -1};                // launch shape of the generic kernel; -1: 256 x 256 tiles
+    std::vector<const Planned*> cls[4];
+    int shape[4] = {-1, -1, -1, -1};            // launch shape; -1: 256 x 256 tiles
 };
-hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
+hipError_t find_general_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
     bool plain = true;                          // no row bits, no segments: the generic kernel could take them too
     for (const Planned& it : items) {
         bool ok = planned_mfma_ok(it, layout, in_dtype);
@@ -274,7 +317,7 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
             if (!planned_narrow_ok(*it, layout, in_dtype)) return us;
         double narrow_us;
         const int narrow = pick_narrow_shape(v, &narrow_us);
-        if (route >= kRouteNarrow) { *shape = kGenericShapes + route - kRouteNarrow; return 0.0; }
+        if (route >= kRouteNarrow && route < kRouteShort) { *shape = kGenericShapes + route - kRouteNarrow; return 0.0; }
         // (both kernels' estimates leave out what a launch adds, of which the generic kernel has 2 us more: over nine sets of
         // layers of widths 256 to 4096, 32 to 2048 tokens, the choice among all three kernels is 3 % off the best on average,
         // 16 % faster than without the one for few rows, and at worst 4 % slower, at 768 tokens of a LLaMA-1B block)
@@ -299,6 +342,45 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
     return hipSuccess;
 }
 
+constexpr int64_t kLargeLayer = 80;               // 256 x 256 tiles: 2048 x 2376 and more, not a LLaMA-8B block's 4096 x 1024
+
+// The same with the kernel for weight gradients of few tokens.  What it takes never goes to the generic kernel (in 168 launches timed on
+// both that one took 1.01 to 2.3 times as long); what may go to 256 x 256 tiles does by the estimates, which count that problems
+// on the same kernel share a launch.
+hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
+    const hipError_t found = find_general_routes(items, layout, in_dtype, out_dtype, accumulate, route, r);
+    const bool forced = route >= kRouteShort;
+    if (found != hipSuccess || layout != Layout::kTN || in_dtype != Dtype::BF16 || route == kRouteGeneric) return found;
+    const int out_bytes = out_dtype == Dtype::BF16 ? 2 : 4;
+    std::vector<const Planned*>& few = r.cls[kFew];
+    double few_us = 0;
+    for (const int c : {kOther, kTail, kWhole}) {
+        std::vector<const Planned*>& v = r.cls[c];
+        bool ok = !v.empty();
+        for (const Planned* it : v) ok = ok && planned_short_ok(*it, layout, in_dtype);
+        if (!ok) continue;
+        std::vector<const Planned*> both = few;
+        both.insert(both.end(), v.begin(), v.end());
+        int s = kFirstShort;
+        const double us = short_launch_us(both, out_bytes, accumulate, &s);
+        const bool on256 = c != kOther && r.shape[c] < 0;
+        if (us == HUGE_VAL) continue;
+        // Contractions with a masked last step stay on 256 x 256 tiles where every layer is a large one.  That is where that step is
+        // held to be tested by estimate; bf16 outputs lose nothing by it (LLaMA-8B block, 100, 200, 400 tokens 112, 152, 209 us, here 124, 159, 233; width 2816,
+        // 200 tokens 71, here 76), fp32 ones whose rows are no whole cache lines up to a quarter (width 2816, 200 tokens, added to: 207, here 150).
+        bool large = c == kTail && !forced;
+        for (const Planned* it : v) large = large && tiles_of(*it, gemm_mfma_tile(), gemm_mfma_tile()) >= kLargeLayer;
+        if (on256 && large) continue;
+        if (on256 && !forced && (route == kRouteAll256 || (route == kRouteWhole256 && c == kWhole) ||
+                                 us >= few_us + tile256_launch_us(v, c == kTail, out_bytes, accumulate))) continue;
+        few = both;
+        few_us = us;
+        r.shape[kFew] = forced ? kFirstShort + route - kRouteShort : s;
+        v.clear();
+    }
+    return hipSuccess;
+}
+
 // Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it.
 hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
                           Dtype in_dtype, Dtype out_dtype, bool accumulate) {
@@ -320,7 +402,7 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
         const int64_t after = std::min(it.rows_after, short_by), before = std::min(it.rows_before, short_by - after);
         gp.m_slack = uint32_t(before) | (uint32_t(after) << 16);
     };
-    for (int c = 0; c < 3; ++c) {
+    for (int c = 0; c < 4; ++c) {
         std::vector<const Planned*>& v = cls[c];
         // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
         std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
@@ -350,6 +432,8 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
             ProfScope prof(ctx, stream, kind);
             const hipError_t e = shape[c] < 0
                 ? launch_gemm_mfma_bf16(stream, batch, n, layout, out_dtype, accumulate, c == kTail)
+                : shape[c] >= kFirstShort
+                ? launch_gemm_short(stream, batch, n, shape[c] - kFirstShort, out_dtype, accumulate)
                 : shape[c] >= kGenericShapes
                 ? launch_gemm_narrow(stream, batch, n, shape[c] - kGenericShapes)
                 : launch_gemm_generic(stream, batch, n, shape[c], layout, in_dtype, out_dtype, accumulate);
@@ -1294,15 +1378,17 @@ extern "C" int tf_internal_check_tables(int32_t n_tables, const int64_t* desc, i
 // Test hook (not part of the public header): the kernels that this context's GEMM launches take, so that a
 // small problem can be sent through each of them.  A context starts with 0, the estimated times.
 extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
-    if (!ctx || route < kRouteEstimated || route >= kRouteNarrow + kNarrowShapes) return TF_ERR_INVALID_ARG;
+    if (!ctx || route < kRouteEstimated || route >= kRouteShort + kShortShapes) return TF_ERR_INVALID_ARG;
     ctx->gemm_route = route;
     return TF_OK;
 }
 
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
-// aligned) are launched together: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the generic kernel.
+// aligned) are launched together: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the generic kernel, behind them those of the
+// kernel for input gradients of few rows.  The kernel for weight gradients of few tokens is left out of
+// it; tf_internal_kernels_few() knows that one's too, last of all.
 // after: rows of the tensor behind the problem's own (it is a run of its rows), or NULL.
-extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
+static int kernels_of(bool few, int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
                                    int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
     const Layout layout = layout_tn ? Layout::kTN : Layout::kNT;
     std::vector<Planned> items;
@@ -1312,10 +1398,20 @@ extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, co
         items.back().rows_after = more;
     }
     Routes r;
-    if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
-    for (int c = 0; c < 3; ++c)
+    const auto find = few ? find_routes : find_general_routes;
+    if (find(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
+    for (int c = 0; c < 4; ++c)
         for (const Planned* it : r.cls[c]) kernel[it - items.data()] = r.shape[c];
     return TF_OK;
+}
+
+extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
+                                   int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
+    return kernels_of(false, n, M, N, Kc, after, layout_tn, in_dtype, out_dtype, accumulate, kernel);
+}
+extern "C" int tf_internal_kernels_few(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
+                                       int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
+    return kernels_of(true, n, M, N, Kc, after, layout_tn, in_dtype, out_dtype, accumulate, kernel);
 }
 
 // Test hook (not part of the public header): which launch shape of the generic kernel a launch of these

@@ -76,6 +76,18 @@ const NarrowShape& narrow_shape(int shape);
 bool narrow_shape_ok(int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb);
 hipError_t launch_gemm_narrow(hipStream_t stream, GemmBatch& batch, int n_problems, int shape);
 
+// bf16 weight gradients (layout kTN) of few tokens, in several launch shapes.  It takes contractions of 64 or more,
+// rows and columns that are multiples of 8, row pitches that are multiples of 8 and at most 2^22, 16-byte aligned tensors.
+struct ShortShape {
+    int rows, cols;                                     // of its tile
+    float step_us, tile_us, chain_us;                   // what a contraction step of 32 and a tile cost (see there)
+    float launch_us, overlap, out_us[4];
+};
+constexpr int kShortShapes = 3;
+const ShortShape& short_shape(int shape);
+bool short_shape_ok(int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb);
+hipError_t launch_gemm_short(hipStream_t stream, GemmBatch& batch, int n_problems, int shape, Dtype out_dtype, bool accumulate);
+
 // MFMA kernel for bf16 inputs.  What it takes (mfma_shape_ok): contraction a multiple of 64; output
 // columns N >= 256 and a multiple of 8; output rows M >= 256, or fewer with rows_before +
 // rows_after >= 256 - M operand rows in memory around them; layout kTN also M a multiple of 8; row

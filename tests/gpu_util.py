@@ -12,6 +12,7 @@ import paper_2602_05754_amd as tf
 # tf_internal_gemm_route: which kernel the GEMM launches of a context take
 BY_ESTIMATE, WHOLE_256, ALL_256, GENERIC = range(4)
 NARROW = {(64, 64): 4, (128, 64): 5, (128, 128): 6, (256, 128): 7}        # input gradients of few rows, by tile
+SHORT = {(128, 64): 8, (128, 128): 9, (256, 128): 10}                                   # weight gradients of few tokens, by tile
 
 
 def set_route(ctx, route: int) -> None:

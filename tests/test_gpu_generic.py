@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, NARROW, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, NARROW, SHORT, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -279,3 +279,58 @@ def test_few_rows_of_pitches_across_4_gib(ctx):
         tf.tf_stage_backward(ctx, [(K, N)], T, tf.TF_BF16, [W], [X], [dY], np.ones(1, np.uint8), [dX], [torch.empty_like(W)], tf.TF_BF16)
     ref = dY[:, cols].double() @ W[:, cols].double().t().contiguous()
     assert rel_fro(host64(dX), ref.cpu().numpy()) < 4e-3
+
+
+@pytest.mark.parametrize("dw,accumulate", [("bf16", False), ("f32", False), ("f32", True)])
+@pytest.mark.parametrize("tile", sorted(SHORT))
+@pytest.mark.parametrize("T", [64, 65, 96, 97, 128, 200, 257, 1000])
+def test_weight_gradients_of_few_tokens(ctx, T, tile, dw, accumulate):
+    """The kernel for few tokens where it can go wrong: rows and columns around its tiles, contractions of two steps (fewer
+    than it has stages), of three and more, 1, 8, 32 or 33 values more than whole ones.  The bits are the generic kernel's; an
+    infinity stays in its row and column; nothing outside the outputs is written."""
+    if accumulate and tile == (256, 128):
+        pytest.skip("the largest tile does not add")
+    shapes = [(8, 8), (64, 136), (128, 128), (136, 64), (120, 264), (264, 120), (1096, 72), (256, 512)]
+    W, X, dY = _random(shapes, T, "bf16", T)
+    X[5][T - 1, 263], dY[5][T - 1, :] = float("inf"), dY[5][T - 1, :].abs() + 1e-3
+    got = {}
+    for which in (SHORT[tile], GENERIC):
+        out = [Guarded(s, dw) for s in shapes]
+        for g, s in zip(out, shapes):
+            g.t.copy_(torch.arange(s[0] * s[1], device="cuda").reshape(s) % 97 * 1e-3)
+        dX = [torch.empty_like(x) for x in X]
+        with route(ctx, which):
+            kinds = kinds_of(ctx, lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_BF16, W, X, dY, None, dX, [g.t for g in out], CODE[dw], accumulate=accumulate))
+        assert "dw_generic" in kinds and "dw_mfma" not in kinds
+        if which != GENERIC:
+            assert kinds.count("dw_generic") == 1                        # one launch, whichever could go elsewhere
+        for l, g in enumerate(out):
+            g.check(f"dW[{l}] {shapes[l]} T={T} {tile}")
+        got[which] = [raw_bytes(g.t) for g in out]
+    assert got[SHORT[tile]] == got[GENERIC]
+    assert torch.isinf(out[5].t[263]).all() and torch.isfinite(out[5].t[:263]).all()
+    for l in (2, 6):
+        ref = X[l].double().t().contiguous() @ dY[l].double()
+        if accumulate:
+            ref += (torch.arange(ref.numel(), device="cuda").reshape(ref.shape) % 97 * 1e-3).double()
+        assert rel_fro(host64(out[l].t), ref.cpu().numpy()) < (4e-3 if dw == "bf16" else 4e-6)
+
+
+def test_weight_gradients_of_few_tokens_in_row_runs(ctx):
+    """Runs of unfrozen 64-row blocks: operands with the tensor's pitch, rows around the run's own; frozen rows stay."""
+    K, N, T = 576, 200, 100
+    W, X, dY = _random([(K, N)], T, "bf16", 5)
+    rows = [np.array([0, 1, 0, 0, 0, 1, 1, 0, 0], np.uint8)]
+    keep = torch.from_numpy(np.repeat(rows[0], 64)).bool()
+    got = []
+    for which in (*SHORT.values(), GENERIC):
+        out = Guarded((K, N), "bf16")
+        out.t.fill_(7.0)
+        with route(ctx, which):
+            tf.tf_stage_backward_blocks(ctx, [(K, N)], T, tf.TF_BF16, W, X, dY, None, rows, 64, [torch.empty_like(X[0])], [out.t], tf.TF_BF16)
+        out.check(f"dW {which}")
+        assert (out.t.cpu()[keep] == 7.0).all()
+        got.append(raw_bytes(out.t))
+    assert all(g == got[0] for g in got)
+    ref = (X[0].double().t().contiguous() @ dY[0].double()).cpu()
+    assert rel_fro(host64(out.t)[~keep.numpy()], ref[~keep].numpy()) < 4e-3

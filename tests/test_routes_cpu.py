@@ -9,11 +9,12 @@ import paper_2602_05754_amd as tf
 TILES_256 = -1
 
 
-def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False, after=None):
+def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False, after=None, few=False):
     n = len(M)
     arr = lambda v: (ctypes.c_int64 * n)(*v)
     kernel = (ctypes.c_int32 * n)(*([99] * n))
-    assert tf.load_library().tf_internal_kernels(n, arr(M), arr(N), arr(Kc), after and arr(after), int(tn), io, out, int(accumulate), kernel) == 0
+    fn = tf.load_library().tf_internal_kernels_few if few else tf.load_library().tf_internal_kernels
+    assert fn(n, arr(M), arr(N), arr(Kc), after and arr(after), int(tn), io, out, int(accumulate), kernel) == 0
     return list(kernel)
 
 
@@ -99,6 +100,33 @@ def test_few_rows_that_their_kernel_cannot_take():
     for M, N, Kc, tn, io in ([32, 256, 56, 0, 1], [32, 256, 100, 0, 1], [32, 256, 128, 0, 0], [32, 256, 128, 1, 1]):
         assert kernels([M], [N], [Kc], tn, io=io, out=io)[0] < 3
     assert kernels([32, 32], [256, 256], [128, 100], False) == kernels([32, 32], [256, 256], [100, 100], False)
+
+
+# us on the kernel for few tokens and on the better one of the others
+@pytest.mark.parametrize("shapes,T,dw,few", [
+    (block(2048, 512, 8192, 2), 64, "set", True),        # 85, 110
+    (block(2048, 512, 8192, 2), 200, "add", True),       # 176, 214
+    (block(2048, 512, 8192, 2), 512, "bf16", False),     # 142, 135
+    (block(2048, 512, 8192, 2), 1024, "add", False),     # 334, 307
+    (block(4096, 1024, 14336), 512, "bf16", False),      # 243, 213
+    (block(2816, 1408, 8200), 512, "add", True),         # 181, 227
+    (block(1024, 256, 2816, 2), 200, "bf16", True),      # 21, 29
+    (block(256, 256, 688, 2), 1000, "bf16", True),       # 12.6, 15.9
+])
+def test_few_tokens_take_their_own_kernel(shapes, T, dw, few):
+    K, N = zip(*shapes)
+    got = set(kernels(K, N, [T] * len(K), True, out=tf.TF_BF16 if dw == "bf16" else tf.TF_F32, accumulate=dw == "add", few=True))
+    assert (got <= {7, 8, 9}) if few else (got == {TILES_256}), got
+
+
+def test_few_tokens_that_their_kernel_cannot_take():
+    """Fewer than 64, extents that are no multiple of 8, fp32 and input gradients go where they went; what it can take in the
+    same launch goes to it."""
+    for M, N, Kc, tn, io in ([256, 256, 63, 1, 1], [36, 256, 128, 1, 1], [256, 36, 128, 1, 1], [256, 256, 128, 1, 0], [64, 256, 128, 0, 1]):
+        assert kernels([M], [N], [Kc], tn, io=io, out=io, few=True) == kernels([M], [N], [Kc], tn, io=io, out=io)
+    assert kernels([256, 128], [256, 64], [128, 128], True, few=True)[0] >= 7
+    mixed = kernels([256, 36], [256, 256], [128, 128], True, few=True)
+    assert mixed[0] >= 7 and 0 <= mixed[1] < 3
 
 
 TILES = {tf.TF_F32: [(32, 32), (32, 64), (64, 64)], tf.TF_BF16: [(64, 64), (128, 64), (128, 128)]}
