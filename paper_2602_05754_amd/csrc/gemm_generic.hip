@@ -202,21 +202,13 @@ __device__ __forceinline__ int logical_tile(int b, int nb) {
 // turn).  The next reader of the outputs pays for it with 1 to 2 us a call (LLaMA-1B block, 200 tokens, dX read
 // once 80.1 (78.6)); from 200 tokens on the rest makes no difference.
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN>
-__global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
+__device__ __forceinline__ void contract_tile(const GemmProblem& P, int lt, char* const lds) {
     typedef Operand<TIn, kContig, kTileM> OpA;
     typedef Operand<TIn, kContig, kTileN> OpB;
     constexpr int kStage = OpA::kStageBytes + OpB::kStageBytes;
     static_assert(kTileM * kTileN * 4 <= 2 * kStage, "the sums are turned around in the stages");
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kStage];
-
-    // this block's problem: lane i looks at the first tile of problem i
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    static_assert(kMaxProblemsPerLaunch == 64, "one lane per problem");
-    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
-    const bool started = lane < batch.n_problems && batch.p[lane].tile_start <= lt;
-    const int pi = __builtin_amdgcn_readfirstlane(__popcll(__ballot(started)) - 1);
-    const GemmProblem& P = batch.p[pi];
     const int M = P.M, N = P.N, Kc = P.Kc;
     const int tiles_m = (M + kTileM - 1) / kTileM, tiles_n = (N + kTileN - 1) / kTileN;
     int t = lt - P.tile_start;
@@ -408,6 +400,34 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     }
 }
 
+// This block's problem: lane i looks at the first tile of problem i.
+__device__ __forceinline__ int find_problem(const GemmBatch& batch, int lt) {
+    static_assert(kMaxProblemsPerLaunch == 64, "one lane per problem");
+    const int lane = threadIdx.x & 63;
+    const bool started = lane < batch.n_problems && batch.p[lane].tile_start <= lt;
+    return __builtin_amdgcn_readfirstlane(__popcll(__ballot(started)) - 1);
+}
+
+template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate, int kTileM, int kTileN>
+__global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch batch) {
+    __shared__ __attribute__((aligned(1024))) char lds[2 * (kTileM + kTileN) * kStepBytes];
+    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
+    contract_tile<TIn, kContig, kOutBf16, kAccumulate, kTileM, kTileN>(batch.p[find_problem(batch, lt)], lt, lds);
+}
+
+// Both halves of an fp32 backward in one launch: neither waits for the other, and a launch of few tiles, or the end of a longer
+// one, leaves most units idle.  Whole calls, us, against two launches: one block of widths 1024 / 512 / 3000, 150 tokens 90 -> 72, 2000 tokens
+// 693 -> 684; 512 / 256 / 1700, 700 tokens 90 -> 80; two blocks of 1024 / 256 / 2731, 1000 tokens 607 -> 594; calls that wait for the
+// host (128 / 32 / 400) 27 -> 23.
+template <bool kAccumulate, int kTileM, int kTileN>
+__global__ __launch_bounds__(kThreads, 2) void gemm_generic_both_kernel(GemmBatch batch) {
+    __shared__ __attribute__((aligned(1024))) char lds[2 * (kTileM + kTileN) * kStepBytes];
+    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
+    const int pi = find_problem(batch, lt);
+    if (batch.tn >> pi & 1) contract_tile<float, false, false, kAccumulate, kTileM, kTileN>(batch.p[pi], lt, lds);
+    else contract_tile<float, true, false, false, kTileM, kTileN>(batch.p[pi], lt, lds);
+}
+
 // The launch shapes.  step_us, chain_us: a step's share of a compute unit when all are full, and its
 // time in a workgroup that has the unit to itself; tile_steps: what a tile costs beside its steps.
 // Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps wait
@@ -454,6 +474,20 @@ hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_probl
     } else {
         accumulate ? launch<uint16_t, false, false, true>(stream, batch, shape) : launch<uint16_t, false, false, false>(stream, batch, shape);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape, bool accumulate) {
+    batch.n_problems = n_problems;
+    if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
+    const dim3 grid(batch.total_tiles), block(kThreads);
+    auto go = [&](auto add) {
+        constexpr bool kAdd = decltype(add)::value;
+        if (shape == 0) hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[0].tile_m, kShapes32[0].tile_n>), grid, block, 0, stream, batch);
+        else if (shape == 1) hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[1].tile_m, kShapes32[1].tile_n>), grid, block, 0, stream, batch);
+        else hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[2].tile_m, kShapes32[2].tile_n>), grid, block, 0, stream, batch);
+    };
+    accumulate ? go(std::true_type{}) : go(std::false_type{});
     return hipGetLastError();
 }
 

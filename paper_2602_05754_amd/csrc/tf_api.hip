@@ -381,6 +381,52 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
     return hipSuccess;
 }
 
+void fill(GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
+    gp.A = it.A; gp.B = it.B; gp.C = it.C;
+    gp.M = int32_t(it.M); gp.N = int32_t(it.N); gp.Kc = int32_t(it.Kc);
+    gp.lda = int32_t(it.lda); gp.ldb = int32_t(it.ldb); gp.row_bits = it.row_bits;
+    gp.tile_start = int32_t(tile_start);
+    gp.n_seg = n_seg;
+    // a problem narrower than one tile window: prefer running over its end to starting before its beginning
+    const int64_t short_by = it.M < gemm_mfma_tile() ? gemm_mfma_tile() - it.M : 0;
+    const int64_t after = std::min(it.rows_after, short_by), before = std::min(it.rows_before, short_by - after);
+    gp.m_slack = uint32_t(before) | (uint32_t(after) << 16);
+}
+
+// fp32: the input gradients `x` and the weight gradients `w` in one launch, where each by itself would be one launch of
+// the generic kernel, of the same shape - so that every sum is what it would have been.  *done says whether they were.
+// A call whose kernels are timed launches them one by one.
+hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planned>& x, const std::vector<Planned>& w, bool accumulate, bool* done) {
+    *done = false;
+    if (ctx->profiling || x.empty() || w.empty() || x.size() + w.size() > size_t(kMaxProblemsPerLaunch)) return hipSuccess;
+    Routes rx, rw;
+    if (find_routes(x, Layout::kNT, Dtype::F32, Dtype::F32, false, ctx->gemm_route, rx) != hipSuccess ||
+        find_routes(w, Layout::kTN, Dtype::F32, Dtype::F32, accumulate, ctx->gemm_route, rw) != hipSuccess) return hipSuccess;
+    const int shape = rx.shape[kOther];
+    if (rx.cls[kOther].size() != x.size() || rw.cls[kOther].size() != w.size() || rw.shape[kOther] != shape || shape < 0) return hipSuccess;
+    uint32_t tile_m, tile_n;
+    tile_of(shape, Dtype::F32, &tile_m, &tile_n);
+    // longest contraction first
+    struct Item { const Planned* it; bool tn; };
+    std::vector<Item> items;
+    items.reserve(x.size() + w.size());
+    for (const Planned& it : x) items.push_back(Item{&it, false});
+    for (const Planned& it : w) items.push_back(Item{&it, true});
+    std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.it->Kc > b.it->Kc; });
+    GemmBatch batch;
+    batch.tn = 0;
+    int64_t tiles = 0;
+    for (size_t i = 0; i < items.size(); ++i) {
+        fill(batch.p[i], *items[i].it, std::min(tiles, kMaxGenericTiles), 1);
+        if (items[i].tn) batch.tn |= uint64_t(1) << i;
+        tiles += tiles_of(*items[i].it, tile_m, tile_n);
+    }
+    if (tiles > kMaxGenericTiles) return hipSuccess;
+    batch.total_tiles = int32_t(tiles);
+    *done = true;
+    return launch_gemm_generic_both(stream, batch, int(items.size()), shape, accumulate);
+}
+
 // Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it.
 hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
                           Dtype in_dtype, Dtype out_dtype, bool accumulate) {
@@ -391,17 +437,6 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
     const int* const shape = routes.shape;
 
     GemmBatch batch;
-    auto fill = [](GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
-        gp.A = it.A; gp.B = it.B; gp.C = it.C;
-        gp.M = int32_t(it.M); gp.N = int32_t(it.N); gp.Kc = int32_t(it.Kc);
-        gp.lda = int32_t(it.lda); gp.ldb = int32_t(it.ldb); gp.row_bits = it.row_bits;
-        gp.tile_start = int32_t(tile_start);
-        gp.n_seg = n_seg;
-        // a problem narrower than one tile window: prefer running over its end to starting before its beginning
-        const int64_t short_by = it.M < gemm_mfma_tile() ? gemm_mfma_tile() - it.M : 0;
-        const int64_t after = std::min(it.rows_after, short_by), before = std::min(it.rows_before, short_by - after);
-        gp.m_slack = uint32_t(before) | (uint32_t(after) << 16);
-    };
     for (int c = 0; c < 4; ++c) {
         std::vector<const Planned*>& v = cls[c];
         // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
@@ -605,31 +640,10 @@ int stage_backward_impl(tf_ctx* ctx, void* hip_stream,
             if (!ok) grouped_slow = true;
         }
     }
-    hipError_t e = hipSuccess;
-    if (!grouped_slow) {
-        e = launch_planned(ctx, stream, plan, Layout::kNT, in_dt, in_dt, false);
-    } else {
-        // A group that the matrix-core kernel cannot take: member after member, each launch adding
-        // onto the one before.  That needs an fp32 output (the fp32 configuration).
-        if (in_dt != Dtype::F32) return TF_ERR_SHAPE;
-        size_t depth = 0;
-        for (const Planned& it : plan) depth = std::max(depth, it.more.size());
-        for (size_t k = 0; k <= depth && e == hipSuccess; ++k) {
-            std::vector<Planned> round;
-            for (const Planned& it : plan) {
-                if (k == 0) { Planned h = it; h.more.clear(); round.push_back(h); }
-                else if (k <= it.more.size()) round.push_back(it.more[k - 1]);
-            }
-            e = launch_planned(ctx, stream, round, Layout::kNT, in_dt, in_dt, k > 0);
-        }
-    }
-    if (e != hipSuccess) return hip_fail(ctx, e);
-
     // weight gradients: what is frozen - a layer, or a block of rows of one - is simply not
     // in the plan.
     // Layers whose gradient is added to what dW_l holds and layers whose gradient overwrites it
     // are two plans (two kernels: the adding one fetches the old values).
-    plan.clear();
     std::vector<Planned> plan_set, plan_add;
     for (int32_t l = 0; l < n_layers; ++l) {
         if (freeze_mask && freeze_mask[l]) continue;
@@ -671,6 +685,34 @@ int stage_backward_impl(tf_ctx* ctx, void* hip_stream,
             b = e1;
         }
     }
+    hipError_t e = hipSuccess;
+    bool both = false;
+    const bool add_first = plan_set.empty();          // (what overwrites, if there is any, goes with the input gradients)
+    if (in_dt == Dtype::F32 && !input_group) {
+        e = launch_both(ctx, stream, plan, add_first ? plan_add : plan_set, add_first, &both);
+        if (e != hipSuccess) return hip_fail(ctx, e);
+        if (both) (add_first ? plan_add : plan_set).clear();
+    }
+    if (both) {
+    } else if (!grouped_slow) {
+        e = launch_planned(ctx, stream, plan, Layout::kNT, in_dt, in_dt, false);
+    } else {
+        // A group that the matrix-core kernel cannot take: member after member, each launch adding
+        // onto the one before.  That needs an fp32 output (the fp32 configuration).
+        if (in_dt != Dtype::F32) return TF_ERR_SHAPE;
+        size_t depth = 0;
+        for (const Planned& it : plan) depth = std::max(depth, it.more.size());
+        for (size_t k = 0; k <= depth && e == hipSuccess; ++k) {
+            std::vector<Planned> round;
+            for (const Planned& it : plan) {
+                if (k == 0) { Planned h = it; h.more.clear(); round.push_back(h); }
+                else if (k <= it.more.size()) round.push_back(it.more[k - 1]);
+            }
+            e = launch_planned(ctx, stream, round, Layout::kNT, in_dt, in_dt, k > 0);
+        }
+    }
+    if (e != hipSuccess) return hip_fail(ctx, e);
+
     e = launch_planned(ctx, stream, plan_set, Layout::kTN, in_dt, to_dtype(dw_dtype), false);
     if (e != hipSuccess) return hip_fail(ctx, e);
     e = launch_planned(ctx, stream, plan_add, Layout::kTN, in_dt, to_dtype(dw_dtype), true);

@@ -46,10 +46,11 @@ struct GemmProblem {
 
 constexpr int kMaxProblemsPerLaunch = 64;
 
-struct GemmBatch {          // passed by value as the kernel argument (64 x 64 B + 8 B = 4104 B)
+struct GemmBatch {          // passed by value as the kernel argument (64 x 64 B + 16 B = 4112 B)
     GemmProblem p[kMaxProblemsPerLaunch];
     int32_t n_problems;
     int32_t total_tiles;
+    uint64_t tn;            // launch_gemm_generic_both only: bit i = problem i is of layout kTN
 };
 
 // Matrix-core kernel for any M, N, Kc >= 1, pitch and alignment.  in: fp32 or bf16, accumulate
@@ -63,6 +64,8 @@ constexpr int kGenericShapes = 3;
 const GenericShape& generic_shape(Dtype in_dtype, int shape);
 hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems, int shape,
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
+// fp32 problems of both layouts in one launch; those of layout kNT are never added to what is there.
+hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape, bool accumulate);
 int compute_units();              // of the current device
 
 // bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of

@@ -334,3 +334,44 @@ def test_weight_gradients_of_few_tokens_in_row_runs(ctx):
     assert all(g == got[0] for g in got)
     ref = (X[0].double().t().contiguous() @ dY[0].double()).cpu()
     assert rel_fro(host64(out.t)[~keep.numpy()], ref[~keep].numpy()) < 4e-3
+
+
+@pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
+@pytest.mark.parametrize("T,shapes", [
+    (1, [(1, 1), (33, 70)]),
+    (256, [(256, 256), (256, 688), (688, 256)]),                   # both halves in 64 bits
+    (391, [(1290, 643), (643, 1283), (31, 5)]),
+    (815, [(2047, 1001), (1046, 1005), (1047, 1001)] * 2),
+    (40, [(96, 40 + l) for l in range(40)]),                       # more problems than one launch holds
+])
+def test_both_halves_in_one_launch_give_the_same_bits(ctx, T, shapes, form):
+    """An fp32 call launches its two halves together where that changes no sum; a call that is profiled launches them one
+    by one."""
+    W, X, dY = _random(shapes, T, "f32", T)
+    old = [torch.randn(s, device="cuda") for s in shapes]
+    L = len(shapes)
+    mask = np.array([(form == "frozen" and l != 1) for l in range(L)], np.uint8)
+    got = []
+    for profiled in (False, True):
+        gX, gW = [Guarded((T, k), "f32") for k, n in shapes], [Guarded(s, "f32", o) for s, o in zip(shapes, old)]
+        out = [g.t for g in gX], [g.t for g in gW]
+        if form == "microbatch":
+            add = np.array([l % 2 for l in range(L)], np.uint8)
+            call = lambda: tf.tf_stage_backward_microbatch(ctx, shapes, T, tf.TF_F32, W, X, dY, None, *out, tf.TF_F32, add)
+        else:
+            call = lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_F32, W, X, dY, mask, *out, tf.TF_F32, accumulate=form == "add")
+        if profiled:
+            kinds = kinds_of(ctx, call)
+            assert "dx_generic" in kinds and "dw_generic" in kinds
+        else:
+            call()
+            torch.cuda.synchronize()
+        for l in range(L):
+            gX[l].check(f"dX[{l}]")
+            gW[l].check(f"dW[{l}]")
+            if mask[l]:
+                assert torch.equal(gW[l].t, old[l])
+        got.append([raw_bytes(g.t) for g in gX + gW])
+    assert got[0] == got[1]
+    ref = dY[1].double() @ W[1].double().t().contiguous()
+    assert rel_fro(host64(gX[1].t), ref.cpu().numpy()) < 4e-6
