@@ -23,11 +23,11 @@ typedef __attribute__((address_space(3))) bf16x4* LdsBf16x4Ptr;
 
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>), in this order
 template <class F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+__host__ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>{}), ...);
 }
 template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
+__host__ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 

@@ -415,19 +415,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_kernel(GemmBatch bat
     contract_tile<TIn, kContig, kOutBf16, kAccumulate, kTileM, kTileN>(batch.p[find_problem(batch, lt)], lt, lds);
 }
 
-// Both halves of an fp32 backward in one launch: neither waits for the other, and a launch of few tiles, or the end of a longer
-// one, leaves most units idle.  Whole calls, us, against two launches: one block of widths 1024 / 512 / 3000, 150 tokens 90 -> 72, 2000 tokens
-// 693 -> 684; 512 / 256 / 1700, 700 tokens 90 -> 80; two blocks of 1024 / 256 / 2731, 1000 tokens 607 -> 594; calls that wait for the
-// host (128 / 32 / 400) 27 -> 23.
-template <bool kAccumulate, int kTileM, int kTileN>
-__global__ __launch_bounds__(kThreads, 2) void gemm_generic_both_kernel(GemmBatch batch) {
-    __shared__ __attribute__((aligned(1024))) char lds[2 * (kTileM + kTileN) * kStepBytes];
-    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
-    const int pi = find_problem(batch, lt);
-    if (batch.tn >> pi & 1) contract_tile<float, false, false, kAccumulate, kTileM, kTileN>(batch.p[pi], lt, lds);
-    else contract_tile<float, true, false, false, kTileM, kTileN>(batch.p[pi], lt, lds);
-}
-
 // The launch shapes.  step_us, chain_us: a step's share of a compute unit when all are full, and its
 // time in a workgroup that has the unit to itself; tile_steps: what a tile costs beside its steps.
 // Measured (LLaMA-1B, LLaMA-8B and small widths, 32 to 3001 tokens, both layouts): the bf16 steps wait
@@ -439,6 +426,20 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_generic_both_kernel(GemmBatc
 constexpr GenericShape kShapes16[] = {{64, 64, 0.222f, 0.40f, 2.7f}, {128, 64, 0.348f, 0.45f, 3.1f}, {128, 128, 0.575f, 0.60f, 3.5f}};
 constexpr GenericShape kShapes32[] = {{32, 32, 0.28f, 0.43f, 1.0f}, {32, 64, 0.275f, 0.42f, 1.2f}, {64, 64, 0.53f, 0.62f, 1.5f}};
 static_assert(sizeof(kShapes16) == kGenericShapes * sizeof(GenericShape) && sizeof(kShapes32) == sizeof(kShapes16), "as many for both types");
+
+// Both halves of an fp32 backward in one launch: neither waits for the other, and a launch of few tiles, or the end of a longer
+// one, leaves most units idle.  Each half has its own tiles.  Whole calls, us, against two launches: one block of widths 1024 / 512 / 3000, 20 tokens
+// 68 -> 49, 150 tokens 90 -> 70, 2000 tokens 693 -> 682; 512 / 256 / 1700, 150 tokens 49 -> 34, 700 tokens 90 -> 79; two blocks of 1024 /
+// 256 / 2731, 1000 tokens 604 -> 591; calls that wait for the host (128 / 32 / 400) 27 -> 23.
+template <bool kAccumulate, int kShapeX, int kShapeW>
+__global__ __launch_bounds__(kThreads, 2) void gemm_generic_both_kernel(GemmBatch batch) {
+    constexpr int kXm = kShapes32[kShapeX].tile_m, kXn = kShapes32[kShapeX].tile_n, kWm = kShapes32[kShapeW].tile_m, kWn = kShapes32[kShapeW].tile_n;
+    __shared__ __attribute__((aligned(1024))) char lds[2 * (kXm + kXn > kWm + kWn ? kXm + kXn : kWm + kWn) * kStepBytes];
+    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
+    const int pi = find_problem(batch, lt);
+    if (batch.tn >> pi & 1) contract_tile<float, false, false, kAccumulate, kWm, kWn>(batch.p[pi], lt, lds);
+    else contract_tile<float, true, false, false, kXm, kXn>(batch.p[pi], lt, lds);
+}
 
 template <typename TIn, bool kContig, bool kOutBf16, bool kAccumulate>
 void launch(hipStream_t stream, const GemmBatch& batch, int shape) {
@@ -477,17 +478,15 @@ hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_probl
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape, bool accumulate) {
+hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape_x, int shape_w, bool accumulate) {
     batch.n_problems = n_problems;
     if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
     const dim3 grid(batch.total_tiles), block(kThreads);
-    auto go = [&](auto add) {
-        constexpr bool kAdd = decltype(add)::value;
-        if (shape == 0) hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[0].tile_m, kShapes32[0].tile_n>), grid, block, 0, stream, batch);
-        else if (shape == 1) hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[1].tile_m, kShapes32[1].tile_n>), grid, block, 0, stream, batch);
-        else hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kShapes32[2].tile_m, kShapes32[2].tile_n>), grid, block, 0, stream, batch);
-    };
-    accumulate ? go(std::true_type{}) : go(std::false_type{});
+    static_for<2 * kGenericShapes * kGenericShapes>([&](auto i) {
+        constexpr bool kAdd = i % 2;
+        constexpr int kX = i / 2 / kGenericShapes, kW = i / 2 % kGenericShapes;
+        if (kAdd == accumulate && kX == shape_x && kW == shape_w) hipLaunchKernelGGL((gemm_generic_both_kernel<kAdd, kX, kW>), grid, block, 0, stream, batch);
+    });
     return hipGetLastError();
 }
 

@@ -394,7 +394,7 @@ void fill(GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
 }
 
 // fp32: the input gradients `x` and the weight gradients `w` in one launch, where each by itself would be one launch of
-// the generic kernel, of the same shape - so that every sum is what it would have been.  *done says whether they were.
+// the generic kernel, each in the tiles it would have had - so that every sum is what it would have been.  *done says whether they were.
 // A call whose kernels are timed launches them one by one.
 hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planned>& x, const std::vector<Planned>& w, bool accumulate, bool* done) {
     *done = false;
@@ -402,10 +402,8 @@ hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planne
     Routes rx, rw;
     if (find_routes(x, Layout::kNT, Dtype::F32, Dtype::F32, false, ctx->gemm_route, rx) != hipSuccess ||
         find_routes(w, Layout::kTN, Dtype::F32, Dtype::F32, accumulate, ctx->gemm_route, rw) != hipSuccess) return hipSuccess;
-    const int shape = rx.shape[kOther];
-    if (rx.cls[kOther].size() != x.size() || rw.cls[kOther].size() != w.size() || rw.shape[kOther] != shape || shape < 0) return hipSuccess;
-    uint32_t tile_m, tile_n;
-    tile_of(shape, Dtype::F32, &tile_m, &tile_n);
+    const int shape[2] = {rx.shape[kOther], rw.shape[kOther]};
+    if (rx.cls[kOther].size() != x.size() || rw.cls[kOther].size() != w.size()) return hipSuccess;
     // longest contraction first
     struct Item { const Planned* it; bool tn; };
     std::vector<Item> items;
@@ -419,12 +417,14 @@ hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planne
     for (size_t i = 0; i < items.size(); ++i) {
         fill(batch.p[i], *items[i].it, std::min(tiles, kMaxGenericTiles), 1);
         if (items[i].tn) batch.tn |= uint64_t(1) << i;
+        uint32_t tile_m, tile_n;
+        tile_of(shape[items[i].tn], Dtype::F32, &tile_m, &tile_n);
         tiles += tiles_of(*items[i].it, tile_m, tile_n);
     }
     if (tiles > kMaxGenericTiles) return hipSuccess;
     batch.total_tiles = int32_t(tiles);
     *done = true;
-    return launch_gemm_generic_both(stream, batch, int(items.size()), shape, accumulate);
+    return launch_gemm_generic_both(stream, batch, int(items.size()), shape[0], shape[1], accumulate);
 }
 
 // Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it.

@@ -65,7 +65,7 @@ const GenericShape& generic_shape(Dtype in_dtype, int shape);
 hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_problems, int shape,
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
 // fp32 problems of both layouts in one launch; those of layout kNT are never added to what is there.
-hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape, bool accumulate);
+hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape_nt, int shape_tn, bool accumulate);
 int compute_units();              // of the current device
 
 // bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of
