@@ -3,6 +3,7 @@ pointers, Python lists -> host arrays.  Names and argument order follow
 include/tf.h.  torch is used for device memory and streams, nothing else."""
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional, Sequence
@@ -169,7 +170,7 @@ class PtrTable:
 
     def __init__(self, seq):
         self._items = list(seq)
-        n = len(self._items)
+        n = self.n = len(self._items)
         self.arr = (ctypes.c_void_p * max(n, 1))()
         self._info = np.empty((4, n), dtype=np.int64)                        # rows of tf_internal_check_tables
         self.nbytes, self.dtype_code, self.device = self._info[:3]
@@ -200,6 +201,8 @@ def _ptr_array(seq, n):
     """Host array of n device pointers (NULL for None); None stays None."""
     if seq is None:
         return None, None
+    if type(seq) is PtrTable and seq.n == n:
+        return seq.arr, seq.ptr
     if len(seq) != n:
         raise ValueError(f"expected {n} entries, got {len(seq)}")
     if isinstance(seq, PtrTable):
@@ -210,13 +213,18 @@ def _ptr_array(seq, n):
     return arr, ctypes.cast(arr, ctypes.c_void_p)
 
 
+def _address(a) -> int:
+    """Address of a numpy array's first element (what a.ctypes.data gives, at a quarter of the time)."""
+    return a.__array_interface__["data"][0]
+
+
 def _host(arr, dtype, n):
     if arr is None:
         return None, None
     a = np.ascontiguousarray(np.asarray(arr, dtype=dtype))
     if a.size != n:
         raise ValueError(f"expected {n} entries, got {a.size}")
-    return a, ctypes.c_void_p(a.ctypes.data)
+    return a, _address(a)
 
 
 def _stream_handle(stream) -> Optional[int]:
@@ -279,25 +287,25 @@ def _check_seq(seq, numels, dtype_code, what, skip=None, ctx=None):
 
 def _check_all(ctx, n, skip, tables):
     """_check_seq over several lists: (list, a, b, stride, scale, element type, what, whether `skip` is looked
-    at), the elements needed being a[i] * b[i] * scale (b may be None; a and b views with that stride).
+    at, addresses of a and b), the elements needed being a[i] * b[i] * scale (b may be None, address 0; a and b views
+    with that stride).
     Lists that were marshalled once are checked by one native call; what does not pass there, and
     all other lists, go through _check_seq, which says what is wrong."""
-    desc, rest = [], []
+    desc, rest = array.array("q"), []
     for t in tables:
-        seq, a, b, stride, scale, code = t[:6]
+        seq, a, b, stride, scale, code, what, skipping, a_address, b_address = t
         if seq is None:
             continue
-        if isinstance(seq, PtrTable) and len(seq) == n and n > 0:
-            desc += [seq.info_address, a.ctypes.data, b.ctypes.data if b is not None else 0, stride, scale, int(code), t[7], 0]
+        if type(seq) is PtrTable and seq.n == n and n > 0:
+            desc.extend((seq.info_address, a_address, b_address, stride, scale, int(code), skipping, 0))
         else:
             rest.append(t)
     if desc:
-        arr = (ctypes.c_int64 * len(desc))(*desc)
-        bad = load_library().tf_internal_check_tables(len(desc) // 8, arr, n, None if skip is None else skip.ctypes.data,
+        bad = load_library().tf_internal_check_tables(len(desc) // 8, desc.buffer_info()[0], n, None if skip is None else _address(skip),
                                                       -1 if ctx is None else int(ctx.device_id))
         if bad >= 0:
             rest = tables
-    for seq, a, b, stride, scale, code, what, skipping in rest:
+    for seq, a, b, stride, scale, code, what, skipping, _, _ in rest:
         _check_seq(seq, a * scale if b is None else a * b * scale, code, what, skip if skipping else None, ctx=ctx)
 
 
@@ -375,9 +383,11 @@ def _ctx_handle(ctx):
 def _check_backward(ctx, sh, T, io_dtype, dw_dtype, fm, W, X, dY, dX, dW):
     K, N = sh[:, 0], sh[:, 1]
     T = int(T)
-    _check_all(ctx, len(sh), fm, [(W, K, N, 2, 1, io_dtype, "W", 0), (dY, N, None, 2, T, io_dtype, "dY", 0),
-                                  (dX, K, None, 2, T, io_dtype, "dX", 0), (X, K, None, 2, T, io_dtype, "X", 1),
-                                  (dW, K, N, 2, 1, dw_dtype, "dW", 1)])
+    k = _address(sh)
+    n = k + 8
+    _check_all(ctx, len(sh), fm, [(W, K, N, 2, 1, io_dtype, "W", 0, k, n), (dY, N, None, 2, T, io_dtype, "dY", 0, n, 0),
+                                  (dX, K, None, 2, T, io_dtype, "dX", 0, k, 0), (X, K, None, 2, T, io_dtype, "X", 1, k, 0),
+                                  (dW, K, N, 2, 1, dw_dtype, "dW", 1, k, n)])
 
 
 # ----------------------------------------------------------------------------
@@ -399,7 +409,7 @@ def tf_stage_backward(ctx, shapes: Sequence[tuple], T: int, io_dtype: int,
     kdX, pdX = _ptr_array(dX, L)
     kdW, pdW = _ptr_array(dW, L)
     rc = lib.tf_stage_backward(_ctx_handle(ctx), _stream_handle(stream) if ctx is not None else None,
-                               L, sh.ctypes.data, int(T), int(io_dtype),
+                               L, _address(sh), int(T), int(io_dtype),
                                pW, pX, pdY, fm_p, pdX, pdW, int(dw_dtype), 1 if accumulate else 0)
     _raise(ctx, rc, "tf_stage_backward")
 
@@ -421,7 +431,7 @@ def tf_stage_backward_microbatch(ctx, shapes: Sequence[tuple], T: int, io_dtype:
     kdX, pdX = _ptr_array(dX, L)
     kdW, pdW = _ptr_array(dW, L)
     rc = lib.tf_stage_backward_microbatch(_ctx_handle(ctx), _stream_handle(stream) if ctx is not None else None,
-                                          L, sh.ctypes.data, int(T), int(io_dtype),
+                                          L, _address(sh), int(T), int(io_dtype),
                                           pW, pX, pdY, fm_p, pdX, pdW, int(dw_dtype), am_p)
     _raise(ctx, rc, "tf_stage_backward_microbatch")
 
@@ -438,7 +448,7 @@ def tf_masked_adamw(ctx, numel: Sequence[int], p_master, m, v, grad, grad_dtype:
     ne, ne_p = _host(numel, np.int64, n)
     st, st_p = _host(step, np.int32, n)
     fm, fm_p = _host(tensor_freeze_mask, np.uint8, n)
-    _check_all(ctx, n, fm, [(seq, ne, None, 1, 1, dt, name, 1)
+    _check_all(ctx, n, fm, [(seq, ne, None, 1, 1, dt, name, 1, ne_p, 0)
                             for name, seq, dt in (("p", p_master, TF_F32), ("m", m, TF_F32), ("v", v, TF_F32),
                                                   ("grad", grad, grad_dtype), ("p_lowp", p_lowp, TF_BF16),
                                                   ("ema", ema, TF_F32), ("ema_abs", ema_abs, TF_F32))])
@@ -630,7 +640,7 @@ def tf_stage_backward_blocks(ctx, shapes: Sequence[tuple], T: int, io_dtype: int
     keep = [_ptr_array(s, L) for s in (W, X, dY, dX, dW)]
     rm_keep, rm_p = _host_mask_table(row_block_mask, [tuple(map(int, r)) for r in sh], int(block_rows))
     rc = lib.tf_stage_backward_blocks(_ctx_handle(ctx), _stream_handle(stream) if ctx is not None else None,
-                                      L, sh.ctypes.data, int(T), int(io_dtype),
+                                      L, _address(sh), int(T), int(io_dtype),
                                       keep[0][1], keep[1][1], keep[2][1], fm_p, rm_p, int(block_rows),
                                       keep[3][1], keep[4][1], int(dw_dtype), 1 if accumulate else 0)
     _raise(ctx, rc, "tf_stage_backward_blocks")
@@ -658,7 +668,7 @@ def tf_stage_backward_shared(ctx, shapes: Sequence[tuple], T: int, io_dtype: int
     keep = [_ptr_array(s, L) for s in (W, X, dY, dX, dW)]
     rm_keep, rm_p = _host_mask_table(row_block_mask, [tuple(map(int, r)) for r in sh], int(block_rows))
     rc = lib.tf_stage_backward_shared(_ctx_handle(ctx), _stream_handle(stream) if ctx is not None else None,
-                                      L, sh.ctypes.data, int(T), int(io_dtype),
+                                      L, _address(sh), int(T), int(io_dtype),
                                       keep[0][1], keep[1][1], keep[2][1], fm_p, rm_p, int(block_rows), ig_p,
                                       keep[3][1], keep[4][1], int(dw_dtype), 1 if accumulate else 0)
     _raise(ctx, rc, "tf_stage_backward_shared")
