@@ -5,6 +5,7 @@ import os
 import re
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -158,9 +159,12 @@ def mfma_hazards(asm_text: str) -> list:
 
 def check_generated_code(hipcc: str, extra: list) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Rpass-analysis=kernel-resource-usage")]
-    for source in ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip"):
-        cmd = [hipcc] + flags + extra + ["-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", "-"]
-        res = subprocess.run(cmd, capture_output=True, text=True)
+    sources = ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip")
+    assemble = lambda source: subprocess.run([hipcc] + flags + extra + ["-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", "-"],
+                                             capture_output=True, text=True)
+    with ThreadPoolExecutor(len(sources)) as pool:
+        results = list(pool.map(assemble, sources))
+    for source, res in zip(sources, results):
         if res.returncode != 0:
             raise RuntimeError("hipcc -S failed:\n" + res.stderr)
         for what, bad in (("inline assembly between a writer and a reader of SCC", scc_hazards(res.stdout)),
