@@ -1426,11 +1426,11 @@ extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
 }
 
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
-// aligned) are launched together: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the generic kernel, behind them those of the
-// kernel for input gradients of few rows.  The kernel for weight gradients of few tokens is left out of
-// it; tf_internal_kernels_few() knows that one's too, last of all.
+// aligned) are launched together, by the estimated times: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the
+// generic kernel, behind them those of the kernel for input gradients of few rows and those of the kernel for weight
+// gradients of few tokens.
 // after: rows of the tensor behind the problem's own (it is a run of its rows), or NULL.
-static int kernels_of(bool few, int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
+extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
                                    int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
     const Layout layout = layout_tn ? Layout::kTN : Layout::kNT;
     std::vector<Planned> items;
@@ -1440,20 +1440,10 @@ static int kernels_of(bool few, int n, const int64_t* M, const int64_t* N, const
         items.back().rows_after = more;
     }
     Routes r;
-    const auto find = few ? find_routes : find_general_routes;
-    if (find(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
+    if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
     for (int c = 0; c < 4; ++c)
         for (const Planned* it : r.cls[c]) kernel[it - items.data()] = r.shape[c];
     return TF_OK;
-}
-
-extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
-                                   int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
-    return kernels_of(false, n, M, N, Kc, after, layout_tn, in_dtype, out_dtype, accumulate, kernel);
-}
-extern "C" int tf_internal_kernels_few(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
-                                       int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
-    return kernels_of(true, n, M, N, Kc, after, layout_tn, in_dtype, out_dtype, accumulate, kernel);
 }
 
 // Test hook (not part of the public header): which launch shape of the generic kernel a launch of these
