@@ -277,11 +277,12 @@ hipError_t launch_shape(hipStream_t stream, const GemmBatch& batch, int out) {
 }
 
 // The launch shapes.  A step's and a tile's share of a compute unit when all are full, a step in a launch's longest chain, what a
-// launch takes beside them, how much of the smaller of computing and storing is left, and the stores per MB (written and added
-// to, each in whole cache lines and not); see short_launch_us().
-constexpr ShortShape kShapes[kShortShapes] = {{128, 64, 0.17f, 0.28f, 0.237f, 5.3f, 0.625f, {0.128f, 0.302f, 0.286f, 0.457f}},
-                                              {128, 128, 0.251f, 0.327f, 0.275f, 6.2f, 0.7f, {0.144f, 0.226f, 0.285f, 0.384f}},
-                                              {256, 128, 0.402f, 0.507f, 0.446f, 6.8f, 0.95f, {0.144f, 0.191f, HUGE_VALF, HUGE_VALF}}};
+// launch takes beside them; for each kind of output how much of the smaller of computing and storing is left, and the stores per
+// MB (those added to counted once), in whole cache lines and not; see short_launch_us().
+constexpr ShortShape kShapes[kShortShapes] = {
+    {128, 64, 0.185f, 0.43f, 0.211f, 5.5f, {{0.213f, 0.11f, 0.6f}, {0.468f, 0.125f, 0.309f}, {0.438f, 0.3f, 0.455f}}},
+    {128, 128, 0.263f, 1.07f, 0.287f, 6.3f, {{0.064f, 0.11f, 0.443f}, {0.496f, 0.117f, 0.235f}, {0.459f, 0.29f, 0.381f}}},
+    {256, 128, 0.417f, 2.46f, 0.474f, 7.1f, {{0.083f, 0.11f, 0.469f}, {0.497f, 0.127f, 0.242f}, {0, HUGE_VALF, HUGE_VALF}}}};
 
 }  // namespace
 

@@ -238,23 +238,26 @@ inline bool planned_short_ok(const Planned& it, Layout layout, Dtype in_dtype) {
            short_shape_ok(it.M, it.N, it.Kc, it.lda, it.ldb) && aligned16(it.A) && aligned16(it.B) && aligned16(it.C);
 }
 
-// What the outputs of weight gradients take, `us` per MB: written, fp32 ones added to, each for rows of whole cache lines and others.
-double outputs_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, const float (&us)[4]) {
+// What the outputs of weight gradients take: written, fp32 ones added to.
+double outputs_us(const std::vector<const Planned*>& items, int out_bytes, const OutputCost& cost) {
     double sum = 0;
-    for (const Planned* it : items) sum += 1e-6 * double(it->M) * double(it->N) * out_bytes * us[(accumulate ? 2 : 0) + (it->N * out_bytes % 128 != 0)];
+    for (const Planned* it : items) sum += 1e-6 * double(it->M) * double(it->N) * out_bytes * (it->N * out_bytes % 128 != 0 ? cost.broken_us : cost.whole_us);
     return sum;
 }
+inline int output_kind(int out_bytes, bool accumulate) { return out_bytes == 2 ? 0 : accumulate ? 2 : 1; }
 
 // Launch time, events included, of weight gradients on the kernel for few tokens (its best launch shape), and on the 256 x 256-tile
-// kernel.  Fitted to 168 launches on each (seven sets of layers of widths 256 to 4096, two of them with rows that are no whole cache
-// lines, 64 to 1024 tokens, bf16, fp32 and added fp32 outputs, three sets of buffers in turn; 7 % and 19 % rms, the second one's misses
-// where it is far slower).  By them, the second one's taken 5 % lower (14 % for bf16
-// outputs, which gain least), these launches take 1.7 % more than on the faster kernel on average, at worst
-// 18 %, and 0.87 of what they took on the better one of the other two kernels (at worst 1.1: LLaMA-8B block, 100 tokens, 112 -> 123 us).
+// kernel.  Fitted to 264 launches on each (eleven sets of layers of widths 256 to 4096, four of them without k and v, four with rows
+// that are no whole cache lines, 64 to 1024 tokens, bf16, fp32 and added fp32 outputs, three sets of buffers in turn): 4.7 to 6.9 % rms and,
+// for the three kinds of output, 3.3, 4.2 and 5.8 %.  By them, the second one's taken 3.5 % lower, these launches take 0.6 % more than on the faster
+// kernel on average, at worst 10 % (LLaMA-1B block without k and v, 136 tokens, fp32: 58 us, 53), and none takes more than on 256 x 256 tiles.
+// 90 launches of other widths (256 to 4096, 64 to 2900 tokens): 1.2 % on average, at worst 18 % (2816 / 704 / 10624, 640 tokens, added to: 268 us,
+// 227), and against 256 x 256 tiles at worst 4 % (1792 / 896 / 6400, four blocks, 150 tokens, fp32: 173 us, 167).
 double short_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, int* shape) {
     double best = HUGE_VAL;
     for (int i = 0; i < kShortShapes; ++i) {
         const ShortShape& s = short_shape(i);
+        const OutputCost& out = s.out[output_kind(out_bytes, accumulate)];
         double most = 0, work = 0, chain = 0;
         for (const Planned* it : items) {
             const double n = double(tiles_of(*it, s.rows, s.cols)), steps = double(it->Kc / 64 * 2 + (it->Kc % 64 > 32 ? 2 : it->Kc % 64 > 0 ? 1 : 0));
@@ -263,14 +266,21 @@ double short_launch_us(const std::vector<const Planned*>& items, int out_bytes, 
             chain = std::max(chain, steps * s.chain_us);
         }
         if (most > kMaxGenericTiles) continue;
-        const double us = s.launch_us + Estimate::us(std::max(work / compute_units(), chain), outputs_us(items, out_bytes, accumulate, s.out_us), s.overlap);
+        const double us = s.launch_us + Estimate::us(std::max(work / compute_units(), chain), outputs_us(items, out_bytes, out), out.overlap);
         if (us < best) { best = us; *shape = kGenericShapes + kNarrowShapes + i; }
     }
     return best;
 }
-double tile256_launch_us(const std::vector<const Planned*>& items, bool tail, int out_bytes, bool accumulate) {
-    constexpr float kOut[4] = {0.116f, 0.258f, 0.326f, 0.596f};
-    return (out_bytes == 2 ? 0.855 : 0.95) * (10 + Estimate::us(0.695 * tile256_us(items, tail, Layout::kTN, false), outputs_us(items, out_bytes, accumulate, kOut), 0.732));
+double tile256_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate) {
+    // of tile256_us()'s time for a step; a tile's epilogue in steps; what a launch adds
+    struct { double scale, tile_steps, launch_us; OutputCost out; } constexpr kCost[3] = {
+        {0.935, 3.3, 10.6, {0.131f, 0.05f, 0.45f}}, {0.946, 3.25, 11.7, {0.417f, 0.149f, 0.33f}}, {0.865, 8, 20.3, {0.469f, 0.268f, 0.561f}}};
+    const auto& c = kCost[output_kind(out_bytes, accumulate)];
+    Estimate e;
+    const int tile = gemm_mfma_tile(), units = compute_units();
+    for (const Planned* it : items) e.add(*it, tile, tile, 64, c.tile_steps, c.tile_steps + 1.5);
+    const double us = c.scale * Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
+    return 0.965 * (c.launch_us + Estimate::us(us, outputs_us(items, out_bytes, c.out), c.out.overlap));
 }
 
 constexpr int kFirstNarrow = kGenericShapes, kFirstShort = kFirstNarrow + kNarrowShapes;     // numbers of their launch shapes
@@ -342,8 +352,6 @@ hipError_t find_general_routes(const std::vector<Planned>& items, Layout layout,
     return hipSuccess;
 }
 
-constexpr int64_t kLargeLayer = 80;               // 256 x 256 tiles: 2048 x 2376 and more, not a LLaMA-8B block's 4096 x 1024
-
 // The same with the kernel for weight gradients of few tokens.  What it takes never goes to the generic kernel (in 168 launches timed on
 // both that one took 1.01 to 2.3 times as long); what may go to 256 x 256 tiles does by the estimates, which count that problems
 // on the same kernel share a launch.
@@ -365,14 +373,8 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
         const double us = short_launch_us(both, out_bytes, accumulate, &s);
         const bool on256 = c != kOther && r.shape[c] < 0;
         if (us == HUGE_VAL) continue;
-        // Contractions with a masked last step stay on 256 x 256 tiles where every layer is a large one.  That is where that step is
-        // held to be tested by estimate; bf16 outputs lose nothing by it (LLaMA-8B block, 100, 200, 400 tokens 112, 152, 209 us, here 124, 159, 233; width 2816,
-        // 200 tokens 71, here 76), fp32 ones whose rows are no whole cache lines up to a quarter (width 2816, 200 tokens, added to: 207, here 150).
-        bool large = c == kTail && !forced;
-        for (const Planned* it : v) large = large && tiles_of(*it, gemm_mfma_tile(), gemm_mfma_tile()) >= kLargeLayer;
-        if (on256 && large) continue;
         if (on256 && !forced && (route == kRouteAll256 || (route == kRouteWhole256 && c == kWhole) ||
-                                 us >= few_us + tile256_launch_us(v, c == kTail, out_bytes, accumulate))) continue;
+                                 us >= few_us + tile256_launch_us(v, out_bytes, accumulate))) continue;
         few = both;
         few_us = us;
         r.shape[kFew] = forced ? kFirstShort + route - kRouteShort : s;

@@ -81,10 +81,11 @@ hipError_t launch_gemm_narrow(hipStream_t stream, GemmBatch& batch, int n_proble
 
 // bf16 weight gradients (layout kTN) of few tokens, in several launch shapes.  It takes contractions of 64 or more,
 // rows and columns that are multiples of 8, row pitches that are multiples of 8 and at most 2^22, 16-byte aligned tensors.
+struct OutputCost { float overlap, whole_us, broken_us; };     // of the smaller of computing and storing; per MB of rows of whole cache lines and others
 struct ShortShape {
     int rows, cols;                                     // of its tile
-    float step_us, tile_us, chain_us;                   // what a contraction step of 32 and a tile cost (see there)
-    float launch_us, overlap, out_us[4];
+    float step_us, tile_us, chain_us, launch_us;        // what a contraction step of 32 and a tile cost (see there)
+    OutputCost out[3];                                  // bf16, fp32, added to fp32
 };
 constexpr int kShortShapes = 3;
 const ShortShape& short_shape(int shape);

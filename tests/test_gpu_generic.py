@@ -118,8 +118,7 @@ def test_every_launch_shape(ctx, half, io, T, shapes, tile):
 
 @pytest.mark.parametrize("dw,accumulate", [("bf16", False), ("f32", False), ("f32", True)])
 @pytest.mark.parametrize("T,shapes", [
-    # layers large enough for 256 x 256 tiles to pay: contractions of the weight gradients with 1, 63, 1, 8 and 1
-    # values more than whole steps; ragged last tiles
+    # contractions of the weight gradients with 1, 63, 1, 8 and 1 values more than whole steps; ragged last tiles
     (1025, [(4096, 4096), (4096, 2048)]),
     (1087, [(4104, 2048), (4096, 4104)]),
     (577, [(4096, 4104), (4104, 2056)]),
@@ -127,7 +126,8 @@ def test_every_launch_shape(ctx, half, io, T, shapes, tile):
     (65, [(8192, 4104), (8192, 4104)]),
 ])
 def test_contractions_that_are_no_multiple_of_a_step_on_256_tiles(ctx, T, shapes, dw, accumulate):
-    kinds = _case(ctx, shapes, T, "bf16", dw, accumulate, seed=T)
+    with route(ctx, ALL_256):
+        kinds = _case(ctx, shapes, T, "bf16", dw, accumulate, seed=T)
     assert "dw_mfma" in kinds and "dw_generic" not in kinds
 
 
@@ -212,7 +212,7 @@ def test_both_kernels_give_the_same_bf16_bits(ctx, T, shapes, dw, accumulate):
     assert out[0] == out[1]
 
 
-@pytest.mark.parametrize("io,T,others", [("bf16", 577, [(4096, 4096)] * 2), ("bf16", 576, [(4096, 4096)] * 2), ("f32", 500, [(1536, 2048)] * 2)])
+@pytest.mark.parametrize("io,T,others", [("bf16", 577, [(4096, 4096)] * 5), ("bf16", 576, [(4096, 4096)] * 5), ("f32", 500, [(1536, 2048)] * 2)])
 def test_a_layers_gradient_does_not_depend_on_the_other_layers(ctx, io, T, others):
     """With the other layers unfrozen the launch takes another kernel or another launch shape.  bf16: the same
     bits.  fp32: the sums are 64-bit ones where the launch is short, in 32 bits otherwise, both

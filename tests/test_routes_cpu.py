@@ -22,6 +22,10 @@ def block(d, kv, ffn, blocks=1):
     return [(d, d), (d, kv), (d, kv), (d, d), (d, ffn), (d, ffn), (ffn, d)] * blocks
 
 
+def without_kv(d, ffn):
+    return [(d, d), (d, d), (d, ffn), (d, ffn), (ffn, d)]
+
+
 # (shapes, tokens, "bf16" / fp32 "set" / fp32 "add", kernel); us on 256 x 256 tiles, on the generic kernel and on the best
 # shape of the kernel for few tokens, three sets of buffers in turn
 @pytest.mark.parametrize("shapes,T,dw,fastest", [
@@ -48,6 +52,18 @@ def block(d, kv, ffn, blocks=1):
     (block(2816, 1408, 8200), 512, "add", FEW_TOKENS),           # 227, 310, 181
     (block(1024, 256, 2816, 2), 200, "bf16", FEW_TOKENS),        # 29, 35, 21
     (block(256, 256, 688, 2), 1000, "bf16", FEW_TOKENS),         # 29.9, 15.9, 12.6
+    # large layers, masked last steps: with and without k and v (a frozen pair must not turn the choice)
+    (block(3328, 832, 11000), 200, "add", FEW_TOKENS),           # 337, 384, 239
+    (without_kv(3328, 11000), 200, "add", FEW_TOKENS),           # 315, -, 232
+    (without_kv(2816, 8200), 65, "set", FEW_TOKENS),             # 112, -, 89
+    (without_kv(2816, 8200), 200, "add", FEW_TOKENS),            # 184, -, 138
+    (without_kv(4096, 14336), 200, "add", FEW_TOKENS),           # 330, -, 308
+    (without_kv(4096, 14336), 264, "add", FEW_TOKENS),           # 338, -, 319
+    (without_kv(4096, 14336), 200, "bf16", [TILES_256]),         # 142, -, 147
+    # few tokens, bf16: large layers take as long on either, and these longer
+    (block(4096, 1024, 14336), 100, "bf16", [TILES_256]),        # 109, 160, 118
+    (without_kv(4096, 14336), 100, "bf16", [TILES_256]),         # 108, -, 113
+    (block(3328, 832, 11000), 100, "bf16", [TILES_256]),         # 92.5, 113, 95.9
 ])
 def test_weight_gradients_take_the_faster_kernel(shapes, T, dw, fastest):
     K, N = zip(*shapes)
