@@ -170,36 +170,19 @@ int pick_generic_shape(const std::vector<const Planned*>& items, Dtype in_dtype,
     return best;
 }
 
-// The 256 x 256-tile kernel on these problems.  A step takes 1.45 us when all units are busy (the power
+// Input gradients on the 256 x 256-tile kernel.  A step takes 1.45 us when all units are busy (the power
 // limit), 1.15 in the long tiles at a launch's end, 1.0 when there are fewer tiles than units; a tile's
 // epilogue is worth 4.5 steps and, at the end of a chain, 6 with the fill of its first stages; where the tile is
-// no whole one (masked stores) 3 more, 5 for weight gradients, 10 when they are added to.  Measured in turn with the generic kernel, us, in
-// brackets the latter: LLaMA-1B block, input gradients, 256 tokens 136 (54), 512 140 (96), 1024 192 (144),
-// 2048 251 (287); LLaMA-8B block 512 tokens 345 (259), 1024 440 (495); weight gradients of a block of width 512, 256
-// tokens 16 (11), of the LLaMA-1B block 51 (72), of that block with half of its 64-row blocks frozen, 1024
-// tokens, 164 (135), of its 128-row blocks, 256 tokens, 47 (39).
-double tile256_us(const std::vector<const Planned*>& items, bool tail, Layout layout, bool accumulate) {
+// no whole one (masked stores) 3 more.  Measured in turn with the generic kernel, us, in
+// brackets the latter: LLaMA-1B block, 256 tokens 136 (54), 512 140 (96), 1024 192 (144),
+// 2048 251 (287); LLaMA-8B block 512 tokens 345 (259), 1024 440 (495).  (Weight gradients: tile256_launch_us().)
+double tile256_us(const std::vector<const Planned*>& items, bool tail) {
     if (items.empty()) return 0;
     Estimate e;
     const uint32_t tile = gemm_mfma_tile();
-    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - int64_t(uint32_t(it->M) / tile) * (uint32_t(it->N) / tile)), layout == Layout::kNT ? 3 : accumulate ? 10 : 5);
+    for (const Planned* it : items) e.add(*it, tile, tile, 64, tail ? 5.5 : 4.5, tail ? 7 : 6, double(tiles_of(*it, tile, tile) - int64_t(uint32_t(it->M) / tile) * (uint32_t(it->N) / tile)), 3);
     const int units = compute_units();
     return Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
-}
-
-// What the generic kernel's launch is compared with tile256_us() by.  Its weight gradients take longer than the
-// estimate, which knows no outputs: they are stored past the caches, and what is added to is fetched again from
-// where an earlier call has left it (MB of outputs, those added to counted both ways).  Timed on both kernels, block
-// widths 256 to 4096, 64 to 3001 tokens: of 410 launches of whole tensors all get the faster kernel or lose at most 7 %
-// by it; of 248 with runs of 64- to 256-row blocks all but 8 are within 10 % (worst: 1.37 times), of 119 with widths
-// that are no multiples of a tile all but 7 (1.32).  Without: up to
-// 1.76 times (block of widths 1024 / 256 / 2816, 256 tokens, added to: 43 us, 256 x 256 tiles 25).  Input gradients
-// as estimated: within 11 %.
-double generic_launch_us(const std::vector<const Planned*>& items, double us, Layout layout, int out_bytes, bool accumulate) {
-    if (layout == Layout::kNT) return us;
-    double mb = 0;
-    for (const Planned* it : items) mb += 1e-6 * double(it->M) * double(it->N) * out_bytes;
-    return accumulate ? us + 0.06 * 2 * mb : 1.15 * us + 0.03 * mb;
 }
 
 // Launch shapes beyond the generic kernel's: the kernel for input gradients of few rows.
@@ -246,41 +229,77 @@ double outputs_us(const std::vector<const Planned*>& items, int out_bytes, const
 }
 inline int output_kind(int out_bytes, bool accumulate) { return out_bytes == 2 ? 0 : accumulate ? 2 : 1; }
 
-// Launch time, events included, of weight gradients on the kernel for few tokens (its best launch shape), and on the 256 x 256-tile
-// kernel.  Fitted to 264 launches on each (eleven sets of layers of widths 256 to 4096, four of them without k and v, four with rows
-// that are no whole cache lines, 64 to 1024 tokens, bf16, fp32 and added fp32 outputs, three sets of buffers in turn): 4.7 to 6.9 % rms and,
-// for the three kinds of output, 3.3, 4.2 and 5.8 %.  By them, the second one's taken 3.5 % lower, these launches take 0.6 % more than on the faster
-// kernel on average, at worst 10 % (LLaMA-1B block without k and v, 136 tokens, fp32: 58 us, 53), and none takes more than on 256 x 256 tiles.
-// 90 launches of other widths (256 to 4096, 64 to 2900 tokens): 1.2 % on average, at worst 18 % (2816 / 704 / 10624, 640 tokens, added to: 268 us,
-// 227), and against 256 x 256 tiles at worst 4 % (1792 / 896 / 6400, four blocks, 150 tokens, fp32: 173 us, 167).
+// Launch time, events included, of weight gradients in bf16 on the kernel for few tokens (its best launch shape) and on the 256 x 256-tile
+// kernel.  Fitted to 264 launches of 64 to 1024 tokens (eleven sets of layers of widths 256 to 4096, four of them without k and v, four
+// with rows that are no whole cache lines, bf16, fp32 and added fp32 outputs, three sets of buffers in turn).  A unit then takes its
+// next tile whenever it is done with one; longer chains end in rounds (kRounds): 256 x 256 tiles, 172 of them 73 us at 3001 tokens, 344 144.
+// The choice among all three kernels, over 708 launches of widths 256 to 4096, 64 to 8192 tokens: 1.6 % more than the fastest on average (with
+// the fit to few tokens alone, 7 % from 2100 tokens on; of the other two kernels the better one, 8 to 21 %), at worst 1.34 times (1280 / 640 / 3400,
+// 320 tokens, fp32: 37 us, 28).
+constexpr int kRounds = 1024;
+double tiles_per_unit(double tiles, int64_t longest) {
+    tiles /= compute_units();
+    return longest > kRounds ? std::ceil(tiles) : tiles;
+}
+int64_t longest_contraction(const std::vector<const Planned*>& items) {
+    int64_t kc = 0;
+    for (const Planned* it : items) kc = std::max(kc, it->Kc);
+    return kc;
+}
 double short_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, int* shape) {
+    const int64_t kc = longest_contraction(items);
+    const double steps = double(kc / 64 * 2 + (kc % 64 > 32 ? 2 : kc % 64 > 0 ? 1 : 0));
     double best = HUGE_VAL;
     for (int i = 0; i < kShortShapes; ++i) {
         const ShortShape& s = short_shape(i);
         const OutputCost& out = s.out[output_kind(out_bytes, accumulate)];
-        double most = 0, work = 0, chain = 0;
+        double most = 0, tiles = 0;
         for (const Planned* it : items) {
-            const double n = double(tiles_of(*it, s.rows, s.cols)), steps = double(it->Kc / 64 * 2 + (it->Kc % 64 > 32 ? 2 : it->Kc % 64 > 0 ? 1 : 0));
+            const double n = double(tiles_of(*it, s.rows, s.cols));
             most = std::max(most, n);
-            work += n * (steps * s.step_us + s.tile_us);
-            chain = std::max(chain, steps * s.chain_us);
+            tiles += n;
         }
         if (most > kMaxGenericTiles) continue;
-        const double us = s.launch_us + Estimate::us(std::max(work / compute_units(), chain), outputs_us(items, out_bytes, out), out.overlap);
-        if (us < best) { best = us; *shape = kGenericShapes + kNarrowShapes + i; }
+        const double us = std::max(tiles_per_unit(tiles, kc) * (steps * s.step_us + s.tile_us), steps * s.chain_us);
+        const double all_us = s.launch_us + Estimate::us(us, outputs_us(items, out_bytes, out), out.overlap);
+        if (all_us < best) { best = all_us; *shape = kGenericShapes + kNarrowShapes + i; }
     }
     return best;
 }
 double tile256_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate) {
-    // of tile256_us()'s time for a step; a tile's epilogue in steps; what a launch adds
-    struct { double scale, tile_steps, launch_us; OutputCost out; } constexpr kCost[3] = {
-        {0.935, 3.3, 10.6, {0.131f, 0.05f, 0.45f}}, {0.946, 3.25, 11.7, {0.417f, 0.149f, 0.33f}}, {0.865, 8, 20.3, {0.469f, 0.268f, 0.561f}}};
+    // a tile's epilogue in steps; up to 1024 tokens what a launch adds, and the share of tile256_us()'s time for a step
+    struct { double tile_steps, launch_us, scale; OutputCost out; } constexpr kCost[3] = {
+        {3.3, 10.6, 0.935, {0.131f, 0.05f, 0.45f}}, {3.25, 11.7, 0.946, {0.417f, 0.149f, 0.33f}}, {8, 20.3, 0.865, {0.469f, 0.268f, 0.561f}}};
     const auto& c = kCost[output_kind(out_bytes, accumulate)];
-    Estimate e;
     const int tile = gemm_mfma_tile(), units = compute_units();
-    for (const Planned* it : items) e.add(*it, tile, tile, 64, c.tile_steps, c.tile_steps + 1.5);
-    const double us = c.scale * Estimate::us(e.work / units * 1.45, e.longest * (e.tiles <= units ? 1.0 : 1.15), 0.4);
-    return 0.965 * (c.launch_us + Estimate::us(us, outputs_us(items, out_bytes, c.out), c.out.overlap));
+    const int64_t kc = longest_contraction(items);
+    const double steps = double(parts_of(kc, 64)) + c.tile_steps, stores = outputs_us(items, out_bytes, c.out);
+    double tiles = 0;
+    for (const Planned* it : items) tiles += double(tiles_of(*it, tile, tile));
+    if (kc > kRounds) return 10.6 + Estimate::us(tiles_per_unit(tiles, kc) * steps * 1.22, stores, c.out.overlap);
+    const double us = c.scale * Estimate::us(tiles / units * steps * 1.45, (steps + 1.5) * (tiles <= units ? 1.0 : 1.15), 0.4);
+    return 0.965 * (c.launch_us + Estimate::us(us, stores, c.out.overlap));
+}
+
+// The same on the generic kernel.  Up to 1024 tokens it is slower than the kernel for few tokens (1.01 to 2.3 times in 168 launches), but
+// a step of 64 in a chain that has its unit to itself takes it 0.29 us, that one 0.38: from some 1500 tokens on it is the faster
+// one where there are few tiles.  us, in brackets the latter: two blocks of widths 64 / 64 / 176, bf16, 1024 tokens 12.3 (11.6), 2048 17.0
+// (17.9), 8192 44.9 (54.2); 128 / 64 / 344, 4096 tokens 27.6 (31.3), 8192 54.5 (70.7); 384 / 128 / 1024, 3001 tokens 45.9 (40.7).
+double generic_launch_us(const std::vector<const Planned*>& items, int out_bytes, bool accumulate, int* shape) {
+    double us;
+    *shape = pick_generic_shape(items, Dtype::BF16, &us);
+    if (us == HUGE_VAL) return us;
+    constexpr double kOut[3] = {0.01, 0.05, 0.34};             // per MB of outputs
+    const GenericShape& s = generic_shape(Dtype::BF16, *shape);
+    const int64_t kc = longest_contraction(items);
+    const double steps = double(parts_of(kc, 64)) + s.tile_steps;
+    double tiles = 0, mb = 0;
+    for (const Planned* it : items) {
+        tiles += double(tiles_of(*it, s.tile_m, s.tile_n));
+        mb += 1e-6 * double(it->M) * double(it->N) * out_bytes;
+    }
+    us = Estimate::us(1.1 * tiles_per_unit(tiles, kc) * steps * s.step_us, 0.75 * steps * s.chain_us, kc > kRounds ? 0 : 0.25);
+    return 7.3 + us + kOut[output_kind(out_bytes, accumulate)] * mb;
 }
 
 constexpr int kFirstNarrow = kGenericShapes, kFirstShort = kFirstNarrow + kNarrowShapes;     // numbers of their launch shapes
@@ -297,31 +316,22 @@ void tile_of(int shape, Dtype in_dtype, uint32_t* m, uint32_t* n) {
 // last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
 enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4, kRouteShort = kRouteNarrow + kNarrowShapes };      // 4 and on: their shapes
 
-// problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others; weight gradients of few tokens
-enum { kWhole = 0, kTail = 1, kOther = 2, kFew = 3 };
+// problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
+enum { kWhole = 0, kTail = 1, kOther = 2, kClasses = 3 };
 
-// Which kernel takes which problems: on the 256 x 256-tile kernel what it takes, on the generic kernel the
-// rest - and what it takes when the generic one's smaller tiles are expected to be done first (few tiles, or
+// Which kernel takes which problems: on the 256 x 256-tile kernel what it takes, on one with smaller tiles the
+// rest - and what it takes when the smaller tiles are expected to be done first (few tiles, or
 // few long ones).
 struct Routes {
-    std::vector<const Planned*> cls[4];
-    int shape[4] = {-1, -1, -1, -1};            // launch shape; -1: 256 x 256 tiles
+    std::vector<const Planned*> cls[kClasses];
+    int shape[kClasses] = {-1, -1, -1};         // launch shape; -1: 256 x 256 tiles
 };
-hipError_t find_general_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
-    bool plain = true;                          // no row bits, no segments: the generic kernel could take them too
-    for (const Planned& it : items) {
-        bool ok = planned_mfma_ok(it, layout, in_dtype);
-        for (const Planned& q : it.more) ok = ok && planned_mfma_ok(q, layout, in_dtype);
-        const bool special = ~it.row_bits != 0 || !it.more.empty();
-        if (ok) { r.cls[kWhole].push_back(&it); plain = plain && !special; }
-        else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
-        else r.cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
-    }
-    const int out_bytes = out_dtype == Dtype::BF16 ? 2 : 4;
-    auto generic = [&](const std::vector<const Planned*>& v, int* shape) {
+
+// Input gradients, and everything in fp32.
+void find_input_routes(Layout layout, Dtype in_dtype, int route, bool plain, Routes& r) {
+    auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
         double us;
         *shape = pick_generic_shape(v, in_dtype, &us);
-        us = generic_launch_us(v, us, layout, out_bytes, accumulate);
         if (v.empty() || route == kRouteGeneric) return us;
         for (const Planned* it : v)
             if (!planned_narrow_ok(*it, layout, in_dtype)) return us;
@@ -336,50 +346,83 @@ hipError_t find_general_routes(const std::vector<Planned>& items, Layout layout,
     };
     if (plain && route != kRouteWhole256 && route != kRouteAll256) {
         int s;
-        if (generic(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false, layout, accumulate) || route == kRouteGeneric) r.shape[kWhole] = s;
+        if (smaller(r.cls[kWhole], &s) < tile256_us(r.cls[kWhole], false) || route == kRouteGeneric) r.shape[kWhole] = s;
     }
     if (!r.cls[kTail].empty() && route != kRouteAll256) {
         std::vector<const Planned*> both = r.cls[kTail];
         both.insert(both.end(), r.cls[kOther].begin(), r.cls[kOther].end());
         int s;
-        const double together = generic(both, &s);
-        if (together < tile256_us(r.cls[kTail], true, layout, accumulate) + generic(r.cls[kOther], &s) || route == kRouteGeneric) {
+        const double together = smaller(both, &s);
+        if (together < tile256_us(r.cls[kTail], true) + smaller(r.cls[kOther], &s) || route == kRouteGeneric) {
             r.cls[kOther] = both;
             r.cls[kTail].clear();
         }
     }
-    generic(r.cls[kOther], &r.shape[kOther]);
-    return hipSuccess;
+    smaller(r.cls[kOther], &r.shape[kOther]);
 }
 
-// The same with the kernel for weight gradients of few tokens.  What it takes never goes to the generic kernel (in 168 launches timed on
-// both that one took 1.01 to 2.3 times as long); what may go to 256 x 256 tiles does by the estimates, which count that problems
-// on the same kernel share a launch.
-hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
-    const hipError_t found = find_general_routes(items, layout, in_dtype, out_dtype, accumulate, route, r);
-    const bool forced = route >= kRouteShort;
-    if (found != hipSuccess || layout != Layout::kTN || in_dtype != Dtype::BF16 || route == kRouteGeneric) return found;
-    const int out_bytes = out_dtype == Dtype::BF16 ? 2 : 4;
-    std::vector<const Planned*>& few = r.cls[kFew];
-    double few_us = 0;
-    for (const int c : {kOther, kTail, kWhole}) {
+// Weight gradients in bf16: each class on 256 x 256 tiles, on smaller ones in a launch of its own, or in one with those
+// that 256 x 256 tiles do not take, whichever is expected to be done first.
+void find_weight_routes(int out_bytes, bool accumulate, int route, Routes& r) {
+    auto can_move = [](const std::vector<const Planned*>& v) {
+        for (const Planned* it : v)
+            if (!planned_short_ok(*it, Layout::kTN, Dtype::BF16)) return false;
+        return true;
+    };
+    auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
+        if (v.empty()) return 0.0;
+        if (route >= kRouteShort && can_move(v)) { *shape = kFirstShort + route - kRouteShort; return 0.0; }
+        const bool few = route != kRouteGeneric && can_move(v);
+        double few_us = HUGE_VAL;
+        int s = 0;
+        if (few) few_us = short_launch_us(v, out_bytes, accumulate, &s);
+        if (few_us < HUGE_VAL && longest_contraction(v) <= kRounds) { *shape = s; return few_us; }      // (see generic_launch_us())
+        const double us = generic_launch_us(v, out_bytes, accumulate, shape);
+        if (few_us < us) *shape = s;
+        return std::min(us, few_us);
+    };
+    double other_us = smaller(r.cls[kOther], &r.shape[kOther]);
+    for (const int c : {kTail, kWhole}) {
         std::vector<const Planned*>& v = r.cls[c];
-        bool ok = !v.empty();
-        for (const Planned* it : v) ok = ok && planned_short_ok(*it, layout, in_dtype);
-        if (!ok) continue;
-        std::vector<const Planned*> both = few;
+        if (v.empty() || !can_move(v) || route == kRouteAll256 || (route == kRouteWhole256 && c == kWhole)) continue;
+        int alone = -1, joint = -1;
+        double alone_us = HUGE_VAL, joint_us;
+        std::vector<const Planned*> both = r.cls[kOther];
         both.insert(both.end(), v.begin(), v.end());
-        int s = kFirstShort;
-        const double us = short_launch_us(both, out_bytes, accumulate, &s);
-        const bool on256 = c != kOther && r.shape[c] < 0;
-        if (us == HUGE_VAL) continue;
-        if (on256 && !forced && (route == kRouteAll256 || (route == kRouteWhole256 && c == kWhole) ||
-                                 us >= few_us + tile256_launch_us(v, out_bytes, accumulate))) continue;
-        few = both;
-        few_us = us;
-        r.shape[kFew] = forced ? kFirstShort + route - kRouteShort : s;
-        v.clear();
+        joint_us = smaller(both, &joint);
+        if (!can_move(r.cls[kOther])) {
+            // The others are for the generic kernel only: it takes all of them if it would take these too, or if that saves more
+            // than a launch: its estimate is up to a fifth short of launches of three to six tiles per unit.  us, whole calls, together
+            // and in two launches: widths 256 / 256 / 688 and an output of 1001, 320 tokens 24.2, 29.4; 2048 x 2048 and 36 x 256, 320 tokens 25.1,
+            // 26.6, 4096 tokens 106, 96.
+            alone_us = smaller(v, &alone);
+            if (alone >= kGenericShapes) joint_us = longest_contraction(v) <= 512 ? 1.2 * joint_us : HUGE_VAL;
+        }
+        const bool forced = route == kRouteGeneric || route >= kRouteShort;
+        if (!forced && tile256_launch_us(v, out_bytes, accumulate) + other_us <= std::min(alone_us + other_us, joint_us)) continue;
+        if (alone_us + other_us < joint_us) {
+            r.shape[c] = alone;
+        } else {
+            r.cls[kOther] = both;
+            r.shape[kOther] = joint;
+            other_us = joint_us;
+            v.clear();
+        }
     }
+}
+
+hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
+    bool plain = true;                          // no row bits, no segments: the kernels with smaller tiles could take them too
+    for (const Planned& it : items) {
+        bool ok = planned_mfma_ok(it, layout, in_dtype);
+        for (const Planned& q : it.more) ok = ok && planned_mfma_ok(q, layout, in_dtype);
+        const bool special = ~it.row_bits != 0 || !it.more.empty();
+        if (ok) { r.cls[kWhole].push_back(&it); plain = plain && !special; }
+        else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
+        else r.cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
+    }
+    if (layout == Layout::kTN && in_dtype == Dtype::BF16) find_weight_routes(out_dtype == Dtype::BF16 ? 2 : 4, accumulate, route, r);
+    else find_input_routes(layout, in_dtype, route, plain, r);
     return hipSuccess;
 }
 
@@ -439,7 +482,7 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
     const int* const shape = routes.shape;
 
     GemmBatch batch;
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < kClasses; ++c) {
         std::vector<const Planned*>& v = cls[c];
         // Longest contraction first: the tail of a launch is then made of the cheapest tiles.
         std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
@@ -1443,14 +1486,13 @@ extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, co
     }
     Routes r;
     if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < kClasses; ++c)
         for (const Planned* it : r.cls[c]) kernel[it - items.data()] = r.shape[c];
     return TF_OK;
 }
 
 // Test hook (not part of the public header): which launch shape of the generic kernel a launch of these
-// problems gets, its tile goes to tile[0..1]; and what it and the 256 x 256-tile kernel (for problems
-// whose contraction is a multiple of 64, or for all others) are expected to take, us[0..1].
+// problems gets, its tile goes to tile[0..1]; and what it is expected to take, *us.
 extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, int in_dtype, int32_t* tile, double* us) {
     std::vector<Planned> items;
     for (int i = 0; i < n; ++i) items.push_back(Planned{nullptr, nullptr, nullptr, M[i], N[i], Kc[i], 0, 0, ~0ull, {}});
@@ -1458,7 +1500,6 @@ extern "C" int tf_internal_generic_shape(int n, const int64_t* M, const int64_t*
     for (const Planned& it : items) p.push_back(&it);
     const Dtype dt = to_dtype(tf_dtype(in_dtype));
     const int shape = pick_generic_shape(p, dt, us);
-    us[1] = tile256_us(p, n > 0 && Kc[0] % 64 != 0, Layout::kTN, false);
     tile[0] = generic_shape(dt, shape).tile_m;
     tile[1] = generic_shape(dt, shape).tile_n;
     return shape;

@@ -7,7 +7,7 @@ import pytest
 import paper_2602_05754_amd as tf
 
 TILES_256 = -1
-FEW_ROWS, FEW_TOKENS = range(3, 7), range(7, 10)                # launch shapes of the kernels for them
+GENERIC, FEW_ROWS, FEW_TOKENS = range(3), range(3, 7), range(7, 10)                # launch shapes of the other kernels
 
 
 def kernels(M, N, Kc, tn, io=tf.TF_BF16, out=tf.TF_BF16, accumulate=False, after=None):
@@ -52,6 +52,19 @@ def without_kv(d, ffn):
     (block(2816, 1408, 8200), 512, "add", FEW_TOKENS),           # 227, 310, 181
     (block(1024, 256, 2816, 2), 200, "bf16", FEW_TOKENS),        # 29, 35, 21
     (block(256, 256, 688, 2), 1000, "bf16", FEW_TOKENS),         # 29.9, 15.9, 12.6
+    # narrow layers, many tokens: one long chain per unit
+    (block(64, 64, 176, 2), 1024, "bf16", FEW_TOKENS),           # -, 12.3, 11.6
+    (block(64, 64, 176, 2), 4096, "bf16", GENERIC),              # -, 26.2, 30.0
+    (block(128, 64, 344, 2), 8192, "add", GENERIC),              # -, 48.8, 57.5
+    (block(192, 96, 512), 3001, "set", GENERIC),                 # -, 21.5, 23.8
+    (block(256, 64, 688), 3001, "bf16", GENERIC),                # -, 22.4, 24.9
+    (block(384, 128, 1024, 2), 3001, "bf16", FEW_TOKENS),        # 97, 45.9, 37.5
+    # many tokens: whole rounds of tiles
+    (block(1024, 256, 2816), 3001, "bf16", [TILES_256]),         # 73, 99, 89
+    (block(1024, 256, 2816), 4096, "set", [TILES_256]),          # 102, 140, 123
+    (without_kv(1024, 4096), 2048, "add", [TILES_256]),          # 71, 131, 89
+    (block(512, 256, 1536), 6000, "bf16", FEW_TOKENS),           # 123, 88, 68
+    (block(512, 512, 1408, 2), 4096, "bf16", FEW_TOKENS),        # 96, 85, 72
     # large layers, masked last steps: with and without k and v (a frozen pair must not turn the choice)
     (block(3328, 832, 11000), 200, "add", FEW_TOKENS),           # 337, 384, 239
     (without_kv(3328, 11000), 200, "add", FEW_TOKENS),           # 315, -, 232
@@ -133,8 +146,9 @@ def test_few_tokens_that_their_kernel_cannot_take():
         assert 0 <= kernels([M], [N], [Kc], tn, io=io, out=io)[0] < 3
     assert kernels([64], [256], [128], False)[0] in FEW_ROWS
     assert kernels([256, 128], [256, 64], [128, 128], True)[0] in FEW_TOKENS
-    mixed = kernels([256, 36], [256, 256], [128, 128], True)
-    assert mixed[0] in FEW_TOKENS and 0 <= mixed[1] < 3
+    for T, apart in ((128, False), (320, False), (1024, True), (4096, True)):           # whole calls, us, apart and together: 21.6 and 19.2,
+        mixed = kernels([2048, 36], [2048, 256], [T, T], True)                          # 26.6 and 25.1, 40.2 and 41.7, 96 and 106
+        assert mixed[0] in (FEW_TOKENS if apart else GENERIC) and mixed[1] in GENERIC
 
 
 TILES = {tf.TF_F32: [(32, 32), (32, 64), (64, 64)], tf.TF_BF16: [(64, 64), (128, 64), (128, 128)]}
