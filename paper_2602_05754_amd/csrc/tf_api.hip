@@ -5,6 +5,7 @@
 #include "tf_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <new>
@@ -28,6 +29,7 @@ struct tf_ctx {
     bool lowp_is_rounded_master;        // tf_assume_lowp_is_rounded_master
     double* ew_partials;                // device memory of the score sums' first level (zero between launches)
     int gemm_route;                     // tf_internal_gemm_route
+    std::atomic<int> common_tiles{-1};  // tf_internal_common_tiles
 };
 
 // Device memory of tf_reconcile_mask_static: one array per GPU, part of the loaded code object,
@@ -314,7 +316,10 @@ void tile_of(int shape, Dtype in_dtype, uint32_t* m, uint32_t* n) {
 
 // tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
 // last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
-enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4, kRouteShort = kRouteNarrow + kNarrowShapes };      // 4 and on: their shapes
+// From kRouteNarrow and kRouteShort on the kernels for few rows and few tokens, by their shapes; from kRouteF32 on fp32 calls in the
+// generic kernel's tiles x (input gradients) and w (weight gradients), kRouteF32 + kGenericShapes x + w.
+enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4, kRouteShort = kRouteNarrow + kNarrowShapes,
+       kRouteF32 = kRouteShort + kShortShapes, kRouteEnd = kRouteF32 + kGenericShapes * kGenericShapes };
 
 // problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
 enum { kWhole = 0, kTail = 1, kOther = 2, kClasses = 3 };
@@ -332,6 +337,7 @@ void find_input_routes(Layout layout, Dtype in_dtype, int route, bool plain, Rou
     auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
         double us;
         *shape = pick_generic_shape(v, in_dtype, &us);
+        if (in_dtype == Dtype::F32 && route >= kRouteF32) *shape = layout == Layout::kNT ? (route - kRouteF32) / kGenericShapes : (route - kRouteF32) % kGenericShapes;
         if (v.empty() || route == kRouteGeneric) return us;
         for (const Planned* it : v)
             if (!planned_narrow_ok(*it, layout, in_dtype)) return us;
@@ -371,7 +377,7 @@ void find_weight_routes(int out_bytes, bool accumulate, int route, Routes& r) {
     };
     auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
         if (v.empty()) return 0.0;
-        if (route >= kRouteShort && can_move(v)) { *shape = kFirstShort + route - kRouteShort; return 0.0; }
+        if (route >= kRouteShort && route < kRouteF32 && can_move(v)) { *shape = kFirstShort + route - kRouteShort; return 0.0; }
         const bool few = route != kRouteGeneric && can_move(v);
         double few_us = HUGE_VAL;
         int s = 0;
@@ -398,7 +404,7 @@ void find_weight_routes(int out_bytes, bool accumulate, int route, Routes& r) {
             alone_us = smaller(v, &alone);
             if (alone >= kGenericShapes) joint_us = longest_contraction(v) <= 512 ? 1.2 * joint_us : HUGE_VAL;
         }
-        const bool forced = route == kRouteGeneric || route >= kRouteShort;
+        const bool forced = route == kRouteGeneric || (route >= kRouteShort && route < kRouteF32);
         if (!forced && tile256_launch_us(v, out_bytes, accumulate) + other_us <= std::min(alone_us + other_us, joint_us)) continue;
         if (alone_us + other_us < joint_us) {
             r.shape[c] = alone;
@@ -469,6 +475,7 @@ hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planne
     if (tiles > kMaxGenericTiles) return hipSuccess;
     batch.total_tiles = int32_t(tiles);
     *done = true;
+    ctx->common_tiles.store(kGenericShapes * shape[0] + shape[1], std::memory_order_relaxed);
     return launch_gemm_generic_both(stream, batch, int(items.size()), shape[0], shape[1], accumulate);
 }
 
@@ -733,6 +740,7 @@ int stage_backward_impl(tf_ctx* ctx, void* hip_stream,
     hipError_t e = hipSuccess;
     bool both = false;
     const bool add_first = plan_set.empty();          // (what overwrites, if there is any, goes with the input gradients)
+    ctx->common_tiles.store(-1, std::memory_order_relaxed);
     if (in_dt == Dtype::F32 && !input_group) {
         e = launch_both(ctx, stream, plan, add_first ? plan_add : plan_set, add_first, &both);
         if (e != hipSuccess) return hip_fail(ctx, e);
@@ -1465,10 +1473,14 @@ extern "C" int tf_internal_check_tables(int32_t n_tables, const int64_t* desc, i
 // Test hook (not part of the public header): the kernels that this context's GEMM launches take, so that a
 // small problem can be sent through each of them.  A context starts with 0, the estimated times.
 extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
-    if (!ctx || route < kRouteEstimated || route >= kRouteShort + kShortShapes) return TF_ERR_INVALID_ARG;
+    if (!ctx || route < kRouteEstimated || route >= kRouteEnd) return TF_ERR_INVALID_ARG;
     ctx->gemm_route = route;
     return TF_OK;
 }
+
+// Test hook (not part of the public header): did the context's last backward call launch both of its halves together?
+// kGenericShapes x + w, the tiles they had (see kRouteF32), or -1.
+extern "C" int tf_internal_common_tiles(const tf_ctx* ctx) { return ctx ? ctx->common_tiles.load(std::memory_order_relaxed) : -1; }
 
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
 // aligned) are launched together, by the estimated times: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the

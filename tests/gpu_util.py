@@ -13,6 +13,12 @@ import paper_2602_05754_amd as tf
 BY_ESTIMATE, WHOLE_256, ALL_256, GENERIC = range(4)
 NARROW = {(64, 64): 4, (128, 64): 5, (128, 128): 6, (256, 128): 7}        # input gradients of few rows, by tile
 SHORT = {(128, 64): 8, (128, 128): 9, (256, 128): 10}                                   # weight gradients of few tokens, by tile
+F32_TILES = 11                                          # + 3 x + w: fp32 calls, tiles x and w of their two halves
+
+
+def common_tiles(ctx) -> int:
+    """3 x + w if the context's last backward call launched its two halves, in tiles x and w, together; or -1."""
+    return tf.load_library().tf_internal_common_tiles(ctx.handle)
 
 
 def set_route(ctx, route: int) -> None:

@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, GENERIC, NARROW, SHORT, TDT, WHOLE_256, assert_elementwise, canary, dev, host64, kinds_of, raw_bytes, rel_fro, route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, F32_TILES, GENERIC, NARROW, SHORT, TDT, WHOLE_256, assert_elementwise, canary, common_tiles, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -335,17 +335,9 @@ def test_weight_gradients_of_few_tokens_in_row_runs(ctx):
     assert rel_fro(host64(out.t)[~keep.numpy()], ref[~keep].numpy()) < 4e-3
 
 
-@pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
-@pytest.mark.parametrize("T,shapes", [
-    (1, [(1, 1), (33, 70)]),
-    (256, [(256, 256), (256, 688), (688, 256)]),                   # both halves in 64 bits
-    (391, [(1290, 643), (643, 1283), (31, 5)]),
-    (815, [(2047, 1001), (1046, 1005), (1047, 1001)] * 2),
-    (40, [(96, 40 + l) for l in range(40)]),                       # more problems than one launch holds
-])
-def test_both_halves_in_one_launch_give_the_same_bits(ctx, T, shapes, form):
-    """An fp32 call launches its two halves together where that changes no sum; a call that is profiled launches them one
-    by one."""
+def _both_halves(ctx, T, shapes, form, tiles):
+    """An fp32 call launches its two halves together, in tiles that `tiles` accepts (-1: not together); a call that is
+    profiled launches them one by one.  The same bits in every gradient."""
     W, X, dY = _random(shapes, T, "f32", T)
     old = [torch.randn(s, device="cuda") for s in shapes]
     L = len(shapes)
@@ -361,10 +353,11 @@ def test_both_halves_in_one_launch_give_the_same_bits(ctx, T, shapes, form):
             call = lambda: tf.tf_stage_backward(ctx, shapes, T, tf.TF_F32, W, X, dY, mask, *out, tf.TF_F32, accumulate=form == "add")
         if profiled:
             kinds = kinds_of(ctx, call)
-            assert "dx_generic" in kinds and "dw_generic" in kinds
+            assert "dx_generic" in kinds and "dw_generic" in kinds and common_tiles(ctx) == -1
         else:
             call()
             torch.cuda.synchronize()
+            assert tiles(common_tiles(ctx)), common_tiles(ctx)
         for l in range(L):
             gX[l].check(f"dX[{l}]")
             gW[l].check(f"dW[{l}]")
@@ -374,3 +367,30 @@ def test_both_halves_in_one_launch_give_the_same_bits(ctx, T, shapes, form):
     assert got[0] == got[1]
     ref = dY[1].double() @ W[1].double().t().contiguous()
     assert rel_fro(host64(gX[1].t), ref.cpu().numpy()) < 4e-6
+    ref = X[1].double().t().contiguous() @ dY[1].double()
+    if form == "add" or form == "microbatch":
+        ref += old[1].double()
+    assert rel_fro(host64(gW[1].t), ref.cpu().numpy()) < 4e-6
+
+
+@pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
+@pytest.mark.parametrize("T,shapes", [
+    (1, [(1, 1), (33, 70)]),
+    (256, [(256, 256), (256, 688), (688, 256)]),                   # both halves in 64 bits
+    (391, [(1290, 643), (643, 1283), (31, 5)]),
+    (815, [(2047, 1001), (1046, 1005), (1047, 1001)] * 2),
+    (40, [(96, 40 + l) for l in range(40)]),                       # more problems than one launch holds, but for `microbatch` and `frozen`
+])
+def test_both_halves_in_one_launch_give_the_same_bits(ctx, T, shapes, form):
+    too_many = len(shapes) == 40 and form in ("set", "add")
+    _both_halves(ctx, T, shapes, form, lambda tiles: (tiles == -1) == too_many)
+
+
+@pytest.mark.parametrize("form", ["set", "add"])
+@pytest.mark.parametrize("pair", range(9))
+def test_both_halves_in_every_pair_of_tiles(ctx, pair, form):
+    """The halves' tiles differ, and the larger ones' stages make the LDS: every pair, at sizes around the tiles of each and a
+    contraction shorter than a step."""
+    with route(ctx, F32_TILES + pair):
+        _both_halves(ctx, 65, [(31, 33), (129, 63), (64, 200), (3, 7), (95, 257)], form, lambda tiles: tiles == pair)
+        _both_halves(ctx, 20, [(33, 12), (70, 129)], form, lambda tiles: tiles == pair)
