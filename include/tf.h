@@ -425,9 +425,10 @@ int tf_autofreeze_select(const double* scores, int32_t n, int32_t n_already_froz
  *   n_freeze         0 <= n_freeze <= sum(numel)
  *   stats            optional DEVICE, 3 x int64, 8-byte aligned: {||base||_1, case (0 kept,
  *                    1 added, 2 removed), largest key drawn}; valid after the stream is synchronised
- * Only enqueues (the rank search runs on the device).  Uses device memory owned by the
- * context: calls on one context must not overlap.  Masks of 2^28 elements or more: the first call, and one with
- * a larger mask than any before it, allocates a copy of the mask's size (at most 512 MB), which the context keeps
+ * Only enqueues (the rank search runs on the device), and never waits for the device.  Uses device memory owned by the
+ * context: calls on one context must not overlap.  Masks of 2^28 elements or more are worked on with a copy: the first call, and
+ * the first one with a mask of over twice the size, allocates it (71, 138, 273 or 541 MB for up to 2^29, 2^30, 2^31 or 2^32
+ * elements; at most 1.02 GB if masks of all these sizes come), and the context keeps it
  * until tf_destroy.  A call whose stream is being captured, or for which there is no memory left, works
  * without it: the same result, in twice the time.
  * Errors: TF_ERR_INVALID_ARG, TF_ERR_SHAPE (numel <= 0, sum >= 2^32), TF_ERR_ALIGN

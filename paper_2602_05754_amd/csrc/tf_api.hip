@@ -16,6 +16,10 @@ struct tf_prof_rec {
     hipEvent_t start, stop;
 };
 
+// Sizes, in words, of the copies of their masks that large reconciliations keep: 2^24 << i and some for partly filled words.
+constexpr int kUndoSizes = 4;
+constexpr int64_t undo_words(int i) { return (int64_t(1) << (24 + i)) + (1 << 20); }
+
 struct tf_ctx {
     int device_id;
     int last_hip_error;
@@ -24,8 +28,7 @@ struct tf_ctx {
     std::vector<hipEvent_t> pool;       // events ready for reuse
     tf::RcState* rc_state;              // device memory of tf_reconcile_mask (radix-select state)
     tf::RcState* rc_state_static;       // this device's static scratch array (tf_reconcile_mask_static)
-    uint32_t* rc_undo;                  // device memory of large reconciliations, made when first needed
-    int64_t rc_undo_words;
+    uint32_t* rc_undo[kUndoSizes];      // device memory of large reconciliations, each size made when first needed
     bool lowp_is_rounded_master;        // tf_assume_lowp_is_rounded_master
     double* ew_partials;                // device memory of the score sums' first level (zero between launches)
     int gemm_route;                     // tf_internal_gemm_route
@@ -811,8 +814,7 @@ int tf_create(tf_ctx** out, int device_id) {
     ctx->profiling = false;
     ctx->rc_state = nullptr;
     ctx->rc_state_static = nullptr;
-    ctx->rc_undo = nullptr;
-    ctx->rc_undo_words = 0;
+    for (uint32_t*& undo : ctx->rc_undo) undo = nullptr;
     ctx->lowp_is_rounded_master = false;
     ctx->gemm_route = 0;
     ctx->ew_partials = nullptr;
@@ -839,7 +841,8 @@ int tf_destroy(tf_ctx* ctx) {
     for (tf_prof_rec& r : ctx->recs) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
     for (hipEvent_t e : ctx->pool) (void)hipEventDestroy(e);
     if (ctx->rc_state) (void)hipFree(ctx->rc_state);
-    if (ctx->rc_undo) (void)hipFree(ctx->rc_undo);
+    for (uint32_t* undo : ctx->rc_undo)
+        if (undo) (void)hipFree(undo);
     if (ctx->ew_partials) (void)hipFree(ctx->ew_partials);
     delete ctx;
     return TF_OK;
@@ -1247,30 +1250,30 @@ static int validate_reconcile(int32_t n_tensors, const int64_t* numel, uint32_t*
 constexpr int64_t kGuessFrom = int64_t(1) << 28;
 
 // Room for a copy of the mask, for a reconciliation that guesses its threshold, or null where it does not: masks too
-// small for it; streams that are being captured (a graph keeps its pointers, the context's memory may be replaced by
-// a later, larger call); no memory left.
+// small for it, or of so many small tensors that their words are far more than their elements; streams that are being captured; no memory
+// left.  What a context has once taken it keeps, a larger mask's copy beside a smaller one's: to free one would wait for the device.
 static uint32_t* reconcile_undo(tf_ctx* ctx, hipStream_t stream, int32_t n_tensors, const int64_t* numel) {
     int64_t elements = 0, words = 0;
     for (int32_t i = 0; i < n_tensors; ++i) { elements += numel[i]; words += (numel[i] + 31) / 32; }
     if (elements < kGuessFrom) return nullptr;
+    int size = 0;
+    while (size < kUndoSizes && words > undo_words(size)) ++size;
+    if (size == kUndoSizes) return nullptr;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone) {
         (void)hipGetLastError();
         return nullptr;
     }
-    if (words > ctx->rc_undo_words) {
+    uint32_t*& undo = ctx->rc_undo[size];
+    if (!undo) {
         // another thread's capture has to live through an allocation here
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-        if (ctx->rc_undo) (void)hipFree(ctx->rc_undo);             // waits for the device
-        ctx->rc_undo = nullptr;
-        ctx->rc_undo_words = 0;
-        if (hipMalloc(reinterpret_cast<void**>(&ctx->rc_undo), size_t(words) * 4) == hipSuccess) ctx->rc_undo_words = words;
-        else ctx->rc_undo = nullptr;
+        if (hipMalloc(reinterpret_cast<void**>(&undo), size_t(undo_words(size)) * 4) != hipSuccess) undo = nullptr;
         if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
         (void)hipGetLastError();
     }
-    return ctx->rc_undo;
+    return undo;
 }
 
 // The passes of the reconciliation on the state `st`.  Allocates nothing, on the host or on the

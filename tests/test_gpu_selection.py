@@ -309,3 +309,40 @@ def test_reconcile_large_mask_of_many_tensors(ctx):
     tf.tf_reconcile_mask(ctx, numel, got, sum(numel) // 4, 99)
     tf.tf_reconcile_mask_static(ctx, numel, ref, sum(numel) // 4, 99)
     assert all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_reconcile_never_waits_for_the_device():
+    """The first large mask of a context, and a larger one after it, while another stream is busy: the call
+    is back long before that stream is."""
+    c = tf.Context(0)
+    try:
+        torch.cuda._sleep(1000)
+        cycles, ms = 1 << 20, 0.0
+        while ms < 300:                                                # how many cycles are 0.3 s
+            cycles *= 2
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            torch.cuda._sleep(cycles)
+            b.record()
+            b.synchronize()
+            ms = a.elapsed_time(b)
+        busy, own = torch.cuda.Stream(), torch.cuda.Stream()
+        g = torch.Generator(device="cuda")
+        g.manual_seed(3)
+        for n in (GUESS_FROM, 2 * GUESS_FROM + 1, 5 * GUESS_FROM):
+            words = [_random_words(g, (n + 31) // 32, 0.3)]
+            if n % 32:
+                words[0][-1] &= (1 << n % 32) - 1
+            ref = [w.clone() for w in words]
+            tf.tf_reconcile_mask_static(c, [n], ref, n // 2, 17)
+            torch.cuda.synchronize()
+            done = torch.cuda.Event()
+            with torch.cuda.stream(busy):
+                torch.cuda._sleep(cycles)
+                done.record()
+            tf.tf_reconcile_mask(c, [n], words, n // 2, 17, stream=own)
+            assert not done.query(), f"{n} elements: the call waited"
+            torch.cuda.synchronize()
+            assert torch.equal(words[0], ref[0])
+    finally:
+        c.close()
