@@ -1485,6 +1485,23 @@ extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
 // kGenericShapes x + w, the tiles they had (see kRouteF32), or -1.
 extern "C" int tf_internal_common_tiles(const tf_ctx* ctx) { return ctx ? ctx->common_tiles.load(std::memory_order_relaxed) : -1; }
 
+// Test hook (not part of the public header): how the context's last tf_reconcile_mask went, once the device is done with it: the
+// window of its guess (top halves of keys; [0, 0): nothing guessed), candidates found by the probe, candidates drawn below
+// the window, whether the guess held.
+extern "C" int tf_internal_reconcile_outcome(tf_ctx* ctx, int64_t* out) {
+    if (!ctx || !out) return TF_ERR_INVALID_ARG;
+    RcState* const st = new (std::nothrow) RcState;
+    if (!st) return TF_ERR_WORKSPACE;
+    hipError_t e = use_device(ctx) ? hipDeviceSynchronize() : hipErrorInvalidDevice;
+    if (e == hipSuccess) e = hipMemcpy(st, ctx->rc_state, sizeof(RcState), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) {
+        out[0] = st->window_lo; out[1] = st->window_hi; out[2] = st->probe;
+        out[3] = int64_t(st->drawn); out[4] = st->done;
+    }
+    delete st;
+    return e == hipSuccess ? TF_OK : hip_fail(ctx, e);
+}
+
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
 // aligned) are launched together, by the estimated times: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the
 // generic kernel, behind them those of the kernel for input gradients of few rows and those of the kernel for weight

@@ -3,6 +3,7 @@ reconciliation (App. "Hybrid Variants Algorithm") against the oracle.
 Bounds: squared norms within 1e-12 relative (fp64 sums of exact differences;
 only the order of summation differs); snapshots, masks, counts and the largest
 key drawn bit-exact."""
+import ctypes
 import math
 
 import numpy as np
@@ -258,11 +259,20 @@ def _key_words(numel, seed, test):
     return out
 
 
-@pytest.mark.parametrize("what", ["added", "removed", "all", "same seed", "too few below", "too many below"])
+def _outcome(ctx):
+    """How the context's last reconciliation went: (window of top halves of keys, candidates in the probe, drawn below
+    the window, the guess held)."""
+    out = (ctypes.c_int64 * 5)()
+    assert tf.load_library().tf_internal_reconcile_outcome(ctx.handle, out) == 0
+    return (out[0], out[1]), out[2], out[3], bool(out[4])
+
+
+@pytest.mark.parametrize("what", ["added", "removed", "all", "same seed", "too few below", "too many below", "few candidates"])
 def test_reconcile_large_masks_against_the_general_passes(ctx, what):
     """tf_reconcile_mask guesses the threshold of a large mask, tf_reconcile_mask_static never does.  Masks
     whose candidates have to do with the keys: so much that the probe sees it (`same seed`: every candidate has a key
-    above the last threshold), and so little that only the count shows it and the mask has to be put back."""
+    above the last threshold), and so little that only the count shows it and the mask has to be put back.  And one with so
+    few candidates that the window would be too wide.  The guess is made, dropped by the probe and held or not as it should be."""
     seed = 0x1234_5678_9ABC_DEF1
     numel = [GUESS_FROM - 77_000_003, 5, 77_000_005, 64]
     N = sum(numel)
@@ -276,10 +286,13 @@ def test_reconcile_large_masks_against_the_general_passes(ctx, what):
     nf = N // 2
     if what == "removed":
         nf = N // 10
+    elif what == "few candidates":                                     # one bit in 16
+        base = [w & _random_words(g, w.numel(), 0.2) for w in base]
+        nf = N // 32
     elif what == "all":
         nf = N                                                         # every candidate is drawn
     elif what == "same seed":
-        tf.tf_reconcile_mask_static(ctx, numel, base, N // 3, seed)
+        tf.tf_reconcile_mask_static(ctx, numel, base, 2 * N // 5, seed)
     elif what != "added":                                              # 5 % of the candidates on one side are none
         limit = int((0.5 - 0.3) / 0.7 * (1 << 32))
         side = _key_words(numel, seed, (lambda k: k < limit) if what == "too few below" else (lambda k: k >= limit))
@@ -297,6 +310,53 @@ def test_reconcile_large_masks_against_the_general_passes(ctx, what):
         assert torch.equal(stats, stats_ref)
         for a, b in zip(ref, base):
             a.copy_(b)
+        (lo, hi), probe, drawn, held = _outcome(ctx)
+        need = abs(nf - int(stats[0]))
+        probe_fits = abs(probe - need / 65536) <= 6 * (need / 65536) ** 0.5 + 8
+        if what == "few candidates":
+            assert hi == 0 and not held
+            continue
+        assert 0 < lo < hi <= lo + 64
+        assert probe_fits == (what != "same seed") and held == (what in ("added", "removed", "all"))
+        if held:
+            assert drawn < need and lo <= int(stats[2]) >> 16 < hi
+        elif what == "same seed":
+            assert drawn == 0
+        else:                                                          # 5 % of them in the way: far outside the window
+            assert drawn < 0.98 * need if what == "too few below" else drawn > 1.02 * need
+
+
+def test_reconcile_of_a_large_mask_in_a_graph():
+    """A captured call makes no guess (a graph would keep the address of a copy) and allocates nothing; replays between
+    eager calls, which do guess."""
+    c = tf.Context(0)
+    try:
+        g = torch.Generator(device="cuda")
+        g.manual_seed(11)
+        numel = [GUESS_FROM, 1000]
+        base = [_random_words(g, (n + 31) // 32, 0.3) for n in numel]
+        base[1][-1] &= (1 << 1000 % 32) - 1
+        words, ref = [w.clone() for w in base], [w.clone() for w in base]
+        nf = sum(numel) // 2
+        tf.tf_reconcile_mask_static(c, numel, ref, nf, 5)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            tf.tf_reconcile_mask(c, numel, words, nf, 5)
+        assert torch.cuda.mem_get_info()[0] >= free - (32 << 20)       # (the smallest copy is 71 MB)
+        for replay in range(3):
+            for w, b in zip(words, base):
+                w.copy_(b)
+            graph.replay()
+            assert _outcome(c)[0] == (0, 0) and not _outcome(c)[3]
+            assert all(torch.equal(w, r) for w, r in zip(words, ref)), f"replay {replay}"
+            eager = [w.clone() for w in base]
+            tf.tf_reconcile_mask(c, numel, eager, nf, 5)
+            assert _outcome(c)[3] and all(torch.equal(w, r) for w, r in zip(eager, ref))
+        del graph
+    finally:
+        c.close()
 
 
 def test_reconcile_large_mask_of_many_tensors(ctx):
@@ -308,7 +368,7 @@ def test_reconcile_large_mask_of_many_tensors(ctx):
     got, ref = [w.clone() for w in base], [w.clone() for w in base]
     tf.tf_reconcile_mask(ctx, numel, got, sum(numel) // 4, 99)
     tf.tf_reconcile_mask_static(ctx, numel, ref, sum(numel) // 4, 99)
-    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    assert all(torch.equal(a, b) for a, b in zip(got, ref)) and _outcome(ctx)[3]
 
 
 def test_reconcile_never_waits_for_the_device():
@@ -343,6 +403,6 @@ def test_reconcile_never_waits_for_the_device():
             tf.tf_reconcile_mask(c, [n], words, n // 2, 17, stream=own)
             assert not done.query(), f"{n} elements: the call waited"
             torch.cuda.synchronize()
-            assert torch.equal(words[0], ref[0])
+            assert torch.equal(words[0], ref[0]) and _outcome(c)[3]
     finally:
         c.close()
