@@ -430,7 +430,9 @@ int tf_autofreeze_select(const double* scores, int32_t n, int32_t n_already_froz
  * the first one with a mask of over twice the size, allocates it (71, 138, 273 or 541 MB for up to 2^29, 2^30, 2^31 or 2^32
  * elements; at most 1.02 GB if masks of all these sizes come), and the context keeps it
  * until tf_destroy.  A call whose stream is being captured, or for which there is no memory left, works
- * without it: the same result, in twice the time.
+ * without it: the same result, in twice the time.  The copy pays for masks that have nothing to do with `seed`, whose
+ * candidates below a rank are as many as expected.  One that depends on it by a few percent (drawn before with the same seed, then
+ * changed) takes half as long again as without the copy; a seed of its own for each call avoids that.
  * Errors: TF_ERR_INVALID_ARG, TF_ERR_SHAPE (numel <= 0, sum >= 2^32), TF_ERR_ALIGN
  * (mask pointers not 4-byte, stats not 8-byte aligned), TF_ERR_HIP.
  */
