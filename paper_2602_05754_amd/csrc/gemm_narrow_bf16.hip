@@ -15,7 +15,8 @@
 // us, in brackets with the generic kernel's 64 x 64 to 128 x 128 tiles through registers: two LLaMA-1B blocks (243 MB of
 // weights), 64 tokens 51 (70), 128 61 (78), 200 71 (103), 256 81 (108), 512 118 (150), 1024 218 (253 on 256 x 256 tiles); one
 // LLaMA-8B block, 64 tokens 96 (124), 256 151 (192), 512 207 (243); one block of widths 1024 / 256 / 2816, 64 tokens 16
-// (22); of width 256, 5.2 (8.0).
+// (22); of width 256, 5.2 (8.0).  With three sets of buffers in turn, which leave less of the weights in the memory-side cache, the two LLaMA-1B
+// blocks take 58 (72) at 64 tokens, 80 (104) at 200, 134 (159) at 512.
 //   stage: [row][64 contraction values], 16-byte chunks of a row XOR-swizzled (nt_swizzle).
 // The contraction's last step, where it is no multiple of 64, is the last 64 values with those contracted
 // before masked out, as on the other two kernels: the same sums in the same order, the same bits.

@@ -349,7 +349,10 @@ void find_input_routes(Layout layout, Dtype in_dtype, int route, bool plain, Rou
         if (route >= kRouteNarrow && route < kRouteShort) { *shape = kGenericShapes + route - kRouteNarrow; return 0.0; }
         // (both kernels' estimates leave out what a launch adds, of which the generic kernel has 2 us more: over nine sets of
         // layers of widths 256 to 4096, 32 to 2048 tokens, the choice among all three kernels is 3 % off the best on average,
-        // 16 % faster than without the one for few rows, and at worst 4 % slower, at 768 tokens of a LLaMA-1B block)
+        // 16 % faster than without the one for few rows, and at worst 4 % slower, at 768 tokens of a LLaMA-1B block.  Between 136 and
+        // 391 tokens, which those sets leave out but for 200 and 256, it misses more: us, chosen and fastest, three sets of buffers in turn: two
+        // LLaMA-1B blocks, 264 tokens 112 and 106; one LLaMA-8B block 200 and 184; widths 3328 / 832 / 11000, 136 tokens 154 and 136, 320 tokens
+        // 257 and 199)
         if (narrow_us < us + 2) { *shape = narrow; us = narrow_us; }
         return us;
     };
