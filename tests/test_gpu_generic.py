@@ -262,33 +262,58 @@ def test_input_gradients_of_few_rows(ctx, T, tile):
     assert got[NARROW[tile]] == got[GENERIC]
 
 
+def _across_4_gib(*shape):
+    """Zeros in bf16, a 4 GiB boundary of addresses in their middle."""
+    size = 2 * int(np.prod(shape))
+    room = torch.empty((1 << 32) + size + 16, dtype=torch.uint8, device="cuda")
+    half = size // 2 & ~15
+    boundary = -(-(room.data_ptr() + half) >> 32) << 32
+    first = boundary - half - room.data_ptr()
+    t = room[first:first + size].view(torch.bfloat16).view(*shape).zero_()
+    assert t.data_ptr() >> 32 != (t.data_ptr() + size - 1) >> 32 and t.data_ptr() % 16 == 0
+    return t
+
+
 def test_few_rows_of_pitches_across_4_gib(ctx):
-    """A weight matrix that crosses a 4 GiB boundary of addresses, whose rows are far apart: 64-bit base addresses,
+    """Operands that cross a 4 GiB boundary of addresses, whose rows are far apart: 64-bit base addresses,
     32-bit offsets in a tile."""
     K, N, T = 300, 1 << 19, 65
-    W, dY = torch.zeros(K, N, dtype=torch.bfloat16, device="cuda"), torch.zeros(T, N, dtype=torch.bfloat16, device="cuda")
+    W, dY = _across_4_gib(K, N), _across_4_gib(T, N)
     cols = torch.arange(0, N, 4099, device="cuda")
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
     W[:, cols] = torch.randn((K, cols.numel()), generator=g, device="cuda").bfloat16()
     dY[:, cols] = torch.randn((T, cols.numel()), generator=g, device="cuda").bfloat16()
-    dX = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
-    X = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
-    with route(ctx, NARROW[(256, 128)]):
-        tf.tf_stage_backward(ctx, [(K, N)], T, tf.TF_BF16, [W], [X], [dY], np.ones(1, np.uint8), [dX], [torch.empty_like(W)], tf.TF_BF16)
     ref = dY[:, cols].double() @ W[:, cols].double().t().contiguous()
-    assert rel_fro(host64(dX), ref.cpu().numpy()) < 4e-3
+    X = torch.empty(T, K, dtype=torch.bfloat16, device="cuda")
+    for tile in NARROW.values():
+        dX = torch.full((T, K), 7.0, dtype=torch.bfloat16, device="cuda")
+        with route(ctx, tile):
+            tf.tf_stage_backward(ctx, [(K, N)], T, tf.TF_BF16, [W], [X], [dY], np.ones(1, np.uint8), [dX], [torch.empty_like(W)], tf.TF_BF16)
+        assert rel_fro(host64(dX), ref.cpu().numpy()) < 4e-3
 
 
-@pytest.mark.parametrize("dw,accumulate", [("bf16", False), ("f32", False), ("f32", True)])
-@pytest.mark.parametrize("tile", sorted(SHORT))
+def test_few_tokens_of_pitches_across_4_gib(ctx):
+    """The same for the weight gradients' operands, and gradients that cross a boundary."""
+    K, N, T = 72, 1 << 19, 100
+    X, dY = torch.randn((T, K), device="cuda").bfloat16(), _across_4_gib(T, N)
+    dY[:, ::3] = torch.randn((T, -(-N // 3)), device="cuda").bfloat16()
+    W, dX, dW = torch.zeros(K, N, dtype=torch.bfloat16, device="cuda"), torch.empty(T, K, dtype=torch.bfloat16, device="cuda"), _across_4_gib(K, N)
+    ref = X.float().t().contiguous() @ dY.float()
+    for tile in SHORT.values():
+        dW.fill_(7.0)
+        with route(ctx, tile):
+            tf.tf_stage_backward(ctx, [(K, N)], T, tf.TF_BF16, [W], [X], [dY], None, [dX], [dW], tf.TF_BF16)
+        assert float((dW.float() - ref).norm() / ref.norm()) < 4e-3
+
+
+@pytest.mark.parametrize("tile,dw,accumulate", [(tile, dw, add) for tile in sorted(SHORT) for dw, add in (("bf16", False), ("f32", False), ("f32", True))
+                                                if not (add and tile == (256, 128))])          # (that tile does not add)
 @pytest.mark.parametrize("T", [64, 65, 96, 97, 128, 200, 257, 1000])
 def test_weight_gradients_of_few_tokens(ctx, T, tile, dw, accumulate):
     """The kernel for few tokens where it can go wrong: rows and columns around its tiles, contractions of two steps (fewer
     than it has stages), of three and more, 1, 8, 32 or 33 values more than whole ones.  The bits are the generic kernel's; an
     infinity stays in its row and column; nothing outside the outputs is written."""
-    if accumulate and tile == (256, 128):
-        pytest.skip("the largest tile does not add")
     shapes = [(8, 8), (64, 136), (128, 128), (136, 64), (120, 264), (264, 120), (1096, 72), (256, 512)]
     W, X, dY = _random(shapes, T, "bf16", T)
     X[5][T - 1, 263], dY[5][T - 1, :] = float("inf"), dY[5][T - 1, :].abs() + 1e-3
