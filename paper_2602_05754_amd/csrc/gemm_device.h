@@ -1,5 +1,6 @@
 // What the matrix-core GEMMs use on the device: vector types, the LDS address space, compile-time loops, the
-// rounding to bf16, the swizzle of row-major stages, direct loads into LDS and the wait in front of the sums.
+// rounding to bf16, the swizzle of row-major stages, direct loads into LDS and the waits for them, the order of tiles and the wait in
+// front of the sums.
 #pragma once
 #include "tf_internal.h"
 
@@ -73,6 +74,27 @@ __device__ __forceinline__ void direct_load_16B(const char* gbase, uint32_t voff
 }
 __device__ __forceinline__ void wait_direct_loads() {
     __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0), other counters untouched
+}
+// vmcnt(n), other counters untouched
+template <int n>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(n < 64, "six bits");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
+}
+// All but the `stages` youngest stages of kPer loads, and kAfter loads behind them, have arrived.
+template <int kPer, int kMost, int kAfter = 0>
+__device__ __forceinline__ void wait_stages(int stages) {
+    if (stages >= kMost) wait_loads<kPer * kMost + kAfter>();
+    else if constexpr (kMost > 0) wait_stages<kPer, kMost - 1, kAfter>(stages);
+}
+
+// Block number -> logical tile of a launch with a block per tile: runs of 8 consecutive tiles stay on one XCD (block b
+// runs on XCD b % 8).
+__device__ __forceinline__ int logical_tile(int b, int nb) {
+    constexpr int kXcdRun = 8, span = kXcds * kXcdRun;
+    if (b >= (nb / span) * span) return b;
+    const int xcd = b % kXcds, idx = b / kXcds;
+    return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
 }
 
 // Between the last matrix instruction and the first vector instruction that reads its result.  Left to

@@ -35,7 +35,6 @@ namespace {
 constexpr int kThreads = 256;           // four waves, 2 x 2 over the tile
 constexpr int kStepBytes = 128;         // contraction bytes of an operand row per step
 constexpr int kDepth = 2;               // steps whose pieces are on their way in registers
-constexpr int kXcdRun = 8;              // consecutive logical tiles kept on one XCD
 constexpr int kGroupM = 8;              // tile rows per L2 locality group
 
 typedef f32x4 F4any __attribute__((aligned(4)));
@@ -187,14 +186,6 @@ struct Operand {
         return x;
     }
 };
-
-// Block number -> logical tile: runs of consecutive tiles stay on one XCD (block b runs on XCD b % 8).
-__device__ __forceinline__ int logical_tile(int b, int nb) {
-    const int span = kXcds * kXcdRun;
-    if (b >= (nb / span) * span) return b;
-    const int xcd = b % kXcds, idx = b / kXcds;
-    return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
-}
 
 // The output is stored past the caches.  What that is for are weight gradients of few tokens, as large as the
 // weights, which they push out of the memory-side cache: a whole call, us, in brackets with ordinary stores: 32 tokens,

@@ -26,7 +26,6 @@ namespace tf {
 namespace {
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kXcdRun = 8;                      // consecutive logical tiles kept on one XCD
 
 template <int kRows, int kCols>
 struct Narrow {
@@ -40,25 +39,6 @@ struct Narrow {
     static_assert(kLoads % 2 == 0 && kFragA * kFragB >= kLoads / 2, "a load behind an MFMA");
     static_assert(kWaves * kRowsW * kColsW * 2 <= kLds, "the output is turned around in the stages");
 };
-
-// vmcnt(n), other counters untouched
-template <int n>
-__device__ __forceinline__ void wait_loads() {
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
-}
-// All but the `stages` youngest stages of kPer loads have arrived.
-template <int kPer, int kMost>
-__device__ __forceinline__ void wait_stages(int stages) {
-    if (stages >= kMost) wait_loads<kPer * kMost>();
-    else if constexpr (kMost > 0) wait_stages<kPer, kMost - 1>(stages);
-}
-
-__device__ __forceinline__ int logical_tile(int b, int nb) {
-    const int span = kXcds * kXcdRun;
-    if (b >= (nb / span) * span) return b;
-    const int xcd = b % kXcds, idx = b / kXcds;
-    return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
-}
 
 template <int kRows, int kCols>
 __global__ __launch_bounds__(kThreads, 2) void gemm_narrow_kernel(GemmBatch batch) {       // (2: the sums stay in vector registers)

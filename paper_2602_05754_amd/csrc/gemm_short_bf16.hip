@@ -26,7 +26,6 @@ namespace tf {
 namespace {
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kXcdRun = 8;                      // consecutive logical tiles kept on one XCD
 constexpr int kGroupM = 8;                      // tile rows per L2 locality group
 
 enum Out { kBf16 = 0, kF32 = 1, kAdd = 2 };
@@ -41,26 +40,6 @@ struct Short {
     static constexpr int kDeep = 3;                                                 // stages: two steps ahead
     static constexpr int kLds = kDeep * kStage;
 };
-
-// vmcnt(n), other counters untouched
-template <int n>
-__device__ __forceinline__ void wait_loads() {
-    static_assert(n < 64, "six bits");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | ((n >> 4) << 14));
-}
-// All but the `stages` youngest stages of kPer loads, and kAfter loads behind them, have arrived.
-template <int kPer, int kMost, int kAfter>
-__device__ __forceinline__ void wait_stages(int stages) {
-    if (stages >= kMost) wait_loads<kPer * kMost + kAfter>();
-    else if constexpr (kMost > 0) wait_stages<kPer, kMost - 1, kAfter>(stages);
-}
-
-__device__ __forceinline__ int logical_tile(int b, int nb) {
-    const int span = kXcds * kXcdRun;
-    if (b >= (nb / span) * span) return b;
-    const int xcd = b % kXcds, idx = b / kXcds;
-    return ((idx / kXcdRun) * kXcds + xcd) * kXcdRun + idx % kXcdRun;
-}
 
 // Stage: [32 contraction rows][rows of the operand], as in memory; 32-byte units of a row XOR-swizzled.  The transpose
 // read of a 16-row block takes a unit of contraction rows 8 G + x, x = 0..3, G = lane / 16, 32 lanes at a time: 8 rows
