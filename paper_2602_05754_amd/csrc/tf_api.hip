@@ -240,7 +240,9 @@ inline int output_kind(int out_bytes, bool accumulate) { return out_bytes == 2 ?
 // next tile whenever it is done with one; longer chains end in rounds (kRounds): 256 x 256 tiles, 172 of them 73 us at 3001 tokens, 344 144.
 // The choice among all three kernels, over 708 launches of widths 256 to 4096, 64 to 8192 tokens: 1.6 % more than the fastest on average (with
 // the fit to few tokens alone, 7 % from 2100 tokens on; of the other two kernels the better one, 8 to 21 %), at worst 1.34 times (1280 / 640 / 3400,
-// 320 tokens, fp32: 37 us, 28).
+// 320 tokens, fp32: 37 us, 28).  Against the choice between those two it takes 12 % less on average, and 3 to 18 % more in some 20 launches
+// whose tiles just fill the units once (widths 1024 / 4096 without k and v, 128 tokens, bf16: 16.3 us, 13.8): counting rounds there as well
+// lost more elsewhere.
 constexpr int kRounds = 1024;
 double tiles_per_unit(double tiles, int64_t longest) {
     tiles /= compute_units();
