@@ -133,7 +133,9 @@ const char* tf_version(void);
  *                (the 1/M of the update rule is applied by tf_masked_adamw's
  *                grad_scale) and requires dw_dtype == TF_F32.
  *   Products accumulate in fp32; bf16 outputs are rounded to nearest even once.
- *   n_layers == 0 is a no-op.  With io_dtype TF_F32 the arithmetic is true fp32.
+ *   n_layers == 0 is a no-op.  With io_dtype TF_F32 nothing is rounded to less than
+ *   fp32: products are those of fp32 values (large launches form them from the values'
+ *   bf16 pieces, all 24 bits of them, with no larger error), sums have 32 bits or 64.
  *   With io_dtype TF_BF16 a layer's outputs depend on that layer alone, bit for bit.
  *   With TF_F32 their last bits also depend on the other layers of the call: the
  *   sums of a launch - all dX, or the dW of all unfrozen layers - are formed in 64

@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtf.so")
-SOURCES = ["tf_api.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip", "gemm_mfma_bf16.hip", "elementwise.hip", "selection.hip", "schedule_lp.hip"]
+SOURCES = ["tf_api.hip", "gemm_generic.hip", "gemm_split_f32.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip", "gemm_mfma_bf16.hip", "elementwise.hip", "selection.hip", "schedule_lp.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -159,7 +159,7 @@ def mfma_hazards(asm_text: str) -> list:
 
 def check_generated_code(hipcc: str, extra: list) -> None:
     flags = [f for f in HIPCC_FLAGS if f not in ("-fPIC", "-shared", "-Rpass-analysis=kernel-resource-usage")]
-    sources = ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip")
+    sources = ("gemm_mfma_bf16.hip", "gemm_generic.hip", "gemm_split_f32.hip", "gemm_narrow_bf16.hip", "gemm_short_bf16.hip")
     assemble = lambda source: subprocess.run([hipcc] + flags + extra + ["-S", "--cuda-device-only", os.path.join(CSRC, source), "-o", "-"],
                                              capture_output=True, text=True)
     with ThreadPoolExecutor(len(sources)) as pool:

@@ -1,0 +1,414 @@
+// fp32 products on the bf16 matrix cores, for launches of the fp32 configuration that the fp32 matrix pipe bounds (TimelyFreeze
+// Sec. 3.2.1, both halves of a backward action).
+//
+// A value is the sum of three bf16 ones, its upper, middle and lower 8 bits: x = x0 + x1 + x2, exactly.  Of the nine products of two
+// values' pieces the six of 2^-16 and more are contracted, 32 values per instruction, in 96 cycles per 16 x 16 block where
+// v_mfma_f32_16x16x4_f32 takes 256; the three left out are 2^-24 of the product and less.  A step's products are summed by themselves, the
+// small ones first, and then added to the sums so far, as in the generic kernel.  Errors against 64 bits, in brackets those of the
+// generic kernel's sums in 32 bits, width 1024: contraction 200 9.1e-8 (1.2e-7), 1000 1.3e-7 (1.5e-7), 2731 1.9e-7 (2.0e-7).  (All six chained
+// into one sum 2.2e-7, 3.2e-7: the instruction rounds four times, after every 8 values.)
+//
+// What bounds it: the vector instructions that split, 11 per pair of values, and add, beside the matrix instructions.  A wave's
+// own two per matrix instruction cost nothing, a third 4 cycles; another wave's get every eighth cycle or so while matrix
+// instructions run.  So larger tiles are faster - a value is split once per tile and step - and every wave does everything: loads, splits,
+// stores to LDS and contracts, its splitting spread evenly behind its matrix instructions, one barrier per step.  256 x 128 tiles
+// of eight waves have 2.1 vector instructions per matrix instruction, 128 x 128 ones 2.6.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us:
+// input gradients 236 (128 x 128 tiles 273, generic kernel 370), weight gradients 245 (281, 368), both in one launch 463 (740).
+// Measured besides, the same input gradients: two workgroups of 128 x 128 tiles per unit that split and contract in turn 270; four
+// waves that load and split beside four that contract 267; the remainders by v_dot2_f32_bf16, exact and half as many instructions, but
+// on the matrix cores' hardware: 290; 64 x 64 tiles 320.
+#include "gemm_tile.h"
+
+#include <algorithm>
+
+namespace tf {
+namespace {
+
+constexpr int kPiecesOf = 3;                    // bf16 pieces of a value
+constexpr int kSplitThreads = 512;              // eight waves
+constexpr int kBK = 32;                         // contraction values per step
+typedef U4 U4any4 __attribute__((aligned(4)));
+
+// Takes the next bf16 pieces off two values; returns them packed.  (The upper 16 bits: a piece is never larger than the value, so
+// that no piece of a finite value is infinite.)
+__device__ __forceinline__ uint32_t take_piece(uint32_t& x0, uint32_t& x1, bool last) {
+    const uint32_t piece = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+    if (!last) {
+        x0 = __float_as_uint(__uint_as_float(x0) - __uint_as_float(x0 & 0xffff0000u));
+        x1 = __float_as_uint(__uint_as_float(x1) - __uint_as_float(x1 & 0xffff0000u));
+    }
+    return piece;
+}
+
+// One operand of a workgroup's tile: kWaves waves contract 16 kFrags rows of it each.
+template <bool kContig, int kWaves, int kFrags>
+struct SplitOperand {
+    static constexpr int kRows = 16 * kWaves * kFrags;
+    static constexpr int kLoads = kRows * kBK / 4 / kSplitThreads;      // 16-byte loads per thread and step
+    static constexpr int kAcross = kContig ? kBK / 4 : kRows / 4;       // loads across a stage row
+    static constexpr int kDown = kSplitThreads / kAcross;               // a thread's loads lie that many stage rows apart
+    static constexpr bool kPadded = !kContig && kRows == 128;           // (256 rows, padded as well, would not fit)
+    static constexpr int kPitch = kContig ? kBK * 2 : kRows * 2 + (kPadded ? 32 : 0);     // bytes of a stage row
+    static constexpr int kPlane = kContig ? kRows * kPitch : kBK * kPitch + (kPadded ? kBK / 8 * 128 : 0);    // of one bf16 piece of a stage
+    static constexpr int kStageBytes = kPiecesOf * kPlane;
+    static_assert(kLoads >= 1 && kRows >= 128, "every thread loads; a contraction row covers all banks");
+
+    const char* matrix;
+    int64_t unit;               // bytes from one contraction value to the next
+    uint32_t off[kLoads];
+    int extent, origin;
+    int to, from;               // bytes inside a stage: of load 0's first piece, of this lane's part of a wave's first fragment
+
+    __device__ __forceinline__ SplitOperand(const void* base, int64_t ld, int ext, int org, int w) : extent(ext), origin(org) {
+        const int thread = int(threadIdx.x), c = thread % kAcross;
+        const int lane = threadIdx.x & 63, q = lane >> 4;
+        matrix = static_cast<const char*>(base) + (kContig ? int64_t(origin) * ld * 4 : 0);
+        unit = kContig ? 4 : ld * 4;
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i)
+            off[i] = kContig ? uint32_t(min(row(i, thread), extent - 1 - origin)) * uint32_t(ld * 4) + c * 16 : uint32_t(row(i, thread)) * uint32_t(ld * 4) + uint32_t(col(thread)) * 4;
+        if (kContig) {
+            to = row(0, thread) * kPitch + c * 8;
+            from = (w * kFrags * 16 + (lane & 15)) * kPitch + q * 16;
+        } else {
+            const int block = c >> 2, r = 8 * q + ((lane & 15) >> 2);
+            to = at(block % kFrags, block / kFrags, row(0, thread)) + ((c & 3) << 3);
+            from = at(0, w, r) + ((lane & 3) << 3);
+        }
+    }
+    __device__ __forceinline__ static int row(int i, int thread) { return thread / kAcross + i * kDown; }
+    // kTN stage: byte offset of contraction row r, wave w's i-th 16-row block.  A transpose read takes 32 bytes (a unit) of contraction
+    // rows 8 G + x, x = 0..3, G = lane / 16, 32 lanes at a time: 8 rows whose units must fall into different banks.  128 rows: a unit of
+    // padding per row and four per eight rows; 256 rows: units XOR-swizzled, block i of wave w in unit kWaves i + w.
+    __device__ __forceinline__ static int at(int i, int w, int r) {
+        const int u = kWaves * i + w;
+        if (kPadded) return r * kPitch + (r >> 3) * 128 + u * 32;
+        return r * kPitch + (((u & 7) ^ (4 * ((r >> 3) & 1) + (r & 3))) << 5) + ((u >> 3) << 8);
+    }
+    // kTN: first column of a thread's loads; elements by which load i of the contraction's last row would run over the end of the matrix
+    __device__ __forceinline__ int col(int thread) const {
+        const int c = origin + thread % kAcross * 4;
+        return c < extent ? c : 0;
+    }
+    __device__ __forceinline__ int over(int i, int thread) const { return !kContig && row(i, thread) == kBK - 1 ? max(col(thread) + 4 - extent, 0) : 0; }
+    // (for what is worked out where it is needed, not once in front of the loop into registers that it has not)
+    __device__ __forceinline__ static int this_thread() {
+        int t = int(threadIdx.x);
+        asm volatile("" : "+v"(t));
+        return t;
+    }
+
+    // Load i of the 32 contraction values from k on; `last`: they are the contraction's last ones.
+    __device__ __forceinline__ U4 load(int i, int k, bool last) const {
+        uint32_t o = kContig ? off[i] : off[i] - (over(i, this_thread()) * 4 & -int(last));
+        asm volatile("" : "+v"(o));             // (a 32-bit offset to a scalar base: widened outside of the loop it takes two registers and an addition)
+        return *reinterpret_cast<const U4any4*>(matrix + k * unit + o);
+    }
+    // What it fetched, in its place, the first `back` contraction values zero.  (No branches: selections only.)
+    __device__ __forceinline__ U4 finish(int i, U4 v, int back, bool last) const {
+        const int thread = this_thread();
+        if constexpr (kContig) {
+            const int n = back - thread % kAcross * 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = e < n ? 0 : v[e];
+        } else {
+            const int n = over(i, thread) & -int(last);
+            v[0] = n & 1 ? v[1] : v[0]; v[1] = n & 1 ? v[2] : v[1]; v[2] = n & 1 ? v[3] : v[2];
+            v[0] = n & 2 ? v[2] : v[0]; v[1] = n & 2 ? v[3] : v[1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = row(i, thread) < back ? 0 : v[e];
+        }
+        return v;
+    }
+    __device__ __forceinline__ char* place(char* stage, int i, int t) const {        // of bf16 piece t of load i
+        static_assert(kContig || kDown % 8 == 0, "rows 8 apart differ in one bit of the swizzle");
+        if (kPadded) return stage + to + (t * kPlane + i * kDown * kPitch + i * kDown / 8 * 128);
+        const int flip = kContig ? 0 : ((i * kDown >> 3) & 1) << 7;
+        return stage + (to ^ flip) + (t * kPlane + i * kDown * kPitch);
+    }
+    __device__ __forceinline__ bf16x8 fragment(const char* stage, int i, int t) const {
+        if (kContig) return *reinterpret_cast<const bf16x8*>(stage + from + (t * kPlane + i * 16 * kPitch));
+        const char* a = kPadded ? stage + from + (t * kPlane + kWaves * i * 32)
+                                : stage + (from ^ ((kWaves * i & 7) << 5)) + (t * kPlane + ((kWaves * i >> 3) << 8));
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsBf16x4Ptr)TF_LPTR(a));
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsBf16x4Ptr)TF_LPTR(a + 4 * kPitch));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+};
+
+// (the layout kTN has the larger stages)
+template <int kTileM, int kTileN, int kWavesM>
+constexpr int split_lds() {
+    return 2 * (SplitOperand<false, kWavesM, kTileM / 16 / kWavesM>::kStageBytes + SplitOperand<false, 8 / kWavesM, kTileN / 16 / (8 / kWavesM)>::kStageBytes);
+}
+
+template <bool kContig, int kTileM, int kTileN, int kWavesM>
+__device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, bool add, char* const lds) {
+    constexpr int kWavesN = kSplitThreads / 64 / kWavesM, kFragA = kTileM / kWavesM / 16, kFragB = kTileN / kWavesN / 16;
+    typedef SplitOperand<kContig, kWavesM, kFragA> OpA;
+    typedef SplitOperand<kContig, kWavesN, kFragB> OpB;
+    constexpr int kStage = OpA::kStageBytes + OpB::kStageBytes, kLoads = OpA::kLoads + OpB::kLoads;
+    static_assert(kFragA % 2 == 0, "the last row of a step and the first of the next hold piece 0 in different registers");
+    static_assert(kTileM * kTileN * 4 <= 2 * kStage, "the sums are turned around in the stages");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / kWavesN, wn = wave % kWavesN;
+    const int M = P.M, N = P.N, Kc = P.Kc, m0 = at.m, n0 = at.n;
+    const int steps = (Kc + kBK - 1) / kBK, back = steps * kBK - Kc;
+    f32x4 acc[kFragA][kFragB];
+#pragma unroll
+    for (int i = 0; i < kFragA; ++i)
+#pragma unroll
+        for (int j = 0; j < kFragB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const OpA a(P.A, P.lda, M, m0, wm);
+    const OpB b(P.B, P.ldb, N, n0, wn);
+    uint32_t lost = 0;              // its lower half: bits that are in none of the three pieces (of values below 2^-110)
+    U4 raw[kLoads];                 // values of the steps ahead: load 0 of the next but one, the others of the next
+    uint32_t packed[2];
+    // (Step `steps` - 1 is the contraction's last 32 values, those contracted before masked out; what would come after it is that
+    // step again, for nothing.)
+    auto load = [&](auto i, int s) __attribute__((always_inline)) {
+        const int k = min(s * kBK, Kc - kBK);
+        const bool last = s >= steps - 1;
+        if constexpr (i < OpA::kLoads) raw[i] = a.load(i, k, last);
+        else raw[i] = b.load(i - OpA::kLoads, k, last);
+    };
+    auto load_whole = [&](auto i, int s) __attribute__((always_inline)) {
+        if constexpr (i < OpA::kLoads) raw[i] = a.load(i, s * kBK, false);
+        else raw[i] = b.load(i - OpA::kLoads, s * kBK, false);
+    };
+    auto finish = [&](auto i, int s) __attribute__((always_inline)) {
+        const bool last = s >= steps - 1;
+        if constexpr (i < OpA::kLoads) raw[i] = a.finish(i, raw[i], last ? back : 0, last);
+        else raw[i] = b.finish(i - OpA::kLoads, raw[i], last ? back : 0, last);
+    };
+    // part n of 6 of splitting load i into a stage
+    constexpr int kParts = 2 * kPiecesOf;
+    auto split = [&](auto i, auto n, char* stage) __attribute__((always_inline)) {
+        constexpr int t = n / 2, h = n % 2;
+        uint32_t x0 = raw[i][2 * h], x1 = raw[i][2 * h + 1];
+        packed[h] = take_piece(x0, x1, t == kPiecesOf - 1);
+        // (left to itself the compiler gathers these at a step's end, with all of their operands held until then)
+        if constexpr (t == kPiecesOf - 1) asm volatile("v_or3_b32 %0, %0, %1, %2" : "+v"(lost) : "v"(x0), "v"(x1));
+        raw[i][2 * h] = x0;
+        raw[i][2 * h + 1] = x1;
+        if constexpr (h == 1) {
+            char* const to = i < OpA::kLoads ? a.place(stage, i, t) : b.place(stage + OpA::kStageBytes, i - OpA::kLoads, t);
+            *reinterpret_cast<U2*>(to) = U2{packed[0], packed[1]};
+        }
+    };
+    bf16x8 fb[kFragB][kPiecesOf], fa[2], fa_low[2];     // of A: piece 0 of this row of blocks and of the next; pieces 1 and 2
+    f32x4 part[1][kFragB];                              // a row's products of one step
+    auto read_a = [&](const char* stage, auto i, auto t) __attribute__((always_inline)) {
+        if constexpr (t == 0) fa[i % 2] = a.fragment(stage, i, 0);
+        else fa_low[t - 1] = a.fragment(stage, i, t);
+    };
+    auto read_b = [&](const char* stage, auto j, auto t) __attribute__((always_inline)) { fb[j][t] = b.fragment(stage + OpA::kStageBytes, j, t); };
+    constexpr std::integral_constant<int, 0> k0;
+
+    auto split_load = [&](auto i, int s, char* stage) __attribute__((always_inline)) {
+        finish(i, s);
+        static_for<kParts>([&](auto n) __attribute__((always_inline)) { split(i, n, stage); });
+    };
+    // Step s.  kWhole: whatever is loaded and split meanwhile are whole steps, and the splitting rides behind the matrix instructions.
+    // (In a tile's last four steps it does not: there are not registers enough for what those loads take besides.)
+    auto step = [&](int s, auto whole) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole)::value;
+        char* const now = lds + (s & 1) * kStage;
+        char* const then = lds + (~s & 1) * kStage;
+        constexpr int kRow = 6 * kFragB, kBefore = (kFragA - 1) * kRow;          // MFMAs of a row, and in front of the barrier
+        if constexpr (!kWhole) static_for<kLoads - 1>([&](auto i) __attribute__((always_inline)) {
+            constexpr std::integral_constant<int, i + 1> which;
+            split_load(which, s + 1, then);
+            load(which, s + 2);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_for<kFragA * kRow>([&](auto m) __attribute__((always_inline)) {
+            constexpr int order[6][2] = {{0, 2}, {1, 1}, {0, 1}, {2, 0}, {1, 0}, {0, 0}};        // pieces of A and B
+            constexpr int i = m / kRow, n = m % kRow, g = n / kFragB, j = n % kFragB, pa = order[g][0], pb = order[g][1];
+            // the sums of the row before (the last one: of the step before): four matrix instructions or so after the last of them
+            if constexpr (g == 0) acc[(i + kFragA - 1) % kFragA][j] += part[0][j];
+            part[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], pa == 0 ? fa[i % 2] : fa_low[pa == 0 ? 0 : pa - 1], g == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[0][j], 0, 0, 0);
+            // the next fragments, each where the one in its place has been used
+            constexpr std::integral_constant<int, (i + 1) % kFragA> row;
+            constexpr std::integral_constant<int, 1> k1;
+            constexpr std::integral_constant<int, 2> k2;
+            char* const from_a = i + 1 < kFragA ? now : then;
+            if constexpr (g == 1 && j == 0) read_a(from_a, row, k0);
+            if constexpr (g == 4 && j == 0) read_a(from_a, row, k2);
+            if constexpr (g == 5 && j == 0) read_a(from_a, row, k1);
+            if constexpr (i + 1 == kFragA) {
+                if constexpr (g == 1) read_b(then, j, k2);
+                if constexpr (g == 3) read_b(then, j, k1);
+                if constexpr (g == 5) read_b(then, j, k0);
+            }
+            // the values of the steps ahead: load 0 of step s + 2 behind the last row, the others of step s + 1 before it
+            constexpr int kItems = i + 1 < kFragA ? (kLoads - 1) * kParts : kParts, kOver = i + 1 < kFragA ? kBefore : kRow, x = i + 1 < kFragA ? int(m) : n;
+            constexpr int from = x * kItems / kOver, to = (x + 1) * kItems / kOver;
+            if constexpr (kWhole) static_for<to - from>([&](auto d) __attribute__((always_inline)) {
+                constexpr int item = from + d;
+                constexpr std::integral_constant<int, i + 1 < kFragA ? 1 + item / kParts : 0> which;
+                constexpr std::integral_constant<int, item % kParts> n_th;
+                const int ahead = i + 1 < kFragA ? s + 1 : s + 2;
+                split(which, n_th, i + 1 < kFragA ? then : now);
+                if constexpr (n_th == kParts - 1) load_whole(which, ahead + 1);
+            });
+            if constexpr (m == kBefore - 1) __syncthreads();        // step s + 1 is there, step s has been read
+            __builtin_amdgcn_sched_barrier(4);         // (scalar instructions may pass)
+        });
+        if constexpr (!kWhole) {
+            split_load(k0, s + 2, now);
+            __builtin_amdgcn_sched_barrier(0);
+            load(k0, s + 3);
+        }
+    };
+
+    auto each_load = [&](auto f) __attribute__((always_inline)) {
+        static_for<kLoads>([&](auto i) __attribute__((always_inline)) {
+            f(i);
+            __builtin_amdgcn_sched_barrier(0);      // in the order in which they are waited for
+        });
+    };
+    each_load([&](auto i) __attribute__((always_inline)) { load(i, 0); });
+    each_load([&](auto i) __attribute__((always_inline)) { split_load(i, 0, lds); });
+    load(k0, 1);
+    split_load(k0, 1, lds + kStage);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<kLoads - 1>([&](auto i) __attribute__((always_inline)) {
+        load(std::integral_constant<int, i + 1>{}, 1);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    load(k0, 2);
+    __syncthreads();
+    static_for<kPiecesOf>([&](auto t) __attribute__((always_inline)) { read_a(lds, k0, t); });
+    static_for<kPiecesOf * kFragB>([&](auto n) __attribute__((always_inline)) {
+        read_b(lds, std::integral_constant<int, n % kFragB>{}, std::integral_constant<int, kPiecesOf - 1 - n / kFragB>{});
+    });
+#pragma unroll
+    for (int j = 0; j < kFragB; ++j) part[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int s = 0;
+    for (; s < steps - 4; ++s) step(s, std::true_type{});
+    for (; s < steps; ++s) step(s, std::false_type{});
+    wait_for_sums(part);
+#pragma unroll
+    for (int j = 0; j < kFragB; ++j) acc[kFragA - 1][j] += part[0][j];
+    __syncthreads();
+
+    // What three pieces cannot hold: an infinity has met zeros among the other value's pieces, a sum of pieces may have left the range
+    // where the sum does not, a piece below bf16's smallest value has lost bits.  Such a tile is computed again from fp32 products.
+    bool odd = (lost & 0xffffu) != 0;
+#pragma unroll
+    for (int i = 0; i < kFragA; ++i)
+#pragma unroll
+        for (int j = 0; j < kFragB; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd = odd || !(__builtin_fabsf(acc[i][j][e]) < __builtin_huge_valf());
+    int* const flags = reinterpret_cast<int*>(lds);
+    const bool wave_odd = __ballot(odd) != 0;
+    if (lane == 0) flags[wave] = wave_odd;
+    __syncthreads();
+    bool redo = false;
+#pragma unroll
+    for (int w = 0; w < kSplitThreads / 64; ++w) redo = redo || flags[w] != 0;
+    __syncthreads();
+    if (redo) {
+        // (beyond the matrix: nothing is stored)
+        constexpr int kSub = 2 * (32 + 64) * kStepBytes;
+        const int half = wave >> 2;
+        for (int m = m0; m < m0 + kTileM && m < M; m += 64)
+            for (int n = n0; n < n0 + kTileN && n < N; n += 64) {
+                if (add) contract_tile<float, kContig, false, true, 32, 64>(P, TileAt{m + 32 * half, n}, lds + half * kSub);
+                else contract_tile<float, kContig, false, false, 32, 64>(P, TileAt{m + 32 * half, n}, lds + half * kSub);
+                __syncthreads();
+            }
+        return;
+    }
+    constexpr int kRow = kTileN * 4, kTurn = 15;
+#pragma unroll
+    for (int i = 0; i < kFragA; ++i)
+#pragma unroll
+        for (int j = 0; j < kFragB; ++j) {
+            const int r = wm * (kTileM / kWavesM) + 16 * i + (lane & 15), c = wn * (kTileN / kWavesN / 4) + 4 * j + (lane >> 4);
+            *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
+        }
+    __syncthreads();
+    constexpr int kLanes = kTileN / 4, kRowsPerPass = kSplitThreads / kLanes;
+    const int c = int(threadIdx.x) % kLanes, n = n0 + c * 4;
+#pragma unroll
+    for (int r0 = 0; r0 < kTileM; r0 += kRowsPerPass) {
+        const int r = r0 + int(threadIdx.x) / kLanes, m = m0 + r;
+        f32x4 v = *reinterpret_cast<const f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4));
+        if (m >= M || n >= N) continue;
+        float* out = static_cast<float*>(P.C) + int64_t(m) * N + n;
+        if (n + 4 <= N) {
+            if (add) v += *reinterpret_cast<const F4any*>(out);
+            __builtin_nontemporal_store(v, reinterpret_cast<F4any*>(out));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < N) out[e] = add ? out[e] + v[e] : v[e];
+        }
+    }
+}
+
+template <int kTileM, int kTileN, int kWavesM>
+__global__ __launch_bounds__(kSplitThreads, 2) void gemm_split_kernel(GemmBatch batch) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int lt = logical_tile(int(blockIdx.x), batch.total_tiles);
+    const int pi = find_problem(batch, lt);
+    const GemmProblem& P = batch.p[pi];
+    const TileAt at = tile_at<kTileM, kTileN>(P, lt);
+    if (batch.tn >> pi & 1) contract_split<false, kTileM, kTileN, kWavesM>(P, at, batch.add >> pi & 1, lds);
+    else contract_split<true, kTileM, kTileN, kWavesM>(P, at, batch.add >> pi & 1, lds);
+}
+
+template <int kTileM, int kTileN, int kWavesM>
+hipError_t launch_shape(hipStream_t stream, const GemmBatch& batch) {
+    auto kern = gemm_split_kernel<kTileM, kTileN, kWavesM>;
+    constexpr int kLds = split_lds<kTileM, kTileN, kWavesM>();
+    // more than 64 KB of dynamic LDS are allowed once per kernel and device
+    constexpr int kMaxDevices = 64;
+    static bool lds_allowed[kMaxDevices] = {false};
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) dev = -1;
+    if (dev < 0 || !lds_allowed[dev]) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        if (e != hipSuccess) return e;
+        if (dev >= 0) lds_allowed[dev] = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(batch.total_tiles), dim3(kSplitThreads), kLds, stream, batch);
+    return hipGetLastError();
+}
+
+// The launch shapes: a step's share of a compute unit when all are busy, and its time in a launch's longest chain; what a tile and
+// the longest chain cost beside their steps; how much of the smaller of the two is left; a launch.
+constexpr SplitShape kShapes[kSplitShapes] = {{128, 128, 1.38f, 1.05f, 4.6f, 1.5f, 0.07f, 5.f}, {256, 128, 2.33f, 1.69f, 3.4f, -2.3f, 0.14f, 13.f}};
+
+}  // namespace
+
+const SplitShape& split_shape(int shape) { return kShapes[shape]; }
+
+bool split_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb) {
+    // 32-bit offsets inside a tile, contraction indices up to two steps past the end; shorter contractions and rows shorter than a
+    // load go to fp32 products in there: no gain
+    constexpr int64_t kMaxPitch = int64_t(1) << 22;
+    return Kc >= kBK && Kc <= (int64_t(1) << 30) && lda <= kMaxPitch && ldb <= kMaxPitch && (layout == Layout::kNT || std::min(M, N) >= 4);
+}
+
+hipError_t launch_gemm_split(hipStream_t stream, GemmBatch& batch, int n_problems, int shape) {
+    batch.n_problems = n_problems;
+    if (n_problems == 0 || batch.total_tiles == 0) return hipSuccess;
+    for (int i = 0; i < n_problems; ++i) {
+        const GemmProblem& p = batch.p[i];
+        const Layout layout = batch.tn >> i & 1 ? Layout::kTN : Layout::kNT;
+        if (p.n_seg != 1 || ~p.row_bits != 0 || !split_shape_ok(layout, p.M, p.N, p.Kc, p.lda, p.ldb)) return hipErrorInvalidValue;
+    }
+    switch (shape) {
+        case 0: return launch_shape<128, 128, 2>(stream, batch);
+        case 1: return launch_shape<256, 128, 4>(stream, batch);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace tf

@@ -309,11 +309,12 @@ double generic_launch_us(const std::vector<const Planned*>& items, int out_bytes
     return 7.3 + us + kOut[output_kind(out_bytes, accumulate)] * mb;
 }
 
-constexpr int kFirstNarrow = kGenericShapes, kFirstShort = kFirstNarrow + kNarrowShapes;     // numbers of their launch shapes
+constexpr int kFirstNarrow = kGenericShapes, kFirstShort = kFirstNarrow + kNarrowShapes, kFirstSplit = kFirstShort + kShortShapes;     // numbers of their launch shapes
 
 // Rows and columns of a launch shape's tile (-1: the 256 x 256-tile kernel).
 void tile_of(int shape, Dtype in_dtype, uint32_t* m, uint32_t* n) {
     if (shape < 0) *m = *n = gemm_mfma_tile();
+    else if (shape >= kFirstSplit) { *m = split_shape(shape - kFirstSplit).tile_m; *n = split_shape(shape - kFirstSplit).tile_n; }
     else if (shape >= kFirstShort) { *m = short_shape(shape - kFirstShort).rows; *n = short_shape(shape - kFirstShort).cols; }
     else if (shape >= kGenericShapes) { *m = narrow_shape(shape - kGenericShapes).rows; *n = narrow_shape(shape - kGenericShapes).cols; }
     else { *m = generic_shape(in_dtype, shape).tile_m; *n = generic_shape(in_dtype, shape).tile_n; }
@@ -322,9 +323,10 @@ void tile_of(int shape, Dtype in_dtype, uint32_t* m, uint32_t* n) {
 // tf_internal_gemm_route: by the estimates; 256 x 256 tiles for every problem that they take, but for the masked
 // last steps (kRouteWhole256) or with them; the generic kernel for every problem that it takes.
 // From kRouteNarrow and kRouteShort on the kernels for few rows and few tokens, by their shapes; from kRouteF32 on fp32 calls in the
-// generic kernel's tiles x (input gradients) and w (weight gradients), kRouteF32 + kGenericShapes x + w.
+// generic kernel's tiles x (input gradients) and w (weight gradients), kRouteF32 + kGenericShapes x + w; from kRouteSplit on fp32 calls on the
+// kernel of bf16 pieces, by its shapes, where it takes all problems of a half.
 enum { kRouteEstimated = 0, kRouteWhole256 = 1, kRouteAll256 = 2, kRouteGeneric = 3, kRouteNarrow = 4, kRouteShort = kRouteNarrow + kNarrowShapes,
-       kRouteF32 = kRouteShort + kShortShapes, kRouteEnd = kRouteF32 + kGenericShapes * kGenericShapes };
+       kRouteF32 = kRouteShort + kShortShapes, kRouteSplit = kRouteF32 + kGenericShapes * kGenericShapes, kRouteEnd = kRouteSplit + kSplitShapes };
 
 // problems for 256 x 256 tiles; those whose contraction is no multiple of 64; all others
 enum { kWhole = 0, kTail = 1, kOther = 2, kClasses = 3 };
@@ -342,7 +344,7 @@ void find_input_routes(Layout layout, Dtype in_dtype, int route, bool plain, Rou
     auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
         double us;
         *shape = pick_generic_shape(v, in_dtype, &us);
-        if (in_dtype == Dtype::F32 && route >= kRouteF32) *shape = layout == Layout::kNT ? (route - kRouteF32) / kGenericShapes : (route - kRouteF32) % kGenericShapes;
+        if (in_dtype == Dtype::F32 && route >= kRouteF32 && route < kRouteSplit) *shape = layout == Layout::kNT ? (route - kRouteF32) / kGenericShapes : (route - kRouteF32) % kGenericShapes;
         if (v.empty() || route == kRouteGeneric) return us;
         for (const Planned* it : v)
             if (!planned_narrow_ok(*it, layout, in_dtype)) return us;
@@ -452,17 +454,88 @@ void fill(GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
     gp.m_slack = uint32_t(before) | (uint32_t(after) << 16);
 }
 
-// fp32: the input gradients `x` and the weight gradients `w` in one launch, where each by itself would be one launch of
-// the generic kernel, each in the tiles it would have had - so that every sum is what it would have been.  *done says whether they were.
-// A call whose kernels are timed launches them one by one.
-hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planned>& x, const std::vector<Planned>& w, bool accumulate, bool* done) {
+// Launches of the kernel of bf16 pieces have blocks of 512 threads, fewer than 2^32 in all.
+constexpr int64_t kMaxSplitTiles = (int64_t(1) << 23) - 1;
+
+// As pick_generic_shape(), of the shapes of the kernel of bf16 pieces.  Fitted to 210 launches on each (seven sets of layers of widths 128
+// to 1280, 20 to 2048 tokens, input gradients, weight gradients and both): 6 and 8 % off the measured times.
+int pick_split_shape(const std::vector<const Planned*>& items, double* best_us) {
+    int best = 0;
+    *best_us = HUGE_VAL;
+    for (int i = 0; i < kSplitShapes; ++i) {
+        const SplitShape& s = split_shape(i);
+        Estimate e;
+        for (const Planned* it : items) e.add(*it, s.tile_m, s.tile_n, 32, s.tile_steps, s.chain_steps);
+        if (e.most_tiles > kMaxSplitTiles) continue;
+        const double us = s.launch_us + Estimate::us(e.work / compute_units() * s.step_us, e.longest * s.chain_us, s.overlap);
+        if (us < *best_us) { best = i; *best_us = us; }
+    }
+    return kFirstSplit + best;
+}
+
+// What the two halves of an fp32 call, input gradients `x` and weight gradients `w`, run on: launch shapes, and whether they share a
+// launch.  The input gradients go to the kernel of bf16 pieces where that is expected to be done first, by themselves - their bits
+// must not depend on which tensors are frozen (5 % sooner: a short launch of the other half that stays on the generic kernel then is one
+// of its own).  The weight gradients join them in one launch or have one of their own on the other kernel, as is expected
+// to be done first.  A launch of the generic kernel takes some 4 us that its estimate leaves out.
+// What the generic kernel would contract in 64 bits (its smallest tiles) stays there: the other's error is a little less than that
+// of sums in 32 bits (1.0e-7 and 1.2e-7 at 256 values, 1.9e-7 and 2.0e-7 at 2731), not than 2.5e-8.
+struct ChoiceF32 { int x, w; bool together; };
+ChoiceF32 choose_f32(const std::vector<const Planned*>& x, const std::vector<const Planned*>& w, int route) {
+    constexpr double kLaunch = 4;
+    struct Half { int generic, split; double generic_us, split_us; };
+    auto half = [&](const std::vector<const Planned*>& v, Layout layout) {
+        Half h{0, kFirstSplit, 0, HUGE_VAL};
+        h.generic = pick_generic_shape(v, Dtype::F32, &h.generic_us);
+        h.generic_us += kLaunch;
+        if (route >= kRouteF32 && route < kRouteSplit) h.generic = layout == Layout::kNT ? (route - kRouteF32) / kGenericShapes : (route - kRouteF32) % kGenericShapes;
+        if (v.empty() || route == kRouteGeneric || (route < kRouteSplit && (route >= kRouteF32 || h.generic == 0))) return h;
+        for (const Planned* it : v)
+            if (!split_shape_ok(layout, it->M, it->N, it->Kc, it->lda, it->ldb)) return h;
+        h.split = pick_split_shape(v, &h.split_us);
+        if (route >= kRouteSplit) { h.split = kFirstSplit + route - kRouteSplit; h.split_us = 0; }
+        return h;
+    };
+    const Half hx = half(x, Layout::kNT), hw = half(w, Layout::kTN);
+    const bool x_split = hx.split_us < 0.95 * hx.generic_us, w_split = hw.split_us < hw.generic_us;
+    const ChoiceF32 apart{x_split ? hx.split : hx.generic, w_split ? hw.split : hw.generic, false};
+    if (x.empty() || w.empty() || x.size() + w.size() > size_t(kMaxProblemsPerLaunch)) return apart;
+    if (!x_split) {
+        const ChoiceF32 joint{hx.generic, hw.generic, true};
+        if (!w_split) return joint;
+        Estimate e;
+        auto add = [&](const std::vector<const Planned*>& v, int shape) {
+            const GenericShape& s = generic_shape(Dtype::F32, shape);
+            Estimate steps;
+            for (const Planned* it : v) steps.add(*it, s.tile_m, s.tile_n, 32, s.tile_steps, s.tile_steps);
+            e.work += steps.work * s.step_us;
+            e.longest = std::max(e.longest, steps.longest * s.chain_us);
+        };
+        add(x, hx.generic);
+        add(w, hw.generic);
+        // (two launches have to promise a tenth: the estimates are up to 8 us short of short launches)
+        const double joint_us = kLaunch + Estimate::us(e.work / compute_units(), e.longest, 0.25);
+        return 0.9 * joint_us <= hx.generic_us + hw.split_us ? joint : apart;
+    }
+    if (hw.split_us == HUGE_VAL) return apart;
+    std::vector<const Planned*> both = x;
+    both.insert(both.end(), w.begin(), w.end());
+    double joint_us = 0;
+    const int shape = route >= kRouteSplit ? hx.split : pick_split_shape(both, &joint_us);
+    return w_split || joint_us <= hx.split_us + hw.generic_us ? ChoiceF32{shape, shape, true} : apart;
+}
+std::vector<const Planned*> pointers(const std::vector<Planned>& v) {
+    std::vector<const Planned*> p;
+    p.reserve(v.size());
+    for (const Planned& it : v) p.push_back(&it);
+    return p;
+}
+
+// fp32: the input gradients `x` and the weight gradients `w` in one launch, in the tiles that `choice` gives them - every sum is what it
+// would have been in a launch of each half.  *done: false if there are too many tiles.
+hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planned>& x, const std::vector<Planned>& w, bool accumulate, const ChoiceF32& choice, bool* done) {
     *done = false;
-    if (ctx->profiling || x.empty() || w.empty() || x.size() + w.size() > size_t(kMaxProblemsPerLaunch)) return hipSuccess;
-    Routes rx, rw;
-    if (find_routes(x, Layout::kNT, Dtype::F32, Dtype::F32, false, ctx->gemm_route, rx) != hipSuccess ||
-        find_routes(w, Layout::kTN, Dtype::F32, Dtype::F32, accumulate, ctx->gemm_route, rw) != hipSuccess) return hipSuccess;
-    const int shape[2] = {rx.shape[kOther], rw.shape[kOther]};
-    if (rx.cls[kOther].size() != x.size() || rw.cls[kOther].size() != w.size()) return hipSuccess;
+    const bool split = choice.x >= kFirstSplit;
     // longest contraction first
     struct Item { const Planned* it; bool tn; };
     std::vector<Item> items;
@@ -470,29 +543,40 @@ hipError_t launch_both(tf_ctx* ctx, hipStream_t stream, const std::vector<Planne
     for (const Planned& it : x) items.push_back(Item{&it, false});
     for (const Planned& it : w) items.push_back(Item{&it, true});
     std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) { return a.it->Kc > b.it->Kc; });
+    const int64_t max_tiles = split ? kMaxSplitTiles : kMaxGenericTiles;
     GemmBatch batch;
     batch.tn = 0;
     int64_t tiles = 0;
     for (size_t i = 0; i < items.size(); ++i) {
-        fill(batch.p[i], *items[i].it, std::min(tiles, kMaxGenericTiles), 1);
+        fill(batch.p[i], *items[i].it, std::min(tiles, max_tiles), 1);
         if (items[i].tn) batch.tn |= uint64_t(1) << i;
         uint32_t tile_m, tile_n;
-        tile_of(shape[items[i].tn], Dtype::F32, &tile_m, &tile_n);
+        tile_of(items[i].tn ? choice.w : choice.x, Dtype::F32, &tile_m, &tile_n);
         tiles += tiles_of(*items[i].it, tile_m, tile_n);
     }
-    if (tiles > kMaxGenericTiles) return hipSuccess;
+    if (tiles > max_tiles) return hipSuccess;
     batch.total_tiles = int32_t(tiles);
+    batch.add = accumulate ? batch.tn : 0;
     *done = true;
-    ctx->common_tiles.store(kGenericShapes * shape[0] + shape[1], std::memory_order_relaxed);
-    return launch_gemm_generic_both(stream, batch, int(items.size()), shape[0], shape[1], accumulate);
+    ctx->common_tiles.store(split ? kGenericShapes * kGenericShapes + choice.x - kFirstSplit : kGenericShapes * choice.x + choice.w, std::memory_order_relaxed);
+    return split ? launch_gemm_split(stream, batch, int(items.size()), choice.x - kFirstSplit)
+                 : launch_gemm_generic_both(stream, batch, int(items.size()), choice.x, choice.w, accumulate);
 }
 
-// Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it.
+// Launch `items` in batches of at most kMaxProblemsPerLaunch, each on the kernel that find_routes() gives it; fp32 ones in launch shape
+// f32_shape, or in one chosen for them alone (-1).
 hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>& items, Layout layout,
-                          Dtype in_dtype, Dtype out_dtype, bool accumulate) {
+                          Dtype in_dtype, Dtype out_dtype, bool accumulate, int f32_shape = -1) {
     Routes routes;
     const hipError_t found = find_routes(items, layout, in_dtype, out_dtype, accumulate, ctx->gemm_route, routes);
     if (found != hipSuccess) return found;
+    if (in_dtype == Dtype::F32 && !items.empty()) {
+        if (f32_shape < 0) {
+            const std::vector<const Planned*> v = pointers(items), none;
+            f32_shape = layout == Layout::kNT ? choose_f32(v, none, ctx->gemm_route).x : choose_f32(none, v, ctx->gemm_route).w;
+        }
+        routes.shape[kOther] = f32_shape;
+    }
     std::vector<const Planned*>* const cls = routes.cls;
     const int* const shape = routes.shape;
 
@@ -503,7 +587,7 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
         std::stable_sort(v.begin(), v.end(), [](const Planned* a, const Planned* b) { return a->total_kc() > b->total_kc(); });
         uint32_t tile_m, tile_n;
         tile_of(shape[c], in_dtype, &tile_m, &tile_n);
-        const int64_t max_tiles = shape[c] < 0 ? kMaxTiles256 : shape[c] >= kGenericShapes ? kMaxNarrowTiles : kMaxGenericTiles;
+        const int64_t max_tiles = shape[c] < 0 ? kMaxTiles256 : shape[c] >= kFirstSplit ? kMaxSplitTiles : shape[c] >= kGenericShapes ? kMaxNarrowTiles : kMaxGenericTiles;
         size_t i = 0;
         while (i < v.size()) {
             int n = 0;
@@ -523,10 +607,14 @@ hipError_t launch_planned(tf_ctx* ctx, hipStream_t stream, std::vector<Planned>&
                 ++i;
             }
             batch.total_tiles = int32_t(tiles);
+            batch.tn = layout == Layout::kTN ? ~0ull : 0;
+            batch.add = accumulate ? ~0ull : 0;
             const int kind = (layout == Layout::kNT ? TF_KERNEL_DX_MFMA : TF_KERNEL_DW_MFMA) + (shape[c] < 0 ? 0 : 2);     // the kernel that runs
             ProfScope prof(ctx, stream, kind);
             const hipError_t e = shape[c] < 0
                 ? launch_gemm_mfma_bf16(stream, batch, n, layout, out_dtype, accumulate, c == kTail)
+                : shape[c] >= kFirstSplit
+                ? launch_gemm_split(stream, batch, n, shape[c] - kFirstSplit)
                 : shape[c] >= kFirstShort
                 ? launch_gemm_short(stream, batch, n, shape[c] - kFirstShort, out_dtype, accumulate)
                 : shape[c] >= kGenericShapes
@@ -749,14 +837,19 @@ int stage_backward_impl(tf_ctx* ctx, void* hip_stream,
     bool both = false;
     const bool add_first = plan_set.empty();          // (what overwrites, if there is any, goes with the input gradients)
     ctx->common_tiles.store(-1, std::memory_order_relaxed);
+    ChoiceF32 choice{-1, -1, false};
+    std::vector<Planned>& first = add_first ? plan_add : plan_set;
     if (in_dt == Dtype::F32 && !input_group) {
-        e = launch_both(ctx, stream, plan, add_first ? plan_add : plan_set, add_first, &both);
-        if (e != hipSuccess) return hip_fail(ctx, e);
-        if (both) (add_first ? plan_add : plan_set).clear();
+        choice = choose_f32(pointers(plan), pointers(first), ctx->gemm_route);
+        if (choice.together && !ctx->profiling) {         // (a call whose kernels are timed launches them one by one)
+            e = launch_both(ctx, stream, plan, first, add_first, choice, &both);
+            if (e != hipSuccess) return hip_fail(ctx, e);
+        }
+        if (both) first.clear();
     }
     if (both) {
     } else if (!grouped_slow) {
-        e = launch_planned(ctx, stream, plan, Layout::kNT, in_dt, in_dt, false);
+        e = launch_planned(ctx, stream, plan, Layout::kNT, in_dt, in_dt, false, choice.x);
     } else {
         // A group that the matrix-core kernel cannot take: member after member, each launch adding
         // onto the one before.  That needs an fp32 output (the fp32 configuration).
@@ -774,9 +867,9 @@ int stage_backward_impl(tf_ctx* ctx, void* hip_stream,
     }
     if (e != hipSuccess) return hip_fail(ctx, e);
 
-    e = launch_planned(ctx, stream, plan_set, Layout::kTN, in_dt, to_dtype(dw_dtype), false);
+    e = launch_planned(ctx, stream, plan_set, Layout::kTN, in_dt, to_dtype(dw_dtype), false, add_first ? -1 : choice.w);
     if (e != hipSuccess) return hip_fail(ctx, e);
-    e = launch_planned(ctx, stream, plan_add, Layout::kTN, in_dt, to_dtype(dw_dtype), true);
+    e = launch_planned(ctx, stream, plan_add, Layout::kTN, in_dt, to_dtype(dw_dtype), true, add_first ? choice.w : -1);
     if (e != hipSuccess) return hip_fail(ctx, e);
     return TF_OK;
 }
@@ -1487,7 +1580,7 @@ extern "C" int tf_internal_gemm_route(tf_ctx* ctx, int route) {
 }
 
 // Test hook (not part of the public header): did the context's last backward call launch both of its halves together?
-// kGenericShapes x + w, the tiles they had (see kRouteF32), or -1.
+// kGenericShapes x + w, the tiles they had (see kRouteF32), behind them the launch shapes of the kernel of bf16 pieces; or -1.
 extern "C" int tf_internal_common_tiles(const tf_ctx* ctx) { return ctx ? ctx->common_tiles.load(std::memory_order_relaxed) : -1; }
 
 // Test hook (not part of the public header): how the context's last tf_reconcile_mask went, once the device is done with it: the
@@ -1509,8 +1602,8 @@ extern "C" int tf_internal_reconcile_outcome(tf_ctx* ctx, int64_t* out) {
 
 // Test hook (not part of the public header): kernel[i] of problem i when these problems (operands packed, buffers
 // aligned) are launched together, by the estimated times: -1 the 256 x 256-tile kernel, 0.. the launch shapes of the
-// generic kernel, behind them those of the kernel for input gradients of few rows and those of the kernel for weight
-// gradients of few tokens.
+// generic kernel, behind them those of the kernel for input gradients of few rows, of the kernel for weight
+// gradients of few tokens and of the kernel of bf16 pieces.
 // after: rows of the tensor behind the problem's own (it is a run of its rows), or NULL.
 extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, const int64_t* Kc, const int64_t* after, int layout_tn,
                                    int in_dtype, int out_dtype, int accumulate, int32_t* kernel) {
@@ -1523,6 +1616,10 @@ extern "C" int tf_internal_kernels(int n, const int64_t* M, const int64_t* N, co
     }
     Routes r;
     if (find_routes(items, layout, to_dtype(tf_dtype(in_dtype)), to_dtype(tf_dtype(out_dtype)), accumulate != 0, kRouteEstimated, r) != hipSuccess) return TF_ERR_SHAPE;
+    if (in_dtype == TF_F32) {
+        const std::vector<const Planned*> v = pointers(items), none;
+        r.shape[kOther] = layout_tn ? choose_f32(none, v, kRouteEstimated).w : choose_f32(v, none, kRouteEstimated).x;
+    }
     for (int c = 0; c < kClasses; ++c)
         for (const Planned* it : r.cls[c]) kernel[it - items.data()] = r.shape[c];
     return TF_OK;

@@ -46,11 +46,12 @@ struct GemmProblem {
 
 constexpr int kMaxProblemsPerLaunch = 64;
 
-struct GemmBatch {          // passed by value as the kernel argument (64 x 64 B + 16 B = 4112 B)
+struct GemmBatch {          // passed by value as the kernel argument (64 x 64 B + 24 B = 4120 B)
     GemmProblem p[kMaxProblemsPerLaunch];
     int32_t n_problems;
     int32_t total_tiles;
-    uint64_t tn;            // launch_gemm_generic_both only: bit i = problem i is of layout kTN
+    uint64_t tn;            // launch_gemm_generic_both and launch_gemm_split only: bit i = problem i is of layout kTN
+    uint64_t add;           // launch_gemm_split only: bit i = problem i is added to what its output holds
 };
 
 // Matrix-core kernel for any M, N, Kc >= 1, pitch and alignment.  in: fp32 or bf16, accumulate
@@ -66,6 +67,17 @@ hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_probl
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
 // fp32 problems of both layouts in one launch; those of layout kNT are never added to what is there.
 hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape_nt, int shape_tn, bool accumulate);
+// fp32 problems of both layouts on the bf16 matrix cores, three bf16 pieces of each value, in several launch shapes.  It
+// takes everything; fast are contractions of 32 or more.  Row pitches of at most 2^22, contractions of at most 2^30.
+struct SplitShape {
+    int tile_m, tile_n;
+    float step_us, chain_us, tile_steps, chain_steps, overlap, launch_us;   // what a contraction step of a tile costs (see there)
+};
+constexpr int kSplitShapes = 2;
+const SplitShape& split_shape(int shape);
+bool split_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb);
+// `batch.tn` and `batch.add` say which problems are of layout kTN and which are added to their outputs.
+hipError_t launch_gemm_split(hipStream_t stream, GemmBatch& batch, int n_problems, int shape);
 int compute_units();              // of the current device
 
 // bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of

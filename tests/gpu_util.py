@@ -13,6 +13,7 @@ import paper_2602_05754_amd as tf
 BY_ESTIMATE, WHOLE_256, ALL_256, GENERIC = range(4)
 NARROW = {(64, 64): 4, (128, 64): 5, (128, 128): 6, (256, 128): 7}        # input gradients of few rows, by tile
 SHORT = {(128, 64): 8, (128, 128): 9, (256, 128): 10}                                   # weight gradients of few tokens, by tile
+SPLIT = {(128, 128): 20, (256, 128): 21}               # fp32 calls on the kernel of bf16 pieces, by tile
 F32_TILES = 11                                          # + 3 x + w: fp32 calls, tiles x and w of their two halves
 
 

@@ -11,7 +11,7 @@ import torch
 import oracle
 import workloads as wl
 import paper_2602_05754_amd as tf
-from gpu_util import ALL_256, BY_ESTIMATE, CODE, F32_TILES, GENERIC, NARROW, SHORT, TDT, WHOLE_256, assert_elementwise, canary, common_tiles, dev, host64, kinds_of, raw_bytes, rel_fro, route
+from gpu_util import ALL_256, BY_ESTIMATE, CODE, F32_TILES, GENERIC, NARROW, SHORT, SPLIT, TDT, WHOLE_256, assert_elementwise, canary, common_tiles, dev, host64, kinds_of, raw_bytes, rel_fro, route
 
 pytestmark = pytest.mark.gpu
 GUARD = 64
@@ -419,3 +419,74 @@ def test_both_halves_in_every_pair_of_tiles(ctx, pair, form):
     with route(ctx, F32_TILES + pair):
         _both_halves(ctx, 65, [(31, 33), (129, 63), (64, 200), (3, 7), (95, 257)], form, lambda tiles: tiles == pair)
         _both_halves(ctx, 20, [(33, 12), (70, 129)], form, lambda tiles: tiles == pair)
+
+
+@pytest.mark.parametrize("tile", sorted(SPLIT))
+@pytest.mark.parametrize("T", [32, 33, 61, 95, 128, 160, 191, 257])
+def test_fp32_calls_of_bf16_pieces(ctx, T, tile):
+    """The kernel that splits fp32 values into three bf16 pieces where it can go wrong: rows and columns around its tiles, rows that
+    end inside a 16-byte load, contractions of one step to more than are on their way, 1 to 31 values more than whole ones.  The same
+    bits in both tiles, in one launch and two; no less exact than sums of fp32 products in 32 bits."""
+    shapes = [(4, 33), (5, 32), (127, 95), (128, 129), (130, 64), (255, 34), (258, 63), (64, 261), (7, 385)]
+    for accumulate in (False, True):
+        with route(ctx, SPLIT[tile]):
+            kinds = _case(ctx, shapes, T, "f32", "f32", accumulate, seed=T)
+        assert kinds == ["dx_generic", "dw_generic"]
+    W, X, dY = _random(shapes, T, "f32", T)
+    got, errors = {}, {}
+    for which in (*SPLIT.values(), F32_TILES + 4):
+        out = [[Guarded((T, k), "f32") for k, n in shapes], [Guarded(s, "f32") for s in shapes]]
+        with route(ctx, which):
+            tf.tf_stage_backward(ctx, shapes, T, tf.TF_F32, W, X, dY, None, *[[g.t for g in half] for half in out], tf.TF_F32)
+        assert common_tiles(ctx) == (4 if which == F32_TILES + 4 else 9 + which - min(SPLIT.values()))
+        got[which] = [raw_bytes(g.t) for half in out for g in half]
+        exact = [y.double() @ w.double().t().contiguous() for y, w in zip(dY, W)] + [x.double().t().contiguous() @ y.double() for x, y in zip(X, dY)]
+        errors[which] = sum(rel_fro(host64(g.t), e.cpu().numpy()) ** 2 for g, e in zip(out[0] + out[1], exact)) ** 0.5
+        for g in out[0] + out[1]:
+            g.check(f"T={T} {which}")
+    assert got[20] == got[21]
+    assert errors[20] <= 1.05 * errors[F32_TILES + 4]              # (of 18 outputs, some of a few values: a rounding more or less)
+
+
+@pytest.mark.parametrize("tile", sorted(SPLIT))
+@pytest.mark.parametrize("what", ["infinity", "overflow", "tiny"])
+def test_values_that_bf16_pieces_cannot_hold(ctx, what, tile):
+    """An infinity meets the zeros among another value's pieces, a sum of pieces may leave the range where the sum does not, and pieces of
+    values below 2^-110 lose bits: such tiles are computed from fp32 products, with the bits of the generic kernel's 32 x 64 tiles."""
+    T, shapes = 100, [(300, 200)]
+    W, X, dY = _random(shapes, T, "f32", 3)
+    if what == "infinity":
+        dY[0][T - 1, 150], W[0][17, 3], X[0][50, 299] = float("inf"), float("-inf"), float("inf")
+    elif what == "overflow":
+        X[0] *= 1e38
+        dY[0] *= 1e35
+        W[0] *= 1e38
+    else:
+        X[0] *= 2.0 ** -115
+        W[0] *= 2.0 ** -112
+    got = []
+    for which in (SPLIT[tile], F32_TILES + 4):
+        dX, dW = [torch.zeros_like(X[0])], [torch.zeros_like(W[0])]
+        with route(ctx, which):
+            tf.tf_stage_backward(ctx, shapes, T, tf.TF_F32, W, X, dY, None, dX, dW, tf.TF_F32)
+        got.append((dX[0], dW[0]))
+    for a, b in zip(*got):
+        redone = torch.ones_like(a, dtype=torch.bool)
+        if what == "infinity":                                     # only tiles with a sum that is not finite
+            odd = ~torch.isfinite(b)
+            redone = torch.zeros_like(redone)
+            for m in range(0, a.shape[0], tile[0]):
+                for n in range(0, a.shape[1], tile[1]):
+                    redone[m:m + tile[0], n:n + tile[1]] = odd[m:m + tile[0], n:n + tile[1]].any()
+            assert redone.any()
+        elif what == "overflow":
+            redone = ~torch.isfinite(b)
+            assert redone.any()
+        assert torch.equal(a[redone].view(torch.int32), b[redone].view(torch.int32))
+        assert torch.equal(torch.isfinite(a), torch.isfinite(b))
+
+
+@pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
+def test_both_halves_of_bf16_pieces_give_the_same_bits(ctx, form):
+    """Both halves in one launch of the kernel of bf16 pieces, by the estimates: the bits of a launch each."""
+    _both_halves(ctx, 1000, [(1024, 1024), (1024, 2731), (2731, 1024)], form, lambda tiles: tiles >= 9)

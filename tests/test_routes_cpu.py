@@ -163,3 +163,38 @@ def test_a_launch_has_fewer_than_2_to_the_32_threads(io, M, N):
         return                                                       # refused, as it was with 64 x 64 tiles
     shape = kernels([M], [N], [3], False, io=io, out=io)[0]
     assert shape >= 0 and tiles[shape] * 256 < 1 << 32
+
+
+PIECES = range(10, 12)                                             # launch shapes of the fp32 kernel of bf16 pieces
+
+
+# fp32 launches of one half, us on the generic kernel and in the better tiles of the one of bf16 pieces, three sets of buffers in turn
+@pytest.mark.parametrize("shapes,T,tn,fastest", [
+    (block(1024, 256, 2731, 2), 1001, False, PIECES),              # 379, 237
+    (block(1024, 256, 2731, 2), 1001, True, PIECES),               # 368, 248
+    (block(1024, 256, 2731, 2), 350, False, PIECES),               # 152, 119
+    (block(1280, 320, 4900), 2048, True, PIECES),                  # 739, 486
+    (block(640, 640, 2000, 2), 512, False, PIECES),                # 104, 81
+    (block(512, 256, 1700), 2048, False, PIECES),                  # 129, 89
+    (block(512, 256, 1700), 512, False, GENERIC),                  # 40, 64: chains of 54 steps in few tiles
+    (block(1024, 256, 2731, 2), 100, False, GENERIC),              # 62, 100
+    (block(1280, 320, 4900), 37, False, GENERIC),                  # 81, 171
+    (block(1024, 256, 2731, 2), 20, True, GENERIC),                # -, 57: less than a step of 32 tokens
+    (block(256, 256, 688, 2), 200, True, [0]),                     # 14, 15: short, so in 64 bits
+    (block(256, 256, 688, 2), 200, False, [0]),                    # 19, 30: the same
+])
+def test_fp32_launches_take_the_fastest_kernel(shapes, T, tn, fastest):
+    K, N = zip(*shapes)
+    M, N, Kc = (K, N, [T] * len(K)) if tn else ([T] * len(K), K, N)
+    got = kernels(M, N, Kc, tn, io=tf.TF_F32, out=tf.TF_F32)
+    assert len(set(got)) == 1 and got[0] in fastest, got
+
+
+def test_fp32_problems_that_the_kernel_of_bf16_pieces_does_not_take():
+    """Pitches past its 32-bit offsets, contractions past its 32-bit indices, rows shorter than a load: the generic kernel."""
+    big = 1 << 22
+    assert kernels([2048], [2048], [big], False, io=tf.TF_F32, out=tf.TF_F32)[0] in PIECES
+    assert kernels([2048], [2048], [big + 1], False, io=tf.TF_F32, out=tf.TF_F32)[0] in GENERIC      # (packed: the pitch)
+    assert kernels([2048], [2048], [(1 << 30) + 1], True, io=tf.TF_F32, out=tf.TF_F32)[0] in GENERIC
+    assert kernels([1 << 20], [260], [4096], True, io=tf.TF_F32, out=tf.TF_F32)[0] in PIECES
+    assert kernels([1 << 20, 1 << 20], [3, 260], [4096, 4096], True, io=tf.TF_F32, out=tf.TF_F32)[0] in GENERIC
