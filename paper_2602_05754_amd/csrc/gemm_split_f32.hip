@@ -199,7 +199,10 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
         }
     };
     bf16x8 fb[kFragB][kPiecesOf], fa[2], fa_low[2];     // of A: piece 0 of this row of blocks and of the next; pieces 1 and 2
-    f32x4 part[1][kFragB];                              // a row's products of one step
+    // A row of blocks' products of one step; added to the sums behind some matrix instructions of the next row, where the last of them
+    // is done (rows of two blocks: a row more to wait in).
+    constexpr int kBuffers = kFragB < 4 ? 2 : 1, kSumAt = kBuffers == 2 ? 2 : 0;
+    f32x4 part[kBuffers][kFragB];
     auto read_a = [&](const char* stage, auto i, auto t) __attribute__((always_inline)) {
         if constexpr (t == 0) fa[i % 2] = a.fragment(stage, i, 0);
         else fa_low[t - 1] = a.fragment(stage, i, t);
@@ -211,31 +214,26 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
         finish(i, s);
         static_for<kParts>([&](auto n) __attribute__((always_inline)) { split(i, n, stage); });
     };
-    // Step s.  kWhole: whatever is loaded and split meanwhile are whole steps, and the splitting rides behind the matrix instructions.
-    // (In a tile's last four steps it does not: there are not registers enough for what those loads take besides.)
+    // Step s.  kWhole: whatever is loaded and split meanwhile are whole steps.
     auto step = [&](int s, auto whole) __attribute__((always_inline)) {
         constexpr bool kWhole = decltype(whole)::value;
         char* const now = lds + (s & 1) * kStage;
         char* const then = lds + (~s & 1) * kStage;
         constexpr int kRow = 6 * kFragB, kBefore = (kFragA - 1) * kRow;          // MFMAs of a row, and in front of the barrier
-        if constexpr (!kWhole) static_for<kLoads - 1>([&](auto i) __attribute__((always_inline)) {
-            constexpr std::integral_constant<int, i + 1> which;
-            split_load(which, s + 1, then);
-            load(which, s + 2);
-            __builtin_amdgcn_sched_barrier(0);
-        });
         static_for<kFragA * kRow>([&](auto m) __attribute__((always_inline)) {
             constexpr int order[6][2] = {{0, 2}, {1, 1}, {0, 1}, {2, 0}, {1, 0}, {0, 0}};        // pieces of A and B
             constexpr int i = m / kRow, n = m % kRow, g = n / kFragB, j = n % kFragB, pa = order[g][0], pb = order[g][1];
-            // the sums of the row before (the last one: of the step before): four matrix instructions or so after the last of them
-            if constexpr (g == 0) acc[(i + kFragA - 1) % kFragA][j] += part[0][j];
-            part[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], pa == 0 ? fa[i % 2] : fa_low[pa == 0 ? 0 : pa - 1], g == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : part[0][j], 0, 0, 0);
+            // the sums of the row before (in the first row: of the last one of the step before)
+            constexpr int was = (i + kFragA - 1) % kFragA;
+            if constexpr (g == kSumAt) acc[was][j] += part[was % kBuffers][j];
+            f32x4& sum = part[i % kBuffers][j];
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][pb], pa == 0 ? fa[i % 2] : fa_low[pa == 0 ? 0 : pa - 1], g == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum, 0, 0, 0);
             // the next fragments, each where the one in its place has been used
             constexpr std::integral_constant<int, (i + 1) % kFragA> row;
             constexpr std::integral_constant<int, 1> k1;
             constexpr std::integral_constant<int, 2> k2;
             char* const from_a = i + 1 < kFragA ? now : then;
-            if constexpr (g == 1 && j == 0) read_a(from_a, row, k0);
+            if constexpr (g == 2 && j == 0) read_a(from_a, row, k0);
             if constexpr (g == 4 && j == 0) read_a(from_a, row, k2);
             if constexpr (g == 5 && j == 0) read_a(from_a, row, k1);
             if constexpr (i + 1 == kFragA) {
@@ -246,22 +244,21 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
             // the values of the steps ahead: load 0 of step s + 2 behind the last row, the others of step s + 1 before it
             constexpr int kItems = i + 1 < kFragA ? (kLoads - 1) * kParts : kParts, kOver = i + 1 < kFragA ? kBefore : kRow, x = i + 1 < kFragA ? int(m) : n;
             constexpr int from = x * kItems / kOver, to = (x + 1) * kItems / kOver;
-            if constexpr (kWhole) static_for<to - from>([&](auto d) __attribute__((always_inline)) {
+            static_for<to - from>([&](auto d) __attribute__((always_inline)) {
                 constexpr int item = from + d;
                 constexpr std::integral_constant<int, i + 1 < kFragA ? 1 + item / kParts : 0> which;
                 constexpr std::integral_constant<int, item % kParts> n_th;
                 const int ahead = i + 1 < kFragA ? s + 1 : s + 2;
+                if constexpr (!kWhole && n_th == 0) finish(which, ahead);
                 split(which, n_th, i + 1 < kFragA ? then : now);
-                if constexpr (n_th == kParts - 1) load_whole(which, ahead + 1);
+                if constexpr (n_th == kParts - 1) {
+                    if constexpr (kWhole) load_whole(which, ahead + 1);
+                    else load(which, ahead + 1);
+                }
             });
             if constexpr (m == kBefore - 1) __syncthreads();        // step s + 1 is there, step s has been read
             __builtin_amdgcn_sched_barrier(4);         // (scalar instructions may pass)
         });
-        if constexpr (!kWhole) {
-            split_load(k0, s + 2, now);
-            __builtin_amdgcn_sched_barrier(0);
-            load(k0, s + 3);
-        }
     };
 
     auto each_load = [&](auto f) __attribute__((always_inline)) {
@@ -271,14 +268,12 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
         });
     };
     each_load([&](auto i) __attribute__((always_inline)) { load(i, 0); });
-    each_load([&](auto i) __attribute__((always_inline)) { split_load(i, 0, lds); });
-    load(k0, 1);
+    each_load([&](auto i) __attribute__((always_inline)) {
+        split_load(i, 0, lds);
+        load(i, 1);
+    });
     split_load(k0, 1, lds + kStage);
     __builtin_amdgcn_sched_barrier(0);
-    static_for<kLoads - 1>([&](auto i) __attribute__((always_inline)) {
-        load(std::integral_constant<int, i + 1>{}, 1);
-        __builtin_amdgcn_sched_barrier(0);
-    });
     load(k0, 2);
     __syncthreads();
     static_for<kPiecesOf>([&](auto t) __attribute__((always_inline)) { read_a(lds, k0, t); });
@@ -286,13 +281,13 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
         read_b(lds, std::integral_constant<int, n % kFragB>{}, std::integral_constant<int, kPiecesOf - 1 - n / kFragB>{});
     });
 #pragma unroll
-    for (int j = 0; j < kFragB; ++j) part[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < kFragB; ++j) part[(kFragA - 1) % kBuffers][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     int s = 0;
     for (; s < steps - 4; ++s) step(s, std::true_type{});
     for (; s < steps; ++s) step(s, std::false_type{});
     wait_for_sums(part);
 #pragma unroll
-    for (int j = 0; j < kFragB; ++j) acc[kFragA - 1][j] += part[0][j];
+    for (int j = 0; j < kFragB; ++j) acc[kFragA - 1][j] += part[(kFragA - 1) % kBuffers][j];
     __syncthreads();
 
     // What three pieces cannot hold: an infinity has met zeros among the other value's pieces, a sum of pieces may have left the range
