@@ -13,8 +13,8 @@
 // instructions run.  So larger tiles are faster - a value is split once per tile and step - and every wave does everything: loads, splits,
 // stores to LDS and contracts, its splitting spread evenly behind its matrix instructions, one barrier per step.  256 x 128 tiles
 // of eight waves have 2.1 vector instructions per matrix instruction, 128 x 128 ones 2.6.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us:
-// input gradients 236 (128 x 128 tiles 273, generic kernel 370), weight gradients 245 (281, 368), both in one launch 463 (740).
-// Measured besides, the same input gradients: two workgroups of 128 x 128 tiles per unit that split and contract in turn 270; four
+// input gradients 233 (128 x 128 tiles 264, generic kernel 365), weight gradients 260 (287, 368), both in one launch 462 (731).
+// Measured besides, the same input gradients (238 then): two workgroups of 128 x 128 tiles per unit that split and contract in turn 270; four
 // waves that load and split beside four that contract 267; the remainders by v_dot2_f32_bf16, exact and half as many instructions, but
 // on the matrix cores' hardware: 290; 64 x 64 tiles 320.
 #include "gemm_tile.h"
@@ -40,7 +40,7 @@ __device__ __forceinline__ uint32_t take_piece(uint32_t& x0, uint32_t& x1, bool 
     return piece;
 }
 
-// One operand of a workgroup's tile: kWaves waves contract 16 kFrags rows of it each.
+// One operand of a workgroup's tile: kWaves waves contract kFrags blocks of 16 rows of it each, block i of wave w being number kWaves i + w.
 template <bool kContig, int kWaves, int kFrags>
 struct SplitOperand {
     static constexpr int kRows = 16 * kWaves * kFrags;
@@ -68,20 +68,24 @@ struct SplitOperand {
         for (int i = 0; i < kLoads; ++i)
             off[i] = kContig ? uint32_t(min(row(i, thread), extent - 1 - origin)) * uint32_t(ld * 4) + c * 16 : uint32_t(row(i, thread)) * uint32_t(ld * 4) + uint32_t(col(thread)) * 4;
         if (kContig) {
-            to = row(0, thread) * kPitch + c * 8;
-            from = (w * kFrags * 16 + (lane & 15)) * kPitch + q * 16;
+            to = row(0, thread) * kPitch + chunk(row(0, thread), c >> 1) + ((c & 1) << 3);
+            from = (w * 16 + (lane & 15)) * kPitch + chunk(lane & 15, q);
         } else {
-            const int block = c >> 2, r = 8 * q + ((lane & 15) >> 2);
-            to = at(block % kFrags, block / kFrags, row(0, thread)) + ((c & 3) << 3);
-            from = at(0, w, r) + ((lane & 3) << 3);
+            const int r = 8 * q + ((lane & 15) >> 2);
+            to = at(c >> 2, row(0, thread)) + ((c & 3) << 3);
+            from = at(w, r) + ((lane & 3) << 3);
         }
     }
     __device__ __forceinline__ static int row(int i, int thread) { return thread / kAcross + i * kDown; }
-    // kTN stage: byte offset of contraction row r, wave w's i-th 16-row block.  A transpose read takes 32 bytes (a unit) of contraction
+    // kNT stage: byte offset in a row of its 16-byte chunk c.  (The LDS takes 16 lanes of a 128-bit read at a time: lanes 0-3, 8-11, 20-23 and
+    // 28-31, the others of the first 32, and so on: rows r and r + 8 of a chunk beside rows r + 4 and r + 12 of its neighbour, four rows to
+    // all banks.  Without the exchange of halves every read takes twice its cycles: a third of the LDS' busy time was conflicts, 238 us
+    // where it is 233 now, 128 x 128 tiles 270 and 264.)
+    __device__ __forceinline__ static int chunk(int r, int c) { return (c ^ ((r >> 3) & 1) << 1) << 4; }
+    // kTN stage: byte offset of contraction row r, 16-row block u.  A transpose read takes 32 bytes (a unit) of contraction
     // rows 8 G + x, x = 0..3, G = lane / 16, 32 lanes at a time: 8 rows whose units must fall into different banks.  128 rows: a unit of
-    // padding per row and four per eight rows; 256 rows: units XOR-swizzled, block i of wave w in unit kWaves i + w.
-    __device__ __forceinline__ static int at(int i, int w, int r) {
-        const int u = kWaves * i + w;
+    // padding per row and four per eight rows; 256 rows: units XOR-swizzled.  (Either: no conflicts, LDS busy a quarter of the time.)
+    __device__ __forceinline__ static int at(int u, int r) {
         if (kPadded) return r * kPitch + (r >> 3) * 128 + u * 32;
         return r * kPitch + (((u & 7) ^ (4 * ((r >> 3) & 1) + (r & 3))) << 5) + ((u >> 3) << 8);
     }
@@ -121,13 +125,13 @@ struct SplitOperand {
         return v;
     }
     __device__ __forceinline__ char* place(char* stage, int i, int t) const {        // of bf16 piece t of load i
-        static_assert(kContig || kDown % 8 == 0, "rows 8 apart differ in one bit of the swizzle");
+        static_assert(kDown % (kContig ? 16 : 8) == 0, "a thread's rows differ in one bit of the swizzle, kNT: in none");
         if (kPadded) return stage + to + (t * kPlane + i * kDown * kPitch + i * kDown / 8 * 128);
         const int flip = kContig ? 0 : ((i * kDown >> 3) & 1) << 7;
         return stage + (to ^ flip) + (t * kPlane + i * kDown * kPitch);
     }
     __device__ __forceinline__ bf16x8 fragment(const char* stage, int i, int t) const {
-        if (kContig) return *reinterpret_cast<const bf16x8*>(stage + from + (t * kPlane + i * 16 * kPitch));
+        if (kContig) return *reinterpret_cast<const bf16x8*>(stage + from + (t * kPlane + kWaves * i * 16 * kPitch));
         const char* a = kPadded ? stage + from + (t * kPlane + kWaves * i * 32)
                                 : stage + (from ^ ((kWaves * i & 7) << 5)) + (t * kPlane + ((kWaves * i >> 3) << 8));
         const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LdsBf16x4Ptr)TF_LPTR(a));
@@ -324,7 +328,7 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
     for (int i = 0; i < kFragA; ++i)
 #pragma unroll
         for (int j = 0; j < kFragB; ++j) {
-            const int r = wm * (kTileM / kWavesM) + 16 * i + (lane & 15), c = wn * (kTileN / kWavesN / 4) + 4 * j + (lane >> 4);
+            const int r = 16 * (kWavesM * i + wm) + (lane & 15), c = 4 * (kWavesN * j + wn) + (lane >> 4);
             *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
         }
     __syncthreads();
