@@ -13,7 +13,7 @@
 // instructions run.  So larger tiles are faster - a value is split once per tile and step - and every wave does everything: loads, splits,
 // stores to LDS and contracts, its splitting spread evenly behind its matrix instructions, one barrier per step.  256 x 128 tiles
 // of eight waves have 2.1 vector instructions per matrix instruction, 128 x 128 ones 2.6.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us:
-// input gradients 233 (128 x 128 tiles 264, generic kernel 365), weight gradients 260 (287, 368), both in one launch 462 (731).
+// input gradients 233 (128 x 128 tiles 258, generic kernel 365), weight gradients 260 (284, 368), both in one launch 462 (731).
 // Measured besides, the same input gradients (238 then): two workgroups of 128 x 128 tiles per unit that split and contract in turn 270; four
 // waves that load and split beside four that contract 267; the remainders by v_dot2_f32_bf16, exact and half as many instructions, but
 // on the matrix cores' hardware: 290; 64 x 64 tiles 320.
@@ -205,7 +205,7 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
     bf16x8 fb[kFragB][kPiecesOf], fa[2], fa_low[2];     // of A: piece 0 of this row of blocks and of the next; pieces 1 and 2
     // A row of blocks' products of one step; added to the sums behind some matrix instructions of the next row, where the last of them
     // is done (rows of two blocks: a row more to wait in).
-    constexpr int kBuffers = kFragB < 4 ? 2 : 1, kSumAt = kBuffers == 2 ? 2 : 0;
+    constexpr int kBuffers = kFragB < 4 ? 2 : 1, kSumAt = kBuffers == 2 ? 5 : 0;
     f32x4 part[kBuffers][kFragB];
     auto read_a = [&](const char* stage, auto i, auto t) __attribute__((always_inline)) {
         if constexpr (t == 0) fa[i % 2] = a.fragment(stage, i, 0);
@@ -218,9 +218,9 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
         finish(i, s);
         static_for<kParts>([&](auto n) __attribute__((always_inline)) { split(i, n, stage); });
     };
-    // Step s.  kWhole: whatever is loaded and split meanwhile are whole steps.
-    auto step = [&](int s, auto whole) __attribute__((always_inline)) {
-        constexpr bool kWhole = decltype(whole)::value;
+    // Step s.  kWhole: whatever is loaded and split meanwhile are whole steps; kLast: nothing is, no step follows.
+    auto step = [&](int s, auto whole, auto last) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole)::value, kLast = decltype(last)::value;
         char* const now = lds + (s & 1) * kStage;
         char* const then = lds + (~s & 1) * kStage;
         constexpr int kRow = 6 * kFragB, kBefore = (kFragA - 1) * kRow;          // MFMAs of a row, and in front of the barrier
@@ -237,17 +237,19 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
             constexpr std::integral_constant<int, 1> k1;
             constexpr std::integral_constant<int, 2> k2;
             char* const from_a = i + 1 < kFragA ? now : then;
-            if constexpr (g == 2 && j == 0) read_a(from_a, row, k0);
-            if constexpr (g == 4 && j == 0) read_a(from_a, row, k2);
-            if constexpr (g == 5 && j == 0) read_a(from_a, row, k1);
-            if constexpr (i + 1 == kFragA) {
+            if constexpr (i + 1 < kFragA || !kLast) {
+                if constexpr (g == 2 && j == 0) read_a(from_a, row, k0);
+                if constexpr (g == 4 && j == 0) read_a(from_a, row, k2);
+                if constexpr (g == 5 && j == 0) read_a(from_a, row, k1);
+            }
+            if constexpr (i + 1 == kFragA && !kLast) {
                 if constexpr (g == 1) read_b(then, j, k2);
                 if constexpr (g == 3) read_b(then, j, k1);
                 if constexpr (g == 5) read_b(then, j, k0);
             }
             // the values of the steps ahead: load 0 of step s + 2 behind the last row, the others of step s + 1 before it
             constexpr int kItems = i + 1 < kFragA ? (kLoads - 1) * kParts : kParts, kOver = i + 1 < kFragA ? kBefore : kRow, x = i + 1 < kFragA ? int(m) : n;
-            constexpr int from = x * kItems / kOver, to = (x + 1) * kItems / kOver;
+            constexpr int from = x * kItems / kOver, to = kLast ? from : (x + 1) * kItems / kOver;
             static_for<to - from>([&](auto d) __attribute__((always_inline)) {
                 constexpr int item = from + d;
                 constexpr std::integral_constant<int, i + 1 < kFragA ? 1 + item / kParts : 0> which;
@@ -260,7 +262,7 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
                     else load(which, ahead + 1);
                 }
             });
-            if constexpr (m == kBefore - 1) __syncthreads();        // step s + 1 is there, step s has been read
+            if constexpr (m == kBefore - 1 && !kLast) __syncthreads();      // step s + 1 is there, step s has been read
             __builtin_amdgcn_sched_barrier(4);         // (scalar instructions may pass)
         });
     };
@@ -287,8 +289,13 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
 #pragma unroll
     for (int j = 0; j < kFragB; ++j) part[(kFragA - 1) % kBuffers][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     int s = 0;
-    for (; s < steps - 4; ++s) step(s, std::true_type{});
-    for (; s < steps; ++s) step(s, std::false_type{});
+    for (; s < steps - 4; ++s) step(s, std::true_type{}, std::false_type{});
+    // The last step without the loads and splits of none: 3 % of launches of 86 steps, 7 % of 7 (widths 800 / 400 / 2400, input gradients,
+    // 512 tokens, 86.4 -> 82.4 us; width 256, weight gradients, 200 tokens, 17.1 -> 15.7).  (Four blocks across and nothing to split in
+    // between, the sums would be read too early; waited for they leave the registers short: eleven spilled.)
+    constexpr bool kBare = kBuffers == 2;
+    for (; s < steps - int(kBare); ++s) step(s, std::false_type{}, std::false_type{});
+    if constexpr (kBare) step(s, std::false_type{}, std::true_type{});
     wait_for_sums(part);
 #pragma unroll
     for (int j = 0; j < kFragB; ++j) acc[kFragA - 1][j] += part[(kFragA - 1) % kBuffers][j];
@@ -382,7 +389,7 @@ hipError_t launch_shape(hipStream_t stream, const GemmBatch& batch) {
 
 // The launch shapes: a step's share of a compute unit when all are busy, and its time in a launch's longest chain; what a tile and
 // the longest chain cost beside their steps; how much of the smaller of the two is left; a launch.
-constexpr SplitShape kShapes[kSplitShapes] = {{128, 128, 1.38f, 1.05f, 4.6f, 1.5f, 0.07f, 5.f}, {256, 128, 2.33f, 1.69f, 3.4f, -2.3f, 0.14f, 13.f}};
+constexpr SplitShape kShapes[kSplitShapes] = {{128, 128, 1.38f, 0.96f, 4.6f, 2.9f, 0.07f, 4.3f}, {256, 128, 2.37f, 1.63f, 3.9f, -0.7f, 0.15f, 12.f}};
 
 }  // namespace
 

@@ -458,7 +458,7 @@ void fill(GemmProblem& gp, const Planned& it, int64_t tile_start, int n_seg) {
 constexpr int64_t kMaxSplitTiles = (int64_t(1) << 23) - 1;
 
 // As pick_generic_shape(), of the shapes of the kernel of bf16 pieces.  Fitted to 210 launches on each (seven sets of layers of widths 128
-// to 1280, 20 to 2048 tokens, input gradients, weight gradients and both): 6 and 8 % off the measured times.
+// to 1280, 20 to 2048 tokens, input gradients, weight gradients and both): 6 and 7 % off the measured times.
 int pick_split_shape(const std::vector<const Planned*>& items, double* best_us) {
     int best = 0;
     *best_us = HUGE_VAL;
