@@ -475,9 +475,10 @@ int pick_split_shape(const std::vector<const Planned*>& items, double* best_us) 
 
 // What the two halves of an fp32 call, input gradients `x` and weight gradients `w`, run on: launch shapes, and whether they share a
 // launch.  The input gradients go to the kernel of bf16 pieces where that is expected to be done first, by themselves - their bits
-// must not depend on which tensors are frozen (5 % sooner: a short launch of the other half that stays on the generic kernel then is one
-// of its own).  The weight gradients join them in one launch or have one of their own on the other kernel, as is expected
-// to be done first.  A launch of the generic kernel takes some 4 us that its estimate leaves out.
+// must not depend on which tensors are frozen.  The weight gradients join them in one launch or have one of their own on the other
+// kernel, as is expected to be done first.  A launch of the generic kernel takes some 4 us that its estimate leaves out.  (Widths 864 / 864 /
+// 2798, 475 tokens, where the two kernels' input gradients are level: 98 and 100 us, with all weight gradients 139 and 193.  Where
+// the generic kernel's are ahead they stay there, 440 tokens 90 and 98 us, though with the weight gradients it is 178 and 134.)
 // What the generic kernel would contract in 64 bits (its smallest tiles) stays there: the other's error is a little less than that
 // of sums in 32 bits (1.0e-7 and 1.2e-7 at 256 values, 1.9e-7 and 2.0e-7 at 2731), not than 2.5e-8.
 struct ChoiceF32 { int x, w; bool together; };
@@ -497,7 +498,7 @@ ChoiceF32 choose_f32(const std::vector<const Planned*>& x, const std::vector<con
         return h;
     };
     const Half hx = half(x, Layout::kNT), hw = half(w, Layout::kTN);
-    const bool x_split = hx.split_us < 0.95 * hx.generic_us, w_split = hw.split_us < hw.generic_us;
+    const bool x_split = hx.split_us < hx.generic_us, w_split = hw.split_us < hw.generic_us;
     const ChoiceF32 apart{x_split ? hx.split : hx.generic, w_split ? hw.split : hw.generic, false};
     if (x.empty() || w.empty() || x.size() + w.size() > size_t(kMaxProblemsPerLaunch)) return apart;
     if (!x_split) {
