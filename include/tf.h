@@ -135,7 +135,10 @@ const char* tf_version(void);
  *   Products accumulate in fp32; bf16 outputs are rounded to nearest even once.
  *   n_layers == 0 is a no-op.  With io_dtype TF_F32 nothing is rounded to less than
  *   fp32: products are those of fp32 values (large launches form them from the values'
- *   bf16 pieces, all 24 bits of them, with no larger error), sums have 32 bits or 64.
+ *   bf16 pieces, all 24 bits of them: to 2^-24 of a product, rounded to either side),
+ *   sums have 32 bits or 64.  An output's error is no larger that way than with fp32
+ *   products summed in 32 bits, up to contractions of 6000 values (T for dW, N_l for
+ *   dX; 1 % more at 8192, 5 % at 32768).
  *   With io_dtype TF_BF16 a layer's outputs depend on that layer alone, bit for bit.
  *   With TF_F32 their last bits also depend on the other layers of the call: the
  *   sums of a launch - all dX, or the dW of all unfrozen layers - are formed in 64

@@ -1,12 +1,19 @@
 // fp32 products on the bf16 matrix cores, for launches of the fp32 configuration that the fp32 matrix pipe bounds (TimelyFreeze
 // Sec. 3.2.1, both halves of a backward action).
 //
-// A value is the sum of three bf16 ones, its upper, middle and lower 8 bits: x = x0 + x1 + x2, exactly.  Of the nine products of two
-// values' pieces the six of 2^-16 and more are contracted, 32 values per instruction, in 96 cycles per 16 x 16 block where
-// v_mfma_f32_16x16x4_f32 takes 256; the three left out are 2^-24 of the product and less.  A step's products are summed by themselves, the
-// small ones first, and then added to the sums so far, as in the generic kernel.  Errors against 64 bits, in brackets those of the
-// generic kernel's sums in 32 bits, width 1024: contraction 200 9.1e-8 (1.2e-7), 1000 1.3e-7 (1.5e-7), 2731 1.9e-7 (2.0e-7).  (All six chained
-// into one sum 2.2e-7, 3.2e-7: the instruction rounds four times, after every 8 values.)
+// A value is the sum of three bf16 ones, exactly: x = x0 + x1 + x2, x0 the value rounded to bf16, x1 what is left rounded to bf16, x2 the
+// rest (Henry, Tang, Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019).  Of
+// the nine products of two values' pieces the six of 2^-16 and more are contracted, 32 values per instruction, in 96 cycles per 16 x 16 block
+// where v_mfma_f32_16x16x4_f32 takes 256.  For x in [1, 2) |x1| <= 2^-8 and |x2| <= 2^-17, of either sign: the three products left out are
+// 2 * 2^-25 of the product and little more, as often too much as too little.  (Pieces cut off and not rounded have the value's sign, x1 <
+// 2^-7 and x2 < 2^-15: 2^-21, always too little.)  A step's products are summed by themselves, the small ones first, and then added to
+// the sums so far, as in the generic kernel.
+// Errors against 64 bits, relative rms, in brackets those of the generic kernel's sums in 32 bits.  Normal operands: contraction 64 4.7e-8
+// (1.06e-7), 200 6.8e-8 (1.16e-7), 1000 1.19e-7 (1.48e-7), 2731 1.84e-7 (1.98e-7), 4900 2.42e-7 (2.48e-7); their absolute values: 200 5.0e-8
+// (5.9e-8), 1000 9.2e-8 (9.3e-8), 2731 1.33e-7 (1.34e-7).  On top of that the instruction aligns small products by cutting them off: sums are
+// too low by 1.7e-9 of the sum of the products' magnitudes.  From some 7000 values of either sign on that is more than the generic
+// kernel's own roundings inside a step: 6000 2.66e-7 (2.69e-7), 8192 3.08e-7 (3.06e-7), 32768 6.06e-7 (5.81e-7).
+// (All six products chained into one sum: 2.2e-7 and more at 200; the instruction rounds four times, after every 8 values.)
 //
 // What bounds it: the vector instructions that split, 11 per pair of values, and add, beside the matrix instructions.  A wave's
 // own two per matrix instruction cost nothing, a third 4 cycles; another wave's get every eighth cycle or so while matrix
@@ -29,14 +36,13 @@ constexpr int kSplitThreads = 512;              // eight waves
 constexpr int kBK = 32;                         // contraction values per step
 typedef U4 U4any4 __attribute__((aligned(4)));
 
-// Takes the next bf16 pieces off two values; returns them packed.  (The upper 16 bits: a piece is never larger than the value, so
-// that no piece of a finite value is infinite.)
+// Takes the next bf16 pieces off two values; returns them packed.  Rounded to nearest even, what is left is at most half of the
+// piece's last place, of either sign; the last piece is all that is left, 8 bits (of values of 2^-110 and more: see `lost`).
 __device__ __forceinline__ uint32_t take_piece(uint32_t& x0, uint32_t& x1, bool last) {
-    const uint32_t piece = __builtin_amdgcn_perm(x1, x0, 0x07060302u);
-    if (!last) {
-        x0 = __float_as_uint(__uint_as_float(x0) - __uint_as_float(x0 & 0xffff0000u));
-        x1 = __float_as_uint(__uint_as_float(x1) - __uint_as_float(x1 & 0xffff0000u));
-    }
+    if (last) return __builtin_amdgcn_perm(x1, x0, 0x07060302u);
+    const uint32_t piece = f32x2_to_bf16x2(__uint_as_float(x0), __uint_as_float(x1));
+    x0 = __float_as_uint(__uint_as_float(x0) - __uint_as_float(piece << 16));
+    x1 = __float_as_uint(__uint_as_float(x1) - __uint_as_float(piece & 0xffff0000u));
     return piece;
 }
 
@@ -55,7 +61,7 @@ struct SplitOperand {
 
     const char* matrix;
     int64_t unit;               // bytes from one contraction value to the next
-    uint32_t off[kLoads];
+    uint32_t off[kContig ? kLoads : 1];
     int extent, origin;
     int to, from;               // bytes inside a stage: of load 0's first piece, of this lane's part of a wave's first fragment
 
@@ -64,13 +70,13 @@ struct SplitOperand {
         const int lane = threadIdx.x & 63, q = lane >> 4;
         matrix = static_cast<const char*>(base) + (kContig ? int64_t(origin) * ld * 4 : 0);
         unit = kContig ? 4 : ld * 4;
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i)
-            off[i] = kContig ? uint32_t(min(row(i, thread), extent - 1 - origin)) * uint32_t(ld * 4) + c * 16 : uint32_t(row(i, thread)) * uint32_t(ld * 4) + uint32_t(col(thread)) * 4;
         if (kContig) {
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) off[kContig ? i : 0] = uint32_t(min(row(i, thread), extent - 1 - origin)) * uint32_t(ld * 4) + c * 16;
             to = row(0, thread) * kPitch + chunk(row(0, thread), c >> 1) + ((c & 1) << 3);
             from = (w * 16 + (lane & 15)) * kPitch + chunk(lane & 15, q);
         } else {
+            off[0] = uint32_t(row(0, thread)) * uint32_t(ld * 4) + uint32_t(col(thread)) * 4;
             const int r = 8 * q + ((lane & 15) >> 2);
             to = at(c >> 2, row(0, thread)) + ((c & 3) << 3);
             from = at(w, r) + ((lane & 3) << 3);
@@ -104,9 +110,9 @@ struct SplitOperand {
 
     // Load i of the 32 contraction values from k on; `last`: they are the contraction's last ones.
     __device__ __forceinline__ U4 load(int i, int k, bool last) const {
-        uint32_t o = kContig ? off[i] : off[i] - (over(i, this_thread()) * 4 & -int(last));
+        uint32_t o = kContig ? off[kContig ? i : 0] : off[0] - (over(i, this_thread()) * 4 & -int(last));
         asm volatile("" : "+v"(o));             // (a 32-bit offset to a scalar base: widened outside of the loop it takes two registers and an addition)
-        return *reinterpret_cast<const U4any4*>(matrix + k * unit + o);
+        return *reinterpret_cast<const U4any4*>(matrix + (kContig ? k : k + i * kDown) * unit + o);
     }
     // What it fetched, in its place, the first `back` contraction values zero.  (No branches: selections only.)
     __device__ __forceinline__ U4 finish(int i, U4 v, int back, bool last) const {

@@ -479,8 +479,8 @@ int pick_split_shape(const std::vector<const Planned*>& items, double* best_us) 
 // kernel, as is expected to be done first.  A launch of the generic kernel takes some 4 us that its estimate leaves out.  (Widths 864 / 864 /
 // 2798, 475 tokens, where the two kernels' input gradients are level: 98 and 100 us, with all weight gradients 139 and 193.  Where
 // the generic kernel's are ahead they stay there, 440 tokens 90 and 98 us, though with the weight gradients it is 178 and 134.)
-// What the generic kernel would contract in 64 bits (its smallest tiles) stays there: the other's error is a little less than that
-// of sums in 32 bits (1.0e-7 and 1.2e-7 at 256 values, 1.9e-7 and 2.0e-7 at 2731), not than 2.5e-8.
+// What the generic kernel would contract in 64 bits (its smallest tiles) stays there: the other's error is less than that of sums in
+// 32 bits (6.8e-8 and 1.16e-7 at 200 values, 1.84e-7 and 1.98e-7 at 2731), not than 2.5e-8.
 struct ChoiceF32 { int x, w; bool together; };
 ChoiceF32 choose_f32(const std::vector<const Planned*>& x, const std::vector<const Planned*>& w, int route) {
     constexpr double kLaunch = 4;

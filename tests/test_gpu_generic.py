@@ -448,6 +448,47 @@ def test_fp32_calls_of_bf16_pieces(ctx, T, tile):
     assert errors[20] <= 1.05 * errors[F32_TILES + 4]              # (of 18 outputs, some of a few values: a rounding more or less)
 
 
+def _against_64_bits(ctx, which, W, X, dY):
+    """dX and dW of one layer on that route: relative rms and mean error (towards larger magnitudes) and the largest relative one of both."""
+    dX, dW = [torch.empty_like(X)], [torch.empty_like(W)]
+    with route(ctx, which):
+        tf.tf_stage_backward(ctx, [tuple(W.shape)], X.shape[0], tf.TF_F32, [W], [X], [dY], None, dX, dW, tf.TF_F32)
+    out = []
+    for got, exact in ((dX[0], dY.double() @ W.double().t().contiguous()), (dW[0], X.double().t().contiguous() @ dY.double())):
+        d = got.double() - exact
+        out.append([float(d.norm() / exact.norm()), float((d * exact.sign()).mean() / exact.abs().mean()), float((d / exact).abs().max())])
+    return np.array(out)
+
+
+@pytest.mark.parametrize("tile", sorted(SPLIT))
+@pytest.mark.parametrize("T", [64, 200, 1000])
+@pytest.mark.parametrize("operands", ["absolute values of normal ones", "1 to 1.01", "1 to 2"])
+def test_fp32_products_of_one_sign_have_no_error_of_one_sign(ctx, operands, T, tile):
+    """What the three pieces of two values leave out of their product is as often too much as too little: sums of products of one sign are no
+    further off than sums of fp32 products in 32 bits.  (Mean of some 10^5 errors of 2^-24 and less, each row's and column's in common: 2^-30;
+    pieces cut off and not rounded are off by 2^-25 to 2^-24 on average.)"""
+    rs = np.random.default_rng(T)
+    draw = {"absolute values of normal ones": lambda *s: np.abs(rs.standard_normal(s)), "1 to 1.01": lambda *s: rs.uniform(1, 1.01, s),
+            "1 to 2": lambda *s: rs.uniform(1, 2, s)}[operands]
+    W, X, dY = (dev(draw(*s).astype(np.float32), "f32") for s in ((260, T), (T, 260), (T, T)))         # both contractions are of T
+    pieces, generic = (_against_64_bits(ctx, which, W, X, dY) for which in (SPLIT[tile], F32_TILES + 4))
+    assert (pieces[:, 0] <= 1.02 * generic[:, 0]).all(), (pieces, generic)
+    assert (np.abs(pieces[:, 1]) <= 2.0 ** -27).all(), pieces
+
+
+@pytest.mark.parametrize("tile", sorted(SPLIT))
+@pytest.mark.parametrize("T", [64, 200])
+@pytest.mark.parametrize("value", [1 + 2.0 ** -7 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -17 - 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -17 + 2.0 ** -23])
+def test_fp32_products_of_the_worst_mantissas(ctx, value, T, tile):
+    """Equal operands, so that all errors add up.  Cut off, pieces lose most where the lower 16 bits are all ones, 2^-21 of the product;
+    rounded, where the first two are off by half of their last places: 2 * 2^-8 * 2^-17.  Besides, in units of 2^-24 of the result: a step's last
+    instruction rounds at 1/4, 1/2, 3/4 and all of its sum, the five before it at 2^-7 of that; S steps' sums are added, at (S + 1) / 2 of the result."""
+    W, X, dY = (torch.full(s, value, device="cuda") for s in ((260, T), (T, 260), (T, T)))
+    bound = 2.0 ** -24 * (1.01 + 2.5 + 5 * 4 * 2.0 ** -7 + ((T + 31) // 32 + 1) / 2)
+    got = _against_64_bits(ctx, SPLIT[tile], W, X, dY)
+    assert (got[:, 2] <= bound).all(), (got, bound)
+
+
 @pytest.mark.parametrize("tile", sorted(SPLIT))
 @pytest.mark.parametrize("what", ["infinity", "overflow", "tiny"])
 def test_values_that_bf16_pieces_cannot_hold(ctx, what, tile):
