@@ -140,11 +140,12 @@ const char* tf_version(void);
  *   products summed in 32 bits, up to contractions of 6000 values (T for dW, N_l for
  *   dX; 1 % more at 8192, 5 % at 32768).
  *   With io_dtype TF_BF16 a layer's outputs depend on that layer alone, bit for bit.
- *   With TF_F32 their last bits also depend on the other layers of the call: the
- *   sums of a launch - all dX, or the dW of all unfrozen layers - are formed in 64
- *   bits if the launch is a short one, in 32 bits otherwise (which of the two
- *   follows from the problems' sizes and the number of compute units).  Under
- *   another freeze mask an fp32 dW may therefore differ by the error of 32-bit sums.
+ *   With TF_F32 their last bits also depend on the other layers of the call: sums are
+ *   formed in 64 bits if the launch is a short one, otherwise in 32 bits, of fp32
+ *   products or of those of bf16 pieces.  Which of the three follows from the number
+ *   of compute units and, for dX, from the sizes of all layers whatever the mask; for
+ *   dW from those of the unfrozen layers and of all dX.  Under another freeze mask an
+ *   fp32 dW may therefore differ by the error of 32-bit sums, a dX by nothing.
  */
 int tf_stage_backward(tf_ctx* ctx, void* hip_stream,
                       int32_t n_layers, const tf_shape* shapes,

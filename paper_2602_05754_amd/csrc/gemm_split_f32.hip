@@ -46,6 +46,13 @@ __device__ __forceinline__ uint32_t take_piece(uint32_t& x0, uint32_t& x1, bool 
     return piece;
 }
 
+// The thread's number, for what is worked out where it is needed and not once in front of the loop into registers that it has not.
+__device__ __forceinline__ int this_thread() {
+    int t = int(threadIdx.x);
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // One operand of a workgroup's tile: kWaves waves contract kFrags blocks of 16 rows of it each, block i of wave w being number kWaves i + w.
 template <bool kContig, int kWaves, int kFrags>
 struct SplitOperand {
@@ -101,13 +108,6 @@ struct SplitOperand {
         return c < extent ? c : 0;
     }
     __device__ __forceinline__ int over(int i, int thread) const { return !kContig && row(i, thread) == kBK - 1 ? max(col(thread) + 4 - extent, 0) : 0; }
-    // (for what is worked out where it is needed, not once in front of the loop into registers that it has not)
-    __device__ __forceinline__ static int this_thread() {
-        int t = int(threadIdx.x);
-        asm volatile("" : "+v"(t));
-        return t;
-    }
-
     // Load i of the 32 contraction values from k on; `last`: they are the contraction's last ones.
     __device__ __forceinline__ U4 load(int i, int k, bool last) const {
         uint32_t o = kContig ? off[kContig ? i : 0] : off[0] - (over(i, this_thread()) * 4 & -int(last));
@@ -146,6 +146,97 @@ struct SplitOperand {
     }
 };
 
+// What three pieces cannot hold: an infinity meets zeros among the other value's pieces, a first piece rounds to infinity or a sum of
+// pieces leaves the range where the sum does not, a piece below bf16's smallest value loses bits.  (The matrix instructions keep
+// subnormal pieces and sums: nothing else is lost from 2^-110 on.)  Outputs that this may have reached are computed again from fp32 products, in
+// blocks of 32 x 64 that lie where they lie in either tile, by the contents of the block's own rows and columns: neither
+// the tile nor anything else in the launch says which way an element is computed.
+constexpr int kBlockM = 32, kBlockN = 64;
+__device__ __forceinline__ bool finite(float x) { return __builtin_fabsf(x) < __builtin_huge_valf(); }
+// Do pieces lose bits of one of the values?
+__device__ __forceinline__ bool lose_bits(f32x4 v) {
+    uint32_t smallest = ~0u;            // magnitude but zero, doubled, minus one
+#pragma unroll
+    for (int e = 0; e < 4; ++e) smallest = min(smallest, (__float_as_uint(v[e]) << 1) - 1);
+    if (smallest >= (__float_as_uint(0x1p-110f) << 1) - 1) return false;
+    uint32_t left = 0;
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+        uint32_t x0 = __float_as_uint(v[e]), x1 = __float_as_uint(v[e + 1]);
+        take_piece(x0, x1, false);
+        take_piece(x0, x1, false);
+        left |= x0 | x1;
+    }
+    return (left & 0xffffu) != 0;
+}
+// Which rows of an operand (kRows from `origin` on) hold values of which pieces lose bits: lost[r] = 1.  One pass over them, eight
+// loads on their way; what would lie beyond the matrix is shifted back inside (at least 32 contraction values, kTN: at least 4 rows).
+template <bool kContig, int kRows>
+__device__ __forceinline__ void look_at_rows(const void* base, int64_t ld, int extent, int origin, int Kc, uint32_t* lost) {
+    const float* const matrix = static_cast<const float*>(base);
+    const int thread = this_thread(), lane = thread & 63, wave = thread >> 6;
+    constexpr int kMany = 8;
+    if constexpr (kContig) {            // a wave: eight rows, 256 contraction values of each at a time
+        for (int r0 = wave * kMany; r0 < kRows; r0 += kSplitThreads / 64 * kMany) {
+            bool found[kMany] = {};
+            for (int k = lane * 4; k < Kc; k += 256) {
+                f32x4 v[kMany];
+#pragma unroll
+                for (int i = 0; i < kMany; ++i) v[i] = *reinterpret_cast<const F4any*>(matrix + int64_t(min(origin + r0 + i, extent - 1)) * ld + min(k, Kc - 4));
+#pragma unroll
+                for (int i = 0; i < kMany; ++i) found[i] = found[i] || lose_bits(v[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < kMany; ++i)
+                if (found[i]) lost[r0 + i] = 1;
+        }
+    } else {                            // a thread: four rows, every kDown-th contraction value
+        constexpr int kAcross = kRows / 4, kDown = kSplitThreads / kAcross;
+        const int first = min(origin + thread % kAcross * 4, extent - 4);
+        uint32_t found = 0;
+        for (int k0 = thread / kAcross; k0 < Kc; k0 += kDown * kMany) {
+            f32x4 v[kMany];
+#pragma unroll
+            for (int i = 0; i < kMany; ++i) v[i] = *reinterpret_cast<const F4any*>(matrix + int64_t(min(k0 + i * kDown, Kc - 1)) * ld + first);
+#pragma unroll
+            for (int i = 0; i < kMany; ++i)
+                if (lose_bits(v[i])) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) found |= uint32_t(lose_bits(f32x4{v[i][e], 0.f, 0.f, 0.f})) << e;
+                }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((found >> e & 1) && first + e >= origin) lost[first + e - origin] = 1;
+    }
+}
+// The blocks of a tile to be computed again, bit 2 (row / 32) + column / 64.  The tile's sums lie in `lds`, `side` is free LDS behind them.
+template <bool kContig, int kTileM, int kTileN>
+__device__ __forceinline__ uint32_t odd_blocks(const GemmProblem& P, TileAt at, const char* lds, uint32_t* side) {
+    static_assert(kTileM / kBlockM * (kTileN / kBlockN) <= 32 && kTileN == 2 * kBlockN, "a bit per block");
+    uint32_t* const blocks = side;
+    uint32_t* const of_row = side + 1;
+    uint32_t* const of_col = of_row + kTileM;
+    const int thread = this_thread();
+    __syncthreads();
+    for (int i = thread; i < 1 + kTileM + kTileN; i += kSplitThreads) side[i] = 0;
+    __syncthreads();
+    look_at_rows<kContig, kTileM>(P.A, P.lda, P.M, at.m, P.Kc, of_row);
+    look_at_rows<kContig, kTileN>(P.B, P.ldb, P.N, at.n, P.Kc, of_col);
+    __syncthreads();
+    constexpr int kLanes = kTileN / 4;
+    const int c = thread % kLanes;
+    for (int r = thread / kLanes; r < kTileM && at.m + r < P.M; r += kSplitThreads / kLanes) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + r * kTileN * 4 + ((c ^ (r & 15)) << 4));
+        bool odd = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) odd = odd || (at.n + c * 4 + e < P.N && (!finite(v[e]) || of_row[r] != 0 || of_col[c * 4 + e] != 0));
+        if (odd) atomicOr(blocks, 1u << (r / kBlockM * 2 + c / (kBlockN / 4)));
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*blocks);
+}
+
 // (the layout kTN has the larger stages)
 template <int kTileM, int kTileN, int kWavesM>
 constexpr int split_lds() {
@@ -159,7 +250,7 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
     typedef SplitOperand<kContig, kWavesN, kFragB> OpB;
     constexpr int kStage = OpA::kStageBytes + OpB::kStageBytes, kLoads = OpA::kLoads + OpB::kLoads;
     static_assert(kFragA % 2 == 0, "the last row of a step and the first of the next hold piece 0 in different registers");
-    static_assert(kTileM * kTileN * 4 <= 2 * kStage, "the sums are turned around in the stages");
+    static_assert(kTileM * kTileN * 4 + (1 + kTileM + kTileN) * 4 <= 2 * kStage, "the sums are turned around in the stages, with odd_blocks()' notes behind them");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / kWavesN, wn = wave % kWavesN;
@@ -307,51 +398,36 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
     for (int j = 0; j < kFragB; ++j) acc[kFragA - 1][j] += part[(kFragA - 1) % kBuffers][j];
     __syncthreads();
 
-    // What three pieces cannot hold: an infinity has met zeros among the other value's pieces, a sum of pieces may have left the range
-    // where the sum does not, a piece below bf16's smallest value has lost bits.  Such a tile is computed again from fp32 products.
-    bool odd = (lost & 0xffffu) != 0;
-#pragma unroll
-    for (int i = 0; i < kFragA; ++i)
-#pragma unroll
-        for (int j = 0; j < kFragB; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) odd = odd || !(__builtin_fabsf(acc[i][j][e]) < __builtin_huge_valf());
-    int* const flags = reinterpret_cast<int*>(lds);
-    const bool wave_odd = __ballot(odd) != 0;
-    if (lane == 0) flags[wave] = wave_odd;
-    __syncthreads();
-    bool redo = false;
-#pragma unroll
-    for (int w = 0; w < kSplitThreads / 64; ++w) redo = redo || flags[w] != 0;
-    __syncthreads();
-    if (redo) {
-        // (beyond the matrix: nothing is stored)
-        constexpr int kSub = 2 * (32 + 64) * kStepBytes;
-        const int half = wave >> 2;
-        for (int m = m0; m < m0 + kTileM && m < M; m += 64)
-            for (int n = n0; n < n0 + kTileN && n < N; n += 64) {
-                if (add) contract_tile<float, kContig, false, true, 32, 64>(P, TileAt{m + 32 * half, n}, lds + half * kSub);
-                else contract_tile<float, kContig, false, false, 32, 64>(P, TileAt{m + 32 * half, n}, lds + half * kSub);
-                __syncthreads();
-            }
-        return;
-    }
+    // The sums are turned around in LDS; beside them the waves say whether pieces may have failed: a sum that is not finite, bits lost.
     constexpr int kRow = kTileN * 4, kTurn = 15;
+    uint32_t* const side = reinterpret_cast<uint32_t*>(lds + kTileM * kRow);
+    bool odd = (lost & 0xffffu) != 0;
 #pragma unroll
     for (int i = 0; i < kFragA; ++i)
 #pragma unroll
         for (int j = 0; j < kFragB; ++j) {
             const int r = 16 * (kWavesM * i + wm) + (lane & 15), c = 4 * (kWavesN * j + wn) + (lane >> 4);
             *reinterpret_cast<f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4)) = acc[i][j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) odd = odd || !finite(acc[i][j][e]);
         }
+    const bool wave_odd = __ballot(odd) != 0;
+    if (lane == 0) side[wave] = wave_odd;
     __syncthreads();
+    bool any_odd = false;
+#pragma unroll
+    for (int w = 0; w < kSplitThreads / 64; ++w) any_odd = any_odd || side[w] != 0;
+    uint32_t again = 0;
+    if (__builtin_amdgcn_readfirstlane(any_odd)) again = odd_blocks<kContig, kTileM, kTileN>(P, at, lds, side);
+
     constexpr int kLanes = kTileN / 4, kRowsPerPass = kSplitThreads / kLanes;
     const int c = int(threadIdx.x) % kLanes, n = n0 + c * 4;
+    const uint32_t skip = again >> (c / (kBlockN / 4));
 #pragma unroll
     for (int r0 = 0; r0 < kTileM; r0 += kRowsPerPass) {
         const int r = r0 + int(threadIdx.x) / kLanes, m = m0 + r;
         f32x4 v = *reinterpret_cast<const f32x4*>(lds + r * kRow + ((c ^ (r & kTurn)) << 4));
-        if (m >= M || n >= N) continue;
+        if (m >= M || n >= N || (skip >> (r0 / kBlockM * (kTileN / kBlockN)) & 1)) continue;
         float* out = static_cast<float*>(P.C) + int64_t(m) * N + n;
         if (n + 4 <= N) {
             if (add) v += *reinterpret_cast<const F4any*>(out);
@@ -361,6 +437,20 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
             for (int e = 0; e < 4; ++e)
                 if (n + e < N) out[e] = add ? out[e] + v[e] : v[e];
         }
+    }
+    // Two blocks at a time, each by four waves; without a second one those contract one that lies beyond the matrix, of which nothing is stored.
+    const int half = wave >> 2;
+    while (again != 0) {
+        __syncthreads();
+        const int first = __builtin_ctz(again);
+        again &= again - 1;
+        const int second = again != 0 ? __builtin_ctz(again) : -1;
+        again &= again - 1;             // (of 0: 0)
+        const int mine = half == 0 ? first : second;
+        const TileAt block = mine < 0 ? TileAt{M, n0} : TileAt{m0 + mine / (kTileN / kBlockN) * kBlockM, n0 + mine % (kTileN / kBlockN) * kBlockN};
+        char* const stages = lds + half * (2 * (kBlockM + kBlockN) * kStepBytes);
+        if (add) contract_tile<float, kContig, false, true, kBlockM, kBlockN>(P, block, stages);
+        else contract_tile<float, kContig, false, false, kBlockM, kBlockN>(P, block, stages);
     }
 }
 

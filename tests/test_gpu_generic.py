@@ -489,11 +489,20 @@ def test_fp32_products_of_the_worst_mantissas(ctx, value, T, tile):
     assert (got[:, 2] <= bound).all(), (got, bound)
 
 
+def _whole_blocks(odd):
+    """The blocks of 32 x 64 that have one."""
+    all_of = torch.zeros_like(odd)
+    for m in range(0, odd.shape[0], 32):
+        for n in range(0, odd.shape[1], 64):
+            all_of[m:m + 32, n:n + 64] = odd[m:m + 32, n:n + 64].any()
+    return all_of
+
+
 @pytest.mark.parametrize("tile", sorted(SPLIT))
 @pytest.mark.parametrize("what", ["infinity", "overflow", "tiny"])
 def test_values_that_bf16_pieces_cannot_hold(ctx, what, tile):
     """An infinity meets the zeros among another value's pieces, a sum of pieces may leave the range where the sum does not, and pieces of
-    values below 2^-110 lose bits: such tiles are computed from fp32 products, with the bits of the generic kernel's 32 x 64 tiles."""
+    values below 2^-110 lose bits: blocks of 32 x 64 outputs that have such ones are computed from fp32 products, with the bits of the generic kernel."""
     T, shapes = 100, [(300, 200)]
     W, X, dY = _random(shapes, T, "f32", 3)
     if what == "infinity":
@@ -513,18 +522,44 @@ def test_values_that_bf16_pieces_cannot_hold(ctx, what, tile):
         got.append((dX[0], dW[0]))
     for a, b in zip(*got):
         redone = torch.ones_like(a, dtype=torch.bool)
-        if what == "infinity":                                     # only tiles with a sum that is not finite
-            odd = ~torch.isfinite(b)
-            redone = torch.zeros_like(redone)
-            for m in range(0, a.shape[0], tile[0]):
-                for n in range(0, a.shape[1], tile[1]):
-                    redone[m:m + tile[0], n:n + tile[1]] = odd[m:m + tile[0], n:n + tile[1]].any()
+        if what == "infinity":                                     # only blocks with a sum that is not finite
+            redone = _whole_blocks(~torch.isfinite(b))
             assert redone.any()
         elif what == "overflow":
             redone = ~torch.isfinite(b)
             assert redone.any()
         assert torch.equal(a[redone].view(torch.int32), b[redone].view(torch.int32))
         assert torch.equal(torch.isfinite(a), torch.isfinite(b))
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("T,where", [(70, 69), (257, 3), (300, 130)])
+def test_infinities_change_the_bits_of_their_own_blocks_only(ctx, T, where, accumulate):
+    """One infinity per layer in dY: its row of dX and its column of dW are computed again, in blocks of 32 x 64 that are the same in both
+    tiles (two at a time, of an odd number the last beside one beyond the matrix), and nothing else changes a bit; with `accumulate` what
+    was there is added to once."""
+    shapes = [(300, 200), (257, 330), (70, 129)]
+    W, X, clean = _random(shapes, T, "f32", T)
+    old = [torch.randn(s, device="cuda") for s in shapes]
+    dY = [y.clone() for y in clean]
+    for y in dY:
+        y[where, y.shape[1] - 1] = float("inf")
+
+    def run(which, dY):
+        dX, dW = [Guarded((T, k), "f32") for k, n in shapes], [Guarded(s, "f32", o) for s, o in zip(shapes, old)]
+        with route(ctx, which):
+            tf.tf_stage_backward(ctx, shapes, T, tf.TF_F32, W, X, dY, None, [g.t for g in dX], [g.t for g in dW], tf.TF_F32, accumulate=accumulate)
+        for g in dX + dW:
+            g.check(f"T={T} {which}")
+        return [g.t for g in dX + dW]
+
+    plain, fp32 = run(20, clean), run(F32_TILES + 4, dY)
+    for which in SPLIT.values():
+        for got, without, generic in zip(run(which, dY), plain, fp32):
+            odd = ~torch.isfinite(generic)
+            assert odd.any() and not odd.all()
+            blocks = _whole_blocks(odd)
+            assert torch.equal(got.view(torch.int32), torch.where(blocks, generic, without).view(torch.int32)), (which, tuple(got.shape))
 
 
 @pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
