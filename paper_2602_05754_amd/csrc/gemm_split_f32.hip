@@ -151,6 +151,10 @@ struct SplitOperand {
 // subnormal pieces and sums: nothing else is lost from 2^-110 on.)  Outputs that this may have reached are computed again from fp32 products, in
 // blocks of 32 x 64 that lie where they lie in either tile, by the contents of the block's own rows and columns: neither
 // the tile nor anything else in the launch says which way an element is computed.
+// What it costs: a tile that notices anything reads its rows and columns once more, 10 to 20 % of its time; a pair of blocks takes a chain of fp32
+// steps, 36 us at 2731 values.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us (generic kernel): ordinary values 522 (769); every dY
+// with one tiny value 558 (736), with one in every row 697 (739), with one infinity 720 (745), all NaN 568 (725); all infinite 1802 (727),
+// all tiny 1860 (1518): every product twice, once in fp32 with two tiles of 32 x 64 per unit.
 constexpr int kBlockM = 32, kBlockN = 64;
 __device__ __forceinline__ bool finite(float x) { return __builtin_fabsf(x) < __builtin_huge_valf(); }
 // Do pieces lose bits of one of the values?
@@ -169,57 +173,91 @@ __device__ __forceinline__ bool lose_bits(f32x4 v) {
     }
     return (left & 0xffffu) != 0;
 }
-// Which rows of an operand (kRows from `origin` on) hold values of which pieces lose bits: lost[r] = 1.  One pass over them, eight
-// loads on their way; what would lie beyond the matrix is shifted back inside (at least 32 contraction values, kTN: at least 4 rows).
+// What a row or column of the tile holds: its largest magnitude, doubled (a NaN is larger than everything), and whether pieces lose
+// bits of one of its values.
+struct RowNotes { uint32_t largest, lost; };
+__device__ __forceinline__ uint32_t twice_magnitude(f32x4 v) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(v[e]) << 1);
+    return m;
+}
+// The notes of kRows rows of an operand from `origin` on.  One pass over them, eight loads on their way; what would lie beyond the
+// matrix is shifted back inside (at least 32 contraction values, kTN: at least 4 rows).
 template <bool kContig, int kRows>
-__device__ __forceinline__ void look_at_rows(const void* base, int64_t ld, int extent, int origin, int Kc, uint32_t* lost) {
+__device__ __forceinline__ void look_at_rows(const void* base, int64_t ld, int extent, int origin, int Kc, RowNotes* notes) {
     const float* const matrix = static_cast<const float*>(base);
     const int thread = this_thread(), lane = thread & 63, wave = thread >> 6;
     constexpr int kMany = 8;
     if constexpr (kContig) {            // a wave: eight rows, 256 contraction values of each at a time
         for (int r0 = wave * kMany; r0 < kRows; r0 += kSplitThreads / 64 * kMany) {
             bool found[kMany] = {};
+            uint32_t largest[kMany] = {};
             for (int k = lane * 4; k < Kc; k += 256) {
                 f32x4 v[kMany];
 #pragma unroll
                 for (int i = 0; i < kMany; ++i) v[i] = *reinterpret_cast<const F4any*>(matrix + int64_t(min(origin + r0 + i, extent - 1)) * ld + min(k, Kc - 4));
 #pragma unroll
-                for (int i = 0; i < kMany; ++i) found[i] = found[i] || lose_bits(v[i]);
+                for (int i = 0; i < kMany; ++i) {
+                    largest[i] = max(largest[i], twice_magnitude(v[i]));
+                    found[i] = found[i] || lose_bits(v[i]);
+                }
             }
 #pragma unroll
-            for (int i = 0; i < kMany; ++i)
-                if (found[i]) lost[r0 + i] = 1;
+            for (int i = 0; i < kMany; ++i) {
+#pragma unroll
+                for (int d = 32; d > 0; d >>= 1) largest[i] = max(largest[i], uint32_t(__shfl_xor(int(largest[i]), d)));
+                if (lane == 0) notes[r0 + i].largest = largest[i];
+                if (found[i]) notes[r0 + i].lost = 1;
+            }
         }
     } else {                            // a thread: four rows, every kDown-th contraction value
         constexpr int kAcross = kRows / 4, kDown = kSplitThreads / kAcross;
         const int first = min(origin + thread % kAcross * 4, extent - 4);
-        uint32_t found = 0;
+        uint32_t found = 0, largest[4] = {};
         for (int k0 = thread / kAcross; k0 < Kc; k0 += kDown * kMany) {
             f32x4 v[kMany];
 #pragma unroll
             for (int i = 0; i < kMany; ++i) v[i] = *reinterpret_cast<const F4any*>(matrix + int64_t(min(k0 + i * kDown, Kc - 1)) * ld + first);
 #pragma unroll
-            for (int i = 0; i < kMany; ++i)
+            for (int i = 0; i < kMany; ++i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) largest[e] = max(largest[e], __float_as_uint(v[i][e]) << 1);
                 if (lose_bits(v[i])) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) found |= uint32_t(lose_bits(f32x4{v[i][e], 0.f, 0.f, 0.f})) << e;
                 }
+            }
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if ((found >> e & 1) && first + e >= origin) lost[first + e - origin] = 1;
+            if (first + e >= origin) {
+                atomicMax(&notes[first + e - origin].largest, largest[e]);
+                if (found >> e & 1) notes[first + e - origin].lost = 1;
+            }
     }
 }
+// Is a sum of row x and column y to be computed again?  Not if one of them holds a NaN: it is one either way.  Else if it is not
+// finite, or if the lost bits, less than 2^-133 of a value each, could change it by 2^-30 of itself (which a single tiny value
+// among ordinary ones does not do).
+__device__ __forceinline__ bool sum_is_odd(float sum, RowNotes x, RowNotes y, float n_values) {
+    const uint32_t infinite = __float_as_uint(__builtin_huge_valf()) << 1;
+    if (x.largest > infinite || y.largest > infinite) return false;
+    const float reach = (x.lost ? __uint_as_float(y.largest >> 1) : 0.f) + (y.lost ? __uint_as_float(x.largest >> 1) : 0.f);
+    return !finite(sum) || !(n_values * 0x1p-103f * reach <= __builtin_fabsf(sum));
+}
 // The blocks of a tile to be computed again, bit 2 (row / 32) + column / 64.  The tile's sums lie in `lds`, `side` is free LDS behind them.
+template <int kTileM, int kTileN>
+constexpr int kNotes = 2 + 2 * (kTileM + kTileN);       // words of `side`
 template <bool kContig, int kTileM, int kTileN>
 __device__ __forceinline__ uint32_t odd_blocks(const GemmProblem& P, TileAt at, const char* lds, uint32_t* side) {
     static_assert(kTileM / kBlockM * (kTileN / kBlockN) <= 32 && kTileN == 2 * kBlockN, "a bit per block");
     uint32_t* const blocks = side;
-    uint32_t* const of_row = side + 1;
-    uint32_t* const of_col = of_row + kTileM;
+    RowNotes* const of_row = reinterpret_cast<RowNotes*>(side + 2);
+    RowNotes* const of_col = of_row + kTileM;
     const int thread = this_thread();
     __syncthreads();
-    for (int i = thread; i < 1 + kTileM + kTileN; i += kSplitThreads) side[i] = 0;
+    for (int i = thread; i < kNotes<kTileM, kTileN>; i += kSplitThreads) side[i] = 0;
     __syncthreads();
     look_at_rows<kContig, kTileM>(P.A, P.lda, P.M, at.m, P.Kc, of_row);
     look_at_rows<kContig, kTileN>(P.B, P.ldb, P.N, at.n, P.Kc, of_col);
@@ -230,7 +268,7 @@ __device__ __forceinline__ uint32_t odd_blocks(const GemmProblem& P, TileAt at, 
         const f32x4 v = *reinterpret_cast<const f32x4*>(lds + r * kTileN * 4 + ((c ^ (r & 15)) << 4));
         bool odd = false;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) odd = odd || (at.n + c * 4 + e < P.N && (!finite(v[e]) || of_row[r] != 0 || of_col[c * 4 + e] != 0));
+        for (int e = 0; e < 4; ++e) odd = odd || (at.n + c * 4 + e < P.N && sum_is_odd(v[e], of_row[r], of_col[c * 4 + e], float(P.Kc)));
         if (odd) atomicOr(blocks, 1u << (r / kBlockM * 2 + c / (kBlockN / 4)));
     }
     __syncthreads();
@@ -250,7 +288,7 @@ __device__ __forceinline__ void contract_split(const GemmProblem& P, TileAt at, 
     typedef SplitOperand<kContig, kWavesN, kFragB> OpB;
     constexpr int kStage = OpA::kStageBytes + OpB::kStageBytes, kLoads = OpA::kLoads + OpB::kLoads;
     static_assert(kFragA % 2 == 0, "the last row of a step and the first of the next hold piece 0 in different registers");
-    static_assert(kTileM * kTileN * 4 + (1 + kTileM + kTileN) * 4 <= 2 * kStage, "the sums are turned around in the stages, with odd_blocks()' notes behind them");
+    static_assert(kTileM * kTileN * 4 + kNotes<kTileM, kTileN> * 4 <= 2 * kStage, "the sums are turned around in the stages, with odd_blocks()' notes behind them");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / kWavesN, wn = wave % kWavesN;

@@ -534,16 +534,21 @@ def test_values_that_bf16_pieces_cannot_hold(ctx, what, tile):
 
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("T,where", [(70, 69), (257, 3), (300, 130)])
-def test_infinities_change_the_bits_of_their_own_blocks_only(ctx, T, where, accumulate):
+@pytest.mark.parametrize("what", ["infinity", "nan", "a tiny value", "a tiny row"])
+def test_odd_values_change_the_bits_of_their_own_blocks_only(ctx, what, T, where, accumulate):
     """One infinity per layer in dY: its row of dX and its column of dW are computed again, in blocks of 32 x 64 that are the same in both
     tiles (two at a time, of an odd number the last beside one beyond the matrix), and nothing else changes a bit; with `accumulate` what
-    was there is added to once."""
+    was there is added to once.  A row of tiny values is computed again where it is all that a sum consists of: in dX.  A NaN, and a
+    tiny value that loses bits (2^-120 + 2^-140: the 2^-140) among ordinary ones, have nothing computed again."""
     shapes = [(300, 200), (257, 330), (70, 129)]
     W, X, clean = _random(shapes, T, "f32", T)
     old = [torch.randn(s, device="cuda") for s in shapes]
     dY = [y.clone() for y in clean]
-    for y in dY:
-        y[where, y.shape[1] - 1] = float("inf")
+    for y, c in zip(dY, clean):
+        at = slice(None) if what == "a tiny row" else y.shape[1] - 1
+        y[where, at] = {"infinity": float("inf"), "nan": float("nan")}.get(what, 2.0 ** -120 + 2.0 ** -140)
+        if what.startswith("a tiny"):
+            c[where, at] = 2.0 ** -120
 
     def run(which, dY):
         dX, dW = [Guarded((T, k), "f32") for k, n in shapes], [Guarded(s, "f32", o) for s, o in zip(shapes, old)]
@@ -555,11 +560,18 @@ def test_infinities_change_the_bits_of_their_own_blocks_only(ctx, T, where, accu
 
     plain, fp32 = run(20, clean), run(F32_TILES + 4, dY)
     for which in SPLIT.values():
-        for got, without, generic in zip(run(which, dY), plain, fp32):
+        for i, (got, without, generic) in enumerate(zip(run(which, dY), plain, fp32)):
             odd = ~torch.isfinite(generic)
-            assert odd.any() and not odd.all()
+            assert odd.any() == (what in ("infinity", "nan")) and not odd.all()
             blocks = _whole_blocks(odd)
-            assert torch.equal(got.view(torch.int32), torch.where(blocks, generic, without).view(torch.int32)), (which, tuple(got.shape))
+            if what == "nan":                                      # (which NaN it is nobody promises)
+                assert torch.equal(torch.isnan(got), odd)
+                blocks[:] = False
+                got, without = torch.where(odd, 0, got), torch.where(odd, 0, without)
+            if what == "a tiny row" and i < len(shapes):
+                odd[where] = True
+                blocks = _whole_blocks(odd)
+            assert torch.equal(got.view(torch.int32), torch.where(blocks, generic, without).view(torch.int32)), (which, i, tuple(got.shape))
 
 
 @pytest.mark.parametrize("form", ["set", "add", "microbatch", "frozen"])
