@@ -10,9 +10,9 @@
 // is chosen for that (measured, sustained, on the 8B stage's 1.74e9 elements):
 //   * a block is ONE wave and covers 256 consecutive elements: each of its loads
 //     and stores is 1 KB (0.5 KB for bf16) of one array, whole 128-byte lines;
-//   * at most ten blocks are resident per compute unit (an unused 16 KB of
-//     dynamic LDS per block caps it; twelve with element masks): with the full 32 waves per unit the same
-//     code runs at 5.0 TB/s, with ten at 6.5 - fewer rows of DRAM open at once;
+//   * at most nine blocks are resident per compute unit (an unused 17.5 KB of
+//     dynamic LDS per block caps it; eleven with element masks): with the full 32 waves per unit the same
+//     code runs at 5.0 TB/s, with nine at 6.5 - fewer rows of DRAM open at once;
 //   * every access is non-temporal: each byte is touched once.
 // Element masks are applied per mask WORD = 32 elements = one 128-byte line of
 // every fp32 array: a word that is all ones is skipped (nothing read, nothing
@@ -28,11 +28,14 @@ namespace {
 constexpr int kThreads = 64;       // one wave
 constexpr int kGroup = 4;          // consecutive elements per thread (one 16-byte fp32 vector)
 constexpr int64_t kElemsPerBlock = int64_t(kThreads) * kGroup;        // 256 = 8 mask words
-constexpr int kResidencyLds = 16384;   // bytes of dynamic LDS per block: 160 KB / 16 KB = 10 blocks per compute unit
-// An optimizer block with an element mask waits for its mask word before it asks for anything else: 12 blocks per unit.  us, with 10 and
-// 13, fp32 gradients, 30 % frozen: 1.1e7 elements 95 (93 with 12; 93), 6.1e7 475 (470; 472), 2.2e8 1683 (1677; 1677); bf16 93 (90; 90), 462 (454;
-// 453), 1655 (1638; 1644).  Without masks 10 are the best: 2.2e8 elements, 30 % of the tensors frozen, 580 (590; 591).
-constexpr int kMaskedResidencyLds = 13440;
+// An optimizer block with an element mask waits for its mask word before it asks for anything else: more blocks per unit.  us, with 8, 9, 10, 11,
+// 12 and 14, 30 % frozen, widths 1024 / 256 / 2816 (1.1e7 elements), 2048 / 512 / 8192 and 4096 / 1024 / 14336 (2.2e8):
+//   element masks, fp32 gradients   107 101 100  99  98  97   500 481 475 474 475 478   1744 1679 1659 1671 1687 1728
+//   element masks, bf16 gradients   103  98  96  95  95  93   488 465 456 453 453 456   1715 1632 1609 1603 1606 1637
+//   whole tensors, fp32 gradients    42  42  41  42  42  42   178 173 173 174 174 178    615  603  617  627  627  644
+//   whole tensors, bf16 gradients    41  40  40  40  40  40   173 167 166 166 168 171    597  582  588  597  599  608
+constexpr int kResidencyLds = residency_lds(9);
+constexpr int kMaskedResidencyLds = residency_lds(11);
 
 typedef float F4 __attribute__((ext_vector_type(4)));
 typedef uint32_t U2 __attribute__((ext_vector_type(2)));
@@ -245,7 +248,7 @@ bool any_sums(const EwBatch& b, int n) {
     return false;
 }
 
-int residency_lds(const EwBatch& b, int n) {
+int lds_per_block(const EwBatch& b, int n) {
     for (int i = 0; i < n; ++i)
         if (b.t[i].bits) return kMaskedResidencyLds;
     return kResidencyLds;
@@ -266,7 +269,7 @@ hipError_t launch_adamw(hipStream_t stream, EwBatch& batch, int n_tensors,
                         const AdamwParams& hp, Dtype grad_dtype) {
     if (!prepare(batch, n_tensors)) return hipErrorInvalidValue;
     if (n_tensors == 0 || batch.total_blocks == 0) return hipSuccess;
-    const int lds = residency_lds(batch, n_tensors);
+    const int lds = lds_per_block(batch, n_tensors);
     if (grad_dtype == Dtype::BF16)
         hipLaunchKernelGGL((ew_kernel<true, true>), dim3(batch.total_blocks), dim3(kThreads), lds, stream, batch, hp);
     else

@@ -34,15 +34,15 @@ constexpr int kThreads = 256;
 // ------------------------------------------------------------------------------------------
 // The launch shape follows the fused optimizer pass (what decides the rate is how the three
 // streams meet in the memory system): a block is ONE wave and each of its accesses is 1 KB of one
-// array (whole 128-byte lines); an unused 8 KB of dynamic LDS per block caps a compute unit at 20
+// array (whole 128-byte lines); an unused 8.75 KB of dynamic LDS per block caps a compute unit at 18
 // blocks; every access is non-temporal.  Measured on the 8B stage's 1.74e9 elements: 6.6 TB/s
-// with 2 iterations per block and 20 blocks per unit (1 iteration: 5.4; 4: 6.5; 8: 5.9; 10 blocks
+// with 2 iterations per block and 18 blocks per unit (1 iteration: 5.4; 4: 6.5; 8: 5.9; 9 blocks
 // per unit: 4.7 .. 6.1), against 5.5 for blocks of four waves and 8 iterations.
 // With 3.4 million blocks the per-tensor sums are gathered in two levels like the optimizer's
 // score sums: a block adds to one of 64 slots of its tensor, a second kernel adds up the slots.
 constexpr int kNormThreads = 64;
 constexpr int kNormGroup = 4, kNormIters = 2;
-constexpr int kNormResidencyLds = 8192;
+constexpr int kNormResidencyLds = residency_lds(18);
 constexpr int kNormSlotDouble = 2;          // which double of a 64-byte slot (0 and 1 are the optimizer's)
 constexpr int64_t kNormElemsPerBlock = int64_t(kNormThreads) * kNormGroup * kNormIters;
 typedef float F4 __attribute__((ext_vector_type(4)));

@@ -80,6 +80,10 @@ bool split_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda
 hipError_t launch_gemm_split(hipStream_t stream, GemmBatch& batch, int n_problems, int shape);
 int compute_units();              // of the current device
 
+// Bytes of LDS per block that let `blocks` blocks and no more be resident on a compute unit: its 160 KB are given out in units of
+// 1280 bytes (measured with blocks that wait a fixed time: 10 fit at 15360 bytes, 9 at 16000 and 16384).
+constexpr int residency_lds(int blocks) { return 160 * 1024 / blocks / 1280 * 1280; }
+
 // bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of
 // 64 or more that are multiples of 8, row pitches that are multiples of 8 and at most 2^22, 16-byte aligned operands.
 struct NarrowShape {
