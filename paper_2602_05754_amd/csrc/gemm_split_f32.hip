@@ -521,8 +521,9 @@ hipError_t launch_shape(hipStream_t stream, const GemmBatch& batch) {
     return hipGetLastError();
 }
 
-// The launch shapes: a step's share of a compute unit when all are busy, and its time in a launch's longest chain; what a tile and
-// the longest chain cost beside their steps; how much of the smaller of the two is left; a launch.
+// The launch shapes, with the numbers of the estimate of a launch's time: a step's share of a compute unit when all are busy and its
+// time in a launch's longest chain, steps added for a tile and for the longest chain, how much of the smaller of the two is added to the larger, and what is
+// added to a launch.  They are one fit to launches' times and mean something together only: -0.7 steps for a chain and 12 us for a launch are no costs of either.
 constexpr SplitShape kShapes[kSplitShapes] = {{128, 128, 1.38f, 0.96f, 4.6f, 2.9f, 0.07f, 4.3f}, {256, 128, 2.37f, 1.63f, 3.9f, -0.7f, 0.15f, 12.f}};
 
 }  // namespace
@@ -530,8 +531,8 @@ constexpr SplitShape kShapes[kSplitShapes] = {{128, 128, 1.38f, 0.96f, 4.6f, 2.9
 const SplitShape& split_shape(int shape) { return kShapes[shape]; }
 
 bool split_shape_ok(Layout layout, int64_t M, int64_t N, int64_t Kc, int64_t lda, int64_t ldb) {
-    // 32-bit offsets inside a tile, contraction indices up to two steps past the end; shorter contractions and rows shorter than a
-    // load go to fp32 products in there: no gain
+    // 32-bit offsets inside a tile, contraction indices up to two steps past the end.  The last step reads 32 contraction values back from
+    // the end, and a load at the end of a row 4 values back: neither may begin before the matrix.
     constexpr int64_t kMaxPitch = int64_t(1) << 22;
     return Kc >= kBK && Kc <= (int64_t(1) << 30) && lda <= kMaxPitch && ldb <= kMaxPitch && (layout == Layout::kNT || std::min(M, N) >= 4);
 }

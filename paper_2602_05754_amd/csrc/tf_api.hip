@@ -339,15 +339,14 @@ struct Routes {
     int shape[kClasses] = {-1, -1, -1};         // launch shape; -1: 256 x 256 tiles
 };
 
-// Input gradients, and everything in fp32.
-void find_input_routes(Layout layout, Dtype in_dtype, int route, bool plain, Routes& r) {
+// Input gradients in bf16.
+void find_input_routes(int route, bool plain, Routes& r) {
     auto smaller = [&](const std::vector<const Planned*>& v, int* shape) {
         double us;
-        *shape = pick_generic_shape(v, in_dtype, &us);
-        if (in_dtype == Dtype::F32 && route >= kRouteF32 && route < kRouteSplit) *shape = layout == Layout::kNT ? (route - kRouteF32) / kGenericShapes : (route - kRouteF32) % kGenericShapes;
+        *shape = pick_generic_shape(v, Dtype::BF16, &us);
         if (v.empty() || route == kRouteGeneric) return us;
         for (const Planned* it : v)
-            if (!planned_narrow_ok(*it, layout, in_dtype)) return us;
+            if (!planned_narrow_ok(*it, Layout::kNT, Dtype::BF16)) return us;
         double narrow_us;
         const int narrow = pick_narrow_shape(v, &narrow_us);
         if (route >= kRouteNarrow && route < kRouteShort) { *shape = kGenericShapes + route - kRouteNarrow; return 0.0; }
@@ -427,6 +426,7 @@ void find_weight_routes(int out_bytes, bool accumulate, int route, Routes& r) {
     }
 }
 
+// (fp32: all are kOther, for a launch shape that choose_f32() gives them)
 hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate, int route, Routes& r) {
     bool plain = true;                          // no row bits, no segments: the kernels with smaller tiles could take them too
     for (const Planned& it : items) {
@@ -437,8 +437,9 @@ hipError_t find_routes(const std::vector<Planned>& items, Layout layout, Dtype i
         else if (special) return hipErrorInvalidValue;          // only the 256 x 256-tile kernel knows these
         else r.cls[planned_tail_ok(it, layout, in_dtype) ? kTail : kOther].push_back(&it);
     }
-    if (layout == Layout::kTN && in_dtype == Dtype::BF16) find_weight_routes(out_dtype == Dtype::BF16 ? 2 : 4, accumulate, route, r);
-    else find_input_routes(layout, in_dtype, route, plain, r);
+    if (in_dtype == Dtype::F32) return hipSuccess;
+    if (layout == Layout::kTN) find_weight_routes(out_dtype == Dtype::BF16 ? 2 : 4, accumulate, route, r);
+    else find_input_routes(route, plain, r);
     return hipSuccess;
 }
 

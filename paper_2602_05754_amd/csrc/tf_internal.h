@@ -67,11 +67,12 @@ hipError_t launch_gemm_generic(hipStream_t stream, GemmBatch& batch, int n_probl
                                Layout layout, Dtype in_dtype, Dtype out_dtype, bool accumulate);
 // fp32 problems of both layouts in one launch; those of layout kNT are never added to what is there.
 hipError_t launch_gemm_generic_both(hipStream_t stream, GemmBatch& batch, int n_problems, int shape_nt, int shape_tn, bool accumulate);
-// fp32 problems of both layouts on the bf16 matrix cores, three bf16 pieces of each value, in several launch shapes.  It
-// takes everything; fast are contractions of 32 or more.  Row pitches of at most 2^22, contractions of at most 2^30.
+// fp32 problems of both layouts on the bf16 matrix cores, three bf16 pieces of each value, in several launch shapes.  It takes
+// contractions of 32 to 2^30, row pitches of at most 2^22 and, of layout kTN, outputs of four rows and columns or more
+// (split_shape_ok); a launch of anything else is refused.
 struct SplitShape {
     int tile_m, tile_n;
-    float step_us, chain_us, tile_steps, chain_steps, overlap, launch_us;   // what a contraction step of a tile costs (see there)
+    float step_us, chain_us, tile_steps, chain_steps, overlap, launch_us;   // of the estimate of a launch's time (see there)
 };
 constexpr int kSplitShapes = 2;
 const SplitShape& split_shape(int shape);
@@ -82,7 +83,9 @@ int compute_units();              // of the current device
 
 // Bytes of LDS per block that let `blocks` blocks and no more be resident on a compute unit: its 160 KB are given out in units of
 // 1280 bytes (measured with blocks that wait a fixed time: 10 fit at 15360 bytes, 9 at 16000 and 16384).
-constexpr int residency_lds(int blocks) { return 160 * 1024 / blocks / 1280 * 1280; }
+constexpr int kUnitLds = 160 * 1024;
+constexpr int residency_lds(int blocks) { return kUnitLds / blocks / 1280 * 1280; }
+static_assert(kUnitLds / residency_lds(9) == 9 && kUnitLds / residency_lds(11) == 11 && kUnitLds / residency_lds(18) == 18, "those in use; not every number is possible");
 
 // bf16 input gradients (layout kNT) of few rows, in several launch shapes as well.  It takes contractions of
 // 64 or more that are multiples of 8, row pitches that are multiples of 8 and at most 2^22, 16-byte aligned operands.
