@@ -489,6 +489,20 @@ def test_fp32_products_of_the_worst_mantissas(ctx, value, T, tile):
     assert (got[:, 2] <= bound).all(), (got, bound)
 
 
+@pytest.mark.parametrize("tile", sorted(SPLIT))
+@pytest.mark.parametrize("T", [64, 200])
+@pytest.mark.parametrize("first,second", [(-106, 0), (-110, 0), (-58, -58), (-64, -64)])
+def test_fp32_pieces_and_products_below_the_smallest_normal_number(ctx, first, second, T, tile):
+    """Third pieces of values of 2^-110 and more, and products of pieces whose whole product is a normal number, may be subnormal; the
+    matrix instructions keep them.  Nothing is computed again (other bits than the generic kernel's), and no error is larger than that
+    kernel's - all operands are +-(1 .. 2) 2^first and 2^second, so that all of them lie in that range."""
+    rs = np.random.default_rng(T)
+    draw = lambda s, e: dev((rs.uniform(1, 2, s) * rs.choice([-1, 1], s) * 2.0 ** e).astype(np.float32), "f32")
+    W, X, dY = draw((260, T), first), draw((T, 260), first), draw((T, T), second)
+    pieces, generic = (_against_64_bits(ctx, which, W, X, dY) for which in (SPLIT[tile], F32_TILES + 4))
+    assert (pieces[:, 0] <= generic[:, 0]).all() and (pieces[:, 0] != generic[:, 0]).all(), (pieces, generic)
+
+
 def _whole_blocks(odd):
     """The blocks of 32 x 64 that have one."""
     all_of = torch.zeros_like(odd)
