@@ -230,7 +230,7 @@ def _host(arr, dtype, n):
 def _stream_handle(stream) -> Optional[int]:
     if stream is None:
         import torch
-        # (what torch.cuda.current_stream().cuda_stream gives, without a Stream object: 0.5 us instead of 3)
+        # (what torch.cuda.current_stream().cuda_stream gives, without a Stream object: 0.3 us instead of 2.7)
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     if isinstance(stream, int):
         return stream or None

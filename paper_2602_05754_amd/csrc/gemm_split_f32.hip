@@ -20,7 +20,7 @@
 // instructions run.  So larger tiles are faster - a value is split once per tile and step - and every wave does everything: loads, splits,
 // stores to LDS and contracts, its splitting spread evenly behind its matrix instructions, one barrier per step.  256 x 128 tiles
 // of eight waves have 2.1 vector instructions per matrix instruction, 128 x 128 ones 2.6.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us:
-// input gradients 233 (128 x 128 tiles 258, generic kernel 365), weight gradients 260 (284, 368), both in one launch 462 (731).
+// input gradients 231 (128 x 128 tiles 248, generic kernel 368), weight gradients 252 (288, 391), both in one launch 455 (739).
 // Measured besides, the same input gradients (238 then): two workgroups of 128 x 128 tiles per unit that split and contract in turn 270; four
 // waves that load and split beside four that contract 267; the remainders by v_dot2_f32_bf16, exact and half as many instructions, but
 // on the matrix cores' hardware: 290; 64 x 64 tiles 320.
@@ -151,10 +151,11 @@ struct SplitOperand {
 // subnormal pieces and sums: nothing else is lost from 2^-110 on.)  Outputs that this may have reached are computed again from fp32 products, in
 // blocks of 32 x 64 that lie where they lie in either tile, by the contents of the block's own rows and columns: neither
 // the tile nor anything else in the launch says which way an element is computed.
-// What it costs: a tile that notices anything reads its rows and columns once more, 10 to 20 % of its time; a pair of blocks takes a chain of fp32
-// steps, 36 us at 2731 values.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us (generic kernel): ordinary values 522 (769); every dY
-// with one tiny value 558 (736), with one in every row 697 (739), with one infinity 720 (745), all NaN 568 (725); all infinite 1802 (727),
-// all tiny 1860 (1518): every product twice, once in fp32 with two tiles of 32 x 64 per unit.
+// What it costs: a tile that notices anything reads its rows and columns once more, a fifth of its time and more; a pair of blocks takes a
+// chain of fp32 steps of 0.8 us.  Two blocks of widths 1024 / 256 / 2731, 1000 tokens, us (generic kernel): ordinary values 467 (739); every dY
+// with one tiny value 559 (738), with one in every row 679 (740), with one infinity 719 (740), all NaN 566 (725); all infinite 1797 (724),
+// all tiny 1855 (742): every product twice, once in fp32 with two tiles of 32 x 64 per unit.  Worst where a launch has a tile per unit:
+// 864 / 864 / 2798, 475 tokens, input gradients alone 98 (101), one tiny value 151 (106), one infinity 215 (110), all infinite 418 (98).
 constexpr int kBlockM = 32, kBlockN = 64;
 __device__ __forceinline__ bool finite(float x) { return __builtin_fabsf(x) < __builtin_huge_valf(); }
 // Do pieces lose bits of one of the values?
